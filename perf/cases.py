@@ -214,3 +214,110 @@ def tolerance(case):
         # such an exchange moves a head's recall by one hit, 2e-4 of its few thousand; the scores themselves stay within 3e-6
         return {"rel": 2e-4, "differ": 1e-3}
     return {"rel": 5e-6, "max": 5e-5} if case["dtype"] == "f32" else {"rel": 1e-2, "max": 0.08}
+
+
+def _slots(shape, grid):
+    """Token of every slot of every tile of one head, raster order, -1 for padding: [tiles, tile tokens]."""
+    ax = []
+    for ext, size in zip(shape, grid):
+        i = torch.arange(-(-size // ext) * ext).view(-1, ext)
+        ax.append(torch.where(i < size, i, -1))
+    t, h, w = (ax[0][:, None, None, :, None, None], ax[1][None, :, None, None, :, None], ax[2][None, None, :, None, None, :])
+    n = torch.where((t >= 0) & (h >= 0) & (w >= 0), (t * grid[1] + h) * grid[2] + w, -1)
+    return n.reshape(-1, int(np.prod(shape)))
+
+
+def _pad(x, slots):
+    """Rows of x [N, d] by slot; padded slots read row 0."""
+    return x[slots.clamp(min=0)]
+
+
+def _kept(score, k):
+    """The k largest of every row as ascending column numbers, ties to the lower column."""
+    return torch.sort(torch.sort(score, dim=1, descending=True, stable=True)[1][:, :k], dim=1)[0]
+
+
+def _estimate(x, slots, e, h):
+    """Descriptors (mean, maximum, minimum of a tile's tokens) through the estimator's head h, in 64 bits."""
+    real = (slots >= 0)[:, :, None]
+    t = _pad(x, slots)
+    z = torch.cat([torch.where(real, t, 0.0).sum(1) / real.sum(1), torch.where(real, t, -math.inf).amax(1),
+                   torch.where(real, t, math.inf).amin(1)], dim=1)
+    w1, b1, w2, b2 = (torch.as_tensor(np.asarray(a[h]), device=x.device).double() for a in (e.w1, e.b1, e.w2, e.b2))
+    y = z @ w1 + b1
+    return (torch.relu(y) if e.relu else y) @ w2 + b2
+
+
+def _target(q, k, slots, scale, rows):
+    """Largest softmax probability of every (query tile, key tile): [tiles, tiles], zero in the rows not asked for."""
+    heat = torch.zeros(slots.shape[0], slots.shape[0], dtype=torch.float64, device=q.device)
+    kt, real = _pad(k, slots).reshape(-1, q.shape[1]).T.contiguous(), (slots >= 0)
+    step = max(1, 2 ** 26 // (slots.numel() * slots.shape[1]))
+    for r in (rows[i:i + step] for i in range(0, len(rows), step)):
+        s = (_pad(q, slots[r]).reshape(-1, q.shape[1]) @ kt) * scale
+        s = torch.softmax(s.masked_fill(~real.reshape(1, -1), -math.inf), dim=1)
+        s = s.masked_fill(~real[r].reshape(-1, 1), 0.0)
+        heat[r] = s.view(len(r), slots.shape[1], slots.shape[0], slots.shape[1]).amax(dim=(1, 3))
+    return heat
+
+
+def _attend(q, k, v, slots, kept, scale):
+    """Attention of every query tile to its kept key tiles: [N, d]."""
+    out, d = torch.empty_like(q), q.shape[1]
+    kt, vt, real = _pad(k, slots), _pad(v, slots), slots >= 0
+    step = max(1, 2 ** 25 // (kept.shape[1] * slots.shape[1] * d))
+    for i in range(0, slots.shape[0], step):
+        c = kept[i:i + step]
+        g = c.shape[0]
+        s = torch.bmm(_pad(q, slots[i:i + step]), kt[c].reshape(g, -1, d).transpose(1, 2).contiguous()) * scale
+        s = torch.softmax(s.masked_fill(~real[c].reshape(g, 1, -1), -math.inf), dim=2)
+        o = torch.bmm(s, vt[c].reshape(g, -1, d))
+        out[slots[i:i + step][real[i:i + step]]] = o[real[i:i + step]]
+    return out
+
+
+def exact(case, seed):
+    """What run returns, from the formulas in 64 bits; the lists have no such value.  None for the largest outputs."""
+    wl, dev = _workload(case, seed), torch.device("cuda:0")
+    if case["kind"] != "search" and case["batch"] * case["heads"] * wl.tokens * wl.head_dim > 2e8:
+        return None
+    if case["kind"] == "search" and case["keep_num"] == case["keep_den"]:
+        return None     # every tile kept: no error but rounding
+    q, k, v = (x.double() for x in wlm.make_qkv(wl, dev))
+    scale = 1.0 / math.sqrt(wl.head_dim)
+    pairs = [(b, h) for b in range(wl.batch) for h in range(wl.heads)]
+    if case["kind"] == "search":
+        grow = 2 if case["tile_tokens"] == 128 else 1
+        errors = torch.zeros(wl.heads, len(wlm.TILE_SHAPES), dtype=torch.float64)
+        for b, h in pairs:
+            full = None
+            for c, (pt, ph, pw) in enumerate(wlm.TILE_SHAPES):
+                slots = _slots((grow * pt, ph, pw), wl.grid).to(dev)
+                n = slots.shape[0]
+                if full is None:
+                    full = _attend(q[b, h], k[b, h], v[b, h], slots, torch.arange(n, device=dev).expand(n, n), scale)
+                heat = _target(q[b, h], k[b, h], slots, scale, torch.arange(n, device=dev))
+                kept = _kept(heat, max(1, -(-wl.keep[0] * n // wl.keep[1])))
+                errors[h, c] += ((_attend(q[b, h], k[b, h], v[b, h], slots, kept, scale) - full) ** 2).sum().item()
+        return {"best": None, "errors": errors.numpy()}
+    shapes = _shapes(case)
+    budget, slots = wlm.keep_budget(wl, None, shapes), [_slots([int(x) for x in s], wl.grid).to(dev) for s in shapes]
+    eq, ek = wlm.make_estimator(wl, "q"), wlm.make_estimator(wl, "k")
+    out, heats, recall, first = torch.empty_like(q), [], torch.zeros(wl.batch, wl.heads, dtype=torch.float64), 0
+    for b, h in pairs:
+        first = 0 if h == 0 else first + slots[h - 1].shape[0]
+        n = slots[h].shape[0]
+        kept = _kept(_estimate(q[b, h], slots[h], eq, h) @ _estimate(k[b, h], slots[h], ek, h).T, int(budget[h]))
+        if case["kind"] == "path":
+            out[b, h] = _attend(q[b, h], k[b, h], v[b, h], slots[h], kept, scale)
+            continue
+        total = sum(s.shape[0] for s in slots)
+        i = torch.arange(n, device=dev)
+        heats.append(_target(q[b, h], k[b, h], slots[h], scale, i[(first + i) % case["rows"] == seed % case["rows"] % total]))
+        target = torch.zeros(n, n, dtype=torch.bool, device=dev).scatter_(1, _kept(heats[-1], int(budget[h])), True)
+        recall[b, h] = target.gather(1, kept).double().mean().item()
+    if case["kind"] == "path":
+        return {"out": out, "row_ptr": None, "col_idx": None}
+    per = len(heats) // wl.batch
+    heat = torch.stack([torch.cat([x.reshape(-1) for x in heats[b * per:(b + 1) * per]]) for b in range(wl.batch)])
+    return {"heat": heat, "target": None, "estimated": None, "recall": recall}
