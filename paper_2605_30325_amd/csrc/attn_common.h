@@ -83,6 +83,17 @@ __device__ inline void pair_tiles(const HeadGeom& g, int p, int& qiA, int& qiB, 
     if (!hasB) qiB = qiA;
 }
 
+// Position of the n-th set bit (from 0) of m; n < popcount(m).
+__device__ inline int nth_bit(uint64_t m, int n) {
+    int pos = 0;
+#pragma unroll
+    for (int w = 32; w >= 1; w >>= 1) {
+        const int c = __popcll((m >> pos) & ((1ull << w) - 1ull));
+        if (n >= c) { n -= c; pos += w; }
+    }
+    return pos;
+}
+
 __device__ inline int rho(int m) {  // swap bits 2 and 3
     return (m & ~12) | ((m & 4) << 1) | ((m & 8) >> 1);
 }

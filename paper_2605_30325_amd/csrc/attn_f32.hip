@@ -138,8 +138,8 @@ __global__ __launch_bounds__(256, 1) void sparse_attn_f32_kernel(AttnArgs a) {
         const int32_t* lists[2] = {a.col_idx + begA, a.col_idx + begB};
         const int counts[2] = {nA, nB};
         total = union_build<2, 256, kF32Chunk>(u, lists, counts, hg.n_tiles, tid);
-        union_fill<2, 256, kF32Chunk, false>(u, 0, total, hg.n_tiles, vmask_g, n0s_g, tid);
-        union_fill<2, 256, kF32Chunk, false>(u, kF32Chunk, total, hg.n_tiles, vmask_g, n0s_g, tid);
+        union_fill<2, 256, kF32Chunk, false, false>(u, 0, total, hg.n_tiles, vmask_g, n0s_g, tid);
+        union_fill<2, 256, kF32Chunk, false, false>(u, kF32Chunk, total, hg.n_tiles, vmask_g, n0s_g, tid);
         __syncthreads();
         raw_next = union_read<kF32Chunk>(tab_lds, 0);
         s_read = 1;
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(256, 1) void sparse_attn_f32_kernel(AttnArgs a) {
         if constexpr (kTable) {   // the table's other half has been left behind: refill it
             ++s_done;
             if ((s_done & (kF32Chunk - 1)) == 0)
-                union_fill<2, 256, kF32Chunk, false>(u, s_done + kF32Chunk, total, hg.n_tiles, vmask_g, n0s_g, tid);
+                union_fill<2, 256, kF32Chunk, false, false>(u, s_done + kF32Chunk, total, hg.n_tiles, vmask_g, n0s_g, tid);
         }
     }
 

@@ -13,6 +13,11 @@
 // the step and only meets the others at the barrier; the matrix cores it leaves idle go to the
 // second workgroup resident on the compute unit.
 //
+// Padding costs little: a query tile's real rows come first, so a wave beyond them idles, and a key tile
+// with few real keys is a half step (attn_union.h).  On a 21 x 30 x 52 grid with 4x4x4 tiles, where 27 % of
+// the tiles are such, full attention of 12 heads went from 8.33 to 7.41 ms, 10 % kept from 1.21 to 1.06 ms;
+// on 61 x 45 x 80, with few of them, 36.4 to 36.1 ms.
+//
 // The products are formed transposed (S^T = K Q^T, O^T = V^T P^T): a lane owns one query, its
 // accumulator registers run over keys, P^T in registers already is the B operand of the second
 // product.  K rows are loaded permuted by rho (bits 2,3 swapped) so that the eight keys a
@@ -46,7 +51,14 @@ __device__ __forceinline__ void finish_pair(const PairState<D>& st, const AttnAr
     int* tok_s = reinterpret_cast<int*>(lse_s + 2 * kTile);              // [2][64] token of each row, -1 = padding
     __syncthreads();
     // the slot -> token map costs a handful of integer divisions: once per row, not once per chunk
-    if (tid < 2 * kTile) tok_s[tid] = slot_token(hg, tid / kTile ? qiB : qiA, tid % kTile, a.T, a.H, a.W);
+    // (row c is the c-th real slot of its tile; rows beyond the real slots have no token)
+    if (tid < 2 * kTile) {
+        const int slot = tid % kTile, base = tid - slot;
+        const int n = slot_token(hg, base ? qiB : qiA, slot, a.T, a.H, a.W);
+        const uint64_t real = __ballot(n >= 0);
+        if (slot >= __popcll(real)) tok_s[tid] = -1;
+        if (n >= 0) tok_s[base + __popcll(real & ((1ull << slot) - 1ull))] = n;
+    }
     {
         char* orow = obuf + (which * kTile + 32 * r + lq) * kRowB;
 #pragma unroll
@@ -81,8 +93,8 @@ __device__ __forceinline__ void finish_pair(const PairState<D>& st, const AttnAr
 // One step of the merged walk over the kept lists of the two query tiles of a workgroup.
 struct MergedStep {
     int j;         // key tile (head-local)
-    int fl;        // bit 0: tile A keeps it, bit 1: tile B keeps it; 0 = past the end
-    uint64_t vm;   // validity mask of key tile j
+    int fl;        // bit 0: tile A keeps it, bit 1: tile B keeps it; kStepHalf, kStepEmpty; 0 = past the end
+    uint64_t vm;   // validity mask of key tile j; half steps: gathered mask | source chunks << 32
     int n0;        // K from token order: token index of its slot 0
 };
 
@@ -109,7 +121,9 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int which = wave >> 1, r = wave & 1;
+    // The wave that a query tile with 32 or fewer real rows leaves idle (r = 1) is not on the same SIMD in
+    // every workgroup: half of them deal their rows the other way round.
+    const int which = wave >> 1, r = (wave ^ __popc(blockIdx.x >> 3)) & 1;
     const int lq = lane & 31, hh = lane >> 5;
 
     int head, pair;
@@ -138,18 +152,22 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     const const_i32_t n0s = (const_i32_t)(uintptr_t)(a.tile_n0 + hg.tile_off);
 
     // Q operand (B matrix of S^T = K Q^T): lane holds query row 32r+lq, channels 16t+8hh..+8.
+    // Rows are the real slots of the query tile in order: with padding among its 64 slots a tile at a ragged
+    // edge fills fewer rows, and a wave whose 32 rows are all beyond the real ones has nothing to compute.
     PairState<D> st;
+    const uint64_t q_real = __ballot(slot_token(hg, qi, lane, a.T, a.H, a.W) >= 0);
+    const int q_rows = __popcll(q_real);
     {
-        // from the tiled tensor, or straight from token order (a padded slot reads as zeros, which is
-        // what the tiled tensor holds there)
+        // from the tiled tensor, or straight from token order
         const char* qrow;
-        bool real = true;
+        const bool real = 32 * r + lq < q_rows;
+        int slot = 32 * r + lq;
+        if (q_real != ~0ull) slot = real ? nth_bit(q_real, slot) : 0;
         if (a.q_tok) {
-            const int n = slot_token(hg, qi, 32 * r + lq, a.T, a.H, a.W);
-            real = n >= 0;
-            qrow = a.q_tok + b * a.sq_b + head * a.sq_h + (int64_t)(real ? n : 0) * a.sq_n + 16 * hh;
+            const int n = real ? slot_token(hg, qi, slot, a.T, a.H, a.W) : 0;
+            qrow = a.q_tok + b * a.sq_b + head * a.sq_h + (int64_t)n * a.sq_n + 16 * hh;
         } else {
-            qrow = a.q + (head_tile0 + qi) * kKBytes + (32 * r + lq) * kRowB + 16 * hh;
+            qrow = a.q + (head_tile0 + qi) * kKBytes + slot * kRowB + 16 * hh;
         }
 #pragma unroll
         for (int t = 0; t < G; ++t) {
@@ -197,13 +215,37 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     }
     const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
     const uint32_t wave_lds = smem_base + (uint32_t)wave * (kLoads * 1024);
+    // Half steps: byte offset of slots 8, 16 and 32 from slot 0 (the extents of a tile are powers of two, so the
+    // offset of any chunk of eight slots is the sum over the bits of its number), and this lane's V^T chunk:
+    // chunk v_c in even instructions, v_c ^ 4 in odd ones.
+    uint32_t k_chunk[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const int sl = 8 << i, lw = sl % hg.pw, lh = (sl / hg.pw) % hg.ph, lt = sl / (hg.pw * hg.ph);
+        k_chunk[i] = kTokK ? (uint32_t)((((int64_t)lt * a.H + lh) * a.W + lw) * a.sk_n) : (uint32_t)(sl * kRowB);
+    }
+    const int v_c = (lane & 7) ^ ((lane >> 4) & 3) ^ (((lane >> 3) & 1) << 2);
+    auto chunk_off = [&](uint32_t c) __attribute__((always_inline)) {
+        return ((c & 1u) ? k_chunk[0] : 0u) + ((c & 2u) ? k_chunk[1] : 0u) + ((c & 4u) ? k_chunk[2] : 0u);
+    };
     // The K tile (which = 0) or the V^T tile (which = 1) of step e into LDS slot `sl`.
     auto load_tile = [&](const MergedStep& e, int sl, int what) __attribute__((always_inline)) {
+        uint32_t off[kLoads];
         if (what == 0) {
             const char* src = (kTokK ? kt + (int64_t)e.n0 * a.sk_n : kt + (int64_t)e.j * kKBytes) - kBias;
             const uint32_t dst = wave_lds + (uint32_t)sl * kSlot;
-            if (kTokK && e.vm != ~0ull) {   // edge tile: padded rows have no token
-                uint32_t off[kLoads];
+            if (e.fl & kStepHalf) {   // the first 32 rows, from the chunks that hold real tokens
+                if (wave < 2) {
+                    const uint32_t from = (uint32_t)(e.vm >> 32);
+#pragma unroll
+                    for (int j = 0; j < kLoads; ++j) {
+                        const int c = (wave * kLoads + j) * (1024 / kRowB) / 8;
+                        const uint32_t moved = k_src[j] + chunk_off((from >> (8 * c)) & 255u) - chunk_off((uint32_t)c);
+                        off[j] = !kTokK || (e.vm >> k_row[j]) & 1ull ? moved : k_src0[j];
+                    }
+                    dma16_group_to_lds<kLoads>(dst, src, off);
+                }
+            } else if (kTokK && e.vm != ~0ull) {   // edge tile: padded rows have no token
 #pragma unroll
                 for (int j = 0; j < kLoads; ++j) off[j] = (e.vm >> k_row[j]) & 1ull ? k_src[j] : k_src0[j];
                 dma16_group_to_lds<kLoads>(dst, src, off);
@@ -211,7 +253,17 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
                 dma16_group_to_lds<kLoads>(dst, src, k_src);
             }
         } else {
-            dma16_group_to_lds<kLoads>(wave_lds + (uint32_t)sl * kSlot + kKBytes, vt + (int64_t)e.j * kVBytes, v_src);
+            const uint32_t dst = wave_lds + (uint32_t)sl * kSlot + kKBytes;
+            const char* src = vt + (int64_t)e.j * kVBytes;
+            if (e.fl & kStepHalf) {   // chunks 0-3 from where the real tokens are; chunks 4-7 are not read
+                const uint32_t from = ((uint32_t)(e.vm >> 32) >> (8 * (v_c & 3))) & 255u;
+                const uint32_t delta = (from - (uint32_t)(v_c & 3)) << 4;
+#pragma unroll
+                for (int j = 0; j < kLoads; ++j) off[j] = v_src[j] + (((v_c >> 2) & 1) == (j & 1) ? delta : 0u);
+                dma16_group_to_lds<kLoads>(dst, src, off);
+            } else {
+                dma16_group_to_lds<kLoads>(dst, src, v_src);
+            }
         }
     };
     // All of this wave's LDS-bound loads have landed (vmcnt 0), then meet the other waves.
@@ -256,8 +308,8 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
         const int32_t* lists[2] = {a.col_idx + begA, a.col_idx + begB};
         const int counts[2] = {nA, kGrouped ? 0 : nB};
         total = union_build<2, 256, kPairChunk>(u, lists, counts, list_range, tid) * (kGrouped ? 2 : 1);
-        union_fill<2, 256, kPairChunk, kGrouped>(u, 0, total, list_range, vmask_g, n0s_g, tid);
-        union_fill<2, 256, kPairChunk, kGrouped>(u, kPairChunk, total, list_range, vmask_g, n0s_g, tid);
+        union_fill<2, 256, kPairChunk, kGrouped, true>(u, 0, total, list_range, vmask_g, n0s_g, tid);
+        union_fill<2, 256, kPairChunk, kGrouped, true>(u, kPairChunk, total, list_range, vmask_g, n0s_g, tid);
         __syncthreads();
     } else {
         rawA = colsA[0];
@@ -286,8 +338,10 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
             fl = ta | (tb << 1);
         }
         e.j = __builtin_amdgcn_readfirstlane(j);
-        e.fl = __builtin_amdgcn_readfirstlane(fl);
-        e.vm = vmask[e.j];
+        uint32_t lo, hi;
+        const int kind = step_kind(vmask[e.j], lo, hi);
+        e.fl = __builtin_amdgcn_readfirstlane(fl == 0 ? 0 : kind == kStepEmpty ? kind : fl | kind);
+        e.vm = (uint64_t)hi << 32 | lo;
         e.n0 = kTokK ? n0s[e.j] : 0;
     };
     auto next_advance = [&]() __attribute__((always_inline)) {
@@ -313,19 +367,20 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
         if constexpr (kTable) {
             ++s_done;
             if ((s_done & (kPairChunk - 1)) == 0)
-                union_fill<2, 256, kPairChunk, kGrouped>(u, s_done + kPairChunk, total, list_range, vmask_g, n0s_g, tid);
+                union_fill<2, 256, kPairChunk, kGrouped, true>(u, s_done + kPairChunk, total, list_range, vmask_g, n0s_g, tid);
         }
     };
     if constexpr (kTable) next_advance();   // entry 0 on its way
 
     // Step s (P = s & 1) computes on slot P while the tiles of step s+1 land in slot P^1.
-    const int my_bit = 1 << which;
+    constexpr int kKeepers = 3;
+    const int my_bit = 32 * r < q_rows ? 1 << which : 64;   // 64: a bit no step has
     MergedStep e0, e1, e2;
     next_head(e0);
     next_advance();
     next_head(e1);
     next_advance();
-    if (e0.fl) {
+    if (e0.fl & kKeepers) {
         load_tile(e0, 0, 0);
         load_tile(e0, 0, 1);
     }
@@ -338,13 +393,13 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
 #define VEDA_STEP(P)                                                                                     \
     do {                                                                                                 \
         int todo = 1;                                                                                    \
-        if (__builtin_expect((e0.fl & my_bit) != 0, 1)) {                                                \
+        if (__builtin_expect((e0.fl & (my_bit | kStepHalf)) == my_bit, 1)) {                             \
             PairStep<D, kExact> w;                                                                       \
             w.begin(fa, (uint32_t)((P) * kSlot));                                                        \
             w.template block0<0>(st);                                                                    \
-            if (e1.fl) load_tile(e1, (P) ^ 1, 0);                                                        \
+            if (e1.fl & kKeepers) load_tile(e1, (P) ^ 1, 0);                                             \
             w.template block0<1>(st);                                                                    \
-            if (e1.fl) load_tile(e1, (P) ^ 1, 1);                                                        \
+            if (e1.fl & kKeepers) load_tile(e1, (P) ^ 1, 1);                                             \
             w.template block0<2>(st);                                                                    \
             next_head(e2);                                                                               \
             w.template block0<3>(st);                                                                    \
@@ -354,12 +409,13 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
         }                                                                                                \
         asm volatile("" : "+s"(todo));                                                                   \
         if (todo) {                                                                                      \
-            if (e1.fl) {                                                                                 \
+            if (e1.fl & kKeepers) {                                                                      \
                 load_tile(e1, (P) ^ 1, 0);                                                               \
                 load_tile(e1, (P) ^ 1, 1);                                                               \
             }                                                                                            \
             next_head(e2);                                                                               \
             next_advance();                                                                              \
+            if (e0.fl & my_bit) pair_half_step<D, kExact>(st, fa, (uint32_t)((P) * kSlot), (uint32_t)e0.vm); \
         }                                                                                                \
         e0 = e1; e1 = e2;                                                                                \
         VEDA_LOADS_DONE_BARRIER();                                                                       \

@@ -63,6 +63,24 @@ struct PairAddr {
 //     forming those exponentials again.
 constexpr int kSideCalls = 4;
 
+// Moves the reference by the row maximum mx (relative to it) and rescales O and l; returns the move, which
+// the caller takes off the scores at hand.
+template <int D, bool kExact> __device__ __forceinline__ float pair_move_ref(PairState<D>& st, float mx) {
+    float delta = st.started ? fmaxf(mx, 0.0f) : mx;
+    delta = delta == -INFINITY ? 0.0f : delta;
+    const float alpha = st.started ? __builtin_amdgcn_exp2f(kExact ? -delta * st.resid : -delta) : 1.0f;   // O = l = 0 before
+    st.ref += delta;
+    st.l_run *= alpha;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) st.start[i] = -st.ref;
+#pragma unroll
+    for (int nb = 0; nb < D / 32; ++nb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) st.o[nb][i] *= alpha;
+    st.started = true;
+    return delta;
+}
+
 template <int D, bool kExact> struct PairStep {
     static constexpr int G = D / 16, NB = D / 32, kAhead = 6;
     static constexpr int kRowB = D * 2;
@@ -161,22 +179,11 @@ template <int D, bool kExact> struct PairStep {
             if (!st.started || __any((kExact ? mx * st.resid : mx) > kPairSlack)) {
                 // Move the reference of every row whose maximum is above it (first step: to the
                 // maximum itself, up or down).
-                float delta = st.started ? fmaxf(mx, 0.0f) : mx;
-                delta = delta == -INFINITY ? 0.0f : delta;
-                const float alpha = st.started ? __builtin_amdgcn_exp2f(kExact ? -delta * st.resid : -delta) : 1.0f;   // O = l = 0 before
-                st.ref += delta;
-                st.l_run *= alpha;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) st.start[i] = -st.ref;
+                const float delta = pair_move_ref<D, kExact>(st, mx);
 #pragma unroll
                 for (int c = 0; c < 2; ++c)
 #pragma unroll
                     for (int i = 0; i < 16; ++i) s[c][i] -= delta;
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) st.o[nb][i] *= alpha;
-                st.started = true;
             }
             psum = 0.0f;   // the speculative exponentials are void
 #pragma unroll
@@ -209,5 +216,53 @@ template <int D, bool kExact> struct PairStep {
 #undef VEDA_KF
 #undef VEDA_VF
 };
+
+// A half step: the tile's real keys are all in the first 32 slots of the LDS tile (attn_union.h), padding among
+// them by mask32.  Half the products of a step; edge tiles only, so without the step's speculation.
+template <int D, bool kExact>
+__device__ __forceinline__ void pair_half_step(PairState<D>& st, const PairAddr& fa, uint32_t slot, uint32_t mask32) {
+    constexpr int G = D / 16, NB = D / 32;
+    const uint32_t ka = fa.k0 + slot, va = fa.v0 + slot;
+    bf16x8 kf[G], vf[2 * NB];
+#pragma unroll
+    for (int t = 0; t < G; ++t) kf[t] = lds_read16(ka ^ (uint32_t)(t << 5));
+    f32x16 s = st.start;
+#pragma unroll
+    for (int t = 0; t < G; ++t) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t], st.qf[t], s, 0, 0, 0);
+#pragma unroll
+    for (int g = 0; g < 2 * NB; ++g) vf[g] = lds_read16((va ^ (uint32_t)((g / NB) << 5)) + (uint32_t)((g % NB) * 4096));
+    if (mask32 != ~0u) {   // register i is key 16*(i/8) + 8*hh + (i%8)
+        const uint32_t half = mask32 >> (8 * fa.hh);
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (!((half >> (16 * (i >> 3) + (i & 7))) & 1u)) s[i] = -INFINITY;
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[i]);
+    if (!st.started || __any((kExact ? mx * st.resid : mx) > kPairSlack)) {
+        mx = max_with_other_half(mx);
+        const float delta = pair_move_ref<D, kExact>(st, mx);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] -= delta;
+    }
+    // keys 0-15, then 16-31 unless they are all padding
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+        if (kk == 1 && !(mask32 >> 16)) break;
+        bf16x8 pf;
+        float psum = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float p = __builtin_amdgcn_exp2f(kExact ? s[8 * kk + e] * st.resid : s[8 * kk + e]);
+            psum += p;
+            pf[e] = (__bf16)p;
+        }
+        st.l_run += psum;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+            st.o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kk * NB + nb], pf, st.o[nb], 0, 0, 0);
+    }
+}
 
 }  // namespace veda

@@ -13,6 +13,11 @@
 //      counting, and stores (key tile, who keeps it, the tile's anchor token, its validity mask).
 // The main loop reads one 16-byte entry per step from LDS, steps ahead.  The table is a ring of
 // two chunks; a chunk is refilled when the loop has left it.
+// Padding.  A key tile at a ragged edge of the grid may hold real tokens in few of its eight 8-slot chunks.
+// With four or fewer the step is a half step: the chunks that hold real tokens are gathered to the front on
+// their way into LDS (a chunk is 16 bytes of a V^T row and eight K rows, so both move freely) and one 32-key
+// block of products serves the tile.  A tile with no real token at all (the second half of a 128-token tile)
+// is neither loaded nor computed.  A tile with five or more such chunks is a full step: it needs both blocks.
 // Lists may come in any order (the union is visited in ascending order regardless) and must not
 // name a tile twice in a row of the CSR (the attention entry points' contract).
 #pragma once
@@ -24,7 +29,36 @@ namespace veda {
 constexpr int kUnionMaxWords = 512;                 // bitmap words: list entries name at most 16384 different tiles
 constexpr int kUnionMaxTiles = kUnionMaxWords * 32;
 
-// x: key tile | keeper bits << 16 (0 = past the last step); y: anchor token; z, w: validity mask.
+// What a step does with its key tile, beside the keeper bits 0..3 of its flags.
+constexpr int kStepHalf = 16;    // one 32-key block after gathering chunks
+constexpr int kStepEmpty = 32;   // nothing to attend to
+
+// Validity mask of a key tile -> kind of step (0 = full).  Half: lo = mask of the 32 gathered slots, hi = the
+// four chunks they come from, one byte each (places without a chunk name one that is all padding: V is zero
+// there).  Otherwise lo, hi = the mask itself.
+__device__ __forceinline__ int step_kind(uint64_t vm, uint32_t& lo, uint32_t& hi) {
+    lo = (uint32_t)vm;
+    hi = (uint32_t)(vm >> 32);
+    if (vm == ~0ull) return 0;
+    uint32_t mask = 0u, from = 0u, none = 0u;
+    int n = 0;
+    for (int c = 0; c < 8; ++c) {
+        const uint32_t byte = (uint32_t)(vm >> (8 * c)) & 255u;
+        if (byte == 0u) none = (uint32_t)c;
+        else if (n++ < 4) {
+            mask |= byte << (8 * (n - 1));
+            from |= (uint32_t)c << (8 * (n - 1));
+        }
+    }
+    if (n == 0) return kStepEmpty;
+    if (n > 4) return 0;
+    for (int i = n; i < 4; ++i) from |= none << (8 * i);
+    lo = mask;
+    hi = from;
+    return kStepHalf;
+}
+
+// x: key tile | flags << 16 (keepers, kind; 0 = past the last step); y: anchor token; z, w: step_kind's lo, hi.
 struct __align__(16) UnionEntry { int32_t x, y; uint32_t z, w; };
 
 // kChunk: table entries filled at a time (a power of two); the ring holds two chunks.
@@ -98,8 +132,9 @@ __device__ inline int union_build(UnionLds<N, kChunk>& u, const int32_t* const (
 // (entry s lives at s % (2 kChunk)).  No barrier inside: the caller separates it from the readers
 // of these places.  total: number of steps.  kGrouped: the lists name whole 128-token tiles and
 // every kept one makes two steps, its 64-slot halves 2o and 2o+1 (vmask, n0s are indexed by half),
-// kept by all N query tiles alike.
-template <int N, int kThreads, int kChunk, bool kGrouped>
+// kept by all N query tiles alike.  kHalf: mark half and empty steps (a kernel without them takes every
+// tile whole).
+template <int N, int kThreads, int kChunk, bool kGrouped, bool kHalf>
 __device__ inline void union_fill(UnionLds<N, kChunk>& u, int first, int total, int n_tiles, const uint64_t* __restrict__ vmask,
                                   const int32_t* __restrict__ n0s, int tid) {
     const int words = (n_tiles + 31) >> 5;
@@ -128,10 +163,11 @@ __device__ inline void union_fill(UnionLds<N, kChunk>& u, int first, int total, 
             for (int t = 0; t < N; ++t) fl |= (int)((b[t] >> bit) & 1u) << t;
             if (kGrouped) fl = (1 << N) - 1;
             const uint64_t vm = vmask[j];
-            e.x = j | (fl << 16);
+            int kind = 0;
+            if (kHalf) kind = step_kind(vm, e.z, e.w);
+            else { e.z = (uint32_t)vm; e.w = (uint32_t)(vm >> 32); }
+            e.x = j | ((kind == kStepEmpty ? kind : fl | kind) << 16);
             e.y = n0s[j];
-            e.z = (uint32_t)vm;
-            e.w = (uint32_t)(vm >> 32);
         }
         u.tab[step & (2 * kChunk - 1)] = e;
     }
@@ -140,8 +176,8 @@ __device__ inline void union_fill(UnionLds<N, kChunk>& u, int first, int total, 
 // One step as the main loop holds it (all fields wave-uniform, in scalar registers).
 struct UnionStep {
     int j;         // key tile (head-local)
-    int fl;        // bit t: query tile t of the workgroup keeps it; 0 = past the end
-    uint64_t vm;   // validity mask of key tile j
+    int fl;        // bit t: query tile t of the workgroup keeps it; kStepHalf, kStepEmpty; 0 = past the end
+    uint64_t vm;   // validity mask of key tile j; half steps: step_kind's lo | hi << 32
     int n0;        // token index of its slot 0
 };
 
