@@ -46,11 +46,10 @@ struct AttnArgs {
 // query tiles and walks the heads in order: all dies then work on the same head at the same
 // time (its K/V, ~120 MB at 220k tokens, stay in the memory-side cache), and the workgroups
 // sharing an L2 hold neighbouring query tiles, whose kept key tiles overlap.
-// The work item is a query tile (unit = 1) or a pair of adjacent query tiles (unit = 2);
-// xcd_cum is the matching table of the plan.  Returns false for the padding workgroups of dies
+// The work item is a pair of adjacent query tiles; xcd_cum is the plan's table of them.  Returns false for the padding workgroups of dies
 // with fewer items.
 __device__ inline bool xcd_work(const int32_t* __restrict__ xcd_cum, const HeadGeom* __restrict__ heads,
-                                int n_heads, int unit, int& head, int& item) {
+                                int n_heads, int& head, int& item) {
     const int x = blockIdx.x % kXcd, local = blockIdx.x / kXcd;
     const int32_t* cum = xcd_cum + x * (n_heads + 1);
     if (local >= cum[n_heads]) return false;
@@ -59,7 +58,7 @@ __device__ inline bool xcd_work(const int32_t* __restrict__ xcd_cum, const HeadG
         const int mid = (h + hi + 1) >> 1;
         if (local >= cum[mid]) h = mid; else hi = mid - 1;
     }
-    const int n = unit == 2 ? heads[h].n_pairs : heads[h].n_tiles;
+    const int n = heads[h].n_pairs;
     head = h;
     item = x * (n / kXcd) + (x < n % kXcd ? x : n % kXcd) + (local - cum[h]);
     return true;
@@ -135,6 +134,11 @@ __device__ __forceinline__ void dma16_group_to_lds(uint32_t lds_base, const void
     } else {
         dma16_to_lds(lds_base, base, voff[0]);
     }
+}
+
+// s_waitcnt with only the vector-memory counter constrained (gfx9 encoding).
+template <int N> __device__ __forceinline__ void wait_vmcnt() {
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
 // x of this lane and x of lane ^ 32, without a trip through LDS: the swap exchanges lanes 32-63

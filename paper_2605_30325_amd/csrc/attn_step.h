@@ -10,11 +10,6 @@ namespace veda {
 typedef const __attribute__((address_space(3))) bf16x8* lds_bf16x8_ptr;
 __device__ __forceinline__ bf16x8 lds_read16(uint32_t addr) { return *(lds_bf16x8_ptr)(uintptr_t)addr; }
 
-// s_waitcnt with only the vector-memory counter constrained (gfx9 encoding).
-template <int N> __device__ __forceinline__ void wait_vmcnt() {
-    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-
 constexpr float kPairSlack = 8.0f;   // log2 units a row maximum may outgrow the softmax reference
 
 // Online-softmax state of one wave: 32 queries of one query tile (one per lane, duplicated in

@@ -11,22 +11,30 @@
 // block: exp(max_v s_uv - m_u) / l_u, then the maximum over the rows u.  Both passes stay in
 // one kernel: m_u and l_u never leave the registers and no workspace is needed.
 //
-// bf16 kernel: one workgroup owns two adjacent query tiles (waves 0,1: rows 0-31 / 32-63 of
-// tile A, waves 2,3: of tile B) so that every K tile pulled into LDS feeds 128 query rows;
-// S^T = K Q^T on bf16 MFMA with fp32 accumulation, lane = query, registers = keys (same
-// operand layout and LDS swizzle as the sparse attention kernel).  Logits are scaled in fp32.
-// fp32 kernel: plain VALU arithmetic, one workgroup per query tile.
+// The same kernel serves bf16 and fp32 (v_mfma_f32_32x32x16_bf16 or v_mfma_f32_32x32x2_f32, fp32
+// accumulation): S^T = K Q^T, so a lane owns a query row and its registers run over keys.  A workgroup holds
+// two query tiles, a wave 32 rows of one.  Pass 1 is bound by its exponentials (one per pair of tokens, with the
+// fused multiply-add before and the addition after it: 48 vector operations per 8 products), pass 2 by the
+// products; the exponentials of one 32-key block are therefore formed behind the products of the next, and the
+// reference of the softmax stays where it is until a sum outgrows it.
+// Measured, the heat map alone, before and after: 12 heads of 624 tiles, bf16, d = 128, 10.0 -> 7.9 ms; one in 16
+// of the query tiles of 40 heads of 21x45x80 23.1 -> 12.0 ms (listed tiles used to run one to a workgroup); 8
+// heads of 144 tiles, fp32, d = 128, 19.1 -> 3.3 ms (on the vector units before).  Tried and left out: 64 rows
+// per wave, four tiles per workgroup (half the operand reads and loads: 8.3 and 11.7 ms, fp32 3.9), a ring of
+// three or four K tiles (0.5 ms slower: it costs a resident workgroup and the loads are not what is waited for).
+// Padding: a tile's real rows come first (a wave runs only the blocks that hold any), and key tiles with few
+// real keys are half steps (attn_union.h).
+#include <type_traits>
+
 #include "attn_common.h"
+#include "attn_union.h"
 
 namespace veda {
-
-typedef const __attribute__((address_space(3))) bf16x8* lds_bf16x8_ptr;
-__device__ __forceinline__ bf16x8 hm_lds_read16(uint32_t addr) { return *(lds_bf16x8_ptr)(uintptr_t)addr; }
 
 struct HeatArgs {
     const HeadGeom* heads;
     const uint8_t* tile_head;
-    const int32_t* xcd_cum;       // pair table (bf16) or tile table (fp32); unused with a query list
+    const int32_t* xcd_cum;       // the pair table; unused with a query list
     const int32_t* query_tiles;   // optional: global tile ids to process
     int64_t n_query_tiles;
     const char* q;
@@ -38,279 +46,359 @@ struct HeatArgs {
     float scale_log2;             // softmax_scale * log2(e)
 };
 
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) x = fmaxf(x, __shfl_xor(x, o));
-    return x;
+// Maximum over the 32 rows of a wave (x alike in both lane halves), wave-uniform: within 16 lanes by DPP, the
+// two groups through scalar registers.
+__device__ __forceinline__ float rows_max(float x) {
+    const auto step = [](float v, auto ctrl) __attribute__((always_inline)) {
+        return fmaxf(v, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, true)));
+    };
+    x = step(x, std::integral_constant<int, 0xB1>{});    // quad_perm [1,0,3,2]
+    x = step(x, std::integral_constant<int, 0x4E>{});    // quad_perm [2,3,0,1]
+    x = step(x, std::integral_constant<int, 0x141>{});   // row_half_mirror
+    x = step(x, std::integral_constant<int, 0x140>{});   // row_mirror
+    return fmaxf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 0)),
+                 __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 16)));
 }
 
-// S^T = K Q^T (64 keys x 32 queries, two 32x32 blocks) of one K tile in LDS: raw dot products,
-// padded key slots of an edge tile set to -inf.  The MFMAs are issued at raised wave priority:
-// the other wave of the SIMD, busy with vector work, otherwise delays them.
-template <int D>
-__device__ __forceinline__ void heat_logits(f32x16 (&s)[2], const bf16x8 (&qf)[D / 16], uint32_t ka, uint64_t vm,
-                                            int hh) {
-    constexpr int G = D / 16, kRowB = D * 2;
-    const f32x16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
-    __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-#pragma unroll
-        for (int t = 0; t < G; ++t) {
-            const bf16x8 kf = hm_lds_read16((ka ^ (uint32_t)(t << 5)) + (uint32_t)(c * 32 * kRowB));
-            s[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[t], t == 0 ? zero : s[c], 0, 0, 0);
-        }
+// One operand fragment: 16 bytes per lane, chunk 2f + hh of a K or Q row, and the products it takes part in.
+template <typename E> struct HeatFrag;
+template <> struct HeatFrag<uint16_t> {
+    typedef bf16x8 type;
+    static __device__ __forceinline__ f32x16 mul(type k, type q, f32x16 c) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(k, q, c, 0, 0, 0);
     }
-    __builtin_amdgcn_s_setprio(0);
-    if (vm != ~0ull) {
-        // register i of key block c is key slot 32c + 16*(i/8) + 8*hh + (i%8).  The empty asm
-        // keeps this a real branch, taken for edge tiles only.
-        asm volatile("" ::: "memory");
+};
+template <> struct HeatFrag<uint32_t> {
+    typedef __attribute__((ext_vector_type(4))) float type;
+    static __device__ __forceinline__ f32x16 mul(type k, type q, f32x16 c) {
 #pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            const uint32_t half = (uint32_t)(vm >> (32 * c)) >> (8 * hh);
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                if (!((half >> (16 * (i >> 3) + (i & 7))) & 1u)) s[c][i] = -INFINITY;
-        }
+        for (int t = 0; t < 4; ++t) c = __builtin_amdgcn_mfma_f32_32x32x2f32(k[t], q[t], c, 0, 0, 0);
+        return c;
     }
-}
+};
 
-// Largest raw dot product of the wave's query row over the 64 keys (both lane halves).
-__device__ __forceinline__ float heat_row_max(const f32x16 (&s)[2]) {
-    float mx = -INFINITY;
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[c][i]);
-    return max_with_other_half(mx);
-}
+constexpr int kHeatFold = 32;          // steps after which the running part of a denominator is put away
+constexpr float kHeatNoRef = -3e38f;   // reference before the first key: everything finite outgrows it
+// A lane's sum over its 16 keys of a block above this moves the reference.  At most 16 where the reference is
+// the row's maximum, so rows of even logits stay below it.
+constexpr float kHeatSlack = 32.0f;
 
-// kGrouped: 128-token tiles.  The geometry in `a` is that of the 64-slot halves; the workgroup's
-// pair is one whole query tile, and the block maximum of a whole (query tile, key tile) pair is
-// the maximum over its four half-tile blocks: both halves of the query tile, two consecutive steps.
-template <int D, bool kGrouped>
-__global__ __launch_bounds__(256) void tile_heatmap_bf16_kernel(HeatArgs a) {
-    constexpr int kRowB = D * 2, kKBytes = kTile * kRowB, kKChunks = kRowB / 16;
+// kGrouped: 128-token tiles.  The geometry in `a` is that of the 64-slot halves; a whole tile is a
+// workgroup and two consecutive key steps, and its block maximum the maximum over them.
+template <typename E, int D, bool kGrouped>
+__global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
+    typedef HeatFrag<E> F;
+    typedef typename F::type frag;
+    typedef const __attribute__((address_space(3))) frag* lds_frag_ptr;
+    constexpr int kRowB = D * (int)sizeof(E), kKBytes = kTile * kRowB, kKChunks = kRowB / 16;
+    constexpr int kF = kRowB / 32;               // fragments of a row
     constexpr int kLoads = kKBytes / 1024 / 4;   // direct-load instructions per wave per K tile
-    constexpr int G = D / 16;
-    // dynamic LDS only, so the base is the workgroup's LDS origin (the XOR swizzle needs address
-    // bits 4-9 of the base clear): two K slots, then the block maxima of the 4 waves by step parity
+    constexpr int kGroup = kLoads < 4 ? kLoads : 4;
+    constexpr int kShare = kGrouped ? 4 : 2;     // waves whose maxima make one result
+    constexpr int kAhead = 4;
+    constexpr int kExps = 16 / kF;               // exponentials behind one fragment's products
+    // dynamic LDS only, so the base is the workgroup's LDS origin (the XOR swizzle needs address bits 4-9 of
+    // the base clear): two K slots, then 64 steps of block maxima of the four waves
     extern __shared__ __align__(1024) char smem[];
-    float (*part)[4] = reinterpret_cast<float (*)[4]>(smem + 2 * kKBytes);
+    float (*part)[64] = reinterpret_cast<float (*)[64]>(smem + 2 * kKBytes);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int which = wave >> 1, r = wave & 1;
-    const int lq = lane & 31, hh = lane >> 5;
+    const int idx = lane & 31, hh = lane >> 5;
+    const int which = wave >> 1, r = wave & 1;   // this wave's tile and 32-row block
 
-    // work item: a pair of adjacent query tiles of one head
-    int head, qiA, qiB;
-    bool hasB;
+    // work item: up to two query tiles of one head; qi < 0: this wave has none
+    int head, qi = -1;
     if (a.query_tiles) {
-        // listed tiles are processed one per workgroup (tile B absent)
-        if ((int64_t)blockIdx.x >= a.n_query_tiles) return;
-        const int g = a.query_tiles[blockIdx.x];
-        if (kGrouped) {   // g counts whole tiles
-            head = a.tile_head[2 * g];
-            qiA = 2 * g - a.heads[head].tile_off;
-            qiB = qiA + 1;
-            hasB = true;
-        } else {
-            head = a.tile_head[g];
-            qiA = qiB = g - a.heads[head].tile_off;
-            hasB = false;
+        // Listed tiles, in any order: entry i leads a workgroup if the number of earlier entries of its head is
+        // even, and takes the next entry of its head along.  (A listed 128-token tile fills a workgroup itself.)
+        const int i = blockIdx.x;
+        const int g = a.query_tiles[i];
+        head = a.tile_head[kGrouped ? 2 * g : g];
+        const int lo = a.heads[head].tile_off, n = a.heads[head].n_tiles;
+        int own = g;   // this wave's entry
+        if (!kGrouped) {
+            int earlier = 0;
+            for (int j = tid; j < i; j += 256) earlier += (unsigned)(a.query_tiles[j] - lo) < (unsigned)n ? 1 : 0;
+            int* count = reinterpret_cast<int*>(smem);
+            if (tid == 0) *count = 0;
+            __syncthreads();
+            if (earlier) atomicAdd(count, earlier);
+            __syncthreads();
+            const int rank = *count;
+            __syncthreads();
+            if (rank & 1) return;
+            if (which == 1) {
+                own = -1;
+                for (int64_t j0 = i + 1; j0 < a.n_query_tiles && own < 0; j0 += 64) {
+                    const int64_t j = j0 + lane;
+                    const int gj = j < a.n_query_tiles ? a.query_tiles[j] : -1;
+                    const uint64_t m = __ballot(j < a.n_query_tiles && (unsigned)(gj - lo) < (unsigned)n);
+                    if (m) own = __shfl(gj, (int)__ffsll((unsigned long long)m) - 1);
+                }
+            }
         }
+        if (own >= 0) qi = (kGrouped ? 2 * own + which : own) - lo;
     } else {
-        int pair;
-        if (!xcd_work(a.xcd_cum, a.heads, a.n_heads, 2, head, pair)) return;
-        pair_tiles(a.heads[head], pair, qiA, qiB, hasB);
+        int item, qiA, qiB;
+        bool hasB;
+        if (!xcd_work(a.xcd_cum, a.heads, a.n_heads, head, item)) return;
+        pair_tiles(a.heads[head], item, qiA, qiB, hasB);
+        qi = which == 0 ? qiA : hasB ? qiB : -1;
     }
+    qi = __builtin_amdgcn_readfirstlane(qi);
     const HeadGeom hg = a.heads[head];
     const int n = hg.n_tiles;
     const int64_t b = blockIdx.y;
-    const bool active = which == 0 || hasB;
-    const int qi = which ? qiB : qiA;
     const int64_t head_tile0 = b * a.total_tiles + hg.tile_off;
     const char* kt = a.k + head_tile0 * kKBytes;
     typedef const __attribute__((address_space(4))) uint64_t* const_u64_t;
     const const_u64_t vmask = (const_u64_t)(uintptr_t)(a.valid_mask + hg.tile_off);
 
-    bf16x8 qf[G];
+    // This lane's row: the real slots of the query tile in order, 32 per wave.
+    const uint64_t q_mask = qi >= 0 ? vmask[qi] : 0ull;
+    const int row = 32 * r + idx, q_rows = __popcll(q_mask);
+    const bool q_real = row < q_rows;
+    const bool active = __builtin_amdgcn_readfirstlane(32 * r < q_rows ? 1 : 0);
+    frag qf[kF];
     {
-        const char* qrow = a.q + (head_tile0 + qi) * kKBytes + (32 * r + lq) * kRowB + 16 * hh;
+        const int slot = q_real ? nth_bit(q_mask, row) : 0;
+        const char* qrow = a.q + (head_tile0 + (qi >= 0 ? qi : 0)) * kKBytes + slot * kRowB + 16 * hh;
 #pragma unroll
-        for (int t = 0; t < G; ++t) qf[t] = *reinterpret_cast<const bf16x8*>(qrow + 32 * t);
+        for (int f = 0; f < kF; ++f) qf[f] = *reinterpret_cast<const frag*>(qrow + 32 * f);
     }
-    const bool q_real = (vmask[qi] >> (32 * r + lq)) & 1ull;
 
+    // global -> LDS copy plan: see the attention kernels.
     uint32_t k_src[kLoads];
 #pragma unroll
     for (int j = 0; j < kLoads; ++j) {
-        const int inst = wave * kLoads + j;
-        const int krow = inst * (1024 / kRowB) + lane / kKChunks, kpos = lane % kKChunks;
-        k_src[j] = krow * kRowB + ((kpos ^ (rho(krow & 31) & (kKChunks - 1))) << 4);
+        const int krow = (wave * kLoads + j) * (1024 / kRowB) + lane / kKChunks, kpos = lane % kKChunks;
+        k_src[j] = krow * kRowB + ((kpos ^ (krow & (kKChunks - 1))) << 4) - 1024u * (j % kGroup);
     }
     const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
     const uint32_t wave_lds = smem_base + (uint32_t)wave * (kLoads * 1024);
-    const uint32_t k0 = smem_base + rho(lq) * kRowB + ((hh ^ (lq & (kKChunks - 1))) << 4);
-#define VEDA_LOAD_K(j_tile, SLOT)                                                                \
-    do {                                                                                         \
-        const char* src_ = kt + (int64_t)(j_tile) * kKBytes;                                     \
-        const uint32_t dst_ = wave_lds + (uint32_t)(SLOT) * kKBytes;                             \
-        _Pragma("unroll") for (int u_ = 0; u_ < kLoads; ++u_)                                    \
-            dma16_to_lds(dst_ + u_ * 1024, src_, k_src[u_]);                                     \
-    } while (0)
-#define VEDA_LOADS_DONE_BARRIER()               \
-    do {                                        \
-        __builtin_amdgcn_s_waitcnt(0x0F70);     \
-        __syncthreads();                        \
-    } while (0)
-
-    // ---- pass 1: row maximum m (log2 units) and denominator l of the full softmax ----
-    float m = -INFINITY, l = 0.0f;
-    VEDA_LOAD_K(0, 0);
-    VEDA_LOADS_DONE_BARRIER();
-    for (int j = 0; j < n; ++j) {
-        if (j + 1 < n) VEDA_LOAD_K(j + 1, (j + 1) & 1);
-        const uint64_t vm = vmask[j];
-        if (active) {
-            f32x16 s[2];
-            heat_logits<D>(s, qf, k0 + (uint32_t)((j & 1) * kKBytes), vm, hh);
-            // softmax_scale > 0: the largest logit is the largest dot product, scaled
-            // finite from j = 0 on: tile 0 starts at the grid origin (a later half tile of a ragged
-            // grid may be all padding: its logits are -inf and add nothing)
-            const float m_new = fmaxf(m, heat_row_max(s) * a.scale_log2);
-            float psum = 0.0f;
+    const uint32_t k0 = smem_base + idx * kRowB + ((hh ^ (idx & (kKChunks - 1))) << 4);
+    // step_kind of 64 key tiles at a time, one per lane; the next 64 masks are fetched a step before their turn
+    // (the wait for the tile loads that ends every step covers them).
+    struct Key { int kind; uint32_t lo, hi; };
+    const uint64_t* vmask_g = a.valid_mask + hg.tile_off;
+    uint64_t vm_next = 0ull;
+    Key k64;
+    auto fetch_masks = [&](int j) __attribute__((always_inline)) { vm_next = j + lane < n ? vmask_g[j + lane] : 0ull; };
+    auto key_of = [&](int j) __attribute__((always_inline)) {   // call for j = 0, 1, 2, ... in order
+        if ((j & 63) == 0) k64.kind = step_kind(vm_next, k64.lo, k64.hi);
+        Key e;
+        e.kind = __builtin_amdgcn_readlane(k64.kind, j & 63);
+        e.lo = (uint32_t)__builtin_amdgcn_readlane((int)k64.lo, j & 63);
+        e.hi = (uint32_t)__builtin_amdgcn_readlane((int)k64.hi, j & 63);
+        if ((j & 63) == 62) fetch_masks(j + 2);
+        return e;
+    };
+    auto load_k = [&](int j_tile, const Key& e, int sl) __attribute__((always_inline)) {
+        if (e.kind == kStepEmpty || (e.kind == kStepHalf && wave >= 2)) return;   // half: only the first 32 rows are read
+        const char* src = kt + (int64_t)j_tile * kKBytes;
+        uint32_t moved[2] = {0u, 0u};   // the eight-slot chunks of this wave's first and last eight rows, moved: by how much
+        if (e.kind == kStepHalf) {
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) psum += __builtin_amdgcn_exp2f(fmaf(s[c][i], a.scale_log2, -m_new));
-            l = l * __builtin_amdgcn_exp2f(m - m_new) + psum;
-            m = m_new;
-        }
-        VEDA_LOADS_DONE_BARRIER();
-    }
-    l = sum_with_other_half(l);                          // the two lane halves hold different keys
-    const float inv_l = 1.0f / l;
-
-    // ---- pass 2: block maxima of exp2(s - m) / l ----
-    // whole-tile score blocks hold a quarter of the half-tile ones
-    float* hrow = a.heat + b * a.score_elems + (kGrouped ? hg.score_off / 4 : hg.score_off);
-    float even_step = 0.0f;   // grouped: maximum of the even step of the current whole key tile
-    // publishes the block maxima of step jj (written before that step's barrier)
-    auto publish = [&](int jj) {
-        if (kGrouped) {
-            if (tid == 0) {
-                const float v = fmaxf(fmaxf(part[jj & 1][0], part[jj & 1][1]), fmaxf(part[jj & 1][2], part[jj & 1][3]));
-                if (jj & 1) hrow[(int64_t)(qiA >> 1) * (n >> 1) + (jj >> 1)] = fmaxf(even_step, v);
-                else even_step = v;
+            for (int u = 0; u < 2; ++u) {
+                const int c = 2 * wave + u;
+                moved[u] = (((e.hi >> (8 * c)) & 255u) - (uint32_t)c) * (8 * kRowB);
             }
-        } else if (tid < 2 && (tid == 0 || hasB)) {
-            hrow[(int64_t)(tid ? qiB : qiA) * n + jj] = fmaxf(part[jj & 1][2 * tid], part[jj & 1][2 * tid + 1]);
+        }
+#pragma unroll
+        for (int g = 0; g < kLoads / kGroup; ++g) {
+            uint32_t off[kGroup];
+#pragma unroll
+            for (int u = 0; u < kGroup; ++u) off[u] = k_src[g * kGroup + u] + moved[(g * kGroup + u) * 2 / kLoads];
+            dma16_group_to_lds<kGroup>(wave_lds + (uint32_t)sl * kKBytes + g * (kGroup * 1024), src, off);
         }
     };
-    VEDA_LOAD_K(0, 0);
-    VEDA_LOADS_DONE_BARRIER();
-    for (int j = 0; j < n; ++j) {
-        if (j + 1 < n) VEDA_LOAD_K(j + 1, (j + 1) & 1);
-        if (j > 0) publish(j - 1);
-        const uint64_t vm = vmask[j];
-        float blockmax = 0.0f;
-        if (active) {
-            f32x16 s[2];
-            heat_logits<D>(s, qf, k0 + (uint32_t)((j & 1) * kKBytes), vm, hh);
-            const float val = q_real ? __builtin_amdgcn_exp2f(fmaf(heat_row_max(s), a.scale_log2, -m)) * inv_l : 0.0f;
-            blockmax = wave_max(val);
+    // The walk over the key tiles: two K tiles in LDS, loads one step ahead.
+    Key e0, e1;
+    auto walk_begin = [&]() __attribute__((always_inline)) {
+        fetch_masks(0);
+        e0 = e1 = key_of(0);
+        load_k(0, e0, 0);
+        wait_vmcnt<0>();
+        __syncthreads();
+    };
+    auto step_begin = [&](int j) __attribute__((always_inline)) {
+        if (j + 1 < n) {
+            e1 = key_of(j + 1);
+            load_k(j + 1, e1, (j + 1) & 1);
         }
-        if (lane == 0) part[j & 1][wave] = blockmax;
-        VEDA_LOADS_DONE_BARRIER();
-    }
-    publish(n - 1);
-#undef VEDA_LOAD_K
-#undef VEDA_LOADS_DONE_BARRIER
-}
+    };
+    auto step_end = [&]() __attribute__((always_inline)) {
+        e0 = e1;
+        wait_vmcnt<0>();
+        __syncthreads();
+    };
+#define VEDA_KF(ka, f) (*(lds_frag_ptr)(uintptr_t)((ka) ^ (uint32_t)((f) << 5)))
 
-// fp32: thread (q = tid/4, part = tid%4) holds the logits of query row q against keys part+4e.
-template <int D>
-__global__ __launch_bounds__(256) void tile_heatmap_f32_kernel(HeatArgs a, float softmax_scale) {
-    constexpr int kPitch = D + 1;
-    __shared__ float ks[kTile * kPitch];
-    __shared__ float wmax[4];
-    const int tid = threadIdx.x, q = tid >> 2, part = tid & 3, wave = tid >> 6;
-    int head, qi;
-    if (a.query_tiles) {
-        if ((int64_t)blockIdx.x >= a.n_query_tiles) return;
-        const int g = a.query_tiles[blockIdx.x];
-        head = a.tile_head[g];
-        qi = g - a.heads[head].tile_off;
-    } else if (!xcd_work(a.xcd_cum, a.heads, a.n_heads, 1, head, qi)) {
-        return;
-    }
-    const HeadGeom hg = a.heads[head];
-    const int n = hg.n_tiles;
-    const int64_t b = blockIdx.y;
-    const int64_t head_tile0 = b * a.total_tiles + hg.tile_off;
-    const float* qrow = reinterpret_cast<const float*>(a.q) + ((head_tile0 + qi) * kTile + q) * D;
-    const float* kt = reinterpret_cast<const float*>(a.k) + head_tile0 * kTile * D;
-    const uint64_t* vmask = a.valid_mask + hg.tile_off;
-    const bool q_real = (vmask[qi] >> q) & 1ull;
-    float* hrow = a.heat + b * a.score_elems + hg.score_off + (int64_t)qi * n;
+    // Raw dot products of this wave's rows with the 32 keys at LDS address ka; `behind(f)` is vector work placed
+    // behind the products of fragment f.
+    auto products = [&](f32x16& s, uint32_t ka, auto behind) __attribute__((always_inline)) {
+        const f32x16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+        frag kf[kF];
+#pragma unroll
+        for (int f = 0; f < kAhead; ++f) kf[f] = VEDA_KF(ka, f);
+#pragma unroll
+        for (int f = 0; f < kF; ++f) {
+            if (f + kAhead < kF) kf[f + kAhead] = VEDA_KF(ka, f + kAhead);
+            s = F::mul(kf[f], qf[f], f == 0 ? zero : s);
+            behind(f);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // padded keys of a block: register i is key 8*(i/4) + 4*hh + i%4
+    auto mask_keys = [&](f32x16& s, uint32_t mask) __attribute__((always_inline)) {
+        if (mask == ~0u) return;
+        asm volatile("" ::: "memory");   // keeps this a branch, taken at edge tiles only
+        const uint32_t half = mask >> (4 * hh);
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (!((half >> (8 * (i >> 2) + (i & 3))) & 1u)) s[i] = -INFINITY;
+    };
+    // relative to ref, log2 units
+    auto logit = [&](float x, float ref) __attribute__((always_inline)) { return fmaf(x, a.scale_log2, -ref); };
 
-    float m = -INFINITY, l = 0.0f, inv_l = 0.0f;
-    for (int pass = 0; pass < 2; ++pass) {
-        for (int j = 0; j < n; ++j) {
-            const uint64_t vm = vmask[j];
-            const float* ksrc = kt + (int64_t)j * kTile * D;
-            __syncthreads();
-            for (int t = tid; t < kTile * D / 4; t += 256) {
-                const float4 kv = *reinterpret_cast<const float4*>(ksrc + 4 * t);
-                const int kr = (4 * t) / D, kc = (4 * t) % D;
-                float* dst = ks + kr * kPitch + kc;
-                dst[0] = kv.x; dst[1] = kv.y; dst[2] = kv.z; dst[3] = kv.w;
+    // ---- pass 1: reference (log2 units) and denominator of this lane's row over the keys of its lane half ----
+    // The denominator is kept as a finished part and that of the last kHeatFold steps, so that its rounding
+    // errors grow with the root of those, not of the key tiles.
+    float ref = kHeatNoRef, l = 0.0f, l_part = 0.0f;
+    // Adds a block's exponentials to the denominator: sum holds them at the present reference.  A row whose sum
+    // is out of range (in either lane half) first moves its reference to the block's maximum; the rule looks at
+    // the row alone, so results do not depend on which rows share a wave.
+    auto settle = [&](const f32x16& s, float sum) __attribute__((always_inline)) {
+        if (__builtin_expect(__any(!(sum <= kHeatSlack)), 0)) {
+            asm volatile("" ::: "memory");
+            const float over = max_with_other_half(sum <= kHeatSlack ? 0.0f : 1.0f);
+            float mx = s[0];
+#pragma unroll
+            for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
+            mx = max_with_other_half(mx) * a.scale_log2;
+            if (over > 0.0f && mx > ref) {
+                const float shrink = __builtin_amdgcn_exp2f(ref - mx);
+                l *= shrink;
+                l_part *= shrink;
+                ref = mx;
+                sum = 0.0f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) sum += __builtin_amdgcn_exp2f(logit(s[i], mx));
             }
-            __syncthreads();
-            float s[16];
+        }
+        l_part += sum;
+    };
+    walk_begin();
+    if (active) {
+        // s1 holds the block whose exponentials are still to come: they are formed behind the next products
+        f32x16 s0, s1;
+        float sum;
+        auto exps = [&](const f32x16& s, int f) __attribute__((always_inline)) {
+            if (f == 0) sum = 0.0f;
 #pragma unroll
-            for (int e = 0; e < 16; ++e) s[e] = 0.0f;
-            for (int cc = 0; cc < D; cc += 4) {
-                const float4 qv = *reinterpret_cast<const float4*>(qrow + cc);
+            for (int i = f * kExps; i < (f + 1) * kExps; ++i) sum += __builtin_amdgcn_exp2f(logit(s[i], ref));
+        };
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const float* kr = ks + (part + 4 * e) * kPitch + cc;
-                    s[e] = fmaf(qv.x, kr[0], s[e]);
-                    s[e] = fmaf(qv.y, kr[1], s[e]);
-                    s[e] = fmaf(qv.z, kr[2], s[e]);
-                    s[e] = fmaf(qv.w, kr[3], s[e]);
+        for (int i = 0; i < 16; ++i) s1[i] = -INFINITY;
+        for (int j = 0; j < n; ++j) {
+            step_begin(j);
+            const uint32_t ka = k0 + (uint32_t)((j & 1) * kKBytes);
+            if (e0.kind != kStepEmpty) {
+                products(s0, ka, [&](int f) __attribute__((always_inline)) { exps(s1, f); });
+                settle(s1, sum);
+                mask_keys(s0, e0.lo);
+                if (e0.kind == kStepHalf) {
+                    s1 = s0;
+                } else {
+                    products(s1, ka + 32 * kRowB, [&](int f) __attribute__((always_inline)) { exps(s0, f); });
+                    settle(s0, sum);   // before the mask's branch: the exponentials would move behind it
+                    mask_keys(s1, e0.hi);
                 }
             }
-            float mx = -INFINITY;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                s[e] = ((vm >> (part + 4 * e)) & 1ull) ? s[e] * softmax_scale : -INFINITY;
-                mx = fmaxf(mx, s[e]);
+            if ((j & (kHeatFold - 1)) == kHeatFold - 1) {
+                l += l_part;
+                l_part = 0.0f;
             }
-            mx = fmaxf(mx, __shfl_xor(mx, 1));
-            mx = fmaxf(mx, __shfl_xor(mx, 2));
-            if (pass == 0) {
-                const float m_new = fmaxf(m, mx);
-                float psum = 0.0f;
+            step_end();
+        }
 #pragma unroll
-                for (int e = 0; e < 16; ++e) psum += expf(s[e] - m_new);
-                psum += __shfl_xor(psum, 1);
-                psum += __shfl_xor(psum, 2);
-                l = l * expf(m - m_new) + psum;
-                m = m_new;
-            } else {
-                const float val = q_real ? expf(mx - m) * inv_l : 0.0f;
-                const float wm = wave_max(val);
-                if ((tid & 63) == 0) wmax[wave] = wm;
-                __syncthreads();
-                if (tid == 0) hrow[j] = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+        for (int f = 0; f < kF; ++f) exps(s1, f);
+        settle(s1, sum);
+    } else {   // a wave without rows loads and meets the others
+        for (int j = 0; j < n; ++j) {
+            step_begin(j);
+            step_end();
+        }
+    }
+    const float inv_l = 1.0f / sum_with_other_half(l + l_part);   // the lane halves hold different keys
+
+    // ---- pass 2: block maxima of exp2(s - ref) / l ----
+    // whole-tile score blocks hold a quarter of the half-tile ones
+    const int n_cols = kGrouped ? n >> 1 : n;
+    float* hrow = a.heat + b * a.score_elems + (kGrouped ? hg.score_off / 4 : hg.score_off) + (int64_t)(kGrouped ? qi >> 1 : qi) * n_cols;
+    float mine = 0.0f;   // block maximum of step 64*m + lane
+    // After the barrier that ends step j: every 64 steps, and at the end, the maxima go out in one store.
+    auto publish = [&](int j) __attribute__((always_inline)) {
+        if ((j & 63) != 63 && j != n - 1) return;
+        part[wave][lane] = mine;
+        __syncthreads();
+        float v = mine;
+        if (wave % kShare == 0) {
+#pragma unroll
+            for (int w = 1; w < kShare; ++w) v = fmaxf(v, part[wave + w][lane]);
+        }
+        __syncthreads();
+        if (wave % kShare == 0 && qi >= 0) {
+            const int first = j & ~63;
+            if (kGrouped) {
+                v = fmaxf(v, __shfl_xor(v, 1));
+                if (!(lane & 1) && first + lane <= j) hrow[(first + lane) >> 1] = v;
+            } else if (first + lane <= j) {
+                hrow[first + lane] = v;
             }
         }
-        inv_l = 1.0f / l;
+        mine = 0.0f;
+    };
+    walk_begin();
+    if (active) {
+        for (int j = 0; j < n; ++j) {
+            step_begin(j);
+            const uint32_t ka = k0 + (uint32_t)((j & 1) * kKBytes);
+            float best = 0.0f;
+            if (e0.kind != kStepEmpty) {
+                f32x16 s0, s1;
+                products(s0, ka, [](int) {});
+                mask_keys(s0, e0.lo);
+                float mx = s0[0];
+                auto maxima = [&](const f32x16& s, int f) __attribute__((always_inline)) {
+#pragma unroll
+                    for (int i = f * kExps; i < (f + 1) * kExps; ++i) mx = fmaxf(mx, s[i]);
+                };
+                if (e0.kind == kStepHalf) {
+                    s1 = s0;
+                } else {
+                    products(s1, ka + 32 * kRowB, [&](int f) __attribute__((always_inline)) { maxima(s0, f); });
+                    asm volatile("" : "+v"(mx));   // the maxima stay behind the products
+                    mask_keys(s1, e0.hi);
+                }
+#pragma unroll
+                for (int f = 0; f < kF; ++f) maxima(s1, f);
+                const float p = __builtin_amdgcn_exp2f(logit(max_with_other_half(mx), ref)) * inv_l;
+                best = rows_max(q_real ? p : 0.0f);
+            }
+            mine = lane == (j & 63) ? best : mine;
+            step_end();
+            publish(j);
+        }
+    } else {
+        for (int j = 0; j < n; ++j) {
+            step_begin(j);
+            step_end();
+            publish(j);
+        }
     }
+#undef VEDA_KF
 }
 
 // Recall@k: one wavefront per row counts the key tiles the two kept lists share (lists of
@@ -379,7 +467,6 @@ extern "C" veda_status veda_tile_heatmap(const veda_plan* pl, const void* q_tile
     HeatArgs a;
     a.heads = ip->d_heads;
     a.tile_head = ip->d_tile_head;
-    a.xcd_cum = bf16 ? ip->d_xcd_cum_pair : ip->d_xcd_cum;
     a.query_tiles = query_tiles;
     a.n_query_tiles = query_tiles ? n_query_tiles : 0;
     a.q = (const char*)q_tiled; a.k = (const char*)k_tiled;
@@ -390,21 +477,25 @@ extern "C" veda_status veda_tile_heatmap(const veda_plan* pl, const void* q_tile
     a.n_heads = pl->prob.heads;
     a.scale_log2 = softmax_scale * kLog2e;
     hipStream_t s = (hipStream_t)stream;
-    const int64_t items = query_tiles ? n_query_tiles : (int64_t)kXcd * (bf16 ? ip->xcd_max_pairs : ip->xcd_max_tiles);
+    a.xcd_cum = ip->d_xcd_cum_pair;
+    const int64_t items = query_tiles ? n_query_tiles : (int64_t)kXcd * ip->xcd_max_pairs;
     dim3 grid((unsigned)items, (unsigned)pl->prob.batch), block(256);
-    if (bf16) {
-        const size_t smem = (size_t)2 * kTile * d * 2 + 2 * 4 * sizeof(float);
-        if (pl->inner) {
-            if (d == 128) hipLaunchKernelGGL((tile_heatmap_bf16_kernel<128, true>), grid, block, smem, s, a);
-            else hipLaunchKernelGGL((tile_heatmap_bf16_kernel<64, true>), grid, block, smem, s, a);
-        } else {
-            if (d == 128) hipLaunchKernelGGL((tile_heatmap_bf16_kernel<128, false>), grid, block, smem, s, a);
-            else hipLaunchKernelGGL((tile_heatmap_bf16_kernel<64, false>), grid, block, smem, s, a);
-        }
+    const size_t smem = (size_t)2 * kTile * d * pl->elem_size() + 4 * 64 * sizeof(float);
+#define VEDA_LAUNCH_HEAT(E, DD, GG)                                                                      \
+    do {                                                                                                 \
+        auto kern = tile_heatmap_kernel<E, DD, GG>;                                                      \
+        if (smem > 64 * 1024)                                                                            \
+            VEDA_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem)); \
+        hipLaunchKernelGGL(kern, grid, block, smem, s, a);                                               \
+    } while (0)
+    if (bf16 && pl->inner) {
+        if (d == 128) VEDA_LAUNCH_HEAT(uint16_t, 128, true); else VEDA_LAUNCH_HEAT(uint16_t, 64, true);
+    } else if (bf16) {
+        if (d == 128) VEDA_LAUNCH_HEAT(uint16_t, 128, false); else VEDA_LAUNCH_HEAT(uint16_t, 64, false);
     } else {
-        if (d == 128) hipLaunchKernelGGL(tile_heatmap_f32_kernel<128>, grid, block, 0, s, a, softmax_scale);
-        else hipLaunchKernelGGL(tile_heatmap_f32_kernel<64>, grid, block, 0, s, a, softmax_scale);
+        if (d == 128) VEDA_LAUNCH_HEAT(uint32_t, 128, false); else VEDA_LAUNCH_HEAT(uint32_t, 64, false);
     }
+#undef VEDA_LAUNCH_HEAT
     return launch_status("veda_tile_heatmap");
 }
 

@@ -113,23 +113,17 @@ static veda_status build_plan(const veda_problem* p, const int32_t* shapes, int 
         for (int32_t i = 0; i < (pl->heads[h].n_tiles + 63) / 64; ++i) row_blk.push_back((int32_t)((uint32_t)h << 24 | (uint32_t)i));
     pl->row_blocks = (int64_t)row_blk.size();
 
-    // unit = 1: query tiles; unit = 2: pairs of adjacent query tiles
-    auto die_split = [&](int unit, int32_t& max_total) {
-        std::vector<int32_t> cum((size_t)veda::kXcd * (p->heads + 1), 0);
-        for (int x = 0; x < veda::kXcd; ++x) {
-            int32_t acc = 0;
-            for (int h = 0; h < p->heads; ++h) {
-                cum[(size_t)x * (p->heads + 1) + h] = acc;
-                const int32_t n = unit == 2 ? pl->heads[h].n_pairs : pl->heads[h].n_tiles;
-                acc += n / veda::kXcd + (x < n % veda::kXcd ? 1 : 0);
-            }
-            cum[(size_t)x * (p->heads + 1) + p->heads] = acc;
-            max_total = acc > max_total ? acc : max_total;
+    std::vector<int32_t> xcd_cum_pair((size_t)veda::kXcd * (p->heads + 1), 0);
+    for (int x = 0; x < veda::kXcd; ++x) {
+        int32_t acc = 0;
+        for (int h = 0; h < p->heads; ++h) {
+            xcd_cum_pair[(size_t)x * (p->heads + 1) + h] = acc;
+            const int32_t n = pl->heads[h].n_pairs;
+            acc += n / veda::kXcd + (x < n % veda::kXcd ? 1 : 0);
         }
-        return cum;
-    };
-    const std::vector<int32_t> xcd_cum = die_split(1, pl->xcd_max_tiles);
-    const std::vector<int32_t> xcd_cum_pair = die_split(2, pl->xcd_max_pairs);
+        xcd_cum_pair[(size_t)x * (p->heads + 1) + p->heads] = acc;
+        pl->xcd_max_pairs = acc > pl->xcd_max_pairs ? acc : pl->xcd_max_pairs;
+    }
 
     hipError_t e = hipGetDevice(&pl->device);
     if (e == hipSuccess) {
@@ -148,7 +142,6 @@ static veda_status build_plan(const veda_problem* p, const int32_t* shapes, int 
     if (e == hipSuccess) e = hipMalloc((void**)&pl->d_tile_n0, tile_n0.size() * sizeof(int32_t));
     if (e == hipSuccess)
         e = hipMemcpy(pl->d_tile_n0, tile_n0.data(), tile_n0.size() * sizeof(int32_t), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc((void**)&pl->d_xcd_cum, xcd_cum.size() * sizeof(int32_t));
     if (e == hipSuccess) e = hipMalloc((void**)&pl->d_row_blk, row_blk.size() * sizeof(int32_t));
     if (e == hipSuccess) e = hipMalloc((void**)&pl->d_xcd_cum_pair, xcd_cum_pair.size() * sizeof(int32_t));
     if (e == hipSuccess)
@@ -156,8 +149,6 @@ static veda_status build_plan(const veda_problem* p, const int32_t* shapes, int 
                       hipMemcpyHostToDevice);
     if (e == hipSuccess)
         e = hipMemcpy(pl->d_row_blk, row_blk.data(), row_blk.size() * sizeof(int32_t), hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-        e = hipMemcpy(pl->d_xcd_cum, xcd_cum.data(), xcd_cum.size() * sizeof(int32_t), hipMemcpyHostToDevice);
     if (e == hipSuccess)
         e = hipMemcpy(pl->d_heads, pl->heads.data(), sizeof(HeadGeom) * p->heads, hipMemcpyHostToDevice);
     if (e == hipSuccess)
@@ -205,7 +196,6 @@ void veda_plan_destroy(veda_plan* pl) {
     if (pl->d_heads) (void)hipFree(pl->d_heads);
     if (pl->d_tile_head) (void)hipFree(pl->d_tile_head);
     if (pl->d_tile_n0) (void)hipFree(pl->d_tile_n0);
-    if (pl->d_xcd_cum) (void)hipFree(pl->d_xcd_cum);
     if (pl->d_row_blk) (void)hipFree(pl->d_row_blk);
     if (pl->d_xcd_cum_pair) (void)hipFree(pl->d_xcd_cum_pair);
     delete pl;

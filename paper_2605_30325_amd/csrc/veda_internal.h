@@ -77,14 +77,11 @@ struct veda_plan {
     // items): d_row_blk[x] = head << 24 | block index inside the head.
     int32_t* d_row_blk = nullptr;       // device [row_blocks]
     int64_t row_blocks = 0;
-    // Work split of the attention launch: die x takes the x-th eighth of every head's query
-    // tiles, heads in order, so all dies work on the same head at the same time.
-    // d_xcd_cum[x*(heads+1) + h] = number of query tiles die x owns in heads < h.
-    int32_t* d_xcd_cum = nullptr;       // device [8][heads+1]
-    int32_t xcd_max_tiles = 0;          // max over dies of the die's total
-    // The same split over the pair work items of the heads (HeadGeom::n_pairs), for the pair kernels.
+    // Work split of the attention and heat-map launches: die x takes the x-th eighth of every head's pair work
+    // items (HeadGeom::n_pairs), heads in order, so all dies work on the same head at the same time.
+    // d_xcd_cum_pair[x*(heads+1) + h] = number of items die x owns in heads < h.
     int32_t* d_xcd_cum_pair = nullptr;  // device [8][heads+1]
-    int32_t xcd_max_pairs = 0;
+    int32_t xcd_max_pairs = 0;          // max over dies of the die's total
     int elem_size() const { return prob.dtype == VEDA_BF16 ? 2 : 4; }
     int64_t tokens() const { return (int64_t)prob.T * prob.H * prob.W; }
 };

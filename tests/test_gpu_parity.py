@@ -1028,6 +1028,36 @@ def test_target_heatmap_and_recall(dtype, d):
     assert bool((same == 1.0).all())
 
 
+@pytest.mark.parametrize("dtype,d,tile_tokens", [("bf16", 128, 64), ("bf16", 64, 64), ("bf16", 128, 128), ("f32", 128, 64), ("f32", 64, 64)])
+@pytest.mark.parametrize("grid", [(5, 9, 13), (17, 6, 7), (1, 5, 67), (9, 31, 33)])
+def test_target_heatmap_at_edge_tiles(dtype, d, tile_tokens, grid):
+    """Key tiles of every fill (half and empty steps), query tiles with fewer real rows than waves, more than 64
+    key tiles for some heads (maxima go out 64 at a time), and listed tiles in no order, an odd number per head."""
+    shapes = [(4, 4, 4), (1, 8, 8), (16, 2, 2), (64, 1, 1), (1, 1, 64)]
+    shapes = np.asarray([(2 * a, b, c) for a, b, c in shapes] if tile_tokens == 128 else shapes, np.int32)
+    wl = wlm.custom_workload("heat_edges", len(shapes), d, dtype, grid, False, (50, 100), seed=29)
+    dev = torch.device("cuda:0")
+    q, k, _ = wlm.make_qkv(wl, dev)
+    plan = veda.Plan(1, wl.heads, d, grid, shapes, wl.torch_dtype, tile_tokens=tile_tokens)
+    qt, vm, _ = veda.veda_tile_layout(plan, q, veda.VEDA_TOKEN_MAJOR)
+    kt, _, _ = veda.veda_tile_layout(plan, k, veda.VEDA_TOKEN_MAJOR, want_mask=False)
+    scale = 1.0 / math.sqrt(d)
+    heat = veda.veda_tile_heatmap(plan, qt, kt, vm, scale)
+    listed = torch.randperm(plan.total_tiles, generator=torch.Generator().manual_seed(1))[:plan.total_tiles // 2 | 1].to(torch.int32)
+    part = veda.veda_tile_heatmap(plan, qt, kt, vm, scale, listed.to(dev), torch.full_like(heat, -7.0))
+    torch.cuda.synchronize()
+    for h in range(wl.heads):
+        nt, soff, toff = plan.tiles[h], plan.score_offset[h], plan.tile_offset[h]
+        ref = vo.tile_heatmap(hz.to_f32_numpy(q[0, h]), hz.to_f32_numpy(k[0, h]), grid, tuple(int(x) for x in shapes[h]), scale)
+        got = heat[0, soff:soff + nt * nt].view(nt, nt)
+        rel = np.abs(got.cpu().numpy().astype(np.float64) - ref) / ref
+        assert rel.max() <= (2e-4 if dtype == "bf16" else 2e-5), (h, rel.max())
+        rows = [int(g) - toff for g in listed if toff <= int(g) < toff + nt]
+        others = np.setdiff1d(np.arange(nt), rows)
+        p = part[0, soff:soff + nt * nt].view(nt, nt)
+        assert torch.equal(p[rows], got[rows]) and bool((p[others] == -7.0).all())
+
+
 @pytest.mark.parametrize("dtype,tile_tokens", [("f32", 64), ("bf16", 64), ("bf16", 128)])
 def test_tiling_search_errors_and_choice(dtype, tile_tokens):
     # Alg. 1 on synthetic calibration tensors: error table against the oracle, same argmin where the
