@@ -3,8 +3,13 @@
 //
 // Same work split as the bf16 kernel: a workgroup of four wavefronts owns a pair of partner query
 // tiles and walks the union of their two kept lists; waves 0,1 hold rows 0-31 / 32-63 of tile A,
-// waves 2,3 those of tile B; K tiles ([64][d]) and V^T tiles ([d][64]) are double buffered in LDS
-// (2 x 64 KB at d = 128) and filled by direct global->LDS loads issued one step ahead.
+// waves 2,3 those of tile B.  The products of a step take 16384 matrix-pipe cycles per wave at d = 128, its
+// loads a sixteenth of that, so one K tile ([64][d]) and one V^T tile ([d][64]) in LDS are enough: the next K
+// tile lands while O^T is formed, the next V^T tile during S^T.  That leaves room for two workgroups on a
+// compute unit (2 x 74 KB at d = 128), and the second one's products fill the matrix pipe while a wave of the
+// first is in its softmax, at a barrier, or skips a key tile that only its partner keeps.  Padding is handled
+// as in the bf16 kernel (real query rows first; half steps, attn_union.h).
+// Measured: MEASURED
 //
 // Products are formed transposed with v_mfma_f32_32x32x2_f32 (S^T = K Q^T, O^T = V^T P^T): a lane
 // owns one query (lane % 32) and one of the two terms of every instruction (h = lane / 32).  The
@@ -26,17 +31,16 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef const __attribute__((address_space(3))) f32x4* lds_f32x4_ptr;
 __device__ __forceinline__ f32x4 lds_read_f32x4(uint32_t addr) { return *(lds_f32x4_ptr)(uintptr_t)addr; }
 
-constexpr int kF32Chunk = 256;   // step-table entries filled at a time
+constexpr int kF32Chunk = 128;   // step-table entries filled at a time
 
 // kTable: the steps come from the table in LDS (attn_union.h), as in the bf16 kernel; otherwise the two
 // lists are merged inside the loop (heads above 16384 tiles, VEDA_OPT_ATTN_LIST_WALK).
 template <int D, bool kTable>
-__global__ __launch_bounds__(256, 1) void sparse_attn_f32_kernel(AttnArgs a) {
+__global__ __launch_bounds__(256, 2) void sparse_attn_f32_kernel(AttnArgs a) {
     constexpr int kKPitch = D * 4;               // bytes of one K row
     constexpr int kKBytes = kTile * kKPitch;     // K tile
     constexpr int kVPitch = kTile * 4;           // bytes of one V^T row (64 keys)
     constexpr int kVBytes = D * kVPitch;         // V^T tile (same size)
-    constexpr int kSlot = kKBytes + kVBytes;
     constexpr int kKChunks = kKPitch / 16;       // 16-byte chunks per K row (32 or 16)
     constexpr int kLoads = kKBytes / 1024 / 4;   // direct loads per wave per tile: 8 (d = 128) or 4
     constexpr int kGroups = kLoads / 4;
@@ -46,7 +50,7 @@ __global__ __launch_bounds__(256, 1) void sparse_attn_f32_kernel(AttnArgs a) {
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int which = wave >> 1, r = wave & 1;
+    const int which = wave >> 1, r = (wave ^ __popc(blockIdx.x >> 3)) & 1;   // see the bf16 kernel
     const int idx = lane & 31, h = lane >> 5;
 
     int head, pair;
@@ -70,9 +74,14 @@ __global__ __launch_bounds__(256, 1) void sparse_attn_f32_kernel(AttnArgs a) {
     const char* vt = a.v + head_tile0 * kVBytes;
 
     // Q operand: lane (query 32r + idx, half h) holds channels 8m + 4h + t, scaled by softmax_scale*log2(e).
+    // Row 32r + idx is the tile's real slot of that rank; rows beyond the real slots read slot 0 and are not written.
+    const uint64_t q_real = __ballot(slot_token(hg, qi, lane, a.T, a.H, a.W) >= 0);
+    const int q_rows = __popcll(q_real);
     float qreg[D / 2];
     {
-        const float* qrow = reinterpret_cast<const float*>(a.q + (head_tile0 + qi) * kKBytes + (32 * r + idx) * kKPitch);
+        int slot = 32 * r + idx;
+        if (q_real != ~0ull) slot = slot < q_rows ? nth_bit(q_real, slot) : 0;
+        const float* qrow = reinterpret_cast<const float*>(a.q + (head_tile0 + qi) * kKBytes + slot * kKPitch);
 #pragma unroll
         for (int m = 0; m < kM; ++m) {
             const f32x4 v = *reinterpret_cast<const f32x4*>(qrow + 8 * m + 4 * h);
@@ -101,34 +110,59 @@ __global__ __launch_bounds__(256, 1) void sparse_attn_f32_kernel(AttnArgs a) {
     }
     const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
     const uint32_t wave_lds = smem_base + (uint32_t)wave * (kLoads * 1024);
-    auto load_tile = [&](int j_tile, int sl) __attribute__((always_inline)) {
+    struct Step { int j, fl; uint64_t vm; };   // vm: the mask, or step_kind's lo | hi << 32 (half steps)
+    constexpr int kKeepers = 3;
+    auto load_k = [&](const Step& e) __attribute__((always_inline)) {
+        if (!(e.fl & kKeepers)) return;
+        uint32_t moved[2] = {0u, 0u};   // half: the chunks of this wave's first and last eight rows, moved
+        if (e.fl & kStepHalf) {
+            if (wave >= 2) return;      // only the first 32 rows are read
 #pragma unroll
-        for (int g = 0; g < kGroups; ++g) {
-            uint32_t off[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) off[j] = k_src[4 * g + j];
-            dma16_group_to_lds<4>(wave_lds + (uint32_t)sl * kSlot + g * 4096, kt + (int64_t)j_tile * kKBytes, off);
+            for (int u = 0; u < 2; ++u) {
+                const int c = 2 * wave + u;
+                moved[u] = (((uint32_t)(e.vm >> (32 + 8 * c)) & 255u) - (uint32_t)c) * (8 * kKPitch);
+            }
         }
 #pragma unroll
         for (int g = 0; g < kGroups; ++g) {
             uint32_t off[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) off[j] = v_src[4 * g + j];
-            dma16_group_to_lds<4>(wave_lds + (uint32_t)sl * kSlot + kKBytes + g * 4096, vt + (int64_t)j_tile * kVBytes, off);
+            for (int j = 0; j < 4; ++j) off[j] = k_src[4 * g + j] + moved[(4 * g + j) * 2 / kLoads];
+            dma16_group_to_lds<4>(wave_lds + g * 4096, kt + (int64_t)e.j * kKBytes, off);
         }
     };
-    // LDS addresses of this lane's operand reads inside a slot, before the per-read XOR.
-    const uint32_t k_row0 = smem_base + idx * kKPitch;               // key block 0: row idx (block 1: + 32 rows)
-    const uint32_t v_row0 = smem_base + kKBytes + idx * kVPitch;     // channel block 0: row idx (block nb: + 32 nb rows)
+    const int v_c = (lane & 15) ^ (lane >> 4);   // this lane's 16-byte chunk (4 keys): v_c ^ 4*(j%4) in instruction j
+    auto load_v = [&](const Step& e) __attribute__((always_inline)) {
+        if (!(e.fl & kKeepers)) return;
+        uint32_t moved[4] = {0u, 0u, 0u, 0u};
+        if (e.fl & kStepHalf) {   // keys 0-31 from the chunks that hold real tokens; the others are not read
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t c = (uint32_t)(v_c ^ (4 * j));
+                const uint32_t from = (uint32_t)((e.vm >> 32) >> (8 * ((c >> 1) & 3))) & 255u;
+                moved[j] = c < 8 ? (from - (c >> 1)) * 32u : 0u;
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) {
+            uint32_t off[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) off[j] = v_src[4 * g + j] + moved[j];
+            dma16_group_to_lds<4>(wave_lds + kKBytes + g * 4096, vt + (int64_t)e.j * kVBytes, off);
+        }
+    };
+    // LDS addresses of this lane's first operand reads: the swizzle only touches bits the row offsets leave clear,
+    // so K chunk 2m + h is at k0 ^ (m << 5), V^T chunk 2g + h at v0 ^ (g << 5).
+    uint32_t k0 = smem_base + idx * kKPitch + (((uint32_t)h ^ (idx & (kKChunks - 1))) << 4);
+    uint32_t v0 = smem_base + kKBytes + idx * kVPitch + (((uint32_t)h ^ (idx & 15)) << 4);
 
     // The steps: the union of the two kept lists.  Table mode: laid out in LDS before the loop; walk mode:
     // merged with scalar loads as the loop goes (32-bit integers on the scalar unit; see the bf16 kernel).
     constexpr int kEnd = 0x7fffffff;
     int ia = 0, ib = 0;
     int rawA = 0, rawB = 0, okA = 0, okB = 0;
-    struct Step { int j, fl; uint64_t vm; };
     typedef UnionLds<2, kF32Chunk> Table;
-    Table& u = *reinterpret_cast<Table*>(smem + 2 * kSlot);
+    Table& u = *reinterpret_cast<Table*>(smem + kKBytes + kVBytes);
     const uint32_t tab_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)&u.tab[0];
     const uint64_t* vmask_g = a.valid_mask + hg.tile_off;
     const int32_t* n0s_g = a.tile_n0 + hg.tile_off;
@@ -138,8 +172,8 @@ __global__ __launch_bounds__(256, 1) void sparse_attn_f32_kernel(AttnArgs a) {
         const int32_t* lists[2] = {a.col_idx + begA, a.col_idx + begB};
         const int counts[2] = {nA, nB};
         total = union_build<2, 256, kF32Chunk>(u, lists, counts, hg.n_tiles, tid);
-        union_fill<2, 256, kF32Chunk, false, false>(u, 0, total, hg.n_tiles, vmask_g, n0s_g, tid);
-        union_fill<2, 256, kF32Chunk, false, false>(u, kF32Chunk, total, hg.n_tiles, vmask_g, n0s_g, tid);
+        union_fill<2, 256, kF32Chunk, false>(u, 0, total, hg.n_tiles, vmask_g, n0s_g, tid);
+        union_fill<2, 256, kF32Chunk, false>(u, kF32Chunk, total, hg.n_tiles, vmask_g, n0s_g, tid);
         __syncthreads();
         raw_next = union_read<kF32Chunk>(tab_lds, 0);
         s_read = 1;
@@ -162,8 +196,11 @@ __global__ __launch_bounds__(256, 1) void sparse_attn_f32_kernel(AttnArgs a) {
         const int live = jm != kEnd ? 1 : 0;
         const int ta = headA == jm ? live : 0, tb = headB == jm ? live : 0;
         e.j = __builtin_amdgcn_readfirstlane(live ? jm : 0);
-        e.fl = __builtin_amdgcn_readfirstlane(ta | (tb << 1));
-        e.vm = vmask[e.j];
+        const int fl = ta | (tb << 1);
+        uint32_t lo, hi;
+        const int kind = step_kind(vmask[e.j], lo, hi);
+        e.fl = __builtin_amdgcn_readfirstlane(fl == 0 ? 0 : kind == kStepEmpty ? kind : fl | kind);
+        e.vm = (uint64_t)hi << 32 | lo;
         ia += ta;
         ib += tb;
         okA = ia < nA ? 1 : 0;
@@ -172,99 +209,120 @@ __global__ __launch_bounds__(256, 1) void sparse_attn_f32_kernel(AttnArgs a) {
         rawB = colsB[okB ? ib : 0];
     };
 
-    const int my_bit = 1 << which;
-    Step e0, e1, e2;
+    const int my_bit = 32 * r < q_rows ? 1 << which : 64;   // 64: a bit no step has
+    // S^T block c = K Q^T: 32 keys x 32 queries
+    auto logits = [&](f32x16& s, int c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = 0.0f;
+#pragma unroll
+        for (int m = 0; m < kM; ++m) {
+            const f32x4 kf = lds_read_f32x4((k0 ^ (uint32_t)(m << 5)) + (uint32_t)(32 * c * kKPitch));
+#pragma unroll
+            for (int t = 0; t < 4; ++t) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[t], qreg[4 * m + t], s, 0, 0, 0);
+        }
+    };
+    // padded key slots: register i of a block is key 8*(i/4) + 4h + i%4
+    auto mask_keys = [&](f32x16& s, uint32_t mask) __attribute__((always_inline)) {
+        if (mask == ~0u) return;
+        asm volatile("" ::: "memory");   // keeps this a branch
+        const uint32_t half = mask >> (4 * h);
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (!((half >> (8 * (i >> 2) + (i & 3))) & 1u)) s[i] = -INFINITY;
+    };
+    // O^T += V^T P^T over the 32 keys of block c
+    auto outputs = [&](const f32x16& p, int c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const f32x4 vf = lds_read_f32x4((v0 ^ (uint32_t)((4 * c + j) << 5)) + (uint32_t)(32 * nb * kVPitch));
+#pragma unroll
+                for (int t = 0; t < 4; ++t) o[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[t], p[4 * j + t], o[nb], 0, 0, 0);
+            }
+        }
+    };
+    Step e0, e1;
     next_step(e0);
-    next_step(e1);
-    if (e0.fl) load_tile(e0.j, 0);
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the Q loads and the first tile
+    load_k(e0);
+    load_v(e0);
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the Q loads and the first tiles
     __syncthreads();
 
-    for (int P = 0; e0.fl; P ^= 1) {
-        if (e1.fl) load_tile(e1.j, P ^ 1);
-        next_step(e2);
-        if (e0.fl & my_bit) {
-            const uint32_t slot = (uint32_t)P * kSlot;
-            // S^T = K Q^T, two key blocks of 32
-            f32x16 s[2];
+    while (e0.fl) {
+        next_step(e1);
+        asm volatile("" : "+v"(k0), "+v"(v0));   // the addresses of the reads are formed as they are needed: kept, they would spill
+        const bool mine = (e0.fl & my_bit) != 0, full = !(e0.fl & kStepHalf);
+        f32x16 s0, s1;
+        if (mine) {
+            logits(s0, 0);
+            mask_keys(s0, (uint32_t)e0.vm);
+            if (full) {
+                logits(s1, 1);
+                mask_keys(s1, (uint32_t)(e0.vm >> 32));
+            } else {
 #pragma unroll
-            for (int c = 0; c < 2; ++c) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) s[c][i] = 0.0f;
-                const int krow = 32 * c + idx;
-                const uint32_t kaddr = k_row0 + slot + (uint32_t)(32 * c * kKPitch);
-#pragma unroll
-                for (int m = 0; m < kM; ++m) {
-                    const f32x4 kf = lds_read_f32x4(kaddr + (uint32_t)((((2 * m + h) ^ krow) & (kKChunks - 1)) << 4));
-#pragma unroll
-                    for (int t = 0; t < 4; ++t)
-                        s[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[t], qreg[4 * m + t], s[c], 0, 0, 0);
-                }
+                for (int i = 0; i < 16; ++i) s1[i] = -INFINITY;
             }
-            // padded key slots: register i of block c is key slot 32c + 8*(i/4) + 4h + i%4
+        }
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's loads of V^T have landed
+        __syncthreads();                      // everybody is done with K
+        load_k(e1);
+        if (mine) {
             float mx = -INFINITY;
-            const uint64_t vm = e0.vm;
 #pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                const uint32_t half = (uint32_t)(vm >> (32 * c)) >> (4 * h);
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    if (vm != ~0ull && !((half >> (8 * (i >> 2) + (i & 3))) & 1u)) s[c][i] = -INFINITY;
-                    mx = fmaxf(mx, s[c][i]);
-                }
-            }
+            for (int i = 0; i < 16; ++i) mx = fmaxf(mx, fmaxf(s0[i], s1[i]));
             mx = max_with_other_half(mx);
             const float m_new = fmaxf(m_run, mx);
             const float m_use = m_new == -INFINITY ? 0.0f : m_new;
             const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);   // 0 on the first step (m_run = -inf)
             float psum = 0.0f;
 #pragma unroll
-            for (int c = 0; c < 2; ++c)
+            for (int i = 0; i < 16; ++i) {
+                s0[i] = __builtin_amdgcn_exp2f(s0[i] - m_use);
+                psum += s0[i];
+            }
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    s[c][i] = __builtin_amdgcn_exp2f(s[c][i] - m_use);
-                    psum += s[c][i];
-                }
+            for (int i = 0; i < 16; ++i) {
+                s1[i] = __builtin_amdgcn_exp2f(s1[i] - m_use);
+                psum += s1[i];
+            }
             l_run = l_run * alpha + psum;
             m_run = m_new;
+            if (__any(alpha != 1.0f)) {
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
+                for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) o[nb][i] *= alpha;
-            // O^T += V^T P^T
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const int vrow = 32 * nb + idx;
-                const uint32_t vaddr = v_row0 + slot + (uint32_t)(32 * nb * kVPitch);
-#pragma unroll
-                for (int c = 0; c < 2; ++c)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const f32x4 vf = lds_read_f32x4(vaddr + (uint32_t)((((8 * c + 2 * j + h) ^ vrow) & 15) << 4));
-#pragma unroll
-                        for (int t = 0; t < 4; ++t)
-                            o[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[t], s[c][4 * j + t], o[nb], 0, 0, 0);
-                    }
+                    for (int i = 0; i < 16; ++i) o[nb][i] *= alpha;
             }
+            outputs(s0, 0);
+            if (full) outputs(s1, 1);
         }
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the next K tile
+        __syncthreads();                      // everybody is done with V^T
+        load_v(e1);
         e0 = e1;
-        e1 = e2;
-        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's loads of the next tiles have landed
-        __syncthreads();
         if constexpr (kTable) {   // the table's other half has been left behind: refill it
             ++s_done;
             if ((s_done & (kF32Chunk - 1)) == 0)
-                union_fill<2, 256, kF32Chunk, false, false>(u, s_done + kF32Chunk, total, hg.n_tiles, vmask_g, n0s_g, tid);
+                union_fill<2, 256, kF32Chunk, false>(u, s_done + kF32Chunk, total, hg.n_tiles, vmask_g, n0s_g, tid);
         }
     }
 
     // Normalise, transpose through LDS ([2 tiles][64 rows][D] fp32) and scatter the real rows.
     const float l_all = l_run + __shfl_xor(l_run, 32);
     const float inv = l_all > 0.0f ? 1.0f / l_all : 0.0f;
+    __syncthreads();   // nobody fills the step table any more
     float* obuf = reinterpret_cast<float*>(smem);
     float* lse_s = obuf + 2 * kTile * D;
     int* tok_s = reinterpret_cast<int*>(lse_s + 2 * kTile);
-    if (tid < 2 * kTile) tok_s[tid] = slot_token(hg, tid / kTile ? qiB : qiA, tid % kTile, a.T, a.H, a.W);
+    if (tid < 2 * kTile) {   // row c is the c-th real slot of its tile
+        const int slot = tid % kTile, base = tid - slot;
+        const int n = slot_token(hg, base ? qiB : qiA, slot, a.T, a.H, a.W);
+        const uint64_t real = __ballot(n >= 0);
+        if (slot >= __popcll(real)) tok_s[tid] = -1;
+        if (n >= 0) tok_s[base + __popcll(real & ((1ull << slot) - 1ull))] = n;
+    }
     {
         float* orow = obuf + (which * kTile + 32 * r + idx) * D;
 #pragma unroll
@@ -299,8 +357,11 @@ veda_status launch_sparse_attn_f32(const veda_plan* pl, const AttnArgs& a, bool 
     dim3 grid((unsigned)(kXcd * pl->xcd_max_pairs), (unsigned)pl->prob.batch), block(256);
     bool table = !walk;   // the step table's bitmaps cover 16384 tiles per head
     for (const HeadGeom& g : pl->heads) table = table && g.n_tiles <= kUnionMaxTiles;
-    // two slots of (K tile + V^T tile), then the step table
-    const size_t smem = (size_t)2 * 2 * kTile * d * 4 + (table ? sizeof(UnionLds<2, kF32Chunk>) : 0);
+    // a K tile and a V^T tile, then the step table; at the end, over all of them, the two output tiles with
+    // their softmax sums and token numbers
+    const size_t tiles = (size_t)2 * kTile * d * 4, out = tiles + 2 * kTile * (sizeof(float) + sizeof(int));
+    const size_t with_table = tiles + (table ? sizeof(UnionLds<2, kF32Chunk>) : 0);
+    const size_t smem = with_table > out ? with_table : out;
 #define VEDA_LAUNCH_F32(DD, TT)                                                                          \
     do {                                                                                                 \
         auto kern = sparse_attn_f32_kernel<DD, TT>;                                                      \

@@ -308,8 +308,8 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
         const int32_t* lists[2] = {a.col_idx + begA, a.col_idx + begB};
         const int counts[2] = {nA, kGrouped ? 0 : nB};
         total = union_build<2, 256, kPairChunk>(u, lists, counts, list_range, tid) * (kGrouped ? 2 : 1);
-        union_fill<2, 256, kPairChunk, kGrouped, true>(u, 0, total, list_range, vmask_g, n0s_g, tid);
-        union_fill<2, 256, kPairChunk, kGrouped, true>(u, kPairChunk, total, list_range, vmask_g, n0s_g, tid);
+        union_fill<2, 256, kPairChunk, kGrouped>(u, 0, total, list_range, vmask_g, n0s_g, tid);
+        union_fill<2, 256, kPairChunk, kGrouped>(u, kPairChunk, total, list_range, vmask_g, n0s_g, tid);
         __syncthreads();
     } else {
         rawA = colsA[0];
@@ -367,7 +367,7 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
         if constexpr (kTable) {
             ++s_done;
             if ((s_done & (kPairChunk - 1)) == 0)
-                union_fill<2, 256, kPairChunk, kGrouped, true>(u, s_done + kPairChunk, total, list_range, vmask_g, n0s_g, tid);
+                union_fill<2, 256, kPairChunk, kGrouped>(u, s_done + kPairChunk, total, list_range, vmask_g, n0s_g, tid);
         }
     };
     if constexpr (kTable) next_advance();   // entry 0 on its way

@@ -132,9 +132,8 @@ __device__ inline int union_build(UnionLds<N, kChunk>& u, const int32_t* const (
 // (entry s lives at s % (2 kChunk)).  No barrier inside: the caller separates it from the readers
 // of these places.  total: number of steps.  kGrouped: the lists name whole 128-token tiles and
 // every kept one makes two steps, its 64-slot halves 2o and 2o+1 (vmask, n0s are indexed by half),
-// kept by all N query tiles alike.  kHalf: mark half and empty steps (a kernel without them takes every
-// tile whole).
-template <int N, int kThreads, int kChunk, bool kGrouped, bool kHalf>
+// kept by all N query tiles alike.
+template <int N, int kThreads, int kChunk, bool kGrouped>
 __device__ inline void union_fill(UnionLds<N, kChunk>& u, int first, int total, int n_tiles, const uint64_t* __restrict__ vmask,
                                   const int32_t* __restrict__ n0s, int tid) {
     const int words = (n_tiles + 31) >> 5;
@@ -162,10 +161,7 @@ __device__ inline void union_fill(UnionLds<N, kChunk>& u, int first, int total, 
 #pragma unroll
             for (int t = 0; t < N; ++t) fl |= (int)((b[t] >> bit) & 1u) << t;
             if (kGrouped) fl = (1 << N) - 1;
-            const uint64_t vm = vmask[j];
-            int kind = 0;
-            if (kHalf) kind = step_kind(vm, e.z, e.w);
-            else { e.z = (uint32_t)vm; e.w = (uint32_t)(vm >> 32); }
+            const int kind = step_kind(vmask[j], e.z, e.w);
             e.x = j | ((kind == kStepEmpty ? kind : fl | kind) << 16);
             e.y = n0s[j];
         }
