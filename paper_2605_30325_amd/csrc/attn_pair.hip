@@ -93,7 +93,7 @@ __device__ __forceinline__ void finish_pair(const PairState<D>& st, const AttnAr
 // One step of the merged walk over the kept lists of the two query tiles of a workgroup.
 struct MergedStep {
     int j;         // key tile (head-local)
-    int fl;        // bit 0: tile A keeps it, bit 1: tile B keeps it; kStepHalf, kStepEmpty; 0 = past the end
+    int fl;        // bit 0: tile A keeps it, bit 1: tile B keeps it; the kind of step; 0 = past the end
     uint64_t vm;   // validity mask of key tile j; half steps: gathered mask | source chunks << 32
     int n0;        // K from token order: token index of its slot 0
 };
@@ -228,13 +228,17 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     auto chunk_off = [&](uint32_t c) __attribute__((always_inline)) {
         return ((c & 1u) ? k_chunk[0] : 0u) + ((c & 2u) ? k_chunk[1] : 0u) + ((c & 4u) ? k_chunk[2] : 0u);
     };
-    // The K tile (which = 0) or the V^T tile (which = 1) of step e into LDS slot `sl`.
+    // The K tile (what = 0) or the V^T tile (what = 1) of step e into LDS slot `sl`; nothing past the end.
+    constexpr int kKeepers = 3;
     auto load_tile = [&](const MergedStep& e, int sl, int what) __attribute__((always_inline)) {
         uint32_t off[kLoads];
         if (what == 0) {
             const char* src = (kTokK ? kt + (int64_t)e.n0 * a.sk_n : kt + (int64_t)e.j * kKBytes) - kBias;
             const uint32_t dst = wave_lds + (uint32_t)sl * kSlot;
-            if (e.fl & kStepHalf) {   // the first 32 rows, from the chunks that hold real tokens
+            if (__builtin_expect(e.fl & kStepWhole, 1)) {
+                dma16_group_to_lds<kLoads>(dst, src, k_src);
+            } else if (!(e.fl & kKeepers)) {
+            } else if (e.fl & kStepHalf) {   // the first 32 rows, from the chunks that hold real tokens
                 if (wave < 2) {
                     const uint32_t from = (uint32_t)(e.vm >> 32);
 #pragma unroll
@@ -255,7 +259,10 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
         } else {
             const uint32_t dst = wave_lds + (uint32_t)sl * kSlot + kKBytes;
             const char* src = vt + (int64_t)e.j * kVBytes;
-            if (e.fl & kStepHalf) {   // chunks 0-3 from where the real tokens are; chunks 4-7 are not read
+            if (__builtin_expect(e.fl & kStepWhole, 1)) {
+                dma16_group_to_lds<kLoads>(dst, src, v_src);
+            } else if (!(e.fl & kKeepers)) {
+            } else if (e.fl & kStepHalf) {   // chunks 0-3 from where the real tokens are; chunks 4-7 are not read
                 const uint32_t from = ((uint32_t)(e.vm >> 32) >> (8 * (v_c & 3))) & 255u;
                 const uint32_t delta = (from - (uint32_t)(v_c & 3)) << 4;
 #pragma unroll
@@ -373,17 +380,14 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     if constexpr (kTable) next_advance();   // entry 0 on its way
 
     // Step s (P = s & 1) computes on slot P while the tiles of step s+1 land in slot P^1.
-    constexpr int kKeepers = 3;
-    const int my_bit = 32 * r < q_rows ? 1 << which : 64;   // 64: a bit no step has
+    const int my_bit = 32 * r < q_rows ? 1 << which : 128;   // 128: a bit no step has
     MergedStep e0, e1, e2;
     next_head(e0);
     next_advance();
     next_head(e1);
     next_advance();
-    if (e0.fl & kKeepers) {
-        load_tile(e0, 0, 0);
-        load_tile(e0, 0, 1);
-    }
+    load_tile(e0, 0, 0);
+    load_tile(e0, 0, 1);
     VEDA_LOADS_DONE_BARRIER();   // also the Q loads: nothing vector-memory is pending below
 
     // One step.  A wave whose query tile keeps the current key tile does its housekeeping (loads of
@@ -397,9 +401,9 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
             PairStep<D, kExact> w;                                                                       \
             w.begin(fa, (uint32_t)((P) * kSlot));                                                        \
             w.template block0<0>(st);                                                                    \
-            if (e1.fl & kKeepers) load_tile(e1, (P) ^ 1, 0);                                             \
+            load_tile(e1, (P) ^ 1, 0);                                                                   \
             w.template block0<1>(st);                                                                    \
-            if (e1.fl & kKeepers) load_tile(e1, (P) ^ 1, 1);                                             \
+            load_tile(e1, (P) ^ 1, 1);                                                                   \
             w.template block0<2>(st);                                                                    \
             next_head(e2);                                                                               \
             w.template block0<3>(st);                                                                    \
@@ -409,10 +413,8 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
         }                                                                                                \
         asm volatile("" : "+s"(todo));                                                                   \
         if (todo) {                                                                                      \
-            if (e1.fl & kKeepers) {                                                                      \
-                load_tile(e1, (P) ^ 1, 0);                                                               \
-                load_tile(e1, (P) ^ 1, 1);                                                               \
-            }                                                                                            \
+            load_tile(e1, (P) ^ 1, 0);                                                                   \
+            load_tile(e1, (P) ^ 1, 1);                                                                   \
             next_head(e2);                                                                               \
             next_advance();                                                                              \
             if (e0.fl & my_bit) pair_half_step<D, kExact>(st, fa, (uint32_t)((P) * kSlot), (uint32_t)e0.vm); \

@@ -32,14 +32,15 @@ constexpr int kUnionMaxTiles = kUnionMaxWords * 32;
 // What a step does with its key tile, beside the keeper bits 0..3 of its flags.
 constexpr int kStepHalf = 16;    // one 32-key block after gathering chunks
 constexpr int kStepEmpty = 32;   // nothing to attend to
+constexpr int kStepWhole = 64;   // no padding: the common case, told apart by one test
 
-// Validity mask of a key tile -> kind of step (0 = full).  Half: lo = mask of the 32 gathered slots, hi = the
+// Validity mask of a key tile -> kind of step (0: both blocks, some padding).  Half: lo = mask of the 32 gathered slots, hi = the
 // four chunks they come from, one byte each (places without a chunk name one that is all padding: V is zero
 // there).  Otherwise lo, hi = the mask itself.
 __device__ __forceinline__ int step_kind(uint64_t vm, uint32_t& lo, uint32_t& hi) {
     lo = (uint32_t)vm;
     hi = (uint32_t)(vm >> 32);
-    if (vm == ~0ull) return 0;
+    if (vm == ~0ull) return kStepWhole;
     uint32_t mask = 0u, from = 0u, none = 0u;
     int n = 0;
     for (int c = 0; c < 8; ++c) {
@@ -172,7 +173,7 @@ __device__ inline void union_fill(UnionLds<N, kChunk>& u, int first, int total, 
 // One step as the main loop holds it (all fields wave-uniform, in scalar registers).
 struct UnionStep {
     int j;         // key tile (head-local)
-    int fl;        // bit t: query tile t of the workgroup keeps it; kStepHalf, kStepEmpty; 0 = past the end
+    int fl;        // bit t: query tile t of the workgroup keeps it; its kind; 0 = past the end
     uint64_t vm;   // validity mask of key tile j; half steps: step_kind's lo | hi << 32
     int n0;        // token index of its slot 0
 };
