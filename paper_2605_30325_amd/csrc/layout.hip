@@ -99,15 +99,41 @@ __global__ void valid_cnt_pairs_kernel(const uint64_t* __restrict__ mask, int32_
 
 // Token-major tiling with the TripPool descriptors (Eq. 4: Avg | Max | Min over the tile's real
 // tokens, per channel) taken on the way, so the tiled tensor is not read back for them.
-// One thread owns 16 bytes of the channel axis of one tile and walks its 64 slots in order:
-// the sum is the same slot-ascending fp32 chain the scoring stage uses, so the descriptors are
-// bit-identical to the ones it derives from the tiled tensor.  A workgroup holds 256 / (D / kN)
-// consecutive global tiles (they may belong to different heads).
+// One thread owns four channels of one tile and walks its 64 slots in order: the sum is the same
+// slot-ascending fp32 chain the scoring stage uses, so the descriptors are bit-identical to the ones it
+// derives from the tiled tensor.  A workgroup holds 256 / (D / 4) consecutive global tiles (they may belong
+// to different heads).
+// Bound by the latency of the loads on small inputs and by memory on large ones, so the rows of kBatch slots
+// are requested before the first is used, padded ones included (from token 0), and four channels instead of
+// eight bf16 ones make twice the wavefronts.  Measured, 8 slots at a time with 16-byte loads and now: 4 heads of
+// 75 tiles, 2 samples (bf16, d = 64) 26 -> 11 us; 12 heads of 624 tiles (bf16, d = 128) 40 -> 23 us, writing tiles
+// 43 -> 39; 24 heads of 219,600 tokens 305 -> 272 us (4.9 TB/s), writing tiles 625 -> 527 (5.1 TB/s).  Without the
+// tiles half a batch is enough (more wavefronts: 12 heads 26 us with a whole one, 4 heads alike).
 // kWrite = false: descriptors (and masks) only, the tiled tensor is not written.
 // GRP = 2: 128-token tiles.  `heads`, `tile_head` and total_tiles are then those of the 64-slot
 // halves (halves 2g, 2g+1 of whole tile g); a thread walks the 128 slots of a whole tile in order
 // (first half, then second half: the oracle's raster slot order), the mask has two words per tile,
 // and the tiled output [tile][128][channel] is the two halves back to back.
+template <typename E> struct Quad;   // four channels
+template <> struct Quad<uint16_t> {
+    typedef uint2 raw;
+    static constexpr int kBatch = 32;
+    __device__ static void unpack(const uint2& u, float* f) {
+        f[0] = __uint_as_float(u.x << 16);
+        f[1] = __uint_as_float(u.x & 0xffff0000u);
+        f[2] = __uint_as_float(u.y << 16);
+        f[3] = __uint_as_float(u.y & 0xffff0000u);
+    }
+};
+template <> struct Quad<uint32_t> {
+    typedef uint4 raw;
+    static constexpr int kBatch = 16;
+    __device__ static void unpack(const uint4& u, float* f) {
+        f[0] = __uint_as_float(u.x); f[1] = __uint_as_float(u.y);
+        f[2] = __uint_as_float(u.z); f[3] = __uint_as_float(u.w);
+    }
+};
+
 #pragma clang fp contract(off)
 template <typename E, int D, bool kWrite, int GRP>
 __global__ __launch_bounds__(256) void layout_stats_kernel(
@@ -115,8 +141,9 @@ __global__ __launch_bounds__(256) void layout_stats_kernel(
     const char* __restrict__ x, int64_t sb, int64_t sh, int64_t sn, char* __restrict__ out,
     float* __restrict__ stats, int64_t total_tiles, int T, int H, int W,
     uint64_t* __restrict__ valid_mask, int32_t* __restrict__ valid_cnt, RecipTable recip) {
-    constexpr int kN = Chunk<E>::kN;
-    constexpr int kTpt = D / kN;            // threads per tile
+    typedef typename Quad<E>::raw raw;
+    constexpr int kBatch = kWrite ? Quad<E>::kBatch : Quad<E>::kBatch / 2;
+    constexpr int kTpt = D / 4;             // threads per tile
     constexpr int kTiles = 256 / kTpt;      // tiles per workgroup
     constexpr int kRowBytes = D * (int)sizeof(E);
     constexpr int kSlots = kTile * GRP;     // slots of a whole tile
@@ -135,51 +162,66 @@ __global__ __launch_bounds__(256) void layout_stats_kernel(
         tok[tl][l] = n;
     }
     __syncthreads();
-    const int tl = threadIdx.x / kTpt, chunk = threadIdx.x % kTpt;
+    const int tl = threadIdx.x / kTpt, quad = threadIdx.x % kTpt;
     const int64_t g = g0 + tl;
     if (g >= whole_tiles) return;
     const int head = tile_head[g * GRP];
-    const char* xb = x + b * sb + head * sh + chunk * 16;
+    const char* xb = x + b * sb + head * sh + quad * sizeof(raw);
     const int64_t row = (int64_t)b * whole_tiles + g;
-    char* ob = out + row * (int64_t)kSlots * kRowBytes + chunk * 16;
-    float sum[kN], mx[kN], mn[kN];
+    char* ob = out + row * (int64_t)kSlots * kRowBytes + quad * sizeof(raw);
+    float sum[4], mx[4], mn[4];
 #pragma unroll
-    for (int j = 0; j < kN; ++j) { sum[j] = 0.0f; mx[j] = -INFINITY; mn[j] = INFINITY; }
+    for (int j = 0; j < 4; ++j) { sum[j] = 0.0f; mx[j] = -INFINITY; mn[j] = INFINITY; }
+    auto take = [&](const raw& v) __attribute__((always_inline)) {
+        float f[4];
+        Quad<E>::unpack(v, f);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            sum[j] = sum[j] + f[j];
+            mx[j] = f[j] > mx[j] ? f[j] : mx[j];
+            mn[j] = f[j] < mn[j] ? f[j] : mn[j];
+        }
+    };
     uint64_t mask[GRP];
 #pragma unroll
     for (int w = 0; w < GRP; ++w) {
         mask[w] = 0ull;
-#pragma unroll 8
-        for (int l = 0; l < kTile; ++l) {
-            const int n = tok[tl][w * kTile + l];
-            uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (n >= 0) {
-                v = *reinterpret_cast<const uint4*>(xb + (int64_t)n * sn);
-                mask[w] |= 1ull << l;
-                float f[kN];
-                Chunk<E>::unpack(v, f);
+        for (int l0 = 0; l0 < kTile; l0 += kBatch) {
+            uint32_t real = 0u;
+            raw v[kBatch];
 #pragma unroll
-                for (int j = 0; j < kN; ++j) {
-                    sum[j] = sum[j] + f[j];
-                    mx[j] = f[j] > mx[j] ? f[j] : mx[j];
-                    mn[j] = f[j] < mn[j] ? f[j] : mn[j];
+            for (int i = 0; i < kBatch; ++i) {
+                const int n = tok[tl][w * kTile + l0 + i];
+                real |= n >= 0 ? 1u << i : 0u;
+                v[i] = *reinterpret_cast<const raw*>(xb + (int64_t)(n >= 0 ? n : 0) * sn);
+            }
+            mask[w] |= (uint64_t)real << l0;
+            constexpr uint32_t kAll = kBatch == 32 ? ~0u : (1u << (kBatch & 31)) - 1u;
+            if (__all(real == kAll)) {
+#pragma unroll
+                for (int i = 0; i < kBatch; ++i) take(v[i]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < kBatch; ++i) {
+                    if ((real >> i) & 1u) take(v[i]);
+                    else v[i] = raw{};
                 }
             }
-            if (kWrite) *reinterpret_cast<uint4*>(ob + (w * kTile + l) * kRowBytes) = v;
+            if (kWrite) {
+#pragma unroll
+                for (int i = 0; i < kBatch; ++i) *reinterpret_cast<raw*>(ob + (w * kTile + l0 + i) * kRowBytes) = v[i];
+            }
         }
     }
     int cnt = 0;
 #pragma unroll
     for (int w = 0; w < GRP; ++w) cnt += __popcll(mask[w]);
     const float inv = recip.v[cnt];
-    float* z = stats + row * (3 * D) + chunk * kN;
-#pragma unroll
-    for (int j = 0; j < kN; ++j) {
-        z[j] = sum[j] * inv;
-        z[D + j] = mx[j];
-        z[2 * D + j] = mn[j];
-    }
-    if (chunk == 0 && b == 0) {
+    float* z = stats + row * (3 * D) + quad * 4;
+    *reinterpret_cast<float4*>(z) = make_float4(sum[0] * inv, sum[1] * inv, sum[2] * inv, sum[3] * inv);
+    *reinterpret_cast<float4*>(z + D) = make_float4(mx[0], mx[1], mx[2], mx[3]);
+    *reinterpret_cast<float4*>(z + 2 * D) = make_float4(mn[0], mn[1], mn[2], mn[3]);
+    if (quad == 0 && b == 0) {
         if (valid_mask) {
 #pragma unroll
             for (int w = 0; w < GRP; ++w) valid_mask[g * GRP + w] = mask[w];
@@ -255,7 +297,7 @@ extern "C" veda_status veda_tile_layout_stats(const veda_plan* pl, const void* x
                        valid_mask, valid_cnt, recip)
 #define VEDA_LAUNCH_LS(E, D)                                                                              \
     do {                                                                                                  \
-        constexpr int tiles = 256 / (D / Chunk<E>::kN);                                                   \
+        constexpr int tiles = 256 / (D / 4);                                                   \
         dim3 grid((unsigned)((pl->total_tiles + tiles - 1) / tiles), (unsigned)pl->prob.batch);           \
         if (pl->inner) {                                                                                  \
             if (x_tiled) VEDA_LAUNCH_LS2(E, D, true, 2);                                                  \
