@@ -286,12 +286,15 @@ __global__ __launch_bounds__(256) void fused_fallback_kernel(const HeadGeom* __r
                                                              int32_t* __restrict__ col_idx,
                                                              const int32_t* __restrict__ flags, int64_t total_tiles,
                                                              int64_t score_elems, int64_t rows) {
-    // one wavefront looks after kFallbackRows rows: a launch of a few workgroups that costs next to
-    // nothing when no flag is up, which is the usual case
+    // One wavefront looks after kFallbackRows rows: a launch of a few workgroups that costs next to nothing when
+    // no flag is up, which is the usual case.  The rows are a grid's width apart, since flagged rows come in
+    // runs (40 heads of 1240 tiles, 20 % kept: 459 us with neighbouring rows, 83 us so).
     const int lane = threadIdx.x & 63;
-    const int64_t first = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kFallbackRows;
-    for (int64_t row = first; row < first + kFallbackRows && row < rows; ++row) {
-        if (!flags[row]) continue;
+    const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6), waves = (int64_t)gridDim.x * 4;
+    const int64_t mine = wave + lane * waves;
+    uint64_t todo = __ballot(lane < kFallbackRows && mine < rows && flags[mine < rows ? mine : 0]);
+    for (; todo; todo &= todo - 1ull) {
+        const int64_t row = wave + (__ffsll((unsigned long long)todo) - 1) * waves;
         const RowInfo ri = locate_row(heads, tile_head, scratch, args, row_ptr, col_idx, total_tiles, score_elems,
                                       rows, row, lane);
         // keep the row in registers when it fits, instead of re-reading it on every pass
