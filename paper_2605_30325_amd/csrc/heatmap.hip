@@ -401,13 +401,19 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
 #undef VEDA_KF
 }
 
-// Recall@k: one wavefront per row counts the key tiles the two kept lists share (lists of
+// Recall@k: a wavefront counts, row by row, the key tiles the two kept lists share (lists of
 // distinct tiles in any order); integer atomics keep the per-head totals order-independent.
+// The tiles of list b become a bitmap in LDS that those of list a are looked up in (12 heads
+// of 624 rows at k = 63: 85 us comparing all pairs, 22 us so; 40 heads of 21x45x80, 5 % kept: 516 and 89 us).  Rows longer than the
+// bitmap, or with an entry that is no tile of theirs, compare all pairs.
 struct RecallArgs {
     int32_t k[kMaxHeads];
     int64_t col_off[kMaxHeads];
     int64_t nnz_per_batch;
 };
+
+constexpr int kRecallWords = 512;   // bitmap words of a row: 16384 key tiles
+constexpr int kRecallRows = 4;      // consecutive rows of a wavefront, to save atomics on the totals
 
 __global__ __launch_bounds__(256) void recall_count_kernel(const HeadGeom* __restrict__ heads,
                                                            const uint8_t* __restrict__ tile_head, RecallArgs args,
@@ -415,23 +421,59 @@ __global__ __launch_bounds__(256) void recall_count_kernel(const HeadGeom* __res
                                                            const int32_t* __restrict__ col_b,
                                                            unsigned long long* __restrict__ counts,
                                                            int64_t total_tiles, int64_t rows, int n_heads) {
+    __shared__ uint32_t bitmap[4][kRecallWords];
     const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= rows) return;
-    const int64_t b = row / total_tiles, g = row - b * total_tiles;
-    const int head = tile_head[g];
-    const int k = args.k[head];
-    const int64_t off = b * args.nnz_per_batch + args.col_off[head] + (g - heads[head].tile_off) * k;
-    const int32_t* la = col_a + off;
-    const int32_t* lb = col_b + off;
+    uint32_t* bits = bitmap[threadIdx.x >> 6];
+    const int64_t first = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kRecallRows;
+    int64_t total_of = -1;   // (batch, head) that `common` counts for
     int common = 0;
-    for (int x = 0; x < k; ++x) {
-        const int want = la[x];
-        bool hit = false;
-        for (int y = lane; y < k; y += 64) hit |= lb[y] == want;
-        common += __any(hit) ? 1 : 0;
+    auto sync = []() {   // LDS of one wavefront: its own operations in order
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    for (int64_t row = first; row < first + kRecallRows && row < rows; ++row) {
+        const int64_t b = row / total_tiles, g = row - b * total_tiles;
+        const int head = tile_head[g], n = heads[head].n_tiles;
+        const int k = args.k[head];
+        if (b * n_heads + head != total_of) {
+            if (lane == 0 && common) atomicAdd(&counts[total_of], (unsigned long long)common);
+            total_of = b * n_heads + head;
+            common = 0;
+        }
+        const int64_t off = b * args.nnz_per_batch + args.col_off[head] + (g - heads[head].tile_off) * k;
+        const int32_t* la = col_a + off;
+        const int32_t* lb = col_b + off;
+        bool strange = n > 32 * kRecallWords;
+        if (!strange) {
+            for (int w = lane; w < (n + 31) / 32; w += 64) bits[w] = 0u;
+            sync();
+            for (int y = lane; y < k; y += 64) {
+                const int v = lb[y];
+                if ((unsigned)v < (unsigned)n) atomicOr(&bits[v >> 5], 1u << (v & 31));
+                else strange = true;
+            }
+            sync();
+            int hits = 0;
+            for (int x = lane; x - lane < k; x += 64) {
+                const int v = x < k ? la[x] : 0;
+                if ((unsigned)v >= (unsigned)n) strange = true;
+                hits += __popcll(__ballot(x < k && (unsigned)v < (unsigned)n && ((bits[v >> 5] >> (v & 31)) & 1u)));
+            }
+            sync();   // before the next row's bitmap
+            strange = __any(strange);
+            if (!strange) common += hits;
+        }
+        if (strange) {
+            for (int x = 0; x < k; ++x) {
+                const int want = la[x];
+                bool hit = false;
+                for (int y = lane; y < k; y += 64) hit |= lb[y] == want;
+                common += __any(hit) ? 1 : 0;
+            }
+        }
     }
-    if (lane == 0) atomicAdd(&counts[b * n_heads + head], (unsigned long long)common);
+    if (lane == 0 && common) atomicAdd(&counts[total_of], (unsigned long long)common);
 }
 
 __global__ void recall_clear_kernel(unsigned long long* counts, int n) {
@@ -521,8 +563,8 @@ extern "C" veda_status veda_tile_recall(const veda_plan* pl, const int32_t* k_pe
     unsigned long long* counts = (unsigned long long*)workspace;
     const int64_t rows = pl->total_tiles * pl->prob.batch;
     hipLaunchKernelGGL(recall_clear_kernel, dim3((n + 255) / 256), dim3(256), 0, s, counts, n);
-    hipLaunchKernelGGL(recall_count_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, pl->d_heads,
-                       pl->d_tile_head, args, col_idx_a, col_idx_b, counts, pl->total_tiles, rows, pl->prob.heads);
+    hipLaunchKernelGGL(recall_count_kernel, dim3((unsigned)((rows + 4 * kRecallRows - 1) / (4 * kRecallRows))), dim3(256), 0, s,
+                       pl->d_heads, pl->d_tile_head, args, col_idx_a, col_idx_b, counts, pl->total_tiles, rows, pl->prob.heads);
     hipLaunchKernelGGL(recall_finish_kernel, dim3((n + 255) / 256), dim3(256), 0, s, pl->d_heads, args, counts,
                        recall, pl->prob.heads, n);
     return launch_status("veda_tile_recall");

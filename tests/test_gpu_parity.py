@@ -1061,6 +1061,31 @@ def test_target_heatmap_at_edge_tiles(dtype, d, tile_tokens, grid):
         assert torch.equal(p[rows], got[rows]) and bool((p[others] == -7.0).all())
 
 
+@pytest.mark.parametrize("grid,k", [((4, 8, 8), 1), ((4, 8, 8), 4), ((9, 36, 36), 65), ((9, 36, 36), 243), ((8, 364, 368), 130)])
+def test_recall_of_constructed_lists(grid, k):
+    """Lists in any order, one to several passes of a wavefront over them, whole rows, entries that are no tile
+    (all pairs are compared then: equal entries count whatever they are), and rows longer than the bitmap."""
+    shapes = np.asarray([[4, 4, 4], [1, 8, 8]], np.int32)
+    plan = veda.Plan(1, 2, 64, grid, shapes, torch.float32)
+    rng = np.random.default_rng(k)
+    ks = [min(k, n) for n in plan.tiles]
+    lists, ref = [[], []], []
+    for n, kk in zip(plan.tiles, ks):
+        m = n
+        a = np.argsort(rng.random((m, min(n, 4 * kk))), axis=1)[:, :kk].astype(np.int32)
+        b = np.argsort(rng.random((m, min(n, 4 * kk))), axis=1)[:, :kk].astype(np.int32)
+        a += n - min(n, 4 * kk)
+        b += n - min(n, 4 * kk)
+        a[m // 2, 0], b[m // 2, -1] = -1, -1
+        a[m - 1, 0] = n
+        for x, y in zip(lists, (a, b)):
+            x.append(y.ravel())
+        ref.append(sum(len(np.intersect1d(x, y)) for x, y in zip(a, b)) / (m * kk))
+    rec = veda.veda_tile_recall(plan, ks, *(torch.as_tensor(np.concatenate(x)).cuda() for x in lists))
+    torch.cuda.synchronize()
+    assert np.abs(rec[0].cpu().numpy() - np.asarray(ref)).max() <= 1e-6, (rec, ref)
+
+
 @pytest.mark.parametrize("dtype,tile_tokens", [("f32", 64), ("bf16", 64), ("bf16", 128)])
 def test_tiling_search_errors_and_choice(dtype, tile_tokens):
     # Alg. 1 on synthetic calibration tensors: error table against the oracle, same argmin where the
