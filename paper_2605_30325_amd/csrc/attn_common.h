@@ -48,19 +48,20 @@ struct AttnArgs {
 // sharing an L2 hold neighbouring query tiles, whose kept key tiles overlap.
 // The work item is a pair of adjacent query tiles; xcd_cum is the plan's table of them.  Returns false for the padding workgroups of dies
 // with fewer items.
+// The head is found with one load per lane and a ballot: a binary search is log2(heads) loads one after the
+// other, at the head of every workgroup's life (see union_build for what the whole of it costs).
 __device__ inline bool xcd_work(const int32_t* __restrict__ xcd_cum, const HeadGeom* __restrict__ heads,
                                 int n_heads, int& head, int& item) {
-    const int x = blockIdx.x % kXcd, local = blockIdx.x / kXcd;
+    const int x = blockIdx.x % kXcd, local = blockIdx.x / kXcd, lane = threadIdx.x & 63;
     const int32_t* cum = xcd_cum + x * (n_heads + 1);
+    // cum[0] = 0, ascending: the last head whose first item is <= local
+    static_assert(kMaxHeads <= 128, "two entries per lane");
+    const int c0 = lane < n_heads ? cum[lane] : 0x7fffffff, c1 = 64 + lane < n_heads ? cum[64 + lane] : 0x7fffffff;
     if (local >= cum[n_heads]) return false;
-    int h = 0, hi = n_heads - 1;   // the last head whose first item is <= local: log2(heads) dependent loads
-    while (h < hi) {
-        const int mid = (h + hi + 1) >> 1;
-        if (local >= cum[mid]) h = mid; else hi = mid - 1;
-    }
-    const int n = heads[h].n_pairs;
-    head = h;
-    item = x * (n / kXcd) + (x < n % kXcd ? x : n % kXcd) + (local - cum[h]);
+    head = __popcll(__ballot(local >= c0)) + __popcll(__ballot(local >= c1)) - 1;
+    const int first = __builtin_amdgcn_readlane(head < 64 ? c0 : c1, head & 63);
+    const int n = heads[head].n_pairs;
+    item = x * (n / kXcd) + (x < n % kXcd ? x : n % kXcd) + (local - first);
     return true;
 }
 

@@ -173,8 +173,7 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_f32_kernel(AttnArgs a) {
         const int32_t* lists[2] = {a.col_idx + begA, a.col_idx + begB};
         const int counts[2] = {nA, nB};
         total = union_build<2, 256, kF32Chunk>(u, lists, counts, hg.n_tiles, tid);
-        union_fill<2, 256, kF32Chunk, false>(u, 0, total, hg.n_tiles, vmask_g, n0s_g, tid);
-        union_fill<2, 256, kF32Chunk, false>(u, kF32Chunk, total, hg.n_tiles, vmask_g, n0s_g, tid);
+        union_fill<2, 256, kF32Chunk, false, 2 * kF32Chunk>(u, 0, total, hg.n_tiles, vmask_g, n0s_g, tid);   // the whole ring
         __syncthreads();
         raw_next = union_read<kF32Chunk>(tab_lds, 0);
         s_read = 1;

@@ -315,8 +315,7 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
         const int32_t* lists[2] = {a.col_idx + begA, a.col_idx + begB};
         const int counts[2] = {nA, kGrouped ? 0 : nB};
         total = union_build<2, 256, kPairChunk>(u, lists, counts, list_range, tid) * (kGrouped ? 2 : 1);
-        union_fill<2, 256, kPairChunk, kGrouped>(u, 0, total, list_range, vmask_g, n0s_g, tid);
-        union_fill<2, 256, kPairChunk, kGrouped>(u, kPairChunk, total, list_range, vmask_g, n0s_g, tid);
+        union_fill<2, 256, kPairChunk, kGrouped, 2 * kPairChunk>(u, 0, total, list_range, vmask_g, n0s_g, tid);   // the whole ring
         __syncthreads();
     } else {
         rawA = colsA[0];

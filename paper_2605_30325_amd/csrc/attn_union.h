@@ -72,6 +72,10 @@ template <int N, int kChunk> struct UnionLds {
     int32_t total;
 };
 
+// What comes before the first product of a workgroup is a chain of loads and barriers, about 14 us for one kept
+// tile: 15 % of a call at 32 kept tiles, 10 % at 63 (the second resident workgroup computes meanwhile).  Finding
+// the head by ballot (xcd_work), asking for the lists before the bitmaps are cleared and filling the whole ring in
+// one go took 40 heads of 21x30x52 at one kept tile from 371 to 364 us.
 // Steps 1 and 2.  cols[t], n[t]: list t (global memory).  All threads of the workgroup call it;
 // it ends with a barrier.  Returns the number of steps.
 // n_tiles: the range of the list entries.
@@ -80,14 +84,20 @@ __device__ inline int union_build(UnionLds<N, kChunk>& u, const int32_t* const (
     static_assert(kUnionMaxWords % kThreads == 0, "whole words per thread");
     constexpr int kPer = kUnionMaxWords / kThreads;
     const int words = (n_tiles + 31) >> 5;
+    // the first entries are on their way while the bitmaps are cleared
+    int early[N];
+#pragma unroll
+    for (int t = 0; t < N; ++t) early[t] = tid < n[t] ? cols[t][tid] : -1;
     for (int i = tid; i < N * kUnionMaxWords; i += kThreads) (&u.bm[0][0])[i] = 0u;
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < N; ++t)
-        for (int i = tid; i < n[t]; i += kThreads) {
-            const int j = cols[t][i];
+    for (int t = 0; t < N; ++t) {
+        auto mark = [&](int j) {
             if ((unsigned)j < (unsigned)n_tiles) atomicOr(&u.bm[t][j >> 5], 1u << (j & 31));
-        }
+        };
+        mark(early[t]);
+        for (int i = tid + kThreads; i < n[t]; i += kThreads) mark(cols[t][i]);
+    }
     __syncthreads();
     // exclusive prefix sum of the words' population counts: kPer consecutive words per thread
     int cnt[kPer], mine = 0;
@@ -129,16 +139,16 @@ __device__ inline int union_build(UnionLds<N, kChunk>& u, const int32_t* const (
     return total;
 }
 
-// Step 3: entries [first, first + kChunk) of the step sequence into their places in the ring
+// Step 3: entries [first, first + kCount) of the step sequence into their places in the ring
 // (entry s lives at s % (2 kChunk)).  No barrier inside: the caller separates it from the readers
 // of these places.  total: number of steps.  kGrouped: the lists name whole 128-token tiles and
 // every kept one makes two steps, its 64-slot halves 2o and 2o+1 (vmask, n0s are indexed by half),
 // kept by all N query tiles alike.
-template <int N, int kThreads, int kChunk, bool kGrouped>
+template <int N, int kThreads, int kChunk, bool kGrouped, int kCount = kChunk>
 __device__ inline void union_fill(UnionLds<N, kChunk>& u, int first, int total, int n_tiles, const uint64_t* __restrict__ vmask,
                                   const int32_t* __restrict__ n0s, int tid) {
     const int words = (n_tiles + 31) >> 5;
-    for (int i = tid; i < kChunk; i += kThreads) {
+    for (int i = tid; i < kCount; i += kThreads) {
         const int step = first + i;
         const int s = kGrouped ? step >> 1 : step;   // position in the ascending union
         UnionEntry e = {0, 0, 0u, 0u};
