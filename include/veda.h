@@ -309,6 +309,15 @@ veda_status veda_sparse_attn_fwd_qk_tokens(const veda_plan*, const void* q, veda
 veda_status veda_tile_heatmap(const veda_plan*, const void* q_tiled, const void* k_tiled,
                               const uint64_t* valid_mask, float softmax_scale, const int32_t* query_tiles,
                               int64_t n_query_tiles, float* heat, void* stream);
+/* The same for all query tiles, with the softmax sums of the rows handed over: they do not depend on how the
+ * tokens are tiled, so a caller that forms the target scores of one Q, K and softmax_scale under several tilings
+ * needs them once.
+ * row_sums device fp32 [batch][heads][tokens][2], 8-byte aligned, in token order: a reference point of the row's
+ *          exponentials and one over their sum.  have_row_sums = 0: formed and written (both passes);
+ *          1: read, and only the second pass runs. */
+veda_status veda_tile_heatmap_rows(const veda_plan*, const void* q_tiled, const void* k_tiled,
+                                   const uint64_t* valid_mask, float softmax_scale, float* row_sums,
+                                   int32_t have_row_sums, float* heat, void* stream);
 /* veda_tile_recall (Sec. 3.2, Recall@k): col_idx_a, col_idx_b device CSR column lists as stage 3
  * writes them for the same k_per_head (host i32 [heads]); each row a list of distinct tiles.
  * recall   device fp32 [batch][heads]: mean over the head's query tiles of |A_i & B_i| / k.

@@ -44,6 +44,10 @@ struct HeatArgs {
     int64_t total_tiles, score_elems;
     int n_heads;
     float scale_log2;             // softmax_scale * log2(e)
+    float2* rows;                 // optional: (ref, 1/l) of every row, token order
+    int have_rows;                // read them instead of running pass 1
+    int64_t tokens;
+    int T, H, W;
 };
 
 // Maximum over the 32 rows of a wave (x alike in both lane halves), wave-uniform: within 16 lanes by DPP, the
@@ -161,11 +165,13 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
     const bool q_real = row < q_rows;
     const bool active = __builtin_amdgcn_readfirstlane(32 * r < q_rows ? 1 : 0);
     frag qf[kF];
+    float2* row_sums = nullptr;   // where this lane's are kept
     {
         const int slot = q_real ? nth_bit(q_mask, row) : 0;
         const char* qrow = a.q + (head_tile0 + (qi >= 0 ? qi : 0)) * kKBytes + slot * kRowB + 16 * hh;
 #pragma unroll
         for (int f = 0; f < kF; ++f) qf[f] = *reinterpret_cast<const frag*>(qrow + 32 * f);
+        if (a.rows && q_real) row_sums = a.rows + (b * a.n_heads + head) * a.tokens + slot_token(hg, qi, slot, a.T, a.H, a.W);
     }
 
     // global -> LDS copy plan: see the attention kernels.
@@ -289,8 +295,9 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
         }
         l_part += sum;
     };
-    walk_begin();
-    if (active) {
+    if (a.have_rows) {
+        // nothing to do
+    } else if (walk_begin(); active) {
         // s1 holds the block whose exponentials are still to come: they are formed behind the next products
         f32x16 s0, s1;
         float sum;
@@ -331,7 +338,15 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
             step_end();
         }
     }
-    const float inv_l = 1.0f / sum_with_other_half(l + l_part);   // the lane halves hold different keys
+    float inv_l;
+    if (a.have_rows) {
+        const float2 known = row_sums ? *row_sums : make_float2(0.0f, 0.0f);
+        ref = known.x;
+        inv_l = known.y;
+    } else {
+        inv_l = 1.0f / sum_with_other_half(l + l_part);   // the lane halves hold different keys
+        if (row_sums && hh == 0) *row_sums = make_float2(ref, inv_l);
+    }
 
     // ---- pass 2: block maxima of exp2(s - ref) / l ----
     // whole-tile score blocks hold a quarter of the half-tile ones
@@ -492,10 +507,10 @@ __global__ void recall_finish_kernel(const HeadGeom* __restrict__ heads, RecallA
 
 }  // namespace veda
 
-extern "C" veda_status veda_tile_heatmap(const veda_plan* pl, const void* q_tiled, const void* k_tiled,
-                                         const uint64_t* valid_mask, float softmax_scale,
-                                         const int32_t* query_tiles, int64_t n_query_tiles, float* heat,
-                                         void* stream) {
+// Both entry points; rows: optional row sums, read if have_rows.
+static veda_status target_heatmap(const veda_plan* pl, const void* q_tiled, const void* k_tiled, const uint64_t* valid_mask,
+                                  float softmax_scale, const int32_t* query_tiles, int64_t n_query_tiles, float2* rows,
+                                  int have_rows, float* heat, void* stream) {
     using namespace veda;
     if (!pl || !q_tiled || !k_tiled || !valid_mask || !heat) return VEDA_ERR_INVALID_ARG;
     if (!(softmax_scale > 0.0f) || !(softmax_scale < INFINITY)) return VEDA_ERR_INVALID_ARG;
@@ -518,6 +533,10 @@ extern "C" veda_status veda_tile_heatmap(const veda_plan* pl, const void* q_tile
     a.score_elems = pl->score_elems;
     a.n_heads = pl->prob.heads;
     a.scale_log2 = softmax_scale * kLog2e;
+    a.rows = rows;
+    a.have_rows = have_rows;
+    a.tokens = pl->tokens();
+    a.T = pl->prob.T; a.H = pl->prob.H; a.W = pl->prob.W;
     hipStream_t s = (hipStream_t)stream;
     a.xcd_cum = ip->d_xcd_cum_pair;
     const int64_t items = query_tiles ? n_query_tiles : (int64_t)kXcd * ip->xcd_max_pairs;
@@ -539,6 +558,22 @@ extern "C" veda_status veda_tile_heatmap(const veda_plan* pl, const void* q_tile
     }
 #undef VEDA_LAUNCH_HEAT
     return launch_status("veda_tile_heatmap");
+}
+
+extern "C" veda_status veda_tile_heatmap(const veda_plan* pl, const void* q_tiled, const void* k_tiled,
+                                         const uint64_t* valid_mask, float softmax_scale,
+                                         const int32_t* query_tiles, int64_t n_query_tiles, float* heat,
+                                         void* stream) {
+    return target_heatmap(pl, q_tiled, k_tiled, valid_mask, softmax_scale, query_tiles, n_query_tiles, nullptr, 0, heat, stream);
+}
+
+extern "C" veda_status veda_tile_heatmap_rows(const veda_plan* pl, const void* q_tiled, const void* k_tiled,
+                                              const uint64_t* valid_mask, float softmax_scale, float* row_sums,
+                                              int32_t have_row_sums, float* heat, void* stream) {
+    if (!row_sums || have_row_sums < 0 || have_row_sums > 1) return VEDA_ERR_INVALID_ARG;
+    if (reinterpret_cast<uintptr_t>(row_sums) & 7u) return VEDA_ERR_UNSUPPORTED;
+    return target_heatmap(pl, q_tiled, k_tiled, valid_mask, softmax_scale, nullptr, 0, reinterpret_cast<float2*>(row_sums),
+                          have_row_sums, heat, stream);
 }
 
 extern "C" veda_status veda_tile_recall(const veda_plan* pl, const int32_t* k_per_head, const int32_t* col_idx_a,

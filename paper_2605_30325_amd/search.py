@@ -1,7 +1,7 @@
 """Head-aware tiling search (Sec. 4.2, Eq. 8; Alg. 1) as a sequence of library calls.
 
 For every candidate tile shape pi the calibration tensors are tiled, the reference top-k mask is
-taken from the full-attention target scores (veda_tile_heatmap + veda_tile_select), the tile-sparse
+taken from the full-attention target scores (veda_tile_heatmap_rows + veda_tile_select), the tile-sparse
 attention is run under that mask, and the squared distance to the full-attention output is added to
 the candidate's error; each head gets the shape with the smallest error.  Everything numeric runs
 in the library's kernels; this module only sequences the calls and takes the final argmin of a
@@ -44,7 +44,7 @@ def tiling_search(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, grid: Seque
     samples, heads, n_tok, d = q.shape
     scale = 1.0 / math.sqrt(d) if softmax_scale is None else float(softmax_scale)
     errors = torch.zeros((heads, len(candidates)), dtype=torch.float64, device=q.device)
-    o_full = None
+    o_full = row_sums = None
     for c, shape in enumerate(candidates):
         shapes = np.tile(np.asarray(shape, np.int32), (heads, 1))
         plan = veda.Plan(samples, heads, d, grid, shapes, q.dtype, tile_tokens=tile_tokens)
@@ -53,7 +53,7 @@ def tiling_search(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, grid: Seque
         vt, _, _ = veda.veda_tile_layout(plan, v, veda.VEDA_CHANNEL_MAJOR, want_mask=False)
         if o_full is None:   # the full-attention output does not depend on the tiling
             o_full = _dense_output(plan, qt, kt, vt, vm, scale)
-        heat = veda.veda_tile_heatmap(plan, qt, kt, vm, scale)
+        heat, row_sums = veda.veda_tile_heatmap_rows(plan, qt, kt, vm, scale, row_sums)   # nor do the rows' softmax sums
         kph = keep_budget(plan.tiles, keep)
         row_ptr, col_idx = veda.veda_tile_select(plan, heat, kph)
         o_sp, _ = veda.veda_sparse_attn_fwd(plan, qt, kt, vt, vm, row_ptr, col_idx, scale)

@@ -33,7 +33,7 @@ EXPORTS = (
     "veda_tile_score_stats", "veda_tile_score_closed_form", "veda_tile_select", "veda_plan_fused_workspace_bytes",
     "veda_tile_score_select", "veda_tile_score_select_stats", "veda_tile_score_select_stats_noalloc",
     "veda_sparse_attn_fwd", "veda_sparse_attn_fwd_q_tokens",
-    "veda_sparse_attn_fwd_qk_tokens", "veda_tile_heatmap",
+    "veda_sparse_attn_fwd_qk_tokens", "veda_tile_heatmap", "veda_tile_heatmap_rows",
     "veda_tile_recall", "veda_output_sqerr", "veda_status_string", "veda_last_error",
 )
 
@@ -130,6 +130,8 @@ def load():
     L.veda_sparse_attn_fwd_qk_tokens.restype = C.c_int
     L.veda_tile_heatmap.argtypes = [vp, vp, vp, vp, C.c_float, vp, i64, vp, vp]
     L.veda_tile_heatmap.restype = C.c_int
+    L.veda_tile_heatmap_rows.argtypes = [vp, vp, vp, vp, C.c_float, vp, i32, vp, vp]
+    L.veda_tile_heatmap_rows.restype = C.c_int
     L.veda_tile_recall.argtypes = [vp, C.POINTER(i32), vp, vp, vp, vp, C.c_size_t, vp]
     L.veda_tile_recall.restype = C.c_int
     L.veda_output_sqerr.argtypes = [vp, vp, veda_strides, vp, veda_strides, vp, vp, C.c_size_t, vp]
@@ -445,6 +447,22 @@ def veda_tile_heatmap(plan: Plan, q_tiled, k_tiled, valid_mask, softmax_scale: f
                                     C.c_float(softmax_scale), _ptr(query_tiles), n_qt, _ptr(heat), _stream()),
            "veda_tile_heatmap")
     return heat
+
+
+def veda_tile_heatmap_rows(plan: Plan, q_tiled, k_tiled, valid_mask, softmax_scale: float, row_sums: Optional[torch.Tensor] = None,
+                           heat: Optional[torch.Tensor] = None):
+    """veda_tile_heatmap of all query tiles with the rows' softmax sums: given (as an earlier call on the same
+    Q, K and scale returned them, under whatever tiling), only the second pass over the keys runs.
+    Returns (heat, row_sums fp32 [batch, heads, tokens, 2])."""
+    dev = q_tiled.device
+    if heat is None:
+        heat = torch.empty((plan.batch, plan.score_elems), dtype=torch.float32, device=dev)
+    have = row_sums is not None
+    if not have:
+        row_sums = torch.empty((plan.batch, plan.heads, plan.tokens, 2), dtype=torch.float32, device=dev)
+    _check(load().veda_tile_heatmap_rows(plan.handle, _ptr(q_tiled), _ptr(k_tiled), _ptr(valid_mask), C.c_float(softmax_scale),
+                                         _ptr(row_sums), 1 if have else 0, _ptr(heat), _stream()), "veda_tile_heatmap_rows")
+    return heat, row_sums
 
 
 def veda_tile_recall(plan: Plan, k_per_head: Sequence[int], col_idx_a, col_idx_b,

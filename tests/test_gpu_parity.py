@@ -1048,6 +1048,8 @@ def test_target_heatmap_at_edge_tiles(dtype, d, tile_tokens, grid):
     heat = veda.veda_tile_heatmap(plan, qt, kt, vm, scale)
     listed = torch.randperm(plan.total_tiles, generator=torch.Generator().manual_seed(1))[:plan.total_tiles // 2 | 1].to(torch.int32)
     part = veda.veda_tile_heatmap(plan, qt, kt, vm, scale, listed.to(dev), torch.full_like(heat, -7.0))
+    kept, sums = veda.veda_tile_heatmap_rows(plan, qt, kt, vm, scale)
+    again, _ = veda.veda_tile_heatmap_rows(plan, qt, kt, vm, scale, sums)
     torch.cuda.synchronize()
     for h in range(wl.heads):
         nt, soff, toff = plan.tiles[h], plan.score_offset[h], plan.tile_offset[h]
@@ -1055,6 +1057,8 @@ def test_target_heatmap_at_edge_tiles(dtype, d, tile_tokens, grid):
         got = heat[0, soff:soff + nt * nt].view(nt, nt)
         rel = np.abs(got.cpu().numpy().astype(np.float64) - ref) / ref
         assert rel.max() <= (2e-4 if dtype == "bf16" else 2e-5), (h, rel.max())
+        # the rows' sums kept under this tiling and read under the same one: the same bits
+        assert torch.equal(kept, heat) and torch.equal(again, heat)
         rows = [int(g) - toff for g in listed if toff <= int(g) < toff + nt]
         others = np.setdiff1d(np.arange(nt), rows)
         p = part[0, soff:soff + nt * nt].view(nt, nt)
