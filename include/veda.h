@@ -305,6 +305,8 @@ veda_status veda_sparse_attn_fwd_qk_tokens(const veda_plan*, const void* q, veda
  * query_tiles  optional device i32 [n_query_tiles] of global tile indices (tile_offset(h) + i,
  *          each in [0, total_tiles), no index twice): only those rows of heat are written, for
  *          every batch entry; NULL with n_query_tiles == 0 means all query tiles.
+ *          Small scores: fp32 plans keep them, and their order, down to fp32's smallest subnormal; bf16 plans
+ *          return 0 once exp(logit - row maximum) is below about 2^-126.
  * q_tiled,k_tiled VEDA_TOKEN_MAJOR.  bf16: Q K^T on bf16 MFMA, fp32 accumulation and softmax. */
 veda_status veda_tile_heatmap(const veda_plan*, const void* q_tiled, const void* k_tiled,
                               const uint64_t* valid_mask, float softmax_scale, const int32_t* query_tiles,

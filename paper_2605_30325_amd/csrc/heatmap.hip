@@ -87,6 +87,17 @@ constexpr float kHeatNoRef = -3e38f;   // reference before the first key: everyt
 // the row's maximum, so rows of even logits stay below it.
 constexpr float kHeatSlack = 32.0f;
 
+// exp2(t) / l of a block's largest logit.  The instruction returns 0 below 2^-126; fp32 target scores keep the order of
+// tiles that far below their row's maximum, so there the exponential is formed 2^64 higher and the score rounded once.
+// (One score per query row and block.  8 heads of 144 tiles, d = 128: the second pass alone 1.46 -> 1.47 ms, d = 64
+// 0.73 -> 0.74, both passes 3.0 ms either way.)
+template <typename E> __device__ __forceinline__ float heat_score(float t, float inv_l) {
+    if (sizeof(E) == 2) return __builtin_amdgcn_exp2f(t) * inv_l;
+    const bool low = t < -126.0f;
+    const float p = __builtin_amdgcn_exp2f(low ? t + 64.0f : t) * inv_l;
+    return low ? p * 0x1p-64f : p;
+}
+
 // kGrouped: 128-token tiles.  The geometry in `a` is that of the 64-slot halves; a whole tile is a
 // workgroup and two consecutive key steps, and its block maximum the maximum over them.
 template <typename E, int D, bool kGrouped>
@@ -399,8 +410,7 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
                 }
 #pragma unroll
                 for (int f = 0; f < kF; ++f) maxima(s1, f);
-                const float p = __builtin_amdgcn_exp2f(logit(max_with_other_half(mx), ref)) * inv_l;
-                best = rows_max(q_real ? p : 0.0f);
+                best = rows_max(q_real ? heat_score<E>(logit(max_with_other_half(mx), ref), inv_l) : 0.0f);
             }
             mine = lane == (j & 63) ? best : mine;
             step_end();

@@ -1065,6 +1065,39 @@ def test_target_heatmap_at_edge_tiles(dtype, d, tile_tokens, grid):
         assert torch.equal(p[rows], got[rows]) and bool((p[others] == -7.0).all())
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_target_scores_below_the_smallest_normal_number(d):
+    """Key tiles up to 102 below the row's maximum (natural units): their scores are subnormal, keep their order,
+    and the top-k goes by it and not by the tile number."""
+    grid, n, spread = (4, 16, 16), 1024, 102.0
+    g = torch.Generator().manual_seed(5)
+    q, k = torch.randn((1, 1, n, d), generator=g), 0.5 * torch.randn((1, 1, n, d), generator=g)
+    q[..., 1:] *= 0.2
+    q[..., 0] = 1.0
+    token = torch.arange(n)
+    tile = (token // 16 % 16) // 4 * 4 + (token % 16) // 4          # 4 x 4 tiles of 4x4x4
+    k[0, 0, :, 0] = (tile - 15) / 15.0 * spread * math.sqrt(d)       # higher tile number, larger score
+    scale = 1.0 / math.sqrt(d)
+    plan = veda.Plan(1, 1, d, grid, np.asarray([[4, 4, 4]], np.int32), torch.float32)
+    qt, vm, _ = veda.veda_tile_layout(plan, q.cuda())
+    kt, _, _ = veda.veda_tile_layout(plan, k.cuda(), want_mask=False)
+    heat = veda.veda_tile_heatmap(plan, qt, kt, vm, scale)
+    kept, sums = veda.veda_tile_heatmap_rows(plan, qt, kt, vm, scale)
+    again, _ = veda.veda_tile_heatmap_rows(plan, qt, kt, vm, scale, sums)
+    _, ci = veda.veda_tile_select(plan, heat, [15])
+    torch.cuda.synchronize()
+    assert torch.equal(kept, heat) and torch.equal(again, heat)
+    ref = vo.tile_heatmap(q[0, 0].numpy(), k[0, 0].numpy(), grid, (4, 4, 4), scale)
+    assert ((ref > 0) & (ref < 2.0 ** -126)).sum() >= 32 and ref.min() < 2.0 ** -149
+    # a logit is a sum of d products, each addition rounded at the size of the sum (at most the spread), then scaled and
+    # taken from the reference; a score is rounded to a multiple of 2^-149 once
+    rtol = (d + 3) * 2.0 ** -24 * (spread + 3.0)
+    got = heat[0].view(16, 16).cpu().numpy().astype(np.float64)
+    excess = (np.abs(got - ref) / (rtol * ref + 2.0 ** -149)).max()
+    assert excess <= 1.0, (excess, int((got == 0.0).sum()))
+    assert np.array_equal(ci.view(16, 15).cpu().numpy(), vo.select(ref.astype(np.float32), 15))
+
+
 @pytest.mark.parametrize("grid,k", [((4, 8, 8), 1), ((4, 8, 8), 4), ((9, 36, 36), 65), ((9, 36, 36), 243), ((8, 364, 368), 130)])
 def test_recall_of_constructed_lists(grid, k):
     """Lists in any order, one to several passes of a wavefront over them, whole rows, entries that are no tile
