@@ -458,8 +458,13 @@ def veda_tile_heatmap_rows(plan: Plan, q_tiled, k_tiled, valid_mask, softmax_sca
     if heat is None:
         heat = torch.empty((plan.batch, plan.score_elems), dtype=torch.float32, device=dev)
     have = row_sums is not None
+    shape = (plan.batch, plan.heads, plan.tokens, 2)
     if not have:
-        row_sums = torch.empty((plan.batch, plan.heads, plan.tokens, 2), dtype=torch.float32, device=dev)
+        row_sums = torch.empty(shape, dtype=torch.float32, device=dev)
+    elif tuple(row_sums.shape) != shape or row_sums.dtype != torch.float32 or row_sums.device != dev or not row_sums.is_contiguous():
+        # the kernel reads one pair per row: a buffer of another problem would be read past its end
+        raise VedaError(VEDA_ERR_INVALID_ARG, "veda_tile_heatmap_rows",
+                        f"row_sums must be contiguous fp32 {list(shape)} on {dev}, as an earlier call returned them")
     _check(load().veda_tile_heatmap_rows(plan.handle, _ptr(q_tiled), _ptr(k_tiled), _ptr(valid_mask), C.c_float(softmax_scale),
                                          _ptr(row_sums), 1 if have else 0, _ptr(heat), _stream()), "veda_tile_heatmap_rows")
     return heat, row_sums

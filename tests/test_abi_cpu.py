@@ -6,6 +6,7 @@ from pathlib import Path
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2605_30325_amd import veda
 
@@ -99,3 +100,21 @@ def test_stage_calls_reject_null_plan(lib):
     assert lib.veda_output_sqerr(None, None, s, None, s, None, None, 0, None) == veda.VEDA_ERR_INVALID_ARG
     assert lib.veda_plan_tiles(None, 0) == -1 and lib.veda_plan_total_tiles(None) == -1
     lib.veda_plan_destroy(None)
+
+
+@pytest.mark.parametrize("bad", [
+    torch.zeros(2, 3, 255, 2),                                   # fewer tokens
+    torch.zeros(1, 3, 256, 2),                                   # another batch
+    torch.zeros(2, 3, 256, 2, dtype=torch.float64),
+    torch.zeros(2, 3, 2, 256).transpose(2, 3),                   # the right shape, other strides
+    torch.zeros(2, 3, 256, 2, device="meta"),
+    torch.zeros(2, 3, 256),
+])
+def test_row_sums_of_another_problem_are_refused(monkeypatch, bad):
+    from types import SimpleNamespace
+    monkeypatch.setattr(veda, "load", lambda: pytest.fail("the library was called"))
+    monkeypatch.setattr(veda, "_stream", lambda: 0)
+    plan = SimpleNamespace(batch=2, heads=3, tokens=256, score_elems=48, handle=None)
+    q = torch.zeros(2, 12, 64 * 64)
+    with pytest.raises(veda.VedaError, match="row_sums must be"):
+        veda.veda_tile_heatmap_rows(plan, q, q, torch.zeros(12, dtype=torch.int64), 0.125, bad)
