@@ -173,7 +173,7 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
     // This lane's row: the real slots of the query tile in order, 32 per wave.
     const uint64_t q_mask = qi >= 0 ? vmask[qi] : 0ull;
     const int row = 32 * r + idx, q_rows = __popcll(q_mask);
-    const bool q_real = row < q_rows;
+    bool q_real = row < q_rows;
     const bool active = __builtin_amdgcn_readfirstlane(32 * r < q_rows ? 1 : 0);
     frag qf[kF];
     float2* row_sums = nullptr;   // where this lane's are kept
@@ -182,7 +182,12 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
         const char* qrow = a.q + (head_tile0 + (qi >= 0 ? qi : 0)) * kKBytes + slot * kRowB + 16 * hh;
 #pragma unroll
         for (int f = 0; f < kF; ++f) qf[f] = *reinterpret_cast<const frag*>(qrow + 32 * f);
-        if (a.rows && q_real) row_sums = a.rows + (b * a.n_heads + head) * a.tokens + slot_token(hg, qi, slot, a.T, a.H, a.W);
+        if (a.rows && q_real) {
+            // a slot without a token has no place there, whatever the mask says of it
+            const int token = slot_token(hg, qi, slot, a.T, a.H, a.W);
+            q_real = token >= 0;
+            if (q_real) row_sums = a.rows + (b * a.n_heads + head) * a.tokens + token;
+        }
     }
 
     // global -> LDS copy plan: see the attention kernels.

@@ -1098,6 +1098,35 @@ def test_fp32_target_scores_below_the_smallest_normal_number(d):
     assert np.array_equal(ci.view(16, 15).cpu().numpy(), vo.select(ref.astype(np.float32), 15))
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_row_sums_have_no_place_for_padded_slots(dtype):
+    """A mask that calls padded slots real: their rows have no token, so no sums are kept for them (what lies around
+    the buffer stays as it was) and they take no part in the scores.  The padded keys count, as zeros."""
+    grid, d, heads, shape = (3, 5, 7), 64, 3, (4, 4, 4)
+    wl = wlm.custom_workload("all_ones", heads, d, dtype, grid, False, (50, 100), seed=31)
+    q, k, _ = wlm.make_qkv(wl, torch.device("cuda:0"))
+    plan = veda.Plan(1, heads, d, grid, np.asarray([shape] * heads, np.int32), wl.torch_dtype)
+    qt, vm, _ = veda.veda_tile_layout(plan, q)
+    kt, _, _ = veda.veda_tile_layout(plan, k, want_mask=False)
+    ones = torch.full_like(vm, -1)
+    around = torch.full((heads * plan.tokens + 128, 2), -7.0, device="cuda:0")
+    sums = around[64:64 + heads * plan.tokens].view(1, heads, plan.tokens, 2)
+    lib, scale, heat = veda.load(), 1.0 / math.sqrt(d), torch.empty((1, plan.score_elems), device="cuda:0")
+    maps = []
+    for have in (0, 1):
+        assert lib.veda_tile_heatmap_rows(plan.handle, qt.data_ptr(), kt.data_ptr(), ones.data_ptr(), scale, sums.data_ptr(), have,
+                                          heat.data_ptr(), torch.cuda.current_stream().cuda_stream) == veda.VEDA_OK
+        torch.cuda.synchronize()
+        maps.append(heat.clone())
+    assert torch.equal(maps[0], maps[1])
+    assert bool((around[:64] == -7.0).all()) and bool((around[-64:] == -7.0).all()) and bool((sums[..., 1] > 0).all())
+    n = plan.tiles[0]
+    real = ((vm.view(heads, n, 1) >> torch.arange(64, device=vm.device)) & 1).bool()
+    s = torch.matmul(qt.view(heads, n * 64, d).float(), kt.view(heads, n * 64, d).float().transpose(1, 2).contiguous()) * scale
+    ref = (torch.softmax(s.double(), dim=2) * real.view(heads, -1, 1)).view(heads, n, 64, n, 64).amax(dim=(2, 4))
+    assert ((maps[0].view(heads, n, n) - ref).abs() / ref).max() <= (2e-4 if dtype == "bf16" else 2e-5)
+
+
 @pytest.mark.parametrize("grid,k", [((4, 8, 8), 1), ((4, 8, 8), 4), ((9, 36, 36), 65), ((9, 36, 36), 243), ((8, 364, 368), 130)])
 def test_recall_of_constructed_lists(grid, k):
     """Lists in any order, one to several passes of a wavefront over them, whole rows, entries that are no tile
