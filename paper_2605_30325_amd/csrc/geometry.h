@@ -66,4 +66,15 @@ inline int32_t tile_anchor_token(const HeadGeom& g, int32_t i, int T, int H, int
     return (int32_t)((t * H + h) * W + w);
 }
 
+// Work split of the target scores over a list of n query tiles, in any order: two entries of one head, the next two in
+// the list, share a workgroup, and workgroup p takes the p-th pair, head by head.  Pairs are formed inside windows of
+// kListWindow entries, so that a workgroup's look at the list is bounded (a longer list loses at most one partner per
+// head and window).  A window of m entries has at most one partnerless entry per head, hence this many workgroups
+// (those past the last pair, at most half the number of heads, have nothing to do).
+constexpr int kListWindow = 4096;
+constexpr int64_t list_window_blocks(int64_t m, int heads) { return (m + (heads < m ? heads : m)) / 2; }
+constexpr int64_t list_blocks(int64_t n, int heads) {
+    return n / kListWindow * list_window_blocks(kListWindow, heads) + list_window_blocks(n % kListWindow, heads);
+}
+
 }  // namespace veda

@@ -18,8 +18,8 @@
 // products; the exponentials of one 32-key block are therefore formed behind the products of the next, and the
 // reference of the softmax stays where it is until a sum outgrows it.
 // Measured, the heat map alone, before and after: 12 heads of 624 tiles, bf16, d = 128, 10.0 -> 7.9 ms; one in 16
-// of the query tiles of 40 heads of 21x45x80 23.1 -> 12.0 ms (listed tiles used to run one to a workgroup); 8
-// heads of 144 tiles, fp32, d = 128, 19.1 -> 3.3 ms (on the vector units before).  Tried and left out: 64 rows
+// of the query tiles of 40 heads of 21x45x80, mixed shapes, 23.1 -> 11.6 ms (listed tiles used to run one to a
+// workgroup); 8 heads of 144 tiles, fp32, d = 128, 19.1 -> 3.0 ms (on the vector units before).  Tried and left out: 64 rows
 // per wave, four tiles per workgroup (half the operand reads and loads: 8.3 and 11.7 ms, fp32 3.9), a ring of
 // three or four K tiles (0.5 ms slower: it costs a resident workgroup and the loads are not what is waited for).
 // Padding: a tile's real rows come first (a wave runs only the blocks that hold any), and key tiles with few
@@ -98,9 +98,71 @@ template <typename E> __device__ __forceinline__ float heat_score(float t, float
     return low ? p * 0x1p-64f : p;
 }
 
+// Sum over the lanes up to and with this one, by DPP.
+__device__ __forceinline__ int wave_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15, 31
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+
+// The two listed query tiles of this workgroup (the second -1 if its head has no more) and their head, or false: the
+// split is in geometry.h.  The heads of the window's entries are counted in LDS and kept there as bytes; every wave then
+// finds the same head and the same two entries.  LDS: kListWindow bytes and a word per head, free again on return.
+// Finding the p-th pair here leaves no workgroup that only exits: with one workgroup per entry, those that had a pair
+// alternated with those that did not in an ordinary list, and the hardware deals workgroups out in turn, over the dies
+// and inside them, so half the chip had nothing.  Measured, one workgroup per entry and now: one tile in 16 of 40 heads of
+// 21x45x80, one shape, bf16 13.7 -> 10.0 ms (mixed shapes 11.7-12.6 -> 11.5, in no order 14.3 -> 11.7); all tiles of
+// 12 heads of 624 in order, bf16 11.4 -> 7.9 and fp32 128 -> 64.6 ms (without a list 7.75 and 64.2), in no order
+// 8.8 -> 7.8 and 77 -> 64.2; all 57,600 of 40 heads at d = 64 142 -> 87 ms; 8 tiles of 2 heads 15.3 -> 15.9 us.  A
+// contiguous piece of the list for each die, followers still exiting, is not enough (13.1, 13.3 and 121 ms).
+__device__ inline bool listed_pair(const HeatArgs& a, char* smem, int tid, int& head, int (&pair)[2]) {
+    static_assert(kMaxHeads == 128, "two heads per lane");
+    const int lane = tid & 63;
+    const int per = (int)list_window_blocks(kListWindow, a.n_heads), p = (int)blockIdx.x % per;
+    const int64_t begin = (int64_t)((int)blockIdx.x / per) * kListWindow;
+    const int m = (int)(a.n_query_tiles - begin < kListWindow ? a.n_query_tiles - begin : kListWindow);
+    const int32_t* list = a.query_tiles + begin;
+    uint8_t* heads = reinterpret_cast<uint8_t*>(smem);
+    int* count = reinterpret_cast<int*>(smem + kListWindow);
+    if (tid < kMaxHeads) count[tid] = 0;
+    __syncthreads();
+    for (int i = tid; i < m; i += 256) {
+        const int h = a.tile_head[list[i]];
+        heads[i] = (uint8_t)h;
+        atomicAdd(&count[h], 1);
+    }
+    __syncthreads();
+    // pairs of heads `lane` and 64 + lane, and of all heads up to them
+    const int n0 = (count[lane] + 1) >> 1, n1 = (count[64 + lane] + 1) >> 1;
+    const int upto0 = wave_scan(n0);
+    int upto1 = __builtin_amdgcn_readlane(upto0, 63);
+    if (a.n_heads > 64) upto1 += wave_scan(n1);
+    head = __popcll(__ballot(upto0 <= p)) + __popcll(__ballot(upto1 <= p));
+    const bool any = head < kMaxHeads;
+    if (any) {
+        const int skip = 2 * (p - __builtin_amdgcn_readlane(head < 64 ? upto0 - n0 : upto1 - n1, head & 63));
+        int first = -1, next = -1, before = 0;   // entries of rank skip and skip + 1 in the head
+        for (int i0 = 0; i0 < m && next < 0; i0 += 64) {
+            const uint64_t same = __ballot(i0 + lane < m && heads[i0 + lane < m ? i0 + lane : 0] == head);
+            const int upto = before + __popcll(same);
+            if (first < 0 && skip < upto) first = i0 + nth_bit(same, skip - before);
+            if (skip + 1 < upto) next = i0 + nth_bit(same, skip + 1 - before);
+            before = upto;
+        }
+        pair[0] = list[first];
+        pair[1] = next >= 0 ? list[next] : -1;
+    }
+    __syncthreads();
+    return any;
+}
+
 // kGrouped: 128-token tiles.  The geometry in `a` is that of the 64-slot halves; a whole tile is a
 // workgroup and two consecutive key steps, and its block maximum the maximum over them.
-template <typename E, int D, bool kGrouped>
+template <typename E, int D, bool kGrouped, bool kListed>
 __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
     typedef HeatFrag<E> F;
     typedef typename F::type frag;
@@ -124,35 +186,17 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
 
     // work item: up to two query tiles of one head; qi < 0: this wave has none
     int head, qi = -1;
-    if (a.query_tiles) {
-        // Listed tiles, in any order: entry i leads a workgroup if the number of earlier entries of its head is
-        // even, and takes the next entry of its head along.  (A listed 128-token tile fills a workgroup itself.)
-        const int i = blockIdx.x;
-        const int g = a.query_tiles[i];
-        head = a.tile_head[kGrouped ? 2 * g : g];
-        const int lo = a.heads[head].tile_off, n = a.heads[head].n_tiles;
-        int own = g;   // this wave's entry
-        if (!kGrouped) {
-            int earlier = 0;
-            for (int j = tid; j < i; j += 256) earlier += (unsigned)(a.query_tiles[j] - lo) < (unsigned)n ? 1 : 0;
-            int* count = reinterpret_cast<int*>(smem);
-            if (tid == 0) *count = 0;
-            __syncthreads();
-            if (earlier) atomicAdd(count, earlier);
-            __syncthreads();
-            const int rank = *count;
-            __syncthreads();
-            if (rank & 1) return;
-            if (which == 1) {
-                own = -1;
-                for (int64_t j0 = i + 1; j0 < a.n_query_tiles && own < 0; j0 += 64) {
-                    const int64_t j = j0 + lane;
-                    const int gj = j < a.n_query_tiles ? a.query_tiles[j] : -1;
-                    const uint64_t m = __ballot(j < a.n_query_tiles && (unsigned)(gj - lo) < (unsigned)n);
-                    if (m) own = __shfl(gj, (int)__ffsll((unsigned long long)m) - 1);
-                }
-            }
+    if constexpr (kListed) {
+        int own;   // this wave's entry
+        if (kGrouped) {   // a listed 128-token tile fills a workgroup
+            own = a.query_tiles[blockIdx.x];
+            head = a.tile_head[2 * own];
+        } else {
+            int pair[2];
+            if (!listed_pair(a, smem, tid, head, pair)) return;
+            own = pair[which];
         }
+        const int lo = a.heads[head].tile_off;
         if (own >= 0) qi = (kGrouped ? 2 * own + which : own) - lo;
     } else {
         int item, qiA, qiB;
@@ -554,12 +598,13 @@ static veda_status target_heatmap(const veda_plan* pl, const void* q_tiled, cons
     a.T = pl->prob.T; a.H = pl->prob.H; a.W = pl->prob.W;
     hipStream_t s = (hipStream_t)stream;
     a.xcd_cum = ip->d_xcd_cum_pair;
-    const int64_t items = query_tiles ? n_query_tiles : (int64_t)kXcd * ip->xcd_max_pairs;
+    const int64_t items = !query_tiles ? (int64_t)kXcd * ip->xcd_max_pairs
+                          : pl->inner  ? n_query_tiles : list_blocks(n_query_tiles, pl->prob.heads);
     dim3 grid((unsigned)items, (unsigned)pl->prob.batch), block(256);
     const size_t smem = (size_t)2 * kTile * d * pl->elem_size() + 4 * 64 * sizeof(float);
 #define VEDA_LAUNCH_HEAT(E, DD, GG)                                                                      \
     do {                                                                                                 \
-        auto kern = tile_heatmap_kernel<E, DD, GG>;                                                      \
+        auto kern = query_tiles ? tile_heatmap_kernel<E, DD, GG, true> : tile_heatmap_kernel<E, DD, GG, false>; \
         if (smem > 64 * 1024)                                                                            \
             VEDA_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem)); \
         hipLaunchKernelGGL(kern, grid, block, smem, s, a);                                               \

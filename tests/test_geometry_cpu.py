@@ -81,3 +81,40 @@ def test_every_tile_anchor_is_a_real_token(geometry_tool, grid, shape, grp):
             empty += 1
     if (grid, shape) in (((21, 5, 6), (16, 2, 4)), ((9, 18, 18), (1, 8, 16))):
         assert empty > 0
+
+
+LIST_PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "geometry.h"
+int main(int argc, char** argv) {
+    printf("%d\n", veda::kListWindow);
+    for (int i = 1; i + 1 < argc; i += 2) printf("%lld\n", (long long)veda::list_blocks(atoll(argv[i]), atoi(argv[i + 1])));
+    return 0;
+}
+"""
+
+
+def test_workgroups_over_a_list_of_query_tiles(tmp_path):
+    """Every pair of listed tiles of one head finds a workgroup, and workgroups without one are few: not one per
+    listed tile, of which half would exit (alternating with the others in ordinary lists, they left half the chip idle)."""
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no C++ compiler")
+    (tmp_path / "list.cc").write_text(LIST_PROGRAM)
+    subprocess.check_call([gxx, "-std=c++17", "-O1", "-Wall", "-Werror", f"-I{CSRC}", str(tmp_path / "list.cc"), "-o", str(tmp_path / "list")])
+    rng = np.random.default_rng(3)
+    lists = []
+    for heads in (1, 2, 40, 128):
+        for n in (1, 2, 3, 16, 127, 3600, 4095, 4096, 4097, 9000, 57600):
+            lists.append((heads, np.sort(np.arange(n) % heads)))                     # head after head
+            lists.append((heads, np.arange(n) % heads))                              # interleaved
+            lists.append((heads, rng.integers(0, heads, n)))
+    args = [str(x) for heads, l in lists for x in (len(l), heads)]
+    out = [int(x) for x in subprocess.run([str(tmp_path / "list"), *args], capture_output=True, text=True, check=True).stdout.split()]
+    window = out[0]
+    for blocks, (heads, l) in zip(out[1:], lists):
+        parts = [l[i:i + window] for i in range(0, len(l), window)]
+        pairs = [int(((np.bincount(p, minlength=heads) + 1) // 2).sum()) for p in parts]
+        rooms = [(len(p) + min(heads, len(p))) // 2 for p in parts]                  # of each window, one after the other
+        assert blocks == sum(rooms) and all(a <= b <= a + heads // 2 for a, b in zip(pairs, rooms)), (heads, len(l))

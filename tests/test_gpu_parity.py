@@ -1065,6 +1065,30 @@ def test_target_heatmap_at_edge_tiles(dtype, d, tile_tokens, grid):
         assert torch.equal(p[rows], got[rows]) and bool((p[others] == -7.0).all())
 
 
+@pytest.mark.parametrize("dtype,batch", [("bf16", 2), ("f32", 1)])
+def test_listed_query_tiles_of_every_pattern(dtype, batch):
+    """100 heads, lists on both sides of the window that pairs are looked for in (4096 entries), in order and not,
+    the same even count in every head, single tiles: the listed rows as in the full run, the others untouched."""
+    grid, heads, d = (8, 16, 24), 100, 64
+    wl = wlm.custom_workload("lists", heads, d, dtype, grid, False, (50, 100), seed=37, batch=batch)
+    q, k, _ = wlm.make_qkv(wl, torch.device("cuda:0"))
+    plan = veda.Plan(batch, heads, d, grid, np.asarray([[4, 4, 4]] * heads, np.int32), wl.torch_dtype)
+    qt, vm, _ = veda.veda_tile_layout(plan, q)
+    kt, _, _ = veda.veda_tile_layout(plan, k, want_mask=False)
+    heat = veda.veda_tile_heatmap(plan, qt, kt, vm, 0.125)
+    n, total = plan.tiles[0], plan.total_tiles
+    mixed = np.random.default_rng(9).permutation(total)
+    lists = [np.arange(total), mixed, mixed[:4096], mixed[:4097], mixed[:257], np.arange(0, total, 2), np.arange(0, total, 12), np.arange(0, total, 24),
+             np.concatenate([np.arange(i, total, n) for i in range(0, n, 3)]), np.asarray([total - 1]), np.asarray([n, n - 1, 1])]
+    full = heat.view(batch, total, n)
+    for listed in lists:
+        listed = torch.as_tensor(listed.astype(np.int32)).cuda()
+        part = veda.veda_tile_heatmap(plan, qt, kt, vm, 0.125, listed, torch.full_like(heat, -7.0)).view(batch, total, n)
+        rest = torch.ones(total, dtype=torch.bool, device="cuda:0")
+        rest[listed.long()] = False
+        assert torch.equal(part[:, ~rest], full[:, ~rest]) and bool((part[:, rest] == -7.0).all()), len(listed)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_fp32_target_scores_below_the_smallest_normal_number(d):
     """Key tiles up to 102 below the row's maximum (natural units): their scores are subnormal, keep their order,
