@@ -457,6 +457,26 @@ def test_select_long_rows_use_every_instantiation():
             assert np.array_equal(got[rows:], np.tile(np.arange(k), (nt - rows, 1))), (grid, k)
 
 
+@pytest.mark.parametrize("grid", [(1, 8, 64), (9, 18, 18), (136, 32, 64)])
+def test_select_rows_of_one_sign_and_of_both(grid):
+    """The search starts below the bits a row's scores share; the sign is the first of them.  Rows in registers and in
+    memory, whole and ragged, with one sign, both, one value, two, and thresholds on either side of zero."""
+    plan = veda.Plan(1, 1, 64, grid, np.asarray([[1, 8, 8]], np.int32), torch.float32)
+    nt = plan.tiles[0]
+    x = np.random.default_rng(nt).standard_normal((9, nt)).astype(np.float32)
+    x[1], x[2] = np.abs(x[1]), -np.abs(x[2])
+    x[3], x[4] = 3.0 + np.abs(x[3]) % 1.0, -3.0 - np.abs(x[4]) % 1.0       # many shared bits
+    x[5], x[6] = -np.inf, np.where(x[6] > 0, np.inf, np.nan)
+    x[7], x[8] = np.where(x[7] > 0, 2.0, -0.0), -1.0
+    x[8, nt // 3] = 1.0                                                    # one of the other sign
+    s = x[np.arange(nt) % 9]
+    for k in sorted({1, nt // 2, nt - 1, nt} - {0}):
+        _, ci = veda.veda_tile_select(plan, torch.as_tensor(s).reshape(1, -1).cuda(), [k])
+        torch.cuda.synchronize()
+        ref, got = vo.select(x, k), ci.cpu().numpy().reshape(nt, k)
+        assert np.array_equal(got, ref[np.arange(nt) % 9]), (grid, k)
+
+
 def test_select_sampled_pivot_paths():
     # 2048-tile rows at 5 % kept go through the sampled-pivot kernel.  Rows are built so that the
     # candidate list comes out well sized, too short (large values only where the sample looks),
