@@ -228,8 +228,7 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     auto chunk_off = [&](uint32_t c) __attribute__((always_inline)) {
         return ((c & 1u) ? k_chunk[0] : 0u) + ((c & 2u) ? k_chunk[1] : 0u) + ((c & 4u) ? k_chunk[2] : 0u);
     };
-    // The K tile (what = 0) or the V^T tile (what = 1) of step e into LDS slot `sl`; nothing past the end.
-    constexpr int kKeepers = 3;
+    // The K tile (what = 0) or the V^T tile (what = 1) of step e into LDS slot `sl`; nothing for an empty one or past the end.
     auto load_tile = [&](const MergedStep& e, int sl, int what) __attribute__((always_inline)) {
         uint32_t off[kLoads];
         if (what == 0) {
@@ -237,39 +236,35 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
             const uint32_t dst = wave_lds + (uint32_t)sl * kSlot;
             if (__builtin_expect(e.fl & kStepWhole, 1)) {
                 dma16_group_to_lds<kLoads>(dst, src, k_src);
-            } else if (!(e.fl & kKeepers)) {
-            } else if (e.fl & kStepHalf) {   // the first 32 rows, from the chunks that hold real tokens
-                if (wave < 2) {
-                    const uint32_t from = (uint32_t)(e.vm >> 32);
+            } else if (e.fl & kStepPart) {
+                if (kTokK) {   // padded rows have no token
 #pragma unroll
-                    for (int j = 0; j < kLoads; ++j) {
-                        const int c = (wave * kLoads + j) * (1024 / kRowB) / 8;
-                        const uint32_t moved = k_src[j] + chunk_off((from >> (8 * c)) & 255u) - chunk_off((uint32_t)c);
-                        off[j] = !kTokK || (e.vm >> k_row[j]) & 1ull ? moved : k_src0[j];
-                    }
+                    for (int j = 0; j < kLoads; ++j) off[j] = (e.vm >> k_row[j]) & 1ull ? k_src[j] : k_src0[j];
                     dma16_group_to_lds<kLoads>(dst, src, off);
+                } else {
+                    dma16_group_to_lds<kLoads>(dst, src, k_src);
                 }
-            } else if (kTokK && e.vm != ~0ull) {   // edge tile: padded rows have no token
+            } else if ((e.fl & kStepHalf) && wave < 2) {   // the first 32 rows, from the chunks that hold real tokens
+                const uint32_t from = (uint32_t)(e.vm >> 32);
 #pragma unroll
-                for (int j = 0; j < kLoads; ++j) off[j] = (e.vm >> k_row[j]) & 1ull ? k_src[j] : k_src0[j];
+                for (int j = 0; j < kLoads; ++j) {
+                    const int c = (wave * kLoads + j) * (1024 / kRowB) / 8;
+                    const uint32_t moved = k_src[j] + chunk_off((from >> (8 * c)) & 255u) - chunk_off((uint32_t)c);
+                    off[j] = !kTokK || (e.vm >> k_row[j]) & 1ull ? moved : k_src0[j];
+                }
                 dma16_group_to_lds<kLoads>(dst, src, off);
-            } else {
-                dma16_group_to_lds<kLoads>(dst, src, k_src);
             }
         } else {
             const uint32_t dst = wave_lds + (uint32_t)sl * kSlot + kKBytes;
             const char* src = vt + (int64_t)e.j * kVBytes;
-            if (__builtin_expect(e.fl & kStepWhole, 1)) {
+            if (__builtin_expect(e.fl & (kStepWhole | kStepPart), 1)) {
                 dma16_group_to_lds<kLoads>(dst, src, v_src);
-            } else if (!(e.fl & kKeepers)) {
             } else if (e.fl & kStepHalf) {   // chunks 0-3 from where the real tokens are; chunks 4-7 are not read
                 const uint32_t from = ((uint32_t)(e.vm >> 32) >> (8 * (v_c & 3))) & 255u;
                 const uint32_t delta = (from - (uint32_t)(v_c & 3)) << 4;
 #pragma unroll
                 for (int j = 0; j < kLoads; ++j) off[j] = v_src[j] + (((v_c >> 2) & 1) == (j & 1) ? delta : 0u);
                 dma16_group_to_lds<kLoads>(dst, src, off);
-            } else {
-                dma16_group_to_lds<kLoads>(dst, src, v_src);
             }
         }
     };
