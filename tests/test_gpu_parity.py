@@ -1085,6 +1085,66 @@ def test_target_heatmap_at_edge_tiles(dtype, d, tile_tokens, grid):
         assert torch.equal(p[rows], got[rows]) and bool((p[others] == -7.0).all())
 
 
+@pytest.mark.parametrize("dtype,d,tile_tokens", [("bf16", 128, 64), ("bf16", 64, 128), ("f32", 64, 64), ("f32", 128, 64)])
+def test_row_sums_formed_under_another_tiling(dtype, d, tile_tokens):
+    """What veda_tile_heatmap_rows is for: the sums written under one set of tile shapes, in token order, read under
+    another (64- and 128-token tiles hand them to each other as well): scores against the oracle."""
+    grid, batch = (9, 10, 14), 2
+    first = np.asarray([[4, 4, 4], [1, 8, 8], [16, 2, 2]], np.int32)
+    second = first[[1, 2, 0]] * np.asarray([tile_tokens // 64, 1, 1], np.int32)
+    wl = wlm.custom_workload("cross", 3, d, dtype, grid, False, (50, 100), seed=41, batch=batch)
+    q, k, _ = wlm.make_qkv(wl, torch.device("cuda:0"))
+    scale, sums = 1.0 / math.sqrt(d), None
+    for shapes, tokens in ((first, 64), (second, tile_tokens), (first, 64)):
+        plan = veda.Plan(batch, 3, d, grid, shapes, wl.torch_dtype, tile_tokens=tokens)
+        qt, vm, _ = veda.veda_tile_layout(plan, q)
+        kt, _, _ = veda.veda_tile_layout(plan, k, want_mask=False)
+        if sums is not None and tokens == 64 and shapes is first:      # and back: sums formed under the second set
+            _, sums = veda.veda_tile_heatmap_rows(last[0], last[1], last[2], last[3], scale)
+        heat, sums = veda.veda_tile_heatmap_rows(plan, qt, kt, vm, scale, sums)
+        torch.cuda.synchronize()
+        for b in range(batch):
+            for h in range(3):
+                nt, soff = plan.tiles[h], plan.score_offset[h]
+                ref = vo.tile_heatmap(hz.to_f32_numpy(q[b, h]), hz.to_f32_numpy(k[b, h]), grid, tuple(int(x) for x in shapes[h]), scale)
+                got = heat[b, soff:soff + nt * nt].view(nt, nt).cpu().numpy().astype(np.float64)
+                rel = (np.abs(got - ref) / ref).max()
+                assert rel <= (2e-4 if dtype == "bf16" else 2e-5), (tokens, b, h, rel)
+        last = (plan, qt, kt, vm)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+def test_target_scores_of_rows_whose_logits_rise_along_the_keys(dtype, d):
+    """The softmax reference of a row moves many times after its first block, on both sides of the places where the
+    running part of its denominator is put away (every 32 steps): logits rise by 60 over 80 key tiles, fall, or do neither,
+    from row to row."""
+    grid, n, rise = (4, 16, 80), 5120, 60.0
+    g = torch.Generator().manual_seed(6)
+    q, k = torch.randn((1, 1, n, d), generator=g), 0.5 * torch.randn((1, 1, n, d), generator=g)
+    token = torch.arange(n)
+    tile = (token // 80 % 16) // 4 * 20 + (token % 80) // 4                     # 4 x 20 tiles of 4x4x4
+    q[0, 0, :, 0] = torch.tensor([1.0, -1.0, 0.0, 0.5])[token % 4]
+    k[0, 0, :, 0] = (tile / 79.0 - 0.5) * rise * math.sqrt(d)
+    q, k = (x.to(torch.bfloat16 if dtype == "bf16" else torch.float32).cuda() for x in (q, k))
+    scale = 1.0 / math.sqrt(d)
+    plan = veda.Plan(1, 1, d, grid, np.asarray([[4, 4, 4]], np.int32), q.dtype)
+    qt, vm, _ = veda.veda_tile_layout(plan, q)
+    kt, _, _ = veda.veda_tile_layout(plan, k, want_mask=False)
+    heat, sums = veda.veda_tile_heatmap_rows(plan, qt, kt, vm, scale)
+    again, _ = veda.veda_tile_heatmap_rows(plan, qt, kt, vm, scale, sums)
+    torch.cuda.synchronize()
+    assert torch.equal(again, heat)
+    rows = np.arange(0, 80, 9)
+    ref = vo.tile_heatmap(hz.to_f32_numpy(q[0, 0]), hz.to_f32_numpy(k[0, 0]), grid, (4, 4, 4), scale, query_tiles=rows)[rows]
+    got = heat[0].view(80, 80)[torch.as_tensor(rows).cuda()].cpu().numpy().astype(np.float64)
+    # a logit (and the row's reference) is a sum of d products rounded at the size of the sum, at most rise / 2 and the
+    # noise beside it, then scaled; the denominator's sums have 16, 64 and 3 terms a lane, and moves beside them
+    rtol = (2 * (d + 3) * (rise / 2 + 6.0) + 256) * 2.0 ** -24
+    rel = np.abs(got - ref) / ref
+    _say(f"[parity] rising logits {dtype} d {d}: max rel err {rel.max():.2e} of {rtol:.2e}, scores {ref.min():.1e} to {ref.max():.2f}")
+    assert rel.max() <= rtol, rel.max()
+
+
 @pytest.mark.parametrize("dtype,batch", [("bf16", 2), ("f32", 1)])
 def test_listed_query_tiles_of_every_pattern(dtype, batch):
     """100 heads, lists on both sides of the window that pairs are looked for in (4096 entries), in order and not,
