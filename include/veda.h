@@ -311,9 +311,11 @@ veda_status veda_sparse_attn_fwd_qk_tokens(const veda_plan*, const void* q, veda
 veda_status veda_tile_heatmap(const veda_plan*, const void* q_tiled, const void* k_tiled,
                               const uint64_t* valid_mask, float softmax_scale, const int32_t* query_tiles,
                               int64_t n_query_tiles, float* heat, void* stream);
-/* The same for all query tiles, with the softmax sums of the rows handed over: they do not depend on how the
- * tokens are tiled, so a caller that forms the target scores of one Q, K and softmax_scale under several tilings
- * needs them once.
+/* The same for all query tiles, with the softmax sums of the rows handed over: up to fp32 rounding they do not
+ * depend on how the tokens are tiled, so a caller that forms the target scores of one Q, K and softmax_scale under
+ * several tilings needs them once.  (The sum runs in tile order, and the reference is that of the key block that last
+ * raised it: scores from sums formed under another tiling differ in the last bits from those formed under their own,
+ * and a selection among scores equal to rounding may go the other way.)
  * row_sums device fp32 [batch][heads][tokens][2], 8-byte aligned, in token order: a reference point of the row's
  *          exponentials and one over their sum.  have_row_sums = 0: formed and written (both passes);
  *          1: read, and only the second pass runs. */

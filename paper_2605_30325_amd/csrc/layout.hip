@@ -105,10 +105,13 @@ __global__ void valid_cnt_pairs_kernel(const uint64_t* __restrict__ mask, int32_
 // to different heads).
 // Bound by the latency of the loads on small inputs and by memory on large ones, so the rows of kBatch slots
 // are requested before the first is used, padded ones included (from token 0), and four channels instead of
-// eight bf16 ones make twice the wavefronts.  Measured, 8 slots at a time with 16-byte loads and now: 4 heads of
-// 75 tiles, 2 samples (bf16, d = 64) 26 -> 11 us; 12 heads of 624 tiles (bf16, d = 128) 40 -> 23 us, writing tiles
-// 43 -> 39; 24 heads of 219,600 tokens 305 -> 272 us (4.9 TB/s), writing tiles 625 -> 527 (5.1 TB/s).  Without the
-// tiles half a batch is enough (more wavefronts: 12 heads 26 us with a whole one, 4 heads alike).
+// eight bf16 ones make twice the wavefronts.  Measured, 8 slots at a time with 16-byte loads and now, calls repeated
+// (inputs of up to 256 MB stay in the memory-side cache): 4 heads of 75 tiles, 2 samples (bf16, d = 64) 26 -> 11 us; 12
+// heads of 624 tiles (bf16, d = 128) 39 -> 22, writing tiles 43 -> 39; 24 heads of 219,600 tokens 309 -> 277 us (1.49 GB,
+// 5.4 TB/s), writing tiles 637 -> 540 (3.0 GB with the padding, 5.6 TB/s).  Single calls on inputs that have left the
+// caches, from event to event: 51 -> 15, 72 -> 46 and 91 -> 73, 363 -> 331 and 660 -> 565.  Without the tiles half a
+// batch is enough and makes more wavefronts: 22.3 us against 24.9 at 12 heads, 164 against 166 at 40 heads of 1440 tiles,
+// alike on inputs that have left the caches.
 // kWrite = false: descriptors (and masks) only, the tiled tensor is not written.
 // GRP = 2: 128-token tiles.  `heads`, `tile_head` and total_tiles are then those of the 64-slot
 // halves (halves 2g, 2g+1 of whole tile g); a thread walks the 128 slots of a whole tile in order

@@ -53,7 +53,9 @@ def tiling_search(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, grid: Seque
         vt, _, _ = veda.veda_tile_layout(plan, v, veda.VEDA_CHANNEL_MAJOR, want_mask=False)
         if o_full is None:   # the full-attention output does not depend on the tiling
             o_full = _dense_output(plan, qt, kt, vt, vm, scale)
-        heat, row_sums = veda.veda_tile_heatmap_rows(plan, qt, kt, vm, scale, row_sums)   # nor do the rows' softmax sums
+        # nor, up to fp32 rounding, do the rows' softmax sums: those of the first candidate serve all, so the scores of a later
+        # one, and its choice between two equal to rounding, can change in the last bits with the order of the candidates
+        heat, row_sums = veda.veda_tile_heatmap_rows(plan, qt, kt, vm, scale, row_sums)
         kph = keep_budget(plan.tiles, keep)
         row_ptr, col_idx = veda.veda_tile_select(plan, heat, kph)
         o_sp, _ = veda.veda_sparse_attn_fwd(plan, qt, kt, vt, vm, row_ptr, col_idx, scale)

@@ -452,7 +452,8 @@ def veda_tile_heatmap(plan: Plan, q_tiled, k_tiled, valid_mask, softmax_scale: f
 def veda_tile_heatmap_rows(plan: Plan, q_tiled, k_tiled, valid_mask, softmax_scale: float, row_sums: Optional[torch.Tensor] = None,
                            heat: Optional[torch.Tensor] = None):
     """veda_tile_heatmap of all query tiles with the rows' softmax sums: given (as an earlier call on the same
-    Q, K and scale returned them, under whatever tiling), only the second pass over the keys runs.
+    Q, K and scale returned them, under whatever tiling), only the second pass over the keys runs.  Sums of another
+    tiling are the same up to fp32 rounding, not bit for bit.
     Returns (heat, row_sums fp32 [batch, heads, tokens, 2])."""
     dev = q_tiled.device
     if heat is None:
