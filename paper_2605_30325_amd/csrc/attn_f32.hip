@@ -9,8 +9,8 @@
 // compute unit (2 x 74 KB at d = 128), and the second one's products fill the matrix pipe while a wave of the
 // first is in its softmax, at a barrier, or skips a key tile that only its partner keeps.  Padding is handled
 // as in the bf16 kernel (real query rows first; half steps, attn_union.h).
-// Measured: 8 heads of 624 tiles, 10 % kept, 8.4 -> 5.3 ms a call; 8 heads of 144 tiles, all kept and 25 % kept,
-// 2.2 -> 1.7 ms on average.
+// Measured, the attention call alone: 8 heads of 624 tiles, 10 % kept, 8.5 -> 5.8 ms repeated back to back (5.3 between
+// the other stages of whole calls); 8 heads of 144 tiles, all kept and 25 % kept, 2.2 -> 1.7 ms on average.
 //
 // Products are formed transposed with v_mfma_f32_32x32x2_f32 (S^T = K Q^T, O^T = V^T P^T): a lane
 // owns one query (lane % 32) and one of the two terms of every instruction (h = lane / 32).  The

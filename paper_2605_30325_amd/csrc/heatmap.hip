@@ -487,7 +487,10 @@ struct RecallArgs {
 };
 
 constexpr int kRecallWords = 512;   // bitmap words of a row: 16384 key tiles
-constexpr int kRecallRows = 4;      // consecutive rows of a wavefront, to save atomics on the totals
+// Consecutive rows of a wavefront, to save atomics on the totals.  One, two, four and eight: 12 heads of 624 rows 76, 40,
+// 24.5 and 20 us for the whole call; 40 heads of 1440 385, 218, 114 and 62; 4 heads of 75 9.4, 8.4, 9.1 and 12.5 (too few
+// wavefronts).
+constexpr int kRecallRows = 4;
 
 __global__ __launch_bounds__(256) void recall_count_kernel(const HeadGeom* __restrict__ heads,
                                                            const uint8_t* __restrict__ tile_head, RecallArgs args,
