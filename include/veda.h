@@ -322,6 +322,15 @@ veda_status veda_tile_heatmap(const veda_plan*, const void* q_tiled, const void*
 veda_status veda_tile_heatmap_rows(const veda_plan*, const void* q_tiled, const void* k_tiled,
                                    const uint64_t* valid_mask, float softmax_scale, float* row_sums,
                                    int32_t have_row_sums, float* heat, void* stream);
+/* veda_tile_heatmap_ws = veda_tile_heatmap (the same values, bit for bit) with scratch: the logits are formed once, their
+ * block maxima are kept there, and the second pass over the key tiles falls away.
+ * row_sums  optional: written as by veda_tile_heatmap_rows with have_row_sums = 0.
+ * workspace device, 16-byte aligned, at least veda_plan_heatmap_workspace_bytes() (512 bytes per key tile of the
+ *           largest head for each of at most 1024 workgroups); contents undefined after. */
+size_t veda_plan_heatmap_workspace_bytes(const veda_plan*, int64_t n_query_tiles);
+veda_status veda_tile_heatmap_ws(const veda_plan*, const void* q_tiled, const void* k_tiled, const uint64_t* valid_mask,
+                                 float softmax_scale, const int32_t* query_tiles, int64_t n_query_tiles, float* row_sums,
+                                 float* heat, void* workspace, size_t workspace_bytes, void* stream);
 /* veda_tile_recall (Sec. 3.2, Recall@k): col_idx_a, col_idx_b device CSR column lists as stage 3
  * writes them for the same k_per_head (host i32 [heads]); each row a list of distinct tiles.
  * recall   device fp32 [batch][heads]: mean over the head's query tiles of |A_i & B_i| / k.

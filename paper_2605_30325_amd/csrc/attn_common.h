@@ -46,13 +46,13 @@ struct AttnArgs {
 // query tiles and walks the heads in order: all dies then work on the same head at the same
 // time (its K/V, ~120 MB at 220k tokens, stay in the memory-side cache), and the workgroups
 // sharing an L2 hold neighbouring query tiles, whose kept key tiles overlap.
-// The work item is a pair of adjacent query tiles; xcd_cum is the plan's table of them.  Returns false for the padding workgroups of dies
-// with fewer items.
+// The work item is a pair of adjacent query tiles; xcd_cum is the plan's table of them, `at` the workgroup's number.  Returns false
+// for the padding workgroups of dies with fewer items.
 // The head is found with one load per lane and a ballot: a binary search is log2(heads) loads one after the
 // other, at the head of every workgroup's life (see union_build for what the whole of it costs).
 __device__ inline bool xcd_work(const int32_t* __restrict__ xcd_cum, const HeadGeom* __restrict__ heads,
-                                int n_heads, int& head, int& item) {
-    const int x = blockIdx.x % kXcd, local = blockIdx.x / kXcd, lane = threadIdx.x & 63;
+                                int n_heads, int at, int& head, int& item) {
+    const int x = at % kXcd, local = at / kXcd, lane = threadIdx.x & 63;
     const int32_t* cum = xcd_cum + x * (n_heads + 1);
     // cum[0] = 0, ascending: the last head whose first item is <= local
     static_assert(kMaxHeads <= 128, "two entries per lane");

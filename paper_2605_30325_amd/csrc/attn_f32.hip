@@ -55,7 +55,7 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_f32_kernel(AttnArgs a) {
     const int idx = lane & 31, h = lane >> 5;
 
     int head, pair;
-    if (!xcd_work(a.xcd_cum, a.heads, a.n_heads, head, pair)) return;
+    if (!xcd_work(a.xcd_cum, a.heads, a.n_heads, blockIdx.x, head, pair)) return;
     const HeadGeom hg = a.heads[head];
     const int64_t b = blockIdx.y;
     int qiA, qiB;

@@ -9,7 +9,9 @@
 // softmax, pass 2 forms the logits again and reduces exp(s_uv - m_u) / l_u over each 64 x 64
 // block.  exp is monotone, so the block maximum needs one exponential per query row and
 // block: exp(max_v s_uv - m_u) / l_u, then the maximum over the rows u.  Both passes stay in
-// one kernel: m_u and l_u never leave the registers and no workspace is needed.
+// one kernel: m_u and l_u never leave the registers.  With scratch (veda_tile_heatmap_ws) the block's
+// max_v s_uv of pass 1 are kept, 4 bytes per row and key tile where the products of that block read 16 KB, and pass 2
+// only reads those: the same bits without forming the logits again.
 //
 // The same kernel serves bf16 and fp32 (v_mfma_f32_32x32x16_bf16 or v_mfma_f32_32x32x2_f32, fp32
 // accumulation): S^T = K Q^T, so a lane owns a query row and its registers run over keys.  A workgroup holds
@@ -22,6 +24,11 @@
 // workgroup); 8 heads of 144 tiles, fp32, d = 128, 19.1 -> 3.0 ms (on the vector units before).  Tried and left out: 64 rows
 // per wave, four tiles per workgroup (half the operand reads and loads: 8.3 and 11.7 ms, fp32 3.9), a ring of
 // three or four K tiles (0.5 ms slower: it costs a resident workgroup and the loads are not what is waited for).
+// With scratch, whole calls of the supervision side (gathers, heat map, both top-k, recall), two walks and one: 12 heads
+// of 624 tiles 8.0 -> 5.0 ms, one in 16 tiles of 40 heads of 21x45x80 13.4 -> 8.8 ms.  Pass 1 then stands at 79 % vector
+// issue (85 instructions per 8 products; 48 of them are the exponentials' three, 8 the maximum) and 45 % matrix pipe; of that, masks
+// on the scalar unit, operand addresses formed once per step and no register copies at the ends of branches gave a fifth,
+// handing work items out as asked for 12 % of the second case.
 // Padding: a tile's real rows come first (a wave runs only the blocks that hold any), and key tiles with few
 // real keys are half steps (attn_union.h).
 #include <type_traits>
@@ -48,6 +55,10 @@ struct HeatArgs {
     int have_rows;                // read them instead of running pass 1
     int64_t tokens;
     int T, H, W;
+    uint32_t* taken;              // one-walk mode: work items handed out, per die, kHeatTakenStride apart; null = one each
+    float* maxima;                // one-walk mode: kept block maxima, max_tiles * 128 floats per workgroup
+    int64_t max_tiles;            // tiles of the largest head
+    uint32_t items, batch;        // work items of a sample; samples
 };
 
 // Maximum over the 32 rows of a wave (x alike in both lane halves), wave-uniform: within 16 lanes by DPP, the
@@ -81,6 +92,7 @@ template <> struct HeatFrag<uint32_t> {
     }
 };
 
+constexpr int kHeatTakenStride = 16;   // counters of the dies, 64 bytes apart
 constexpr int kHeatFold = 32;          // steps after which the running part of a denominator is put away
 constexpr float kHeatNoRef = -3e38f;   // reference before the first key: everything finite outgrows it
 // A lane's sum over its 16 keys of a block above this moves the reference.  At most 16 where the reference is
@@ -119,11 +131,11 @@ __device__ __forceinline__ int wave_scan(int x) {
 // 12 heads of 624 in order, bf16 11.4 -> 7.9 and fp32 128 -> 64.6 ms (without a list 7.75 and 64.2), in no order
 // 8.8 -> 7.8 and 77 -> 64.2; all 57,600 of 40 heads at d = 64 142 -> 87 ms; 8 tiles of 2 heads 15.3 -> 15.9 us.  A
 // contiguous piece of the list for each die, followers still exiting, is not enough (13.1, 13.3 and 121 ms).
-__device__ inline bool listed_pair(const HeatArgs& a, char* smem, int tid, int& head, int (&pair)[2]) {
+__device__ inline bool listed_pair(const HeatArgs& a, int item, char* smem, int tid, int& head, int (&pair)[2]) {
     static_assert(kMaxHeads == 128, "two heads per lane");
     const int lane = tid & 63;
-    const int per = (int)list_window_blocks(kListWindow, a.n_heads), p = (int)blockIdx.x % per;
-    const int64_t begin = (int64_t)((int)blockIdx.x / per) * kListWindow;
+    const int per = (int)list_window_blocks(kListWindow, a.n_heads), p = item % per;
+    const int64_t begin = (int64_t)(item / per) * kListWindow;
     const int m = (int)(a.n_query_tiles - begin < kListWindow ? a.n_query_tiles - begin : kListWindow);
     const int32_t* list = a.query_tiles + begin;
     uint8_t* heads = reinterpret_cast<uint8_t*>(smem);
@@ -162,8 +174,10 @@ __device__ inline bool listed_pair(const HeatArgs& a, char* smem, int tid, int& 
 
 // kGrouped: 128-token tiles.  The geometry in `a` is that of the 64-slot halves; a whole tile is a
 // workgroup and two consecutive key steps, and its block maximum the maximum over them.
-template <typename E, int D, bool kGrouped, bool kListed>
-__global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
+// kOneWalk: the logits are formed once.  Pass 1 keeps the largest raw logit of every row and key tile in scratch, one
+// place per workgroup and written over for its next work item; pass 2 reads those instead of forming the products again.
+template <typename E, int D, bool kGrouped, bool kListed, bool kOneWalk>
+__global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : 3) void tile_heatmap_kernel(HeatArgs a) {
     typedef HeatFrag<E> F;
     typedef typename F::type frag;
     typedef const __attribute__((address_space(3))) frag* lds_frag_ptr;
@@ -184,16 +198,19 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
     const int idx = lane & 31, hh = lane >> 5;
     const int which = wave >> 1, r = wave & 1;   // this wave's tile and 32-row block
 
-    // work item: up to two query tiles of one head; qi < 0: this wave has none
-    int head, qi = -1;
+    // A work item is up to two query tiles of one head.
+    auto run = [&](uint32_t work) __attribute__((always_inline)) {
+    const int64_t b = work / a.items;
+    const int at = (int)(work - (uint32_t)b * a.items);
+    int head, qi = -1;   // qi < 0: this wave has none
     if constexpr (kListed) {
         int own;   // this wave's entry
         if (kGrouped) {   // a listed 128-token tile fills a workgroup
-            own = a.query_tiles[blockIdx.x];
+            own = a.query_tiles[at];
             head = a.tile_head[2 * own];
         } else {
             int pair[2];
-            if (!listed_pair(a, smem, tid, head, pair)) return;
+            if (!listed_pair(a, at, smem, tid, head, pair)) return;
             own = pair[which];
         }
         const int lo = a.heads[head].tile_off;
@@ -201,14 +218,13 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
     } else {
         int item, qiA, qiB;
         bool hasB;
-        if (!xcd_work(a.xcd_cum, a.heads, a.n_heads, head, item)) return;
+        if (!xcd_work(a.xcd_cum, a.heads, a.n_heads, at, head, item)) return;
         pair_tiles(a.heads[head], item, qiA, qiB, hasB);
         qi = which == 0 ? qiA : hasB ? qiB : -1;
     }
     qi = __builtin_amdgcn_readfirstlane(qi);
     const HeadGeom hg = a.heads[head];
     const int n = hg.n_tiles;
-    const int64_t b = blockIdx.y;
     const int64_t head_tile0 = b * a.total_tiles + hg.tile_off;
     const char* kt = a.k + head_tile0 * kKBytes;
     typedef const __attribute__((address_space(4))) uint64_t* const_u64_t;
@@ -299,18 +315,24 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
         wait_vmcnt<0>();
         __syncthreads();
     };
-#define VEDA_KF(ka, f) (*(lds_frag_ptr)(uintptr_t)((ka) ^ (uint32_t)((f) << 5)))
+#define VEDA_KF(block, f) (*(lds_frag_ptr)(uintptr_t)(kx[f] + (block) * (uint32_t)(32 * kRowB)))
 
-    // Raw dot products of this wave's rows with the 32 keys at LDS address ka; `behind(f)` is vector work placed
+    // Raw dot products of this wave's rows with the 32 keys of the step's block 0 or 1; `behind(f)` is vector work placed
     // behind the products of fragment f.
-    auto products = [&](f32x16& s, uint32_t ka, auto behind) __attribute__((always_inline)) {
+    uint32_t kx[kF];   // operand addresses of a step's first block; the second is a constant distance away
+    auto addresses = [&](int j) __attribute__((always_inline)) {
+        const uint32_t ka = k0 + (uint32_t)((j & 1) * kKBytes);
+#pragma unroll
+        for (int f = 0; f < kF; ++f) kx[f] = ka ^ (uint32_t)(f << 5);
+    };
+    auto products = [&](f32x16& s, uint32_t block, auto behind) __attribute__((always_inline)) {
         const f32x16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
         frag kf[kF];
 #pragma unroll
-        for (int f = 0; f < kAhead; ++f) kf[f] = VEDA_KF(ka, f);
+        for (int f = 0; f < kAhead; ++f) kf[f] = VEDA_KF(block, f);
 #pragma unroll
         for (int f = 0; f < kF; ++f) {
-            if (f + kAhead < kF) kf[f + kAhead] = VEDA_KF(ka, f + kAhead);
+            if (f + kAhead < kF) kf[f + kAhead] = VEDA_KF(block, f + kAhead);
             s = F::mul(kf[f], qf[f], f == 0 ? zero : s);
             behind(f);
             __builtin_amdgcn_sched_barrier(0);
@@ -320,10 +342,13 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
     auto mask_keys = [&](f32x16& s, uint32_t mask) __attribute__((always_inline)) {
         if (mask == ~0u) return;
         asm volatile("" ::: "memory");   // keeps this a branch, taken at edge tiles only
-        const uint32_t half = mask >> (4 * hh);
+        // a register's two keys as a lane mask, on the scalar unit: the vector unit is what pass 1 waits for
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-            if (!((half >> (8 * (i >> 2) + (i & 3))) & 1u)) s[i] = -INFINITY;
+        for (int i = 0; i < 16; ++i) {
+            const int bit = 8 * (i >> 2) + (i & 3);
+            const uint32_t lo = (uint32_t)((int)(mask << (31 - bit)) >> 31), up = (uint32_t)((int)(mask << (27 - bit)) >> 31);
+            s[i] = __builtin_amdgcn_inverse_ballot_w64((uint64_t)up << 32 | lo) ? s[i] : -INFINITY;
+        }
     };
     // relative to ref, log2 units
     auto logit = [&](float x, float ref) __attribute__((always_inline)) { return fmaf(x, a.scale_log2, -ref); };
@@ -355,12 +380,26 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
         }
         l_part += sum;
     };
-    if (a.have_rows) {
+    // One walk: the largest raw logits of this wave's rows, [key tile][32 rows], nothing for tiles without a real key.
+    float* const kept = kOneWalk ? a.maxima + ((int64_t)blockIdx.x * 4 + wave) * a.max_tiles * 32 : nullptr;
+    if (!kOneWalk && a.have_rows) {
         // nothing to do
     } else if (walk_begin(); active) {
-        // s1 holds the block whose exponentials are still to come: they are formed behind the next products
+        // s1 holds the block whose exponentials are still to come: they are formed behind the next products, and with
+        // them the maximum of its tile, `last`
         f32x16 s0, s1;
-        float sum;
+        float sum, mx = -INFINITY;
+        int last = -1;
+        auto maxima = [&](const f32x16& s, int f, bool first) __attribute__((always_inline)) {
+            if (!kOneWalk) return;
+#pragma unroll
+            for (int i = f * kExps; i < (f + 1) * kExps; ++i) mx = first && i == 0 ? s[0] : fmaxf(mx, s[i]);
+        };
+        auto keep = [&]() __attribute__((always_inline)) {
+            if (!kOneWalk || last < 0) return;
+            float* const rows = kept + (int64_t)last * 32;
+            rows[idx] = max_with_other_half(mx);   // alike in both halves
+        };
         auto exps = [&](const f32x16& s, int f) __attribute__((always_inline)) {
             if (f == 0) sum = 0.0f;
 #pragma unroll
@@ -370,15 +409,22 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
         for (int i = 0; i < 16; ++i) s1[i] = -INFINITY;
         for (int j = 0; j < n; ++j) {
             step_begin(j);
-            const uint32_t ka = k0 + (uint32_t)((j & 1) * kKBytes);
+            addresses(j);
             if (e0.kind != kStepEmpty) {
-                products(s0, ka, [&](int f) __attribute__((always_inline)) { exps(s1, f); });
+                products(s0, 0u, [&](int f) __attribute__((always_inline)) { exps(s1, f); maxima(s1, f, false); });
+                asm volatile("" : "+v"(sum), "+v"(mx));   // they stay behind the products: the branches below would take them along
+                keep();
+                last = j;
                 settle(s1, sum);
                 mask_keys(s0, e0.lo);
                 if (e0.kind == kStepHalf) {
-                    s1 = s0;
+                    // moves of this branch alone: as a plain copy the other branch would carry sixteen as well
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) s1[i] = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s0[i]), 0xE4, 0xf, 0xf, true));   // quad_perm [0,1,2,3]
+                    mx = -INFINITY;
                 } else {
-                    products(s1, ka + 32 * kRowB, [&](int f) __attribute__((always_inline)) { exps(s0, f); });
+                    products(s1, 1u, [&](int f) __attribute__((always_inline)) { exps(s0, f); maxima(s0, f, true); });
+                    asm volatile("" : "+v"(sum), "+v"(mx));
                     settle(s0, sum);   // before the mask's branch: the exponentials would move behind it
                     mask_keys(s1, e0.hi);
                 }
@@ -390,7 +436,8 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
             step_end();
         }
 #pragma unroll
-        for (int f = 0; f < kF; ++f) exps(s1, f);
+        for (int f = 0; f < kF; ++f) { exps(s1, f); maxima(s1, f, false); }
+        keep();
         settle(s1, sum);
     } else {   // a wave without rows loads and meets the others
         for (int j = 0; j < n; ++j) {
@@ -399,7 +446,7 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
         }
     }
     float inv_l;
-    if (a.have_rows) {
+    if (!kOneWalk && a.have_rows) {
         const float2 known = row_sums ? *row_sums : make_float2(0.0f, 0.0f);
         ref = known.x;
         inv_l = known.y;
@@ -435,15 +482,51 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
         }
         mine = 0.0f;
     };
+    if constexpr (kOneWalk) {
+        // A lane takes a key tile and goes through the wave's rows, whose reference and denominator are then scalars.
+        __syncthreads();   // what other lanes of this wave kept is read below; the last key tile has been read
+        const uint32_t rows_real = (uint32_t)__ballot(q_real);
+        for (int first = 0; first < n; first += 64) {
+            if (active) {
+                const int tile = first + lane < n ? first + lane : n - 1;
+                const float4* src = reinterpret_cast<const float4*>(kept + tile * 32);
+                float4 x[8];
+#pragma unroll
+                for (int g = 0; g < 8; ++g) x[g] = src[g];
+                const bool empty = vmask_g[tile] == 0ull;
+                float best = 0.0f;
+                asm volatile("" : "+v"(ref), "+v"(inv_l));   // 64 scalars, formed where they are used: kept, they would spill
+                auto take = [&](int i) __attribute__((always_inline)) {
+                    const float4& v = x[i >> 2];
+                    const float m = (i & 3) == 0 ? v.x : (i & 3) == 1 ? v.y : (i & 3) == 2 ? v.z : v.w;
+                    const float row_ref = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ref), i));
+                    const float row_inv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(inv_l), i));
+                    return heat_score<E>(logit(m, row_ref), row_inv);
+                };
+                if (rows_real == ~0u) {
+                    best = take(0);
+#pragma unroll
+                    for (int i = 1; i < 32; ++i) best = fmaxf(best, take(i));
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 32; ++i)
+                        if ((rows_real >> i) & 1u) best = fmaxf(best, take(i));
+                }
+                mine = empty ? 0.0f : best;
+            }
+            publish(first + 63 < n ? first + 63 : n - 1);
+        }
+        return;
+    }
     walk_begin();
     if (active) {
         for (int j = 0; j < n; ++j) {
             step_begin(j);
-            const uint32_t ka = k0 + (uint32_t)((j & 1) * kKBytes);
+            addresses(j);
             float best = 0.0f;
             if (e0.kind != kStepEmpty) {
                 f32x16 s0, s1;
-                products(s0, ka, [](int) {});
+                products(s0, 0u, [](int) {});
                 mask_keys(s0, e0.lo);
                 float mx = s0[0];
                 auto maxima = [&](const f32x16& s, int f) __attribute__((always_inline)) {
@@ -453,7 +536,7 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
                 if (e0.kind == kStepHalf) {
                     s1 = s0;
                 } else {
-                    products(s1, ka + 32 * kRowB, [&](int f) __attribute__((always_inline)) { maxima(s0, f); });
+                    products(s1, 1u, [&](int f) __attribute__((always_inline)) { maxima(s0, f); });
                     asm volatile("" : "+v"(mx));   // the maxima stay behind the products
                     mask_keys(s1, e0.hi);
                 }
@@ -472,8 +555,26 @@ __global__ __launch_bounds__(256, 2) void tile_heatmap_kernel(HeatArgs a) {
             publish(j);
         }
     }
+    };   // run
 #undef VEDA_KF
+
+    // With more items than places in the scratch a workgroup goes on with the next one of its die.  Handed out as they
+    // are asked for: a fixed share each left a quarter of the chip idle at the end where tiles differ (one in 16 of 40
+    // heads of 21x45x80, mixed shapes).
+    const uint32_t die = blockIdx.x % kXcd;
+    uint32_t* const next = reinterpret_cast<uint32_t*>(part + 4);
+    for (uint32_t work = blockIdx.x;;) {
+        run(work);
+        if (!kOneWalk || a.taken == nullptr) return;
+        if (tid == 0) *next = (gridDim.x / kXcd + atomicAdd(a.taken + die * kHeatTakenStride, 1u)) * kXcd + die;
+        __syncthreads();
+        work = (uint32_t)__builtin_amdgcn_readfirstlane((int)*next);
+        __syncthreads();
+        if (work >= a.items * a.batch) return;
+    }
 }
+
+__global__ void heat_taken_clear_kernel(uint32_t* taken) { taken[threadIdx.x * kHeatTakenStride] = 0u; }
 
 // Recall@k: a wavefront counts, row by row, the key tiles the two kept lists share (lists of
 // distinct tiles in any order); integer atomics keep the per-head totals order-independent.
@@ -569,10 +670,33 @@ __global__ void recall_finish_kernel(const HeadGeom* __restrict__ heads, RecallA
 
 }  // namespace veda
 
-// Both entry points; rows: optional row sums, read if have_rows.
+namespace veda {
+
+// One walk: the workgroups of a launch, each with a place in the scratch.  As many as are resident at once, which their
+// registers decide; a multiple of the dies.
+static int64_t heat_places(const veda_plan* pl) {
+    return 256 * (pl->prob.dtype == VEDA_BF16 ? (pl->prob.head_dim == 128 ? 4 : 5) : 3);
+}
+constexpr size_t kHeatTakenBytes = kXcd * kHeatTakenStride * sizeof(uint32_t);   // at the start of the scratch
+
+static int64_t heat_items(const veda_plan* pl, int64_t n_listed) {
+    const veda_plan* ip = pl->inner ? pl->inner : pl;
+    return n_listed == 0 ? (int64_t)kXcd * ip->xcd_max_pairs : pl->inner ? n_listed : list_blocks(n_listed, pl->prob.heads);
+}
+
+static int64_t heat_max_tiles(const veda_plan* pl) {
+    const veda_plan* ip = pl->inner ? pl->inner : pl;
+    int64_t n = 0;
+    for (const HeadGeom& g : ip->heads) n = g.n_tiles > n ? g.n_tiles : n;
+    return n;
+}
+
+}  // namespace veda
+
+// All entry points; rows: optional row sums, read if have_rows; workspace: optional.
 static veda_status target_heatmap(const veda_plan* pl, const void* q_tiled, const void* k_tiled, const uint64_t* valid_mask,
                                   float softmax_scale, const int32_t* query_tiles, int64_t n_query_tiles, float2* rows,
-                                  int have_rows, float* heat, void* stream) {
+                                  int have_rows, float* heat, void* workspace, size_t workspace_bytes, void* stream) {
     using namespace veda;
     if (!pl || !q_tiled || !k_tiled || !valid_mask || !heat) return VEDA_ERR_INVALID_ARG;
     if (!(softmax_scale > 0.0f) || !(softmax_scale < INFINITY)) return VEDA_ERR_INVALID_ARG;
@@ -601,33 +725,69 @@ static veda_status target_heatmap(const veda_plan* pl, const void* q_tiled, cons
     a.T = pl->prob.T; a.H = pl->prob.H; a.W = pl->prob.W;
     hipStream_t s = (hipStream_t)stream;
     a.xcd_cum = ip->d_xcd_cum_pair;
-    const int64_t items = !query_tiles ? (int64_t)kXcd * ip->xcd_max_pairs
-                          : pl->inner  ? n_query_tiles : list_blocks(n_query_tiles, pl->prob.heads);
-    dim3 grid((unsigned)items, (unsigned)pl->prob.batch), block(256);
-    const size_t smem = (size_t)2 * kTile * d * pl->elem_size() + 4 * 64 * sizeof(float);
-#define VEDA_LAUNCH_HEAT(E, DD, GG)                                                                      \
-    do {                                                                                                 \
-        auto kern = query_tiles ? tile_heatmap_kernel<E, DD, GG, true> : tile_heatmap_kernel<E, DD, GG, false>; \
-        if (smem > 64 * 1024)                                                                            \
-            VEDA_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem)); \
-        hipLaunchKernelGGL(kern, grid, block, smem, s, a);                                               \
-    } while (0)
-    if (bf16 && pl->inner) {
-        if (d == 128) VEDA_LAUNCH_HEAT(uint16_t, 128, true); else VEDA_LAUNCH_HEAT(uint16_t, 64, true);
-    } else if (bf16) {
-        if (d == 128) VEDA_LAUNCH_HEAT(uint16_t, 128, false); else VEDA_LAUNCH_HEAT(uint16_t, 64, false);
-    } else {
-        if (d == 128) VEDA_LAUNCH_HEAT(uint32_t, 128, false); else VEDA_LAUNCH_HEAT(uint32_t, 64, false);
+    const int64_t items = heat_items(pl, a.n_query_tiles);
+    a.items = (uint32_t)items;
+    a.batch = (uint32_t)pl->prob.batch;
+    a.maxima = nullptr;
+    a.taken = nullptr;
+    a.max_tiles = heat_max_tiles(pl);
+    int64_t blocks = items * pl->prob.batch;
+    if (blocks > 0x7fffffff) return VEDA_ERR_UNSUPPORTED;
+    if (workspace) {
+        if (reinterpret_cast<uintptr_t>(workspace) & 15u) return VEDA_ERR_UNSUPPORTED;
+        const int64_t places = heat_places(pl);
+        const bool share = blocks > places;
+        blocks = share ? places : blocks;
+        if (workspace_bytes < kHeatTakenBytes + (size_t)(blocks * a.max_tiles) * 128 * sizeof(float)) return VEDA_ERR_WORKSPACE;
+        a.maxima = reinterpret_cast<float*>((char*)workspace + kHeatTakenBytes);
+        if (share) {
+            a.taken = reinterpret_cast<uint32_t*>(workspace);
+            hipLaunchKernelGGL(heat_taken_clear_kernel, dim3(1), dim3(kXcd), 0, s, a.taken);
+        }
     }
+    dim3 grid((unsigned)blocks), block(256);
+    const size_t smem = (size_t)2 * kTile * d * pl->elem_size() + 4 * 64 * sizeof(float) + 16;
+    auto launch = [&](auto kern) {
+        if (smem > 64 * 1024)
+            VEDA_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+        hipLaunchKernelGGL(kern, grid, block, smem, s, a);
+        return launch_status("veda_tile_heatmap");
+    };
+#define VEDA_LAUNCH_HEAT(E, DD, GG)                                                                      \
+    (workspace ? query_tiles ? launch(tile_heatmap_kernel<E, DD, GG, true, true>)                        \
+                             : launch(tile_heatmap_kernel<E, DD, GG, false, true>)                       \
+               : query_tiles ? launch(tile_heatmap_kernel<E, DD, GG, true, false>)                       \
+                             : launch(tile_heatmap_kernel<E, DD, GG, false, false>))
+    if (bf16 && pl->inner) return d == 128 ? VEDA_LAUNCH_HEAT(uint16_t, 128, true) : VEDA_LAUNCH_HEAT(uint16_t, 64, true);
+    if (bf16) return d == 128 ? VEDA_LAUNCH_HEAT(uint16_t, 128, false) : VEDA_LAUNCH_HEAT(uint16_t, 64, false);
+    return d == 128 ? VEDA_LAUNCH_HEAT(uint32_t, 128, false) : VEDA_LAUNCH_HEAT(uint32_t, 64, false);
 #undef VEDA_LAUNCH_HEAT
-    return launch_status("veda_tile_heatmap");
+}
+
+extern "C" size_t veda_plan_heatmap_workspace_bytes(const veda_plan* pl, int64_t n_query_tiles) {
+    using namespace veda;
+    if (!pl || n_query_tiles < 0 || n_query_tiles > pl->total_tiles) return 0;
+    const int64_t blocks = heat_items(pl, n_query_tiles) * pl->prob.batch, places = heat_places(pl);
+    return kHeatTakenBytes + (size_t)((blocks < places ? blocks : places) * heat_max_tiles(pl)) * 128 * sizeof(float);
 }
 
 extern "C" veda_status veda_tile_heatmap(const veda_plan* pl, const void* q_tiled, const void* k_tiled,
                                          const uint64_t* valid_mask, float softmax_scale,
                                          const int32_t* query_tiles, int64_t n_query_tiles, float* heat,
                                          void* stream) {
-    return target_heatmap(pl, q_tiled, k_tiled, valid_mask, softmax_scale, query_tiles, n_query_tiles, nullptr, 0, heat, stream);
+    return target_heatmap(pl, q_tiled, k_tiled, valid_mask, softmax_scale, query_tiles, n_query_tiles, nullptr, 0, heat, nullptr, 0,
+                          stream);
+}
+
+extern "C" veda_status veda_tile_heatmap_ws(const veda_plan* pl, const void* q_tiled, const void* k_tiled,
+                                            const uint64_t* valid_mask, float softmax_scale, const int32_t* query_tiles,
+                                            int64_t n_query_tiles, float* row_sums, float* heat, void* workspace,
+                                            size_t workspace_bytes, void* stream) {
+    if (!pl) return VEDA_ERR_INVALID_ARG;
+    if (!workspace) return VEDA_ERR_WORKSPACE;
+    if (reinterpret_cast<uintptr_t>(row_sums) & 7u) return VEDA_ERR_UNSUPPORTED;
+    return target_heatmap(pl, q_tiled, k_tiled, valid_mask, softmax_scale, query_tiles, n_query_tiles,
+                          reinterpret_cast<float2*>(row_sums), 0, heat, workspace, workspace_bytes, stream);
 }
 
 extern "C" veda_status veda_tile_heatmap_rows(const veda_plan* pl, const void* q_tiled, const void* k_tiled,
@@ -636,7 +796,7 @@ extern "C" veda_status veda_tile_heatmap_rows(const veda_plan* pl, const void* q
     if (!row_sums || have_row_sums < 0 || have_row_sums > 1) return VEDA_ERR_INVALID_ARG;
     if (reinterpret_cast<uintptr_t>(row_sums) & 7u) return VEDA_ERR_UNSUPPORTED;
     return target_heatmap(pl, q_tiled, k_tiled, valid_mask, softmax_scale, nullptr, 0, reinterpret_cast<float2*>(row_sums),
-                          have_row_sums, heat, stream);
+                          have_row_sums, heat, nullptr, 0, stream);
 }
 
 extern "C" veda_status veda_tile_recall(const veda_plan* pl, const int32_t* k_per_head, const int32_t* col_idx_a,

@@ -34,6 +34,7 @@ EXPORTS = (
     "veda_tile_score_select", "veda_tile_score_select_stats", "veda_tile_score_select_stats_noalloc",
     "veda_sparse_attn_fwd", "veda_sparse_attn_fwd_q_tokens",
     "veda_sparse_attn_fwd_qk_tokens", "veda_tile_heatmap", "veda_tile_heatmap_rows",
+    "veda_tile_heatmap_ws", "veda_plan_heatmap_workspace_bytes",
     "veda_tile_recall", "veda_output_sqerr", "veda_status_string", "veda_last_error",
 )
 
@@ -132,6 +133,10 @@ def load():
     L.veda_tile_heatmap.restype = C.c_int
     L.veda_tile_heatmap_rows.argtypes = [vp, vp, vp, vp, C.c_float, vp, i32, vp, vp]
     L.veda_tile_heatmap_rows.restype = C.c_int
+    L.veda_plan_heatmap_workspace_bytes.argtypes = [vp, i64]
+    L.veda_plan_heatmap_workspace_bytes.restype = C.c_size_t
+    L.veda_tile_heatmap_ws.argtypes = [vp, vp, vp, vp, C.c_float, vp, i64, vp, vp, vp, C.c_size_t, vp]
+    L.veda_tile_heatmap_ws.restype = C.c_int
     L.veda_tile_recall.argtypes = [vp, C.POINTER(i32), vp, vp, vp, vp, C.c_size_t, vp]
     L.veda_tile_recall.restype = C.c_int
     L.veda_output_sqerr.argtypes = [vp, vp, veda_strides, vp, veda_strides, vp, vp, C.c_size_t, vp]
@@ -443,10 +448,24 @@ def veda_tile_heatmap(plan: Plan, q_tiled, k_tiled, valid_mask, softmax_scale: f
     if heat is None:
         heat = torch.zeros((plan.batch, plan.score_elems), dtype=torch.float32, device=dev)
     n_qt = 0 if query_tiles is None else int(query_tiles.numel())
-    _check(load().veda_tile_heatmap(plan.handle, _ptr(q_tiled), _ptr(k_tiled), _ptr(valid_mask),
-                                    C.c_float(softmax_scale), _ptr(query_tiles), n_qt, _ptr(heat), _stream()),
-           "veda_tile_heatmap")
+    _heatmap_ws(plan, q_tiled, k_tiled, valid_mask, softmax_scale, query_tiles, n_qt, None, heat, "veda_tile_heatmap")
     return heat
+
+
+def _heatmap_ws(plan, q_tiled, k_tiled, valid_mask, softmax_scale, query_tiles, n_qt, row_sums, heat, what):
+    """One walk over the keys, with scratch from torch's allocator (taken on every call: no state that calls on other
+    streams or threads could share); two walks without scratch where there is no memory left for it."""
+    args = (plan.handle, _ptr(q_tiled), _ptr(k_tiled), _ptr(valid_mask), C.c_float(softmax_scale))
+    need = int(load().veda_plan_heatmap_workspace_bytes(plan.handle, n_qt))
+    try:
+        ws = torch.empty(need, dtype=torch.uint8, device=q_tiled.device)
+    except torch.cuda.OutOfMemoryError:
+        if row_sums is None:
+            _check(load().veda_tile_heatmap(*args, _ptr(query_tiles), n_qt, _ptr(heat), _stream()), what)
+        else:
+            _check(load().veda_tile_heatmap_rows(*args, _ptr(row_sums), 0, _ptr(heat), _stream()), what)
+        return
+    _check(load().veda_tile_heatmap_ws(*args, _ptr(query_tiles), n_qt, _ptr(row_sums), _ptr(heat), _ptr(ws), need, _stream()), what)
 
 
 def veda_tile_heatmap_rows(plan: Plan, q_tiled, k_tiled, valid_mask, softmax_scale: float, row_sums: Optional[torch.Tensor] = None,
@@ -466,8 +485,11 @@ def veda_tile_heatmap_rows(plan: Plan, q_tiled, k_tiled, valid_mask, softmax_sca
         # the kernel reads one pair per row: a buffer of another problem would be read past its end
         raise VedaError(VEDA_ERR_INVALID_ARG, "veda_tile_heatmap_rows",
                         f"row_sums must be contiguous fp32 {list(shape)} on {dev}, as an earlier call returned them")
+    if not have:
+        _heatmap_ws(plan, q_tiled, k_tiled, valid_mask, softmax_scale, None, 0, row_sums, heat, "veda_tile_heatmap_rows")
+        return heat, row_sums
     _check(load().veda_tile_heatmap_rows(plan.handle, _ptr(q_tiled), _ptr(k_tiled), _ptr(valid_mask), C.c_float(softmax_scale),
-                                         _ptr(row_sums), 1 if have else 0, _ptr(heat), _stream()), "veda_tile_heatmap_rows")
+                                         _ptr(row_sums), 1, _ptr(heat), _stream()), "veda_tile_heatmap_rows")
     return heat, row_sums
 
 

@@ -96,6 +96,8 @@ def test_stage_calls_reject_null_plan(lib):
                                             None) == veda.VEDA_ERR_INVALID_ARG
     assert lib.veda_plan_fused_workspace_bytes(None, None, None) == 0
     assert lib.veda_tile_heatmap(None, None, None, None, 0.125, None, 0, None, None) == veda.VEDA_ERR_INVALID_ARG
+    assert lib.veda_tile_heatmap_ws(None, None, None, None, 0.125, None, 0, None, None, None, 0, None) == veda.VEDA_ERR_INVALID_ARG
+    assert lib.veda_plan_heatmap_workspace_bytes(None, 0) == 0
     assert lib.veda_tile_recall(None, None, None, None, None, None, 0, None) == veda.VEDA_ERR_INVALID_ARG
     assert lib.veda_output_sqerr(None, None, s, None, s, None, None, 0, None) == veda.VEDA_ERR_INVALID_ARG
     assert lib.veda_plan_tiles(None, 0) == -1 and lib.veda_plan_total_tiles(None) == -1

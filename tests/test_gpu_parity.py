@@ -1202,6 +1202,50 @@ def test_fp32_target_scores_below_the_smallest_normal_number(d):
     assert np.array_equal(ci.view(16, 15).cpu().numpy(), vo.select(ref.astype(np.float32), 15))
 
 
+@pytest.mark.parametrize("dtype,d,tile_tokens,grid,heads", [
+    ("bf16", 128, 64, (5, 30, 33), 5),       # tiles of every fill
+    ("bf16", 64, 64, (8, 66, 64), 12),       # more work items than places in the scratch: 12 x 136 pairs and more
+    ("bf16", 128, 128, (9, 31, 33), 5),      # halves without a token
+    ("f32", 128, 64, (4, 62, 64), 15),       # more work items than places
+    ("f32", 64, 64, (1, 5, 67), 5),
+])
+def test_heatmap_with_and_without_scratch(dtype, d, tile_tokens, grid, heads):
+    """The logits formed once (with scratch) or twice: the same bits, all rows and listed ones, with rows and keys that
+    are not finite among them, and nothing outside the scratch is touched."""
+    shapes = [(4, 4, 4), (1, 8, 8), (16, 2, 2), (64, 1, 1), (1, 1, 64)]
+    shapes = [(2 * a, b, c) for a, b, c in shapes] if tile_tokens == 128 else shapes
+    shapes = np.asarray([shapes[h % 5] for h in range(heads)] if heads < 12 else [shapes[h % 2] for h in range(heads)], np.int32)
+    wl = wlm.custom_workload("one_walk", heads, d, dtype, grid, False, (50, 100), seed=37)
+    dev = torch.device("cuda:0")
+    q, k, _ = wlm.make_qkv(wl, dev)
+    n_tok = q.shape[2]
+    q[0, 0, 3] = float("nan")
+    q[0, 1, :n_tok // 2] = float("inf")
+    k[0, 2, 5] = float("-inf")
+    k[0, 3, n_tok // 3:n_tok // 2] = float("nan")
+    plan = veda.Plan(1, heads, d, grid, shapes, wl.torch_dtype, tile_tokens=tile_tokens)
+    qt, vm, _ = veda.veda_tile_layout(plan, q, veda.VEDA_TOKEN_MAJOR)
+    kt, _, _ = veda.veda_tile_layout(plan, k, veda.VEDA_TOKEN_MAJOR, want_mask=False)
+    lib, scale, stream = veda.load(), 1.0 / math.sqrt(d), torch.cuda.current_stream().cuda_stream
+    listed = torch.randperm(plan.total_tiles, generator=torch.Generator().manual_seed(2))[:plan.total_tiles * 3 // 4 | 1]
+    for rows in (None, listed.to(torch.int32).to(dev)):
+        n = 0 if rows is None else rows.numel()
+        ptr = None if rows is None else rows.data_ptr()
+        heats = [torch.full((1, plan.score_elems), -7.0, device=dev) for _ in range(3)]
+        need = int(lib.veda_plan_heatmap_workspace_bytes(plan.handle, n))
+        around = torch.full((need + 512,), 77, dtype=torch.uint8, device=dev)
+        args = (plan.handle, qt.data_ptr(), kt.data_ptr(), vm.data_ptr(), scale, ptr, n)
+        ws = around.data_ptr() + 256
+        assert lib.veda_tile_heatmap(*args, heats[0].data_ptr(), stream) == veda.VEDA_OK
+        assert lib.veda_tile_heatmap_ws(*args, None, heats[1].data_ptr(), ws, need - 1, stream) == veda.VEDA_ERR_WORKSPACE
+        assert lib.veda_tile_heatmap_ws(*args, None, heats[1].data_ptr(), ws, need, stream) == veda.VEDA_OK
+        veda.veda_tile_heatmap(plan, qt, kt, vm, scale, rows, heats[2])
+        torch.cuda.synchronize()
+        assert bool((around[:256] == 77).all()) and bool((around[-256:] == 77).all())
+        assert torch.equal(heats[0].view(torch.int32), heats[1].view(torch.int32))
+        assert torch.equal(heats[0].view(torch.int32), heats[2].view(torch.int32))
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_row_sums_have_no_place_for_padded_slots(dtype):
     """A mask that calls padded slots real: their rows have no token, so no sums are kept for them (what lies around
