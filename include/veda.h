@@ -273,7 +273,8 @@ veda_status veda_tile_score_select_stats_noalloc(const veda_plan*, const float* 
  * of two nearest below that factor (exact in bf16) and the logits by the remaining factor in fp32
  * on their way into the exponential: the error no longer depends on the logits' size (max-abs
  * <= 1.7e-2, mean-abs <= 1e-3, lse 1e-5 up to a standard deviation of 16) at about 4 % more time.
- * f32: fp32 arithmetic throughout. */
+ * f32: fp32 arithmetic; products are formed from exact splits of their operands into three bf16 parts and summed in
+ * fp32, nearer to the exact sum than fp32 fused multiply-adds in turn. */
 veda_status veda_sparse_attn_fwd(const veda_plan*, const void* q_tiled, const void* k_tiled,
                                  const void* v_tiled, const uint64_t* valid_mask,
                                  const int32_t* row_ptr, const int32_t* col_idx, float softmax_scale,

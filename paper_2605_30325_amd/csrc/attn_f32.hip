@@ -1,38 +1,41 @@
 // Stage 4, fp32 (Eq. 2; Sec. 3.1 masked form; Sec. 4.3 tile skipping; Alg. 1 "UnTile"): the
-// accuracy path (1e-4 against the double-precision definition), on the fp32 matrix cores.
+// accuracy path (1e-4 against the double-precision definition), fp32 products on the bf16 matrix cores.
 //
 // Same work split as the bf16 kernel: a workgroup of four wavefronts owns a pair of partner query
 // tiles and walks the union of their two kept lists; waves 0,1 hold rows 0-31 / 32-63 of tile A,
-// waves 2,3 those of tile B.  The products of a step take 16384 matrix-pipe cycles per wave at d = 128, its
-// loads a sixteenth of that, so one K tile ([64][d]) and one V^T tile ([d][64]) in LDS are enough: the next K
-// tile lands while O^T is formed, the next V^T tile during S^T.  That leaves room for two workgroups on a
-// compute unit (2 x 74 KB at d = 128), and the second one's products fill the matrix pipe while a wave of the
-// first is in its softmax, at a barrier, or skips a key tile that only its partner keeps.  Padding is handled
-// as in the bf16 kernel (real query rows first; half steps, attn_union.h).
-// Measured, the attention call alone: 8 heads of 624 tiles, 10 % kept, 8.5 -> 5.8 ms repeated back to back (5.3 between
-// the other stages of whole calls); 8 heads of 144 tiles, all kept and 25 % kept, 2.2 -> 1.7 ms on average.
+// waves 2,3 those of tile B.  Padding is handled as in the bf16 kernel (real query rows first; half steps, attn_union.h).
+// Every operand is split into three bf16 parts and a product is six bf16 ones (split_f32.h: why that is no less exact),
+// 32 keys at a time:
+//   S^T = K Q^T from the K planes, in the shadow of its last products V^T converted (landing area -> registers -> planes)
+//   O^T += V^T P^T, in the shadow of its last products the next 32 keys' K converted
+// with a barrier after each, so that one set of K planes and one of V^T planes serve (24 KB each at d = 128, 16 KB of
+// landing area; 74 KB with the step table: two workgroups on a compute unit).  The query rows stay split in registers (96
+// at d = 128, with 64 of O^T: this is why 32 keys, not 64).  K rows are read in the order rho, which leaves each lane eight
+// consecutive keys of S^T as in the bf16 kernel.
+// Measured, whole calls: 8 heads of 624 tiles, 10 % kept, 5.9 -> 3.3 ms (the products on fp32 matrix cores at 93 % of their
+// rate before); 1.1 PFLOP/s of bf16 products, matrix pipes 52 % busy.  What is left: a fifth of the wave-steps belong
+// to waves whose query tile does not keep the key tile, and two waves on a SIMD cover each other's
+// softmax only so far.  Reading a group of products ahead gave 7 %, rounding pairs once 3 %, V^T rows on all banks 2 %;
+// loads one phase earlier, priorities: 1-2 %.
 //
-// Products are formed transposed with v_mfma_f32_32x32x2_f32 (S^T = K Q^T, O^T = V^T P^T): a lane
-// owns one query (lane % 32) and one of the two terms of every instruction (h = lane / 32).  The
-// pairing of the reduction index with h is free as long as both operands agree, and it is chosen so
-// that one 16-byte LDS read feeds four instructions:
+// Numbers that are not finite come out of the split products as NaN: a workgroup that finds any in its results walks
+// again on v_mfma_f32_32x32x2_f32.  There a lane owns one query (lane % 32) and one of the two terms of every instruction
+// (h = lane / 32).  The pairing of the reduction index with h is free as long as both operands agree, and it is
+// chosen so that one 16-byte LDS read feeds four instructions:
 //   S^T, step (m, t):  h supplies channel 8m + 4h + t   (K row: float4 at channel 8m + 4h),
 //   O^T, step (c, j, t): h supplies key 32c + 8j + 4h + t, which is exactly register 4j + t of the
 //                        lane's S^T block c -- P^T needs no rearrangement at all.
 // LDS rows are XOR-swizzled by 16-byte chunk (chunk ^ row) so that the 32 lanes reading the same
 // chunk of 32 different rows spread over all banks; the swizzle is applied on the global side of
-// the direct loads.  Plain online softmax (reference = running row maximum), exp2 with log2(e)
-// folded into Q in fp32.
+// the direct loads.  Online softmax, exp2 with log2(e) folded into Q in fp32.
 #include "attn_common.h"
 #include "attn_union.h"
+#include "split_f32.h"
 
 namespace veda {
 
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef const __attribute__((address_space(3))) f32x4* lds_f32x4_ptr;
-__device__ __forceinline__ f32x4 lds_read_f32x4(uint32_t addr) { return *(lds_f32x4_ptr)(uintptr_t)addr; }
-
 constexpr int kF32Chunk = 128;   // step-table entries filled at a time
+constexpr float kF32Slack = 8.0f;   // log2 units a row maximum may outgrow the softmax reference
 
 // kTable: the steps come from the table in LDS (attn_union.h), as in the bf16 kernel; otherwise the two
 // lists are merged inside the loop (heads above 16384 tiles, VEDA_OPT_ATTN_LIST_WALK).
@@ -74,89 +77,30 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_f32_kernel(AttnArgs a) {
     const char* kt = a.k + head_tile0 * kKBytes;
     const char* vt = a.v + head_tile0 * kVBytes;
 
-    // Q operand: lane (query 32r + idx, half h) holds channels 8m + 4h + t, scaled by softmax_scale*log2(e).
     // Row 32r + idx is the tile's real slot of that rank; rows beyond the real slots read slot 0 and are not written.
     const uint64_t q_real = __ballot(slot_token(hg, qi, lane, a.T, a.H, a.W) >= 0);
     const int q_rows = __popcll(q_real);
-    float qreg[D / 2];
+    const float* qrow;
     {
         int slot = 32 * r + idx;
         if (q_real != ~0ull) slot = slot < q_rows ? nth_bit(q_real, slot) : 0;
-        const float* qrow = reinterpret_cast<const float*>(a.q + (head_tile0 + qi) * kKBytes + slot * kKPitch);
-#pragma unroll
-        for (int m = 0; m < kM; ++m) {
-            const f32x4 v = *reinterpret_cast<const f32x4*>(qrow + 8 * m + 4 * h);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) qreg[4 * m + t] = v[t] * a.scale_log2;
-        }
+        qrow = reinterpret_cast<const float*>(a.q + (head_tile0 + qi) * kKBytes + slot * kKPitch);
     }
     f32x16 o[NB];
+    float m_run, l_run;
+    auto begin_rows = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+        for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) o[nb][i] = 0.0f;
-    float m_run = -INFINITY, l_run = 0.0f;
+            for (int i = 0; i < 16; ++i) o[nb][i] = 0.0f;
+        m_run = -INFINITY;
+        l_run = 0.0f;
+    };
 
-    // global -> LDS copy plan (see the bf16 kernel): wave w issues instructions w*kLoads .. of each
-    // tile, four to an M0 set-up, instruction j of a group with immediate offset 1024*(j%4), which
-    // moves the LDS and the global address alike.
-    uint32_t k_src[kLoads], v_src[kLoads];
-#pragma unroll
-    for (int j = 0; j < kLoads; ++j) {
-        const int inst = wave * kLoads + j;
-        const int krow = inst * (1024 / kKPitch) + lane / kKChunks, kpos = lane % kKChunks;
-        k_src[j] = krow * kKPitch + ((kpos ^ (krow & (kKChunks - 1))) << 4) - 1024u * (j % 4);
-        const int vrow = inst * 4 + (lane >> 4), vpos = lane & 15;
-        v_src[j] = vrow * kVPitch + ((vpos ^ (vrow & 15)) << 4) - 1024u * (j % 4);
-    }
     const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
     const uint32_t wave_lds = smem_base + (uint32_t)wave * (kLoads * 1024);
     struct Step { int j, fl; uint64_t vm; };   // vm: the mask, or step_kind's lo | hi << 32 (half steps)
     constexpr int kKeepers = 3;
-    auto load_k = [&](const Step& e) __attribute__((always_inline)) {
-        if (!(e.fl & kKeepers)) return;
-        uint32_t moved[2] = {0u, 0u};   // half: the chunks of this wave's first and last eight rows, moved
-        if (e.fl & kStepHalf) {
-            if (wave >= 2) return;      // only the first 32 rows are read
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int c = 2 * wave + u;
-                moved[u] = (((uint32_t)(e.vm >> (32 + 8 * c)) & 255u) - (uint32_t)c) * (8 * kKPitch);
-            }
-        }
-#pragma unroll
-        for (int g = 0; g < kGroups; ++g) {
-            uint32_t off[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) off[j] = k_src[4 * g + j] + moved[(4 * g + j) * 2 / kLoads];
-            dma16_group_to_lds<4>(wave_lds + g * 4096, kt + (int64_t)e.j * kKBytes, off);
-        }
-    };
-    const int v_c = (lane & 15) ^ (lane >> 4);   // this lane's 16-byte chunk (4 keys): v_c ^ 4*(j%4) in instruction j
-    auto load_v = [&](const Step& e) __attribute__((always_inline)) {
-        if (!(e.fl & kKeepers)) return;
-        uint32_t moved[4] = {0u, 0u, 0u, 0u};
-        if (e.fl & kStepHalf) {   // keys 0-31 from the chunks that hold real tokens; the others are not read
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t c = (uint32_t)(v_c ^ (4 * j));
-                const uint32_t from = (uint32_t)((e.vm >> 32) >> (8 * ((c >> 1) & 3))) & 255u;
-                moved[j] = c < 8 ? (from - (c >> 1)) * 32u : 0u;
-            }
-        }
-#pragma unroll
-        for (int g = 0; g < kGroups; ++g) {
-            uint32_t off[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) off[j] = v_src[4 * g + j] + moved[j];
-            dma16_group_to_lds<4>(wave_lds + kKBytes + g * 4096, vt + (int64_t)e.j * kVBytes, off);
-        }
-    };
-    // LDS addresses of this lane's first operand reads: the swizzle only touches bits the row offsets leave clear,
-    // so K chunk 2m + h is at k0 ^ (m << 5), V^T chunk 2g + h at v0 ^ (g << 5).
-    uint32_t k0 = smem_base + idx * kKPitch + (((uint32_t)h ^ (idx & (kKChunks - 1))) << 4);
-    uint32_t v0 = smem_base + kKBytes + idx * kVPitch + (((uint32_t)h ^ (idx & 15)) << 4);
-
     // The steps: the union of the two kept lists.  Table mode: laid out in LDS before the loop; walk mode:
     // merged with scalar loads as the loop goes (32-bit integers on the scalar unit; see the bf16 kernel).
     constexpr int kEnd = 0x7fffffff;
@@ -173,16 +117,24 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_f32_kernel(AttnArgs a) {
         const int32_t* lists[2] = {a.col_idx + begA, a.col_idx + begB};
         const int counts[2] = {nA, nB};
         total = union_build<2, 256, kF32Chunk>(u, lists, counts, hg.n_tiles, tid);
-        union_fill<2, 256, kF32Chunk, false, 2 * kF32Chunk>(u, 0, total, hg.n_tiles, vmask_g, n0s_g, tid);   // the whole ring
-        __syncthreads();
-        raw_next = union_read<kF32Chunk>(tab_lds, 0);
-        s_read = 1;
-    } else {
-        rawA = colsA[0];
-        rawB = colsB[0];
-        okA = nA > 0 ? 1 : 0;
-        okB = nB > 0 ? 1 : 0;
     }
+    // to the first step; ends with a barrier
+    auto begin_walk = [&]() __attribute__((always_inline)) {
+        s_done = 0;
+        if constexpr (kTable) {
+            union_fill<2, 256, kF32Chunk, false, 2 * kF32Chunk>(u, 0, total, hg.n_tiles, vmask_g, n0s_g, tid);   // the whole ring
+            __syncthreads();
+            raw_next = union_read<kF32Chunk>(tab_lds, 0);
+            s_read = 1;
+        } else {
+            ia = ib = 0;
+            rawA = colsA[0];
+            rawB = colsB[0];
+            okA = nA > 0 ? 1 : 0;
+            okB = nB > 0 ? 1 : 0;
+            __syncthreads();
+        }
+    };
     auto next_step = [&](Step& e) __attribute__((always_inline)) {
         if constexpr (kTable) {
             const UnionStep t = union_step(raw_next);
@@ -210,102 +162,368 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_f32_kernel(AttnArgs a) {
     };
 
     const int my_bit = 32 * r < q_rows ? 1 << which : 128;   // 128: a bit no step has
-    // S^T block c = K Q^T: 32 keys x 32 queries
-    auto logits = [&](f32x16& s, int c) __attribute__((always_inline)) {
+    // The walk on bf16 matrix cores: every operand as the sum of three bf16 numbers, six products (see the head of the file).
+    auto split_walk = [&]() __attribute__((always_inline)) {
+        typedef SplitK<D> K;
+        constexpr int G = D / 16, kI = K::kI;
+        // Short rows round less often to begin with, so at d = 64 the sums are kept apart (there are registers for it): the
+        // table of the tiling search, squares of differences of two outputs, stayed within 1.2e-8 of the 64-bit one only so.
+        constexpr bool kTight = D == 64;
+        constexpr uint32_t kV = K::kPlanes, kRaw = 2 * K::kPlanes;   // V^T planes, landing area: 64 KB (d = 128) in all
+        K ks;
+        ks.init(smem_base, smem_base + kRaw, wave, lane);
+        bf16x8 q[3][G];
+        split_row<D>(qrow, h, a.scale_log2, q);
+        struct Sub { int j, fl, c; uint32_t mask, hi, from; };   // 32 keys of a step: c-th half of key tile j, or a half step
+        // K and V^T take turns in the landing area.  Past the end the loads go on, from key tile 0.
+        auto load_k = [&](const Sub& e, int j) __attribute__((always_inline)) { ks.load(j, kt + (int64_t)e.j * kKBytes, e.from); };
+        // V^T planes: [D][32], 16-byte chunk ^ row / 4 (any sixteen rows of a read on all banks); a wave has D / 4 rows
+        const uint32_t v_lane = (uint32_t)(((D / 4) * wave + (lane >> 3)) * kVPitch + (lane & 1) * 16);
+        auto load_v = [&](const Sub& e, int j) __attribute__((always_inline)) {
+            const uint32_t chunk = (e.from >> (8 * ((lane >> 1) & 3))) & 255u;
+            dma16_to_lds(ks.raw + 1024u * j, vt + (int64_t)e.j * kVBytes + 2048 * j, v_lane + chunk * 32u);
+        };
+        const int v_row = (D / 4) * wave + (lane >> 3), v_c = lane & 7;
+        const uint32_t vw = smem_base + kV + v_row * 64 + (((v_c >> 1) ^ ((v_row >> 2) & 3)) << 4) + (v_c & 1) * 8;
+        auto convert_v = [&](int j) __attribute__((always_inline)) { ks.put(j, (vw ^ (uint32_t)((j & 1) << 5)) + (uint32_t)(j * 8 * 64)); };
+        const uint32_t vr = smem_base + kV + idx * 64 + ((h ^ ((idx >> 2) & 3)) << 4);
+        auto of_step = [&](Sub& n) __attribute__((always_inline)) {
+            Step e;
+            next_step(e);
+            n.j = e.j; n.fl = e.fl; n.c = 0;
+            n.mask = (uint32_t)e.vm;
+            n.hi = (uint32_t)(e.vm >> 32);
+            n.from = e.fl & kStepHalf ? n.hi : 0x03020100u;
+        };
+        float thr = -INFINITY, ref = 0.0f;   // a row maximum above thr moves the reference
+        begin_rows();
+        begin_walk();
+        Sub cur, nx;
+        of_step(cur);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s[i] = 0.0f;
+        for (int j = 0; j < kI; ++j) load_k(cur, j);
+#pragma unroll
+        for (int j = 0; j < kI; ++j) {
+            ks.convert(j);
+            load_v(cur, j);
+        }
+        K::meet();
+        while (cur.fl) {
+            const bool mine = (cur.fl & my_bit) != 0;
+            if (cur.c == 0 && (cur.fl & (kStepWhole | kStepPart))) {
+                nx = cur;
+                nx.c = 1;
+                nx.mask = cur.hi;
+                nx.from = 0x07060504u;
+            } else {
+                of_step(nx);
+            }
+            // S^T = K Q^T from the K planes, the V^T planes written
+            // (two conditionals with an opaque flag rather than if / else: see the bf16 kernel)
+            f32x16 s;
+            int todo = 1;
+            if (mine) {
+                todo = 0;
+                ks.template products<kTight>(s, q, 0u, [&](int t) __attribute__((always_inline)) {
+                    if (t >= G - kI) {
+                        convert_v(t - (G - kI));
+                        load_k(nx, t - (G - kI));
+                    }
+                });
+            }
+            asm volatile("" : "+s"(todo));
+            if (todo) {
+#pragma unroll
+                for (int j = 0; j < kI; ++j) {
+                    convert_v(j);
+                    load_k(nx, j);
+                }
+            }
+            K::meet();
+            // O^T += V^T P^T, the next K planes written
+            if (!todo) {
+                bf16x8 vf[2][3];
+#pragma unroll
+                for (int u = 0; u < 3; ++u) vf[0][u] = K::frag(vr, u);
+                __builtin_amdgcn_sched_barrier(0);
+                if (cur.mask != ~0u) {   // register i is key 16*(i/8) + 8*h + i%8
+                    asm volatile("" ::: "memory");
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int bit = 16 * (i >> 3) + (i & 7);
+                        const uint32_t lo = (uint32_t)((int)(cur.mask << (31 - bit)) >> 31), up = (uint32_t)((int)(cur.mask << (23 - bit)) >> 31);
+                        s[i] = __builtin_amdgcn_inverse_ballot_w64((uint64_t)up << 32 | lo) ? s[i] : -INFINITY;
+                    }
+                }
+                float mx = s[0];
+#pragma unroll
+                for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
+                if (__any(mx > thr)) {
+                    asm volatile("" ::: "memory");
+                    m_run = fmaxf(m_run, max_with_other_half(mx));
+                    const float use = m_run == -INFINITY ? 0.0f : m_run;
+                    const float alpha = thr == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(ref - use);
+                    ref = use;
+                    thr = m_run + kF32Slack;
+                    l_run *= alpha;
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) o[nb][i] *= alpha;
+                }
+                float psum = 0.0f;
+                uint32_t pw[2][3][4];
+                auto prob = [&](int kk, int e) __attribute__((always_inline)) {   // registers 8*kk + 2e, +1
+                    const float p0 = __builtin_amdgcn_exp2f(s[8 * kk + 2 * e] - ref), p1 = __builtin_amdgcn_exp2f(s[8 * kk + 2 * e + 1] - ref);
+                    psum += p0;
+                    psum += p1;
+                    uint32_t p[3];
+                    split2(p0, p1, p);
+#pragma unroll
+                    for (int u = 0; u < 3; ++u) pw[kk][u][e] = p[u];
+                };
+#pragma unroll
+                for (int e = 0; e < 4; ++e) prob(0, e);
+                __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+                for (int g = 0; g < 2 * NB; ++g) {
+                    const int kk = g / NB, nb = g % NB;
+                    if (g + 1 < 2 * NB) {
+#pragma unroll
+                        for (int u = 0; u < 3; ++u) vf[(g + 1) & 1][u] = K::frag((vr ^ (uint32_t)(((g + 1) / NB) << 5)) + (uint32_t)(((g + 1) % NB) * 2048), u);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    const bf16x8 y0 = __builtin_bit_cast(bf16x8, u32x4{pw[kk][0][0], pw[kk][0][1], pw[kk][0][2], pw[kk][0][3]});
+                    const bf16x8 y1 = __builtin_bit_cast(bf16x8, u32x4{pw[kk][1][0], pw[kk][1][1], pw[kk][1][2], pw[kk][1][3]});
+                    const bf16x8 y2 = __builtin_bit_cast(bf16x8, u32x4{pw[kk][2][0], pw[kk][2][1], pw[kk][2][2], pw[kk][2][3]});
+                    if constexpr (kTight) {
+                        f32x16 z;
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) z[i] = 0.0f;
+                        o[nb] += mul6(z, vf[g & 1], y0, y1, y2);
+                    } else {
+                        o[nb] = mul6(o[nb], vf[g & 1], y0, y1, y2);
+                    }
+                    if (kk == 0) {
+#pragma unroll
+                        for (int e = nb * 4 / NB; e < (nb + 1) * 4 / NB; ++e) prob(1, e);
+                    } else {
+#pragma unroll
+                        for (int j = nb * kI / NB; j < (nb + 1) * kI / NB; ++j) {
+                            ks.convert(j);
+                            load_v(nx, j);
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                __builtin_amdgcn_s_setprio(0);
+                l_run += psum;
+            }
+            asm volatile("" : "+s"(todo));
+            if (todo) {
+#pragma unroll
+                for (int j = 0; j < kI; ++j) {
+                    ks.convert(j);
+                    load_v(nx, j);
+                }
+            }
+            K::meet();
+            if constexpr (kTable) {   // a step is done: the table's other half may have been left behind
+                if (nx.c == 0) {
+                    ++s_done;
+                    if ((s_done & (kF32Chunk - 1)) == 0)
+                        union_fill<2, 256, kF32Chunk, false>(u, s_done + kF32Chunk, total, hg.n_tiles, vmask_g, n0s_g, tid);
+                }
+            }
+            cur = nx;
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing lands any more
+        __syncthreads();
+    };
+
+    // The walk on fp32 matrix cores, where a number is not finite.
+    auto exact_walk = [&]() __attribute__((always_inline)) {
+        // Q operand: lane (query 32r + idx, half h) holds channels 8m + 4h + t, scaled by softmax_scale*log2(e).
+        float qreg[D / 2];
 #pragma unroll
         for (int m = 0; m < kM; ++m) {
-            const f32x4 kf = lds_read_f32x4((k0 ^ (uint32_t)(m << 5)) + (uint32_t)(32 * c * kKPitch));
+            const f32x4 v = *reinterpret_cast<const f32x4*>(qrow + 8 * m + 4 * h);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[t], qreg[4 * m + t], s, 0, 0, 0);
+            for (int t = 0; t < 4; ++t) qreg[4 * m + t] = v[t] * a.scale_log2;
         }
-    };
-    // padded key slots: register i of a block is key 8*(i/4) + 4h + i%4
-    auto mask_keys = [&](f32x16& s, uint32_t mask) __attribute__((always_inline)) {
-        if (mask == ~0u) return;
-        asm volatile("" ::: "memory");   // keeps this a branch
-        const uint32_t half = mask >> (4 * h);
+        // global -> LDS copy plan (see the bf16 kernel): wave w issues instructions w*kLoads .. of each
+        // tile, four to an M0 set-up, instruction j of a group with immediate offset 1024*(j%4), which
+        // moves the LDS and the global address alike.
+        uint32_t k_src[kLoads], v_src[kLoads];
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-            if (!((half >> (8 * (i >> 2) + (i & 3))) & 1u)) s[i] = -INFINITY;
-    };
-    // O^T += V^T P^T over the 32 keys of block c
-    auto outputs = [&](const f32x16& p, int c) __attribute__((always_inline)) {
+        for (int j = 0; j < kLoads; ++j) {
+            const int inst = wave * kLoads + j;
+            const int krow = inst * (1024 / kKPitch) + lane / kKChunks, kpos = lane % kKChunks;
+            k_src[j] = krow * kKPitch + ((kpos ^ (krow & (kKChunks - 1))) << 4) - 1024u * (j % 4);
+            const int vrow = inst * 4 + (lane >> 4), vpos = lane & 15;
+            v_src[j] = vrow * kVPitch + ((vpos ^ (vrow & 15)) << 4) - 1024u * (j % 4);
+        }
+        auto load_k = [&](const Step& e) __attribute__((always_inline)) {
+            if (!(e.fl & kKeepers)) return;
+            uint32_t moved[2] = {0u, 0u};   // half: the chunks of this wave's first and last eight rows, moved
+            if (e.fl & kStepHalf) {
+                if (wave >= 2) return;      // only the first 32 rows are read
 #pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const f32x4 vf = lds_read_f32x4((v0 ^ (uint32_t)((4 * c + j) << 5)) + (uint32_t)(32 * nb * kVPitch));
-#pragma unroll
-                for (int t = 0; t < 4; ++t) o[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[t], p[4 * j + t], o[nb], 0, 0, 0);
+                for (int u = 0; u < 2; ++u) {
+                    const int c = 2 * wave + u;
+                    moved[u] = (((uint32_t)(e.vm >> (32 + 8 * c)) & 255u) - (uint32_t)c) * (8 * kKPitch);
+                }
             }
-        }
-    };
-    Step e0, e1;
-    next_step(e0);
-    load_k(e0);
-    load_v(e0);
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the Q loads and the first tiles
-    __syncthreads();
+#pragma unroll
+            for (int g = 0; g < kGroups; ++g) {
+                uint32_t off[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) off[j] = k_src[4 * g + j] + moved[(4 * g + j) * 2 / kLoads];
+                dma16_group_to_lds<4>(wave_lds + g * 4096, kt + (int64_t)e.j * kKBytes, off);
+            }
+        };
+        const int v_c = (lane & 15) ^ (lane >> 4);   // this lane's 16-byte chunk (4 keys): v_c ^ 4*(j%4) in instruction j
+        auto load_v = [&](const Step& e) __attribute__((always_inline)) {
+            if (!(e.fl & kKeepers)) return;
+            uint32_t moved[4] = {0u, 0u, 0u, 0u};
+            if (e.fl & kStepHalf) {   // keys 0-31 from the chunks that hold real tokens; the others are not read
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const uint32_t c = (uint32_t)(v_c ^ (4 * j));
+                    const uint32_t from = (uint32_t)((e.vm >> 32) >> (8 * ((c >> 1) & 3))) & 255u;
+                    moved[j] = c < 8 ? (from - (c >> 1)) * 32u : 0u;
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < kGroups; ++g) {
+                uint32_t off[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) off[j] = v_src[4 * g + j] + moved[j];
+                dma16_group_to_lds<4>(wave_lds + kKBytes + g * 4096, vt + (int64_t)e.j * kVBytes, off);
+            }
+        };
+        // LDS addresses of this lane's first operand reads: the swizzle only touches bits the row offsets leave clear,
+        // so K chunk 2m + h is at k0 ^ (m << 5), V^T chunk 2g + h at v0 ^ (g << 5).
+        uint32_t k0 = smem_base + idx * kKPitch + (((uint32_t)h ^ (idx & (kKChunks - 1))) << 4);
+        uint32_t v0 = smem_base + kKBytes + idx * kVPitch + (((uint32_t)h ^ (idx & 15)) << 4);
 
-    while (e0.fl) {
-        next_step(e1);
-        asm volatile("" : "+v"(k0), "+v"(v0));   // the addresses of the reads are formed as they are needed: kept, they would spill
-        const bool mine = (e0.fl & my_bit) != 0, full = !(e0.fl & kStepHalf);
-        f32x16 s0, s1;
-        if (mine) {
-            logits(s0, 0);
-            mask_keys(s0, (uint32_t)e0.vm);
-            if (full) {
-                logits(s1, 1);
-                mask_keys(s1, (uint32_t)(e0.vm >> 32));
-            } else {
+        // S^T block c = K Q^T: 32 keys x 32 queries
+        auto logits = [&](f32x16& s, int c) __attribute__((always_inline)) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) s1[i] = -INFINITY;
+            for (int i = 0; i < 16; ++i) s[i] = 0.0f;
+#pragma unroll
+            for (int m = 0; m < kM; ++m) {
+                const f32x4 kf = lds_read_f32x4((k0 ^ (uint32_t)(m << 5)) + (uint32_t)(32 * c * kKPitch));
+#pragma unroll
+                for (int t = 0; t < 4; ++t) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[t], qreg[4 * m + t], s, 0, 0, 0);
+            }
+        };
+        // padded key slots: register i of a block is key 8*(i/4) + 4h + i%4
+        auto mask_keys = [&](f32x16& s, uint32_t mask) __attribute__((always_inline)) {
+            if (mask == ~0u) return;
+            asm volatile("" ::: "memory");   // keeps this a branch
+            const uint32_t half = mask >> (4 * h);
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if (!((half >> (8 * (i >> 2) + (i & 3))) & 1u)) s[i] = -INFINITY;
+        };
+        // O^T += V^T P^T over the 32 keys of block c
+        auto outputs = [&](const f32x16& p, int c) __attribute__((always_inline)) {
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const f32x4 vf = lds_read_f32x4((v0 ^ (uint32_t)((4 * c + j) << 5)) + (uint32_t)(32 * nb * kVPitch));
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) o[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[t], p[4 * j + t], o[nb], 0, 0, 0);
+                }
+            }
+        };
+        begin_rows();
+        begin_walk();
+        Step e0, e1;
+        next_step(e0);
+        load_k(e0);
+        load_v(e0);
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the Q loads and the first tiles
+        __syncthreads();
+
+        while (e0.fl) {
+            next_step(e1);
+            asm volatile("" : "+v"(k0), "+v"(v0));   // the addresses of the reads are formed as they are needed: kept, they would spill
+            const bool mine = (e0.fl & my_bit) != 0, full = !(e0.fl & kStepHalf);
+            f32x16 s0, s1;
+            if (mine) {
+                logits(s0, 0);
+                mask_keys(s0, (uint32_t)e0.vm);
+                if (full) {
+                    logits(s1, 1);
+                    mask_keys(s1, (uint32_t)(e0.vm >> 32));
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) s1[i] = -INFINITY;
+                }
+            }
+            __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's loads of V^T have landed
+            __syncthreads();                      // everybody is done with K
+            load_k(e1);
+            if (mine) {
+                float mx = -INFINITY;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) mx = fmaxf(mx, fmaxf(s0[i], s1[i]));
+                mx = max_with_other_half(mx);
+                const float m_new = fmaxf(m_run, mx);
+                const float m_use = m_new == -INFINITY ? 0.0f : m_new;
+                const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);   // 0 on the first step (m_run = -inf)
+                float psum = 0.0f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    s0[i] = __builtin_amdgcn_exp2f(s0[i] - m_use);
+                    psum += s0[i];
+                }
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    s1[i] = __builtin_amdgcn_exp2f(s1[i] - m_use);
+                    psum += s1[i];
+                }
+                l_run = l_run * alpha + psum;
+                m_run = m_new;
+                if (__any(alpha != 1.0f)) {
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) o[nb][i] *= alpha;
+                }
+                outputs(s0, 0);
+                if (full) outputs(s1, 1);
+            }
+            __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the next K tile
+            __syncthreads();                      // everybody is done with V^T
+            load_v(e1);
+            e0 = e1;
+            if constexpr (kTable) {   // the table's other half has been left behind: refill it
+                ++s_done;
+                if ((s_done & (kF32Chunk - 1)) == 0)
+                    union_fill<2, 256, kF32Chunk, false>(u, s_done + kF32Chunk, total, hg.n_tiles, vmask_g, n0s_g, tid);
             }
         }
-        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): this wave's loads of V^T have landed
-        __syncthreads();                      // everybody is done with K
-        load_k(e1);
-        if (mine) {
-            float mx = -INFINITY;
+
+    };
+
+    split_walk();
+    {
+        float bad = l_run * 0.0f;   // NaN if anything is not finite
 #pragma unroll
-            for (int i = 0; i < 16; ++i) mx = fmaxf(mx, fmaxf(s0[i], s1[i]));
-            mx = max_with_other_half(mx);
-            const float m_new = fmaxf(m_run, mx);
-            const float m_use = m_new == -INFINITY ? 0.0f : m_new;
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_use);   // 0 on the first step (m_run = -inf)
-            float psum = 0.0f;
+        for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                s0[i] = __builtin_amdgcn_exp2f(s0[i] - m_use);
-                psum += s0[i];
-            }
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                s1[i] = __builtin_amdgcn_exp2f(s1[i] - m_use);
-                psum += s1[i];
-            }
-            l_run = l_run * alpha + psum;
-            m_run = m_new;
-            if (__any(alpha != 1.0f)) {
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) o[nb][i] *= alpha;
-            }
-            outputs(s0, 0);
-            if (full) outputs(s1, 1);
-        }
-        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the next K tile
-        __syncthreads();                      // everybody is done with V^T
-        load_v(e1);
-        e0 = e1;
-        if constexpr (kTable) {   // the table's other half has been left behind: refill it
-            ++s_done;
-            if ((s_done & (kF32Chunk - 1)) == 0)
-                union_fill<2, 256, kF32Chunk, false>(u, s_done + kF32Chunk, total, hg.n_tiles, vmask_g, n0s_g, tid);
+            for (int i = 0; i < 16; ++i) bad = fmaf(o[nb][i], 0.0f, bad);
+        uint32_t* flag = reinterpret_cast<uint32_t*>(smem);   // the planes are done with
+        const bool any_bad = __any(bad != 0.0f);
+        if (lane == 0) flag[wave] = any_bad ? 1u : 0u;
+        __syncthreads();
+        if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)(flag[0] | flag[1] | flag[2] | flag[3])), 0)) {
+            __syncthreads();
+            exact_walk();
         }
     }
 
