@@ -10,6 +10,7 @@
 //              with 1/count rounded once on the host; max/min by plain comparisons.
 //   phi      : per output, one fmaf chain over ascending input index started from the bias.
 //   score    : per (i,j), one fmaf chain over ascending latent index from +0, then * scale.
+#include "direct_load.h"
 #include "score_common.h"
 
 #pragma clang fp contract(off)
@@ -261,6 +262,166 @@ __global__ __launch_bounds__(kMlpThreads, 3) void mlp_kernel(const HeadGeom* __r
     }
 }
 
+// The same projections for the usual sizes (hidden 128 or 64, in_dim a multiple of 16): 16 reduction indices of weights and
+// inputs at a time through a ring of kDepth stages in LDS, filled by direct loads two stages ahead, one barrier per stage.
+// Bound by the matrix pipe where there are many blocks and by the chain of a block where there are few, so a workgroup
+// takes as few rows as give its four waves a 32 x 32 block each: 32 of 128 outputs (half the chain of the kernel above, and
+// twice the workgroups: 40 heads of 624 tiles were 800 workgroups on 768 places, a second round for 32 of them), 64 of 64.
+// The hidden layer stays in LDS, over the first layer's stages.
+// Measured, kernel above and this one, between the other kernels of a call: 4 heads of 75 tiles, 2 samples (192 -> 64 -> 32)
+// 22 -> 13 us; 384 -> 128 -> 64: 12 heads of 624 tiles 51 -> 32, 40 heads 130 -> 87, 24 heads of 219,600 tokens 282 -> 232 us
+// (88 TFLOP/s).  A block's 32 stages take 1700 cycles each where two share a SIMD, 1024 of them products.
+// LDS stages: weights [16][N] as they lie in memory, odd rows with the 128-byte halves of each 256 bytes exchanged (lanes
+// 0-31 read row k, lanes 32-63 row k + 1); inputs [rows][16], 16-byte chunk ^ row / 4.
+template <int N> struct MlpStage {
+    static constexpr int kBytes = 16 * N * 4, kLoads = kBytes / 1024, kRowChunks = N / 4;
+    static constexpr int kPer = kLoads >= 4 ? kLoads / 4 : 1;   // loads per wave; two loads: waves 2, 3 repeat those of 0, 1
+    static __device__ __forceinline__ uint32_t lane_offset(int lane) {
+        const int row = lane / kRowChunks, c = lane % kRowChunks;
+        return (uint32_t)(row * kRowChunks + (N % 64 == 0 ? c ^ ((row & 1) << 3) : c)) * 16u;
+    }
+    // rows k .. k + 15 of w, k = 16 * stage
+    static __device__ __forceinline__ void load(const float* w, int stage, uint32_t lds, int wave, uint32_t lane_off) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int q = kLoads >= 4 ? wave * kPer + i : wave & 1;
+            dma16_to_lds(lds + 1024u * q, (const char*)w + (int64_t)stage * kBytes + 1024 * q, lane_off);
+        }
+    }
+};
+
+// Stages of the ring: four, 40 KB for 128 outputs (three: 215 instead of 210 us for stages 2+3 of 40 heads of 624 tiles, six: 237).
+constexpr int kMlpDepth = 4;
+
+template <int N1, int N2, int kRows>
+__global__ __launch_bounds__(256) void mlp_staged_kernel(const HeadGeom* __restrict__ heads, const int32_t* __restrict__ row_blk,
+                                                            const float* __restrict__ zq, const float* __restrict__ zk,
+                                                            float* __restrict__ yq, float* __restrict__ yk, MlpDev pq, MlpDev pk,
+                                                            int64_t total_tiles) {
+    typedef MlpStage<N1> W1;
+    typedef MlpStage<N2> W2;
+    constexpr int kXLoads = kRows / 16;                         // 1024-byte loads of a stage's inputs: 2 or 4
+    constexpr int kStage = W1::kBytes + kXLoads * 1024, kDepth = kMlpDepth;
+    constexpr int kC1 = W1::kPer + 1, kC2 = W2::kPer;           // loads per wave and stage
+    constexpr int kPitchB = (N1 + 4) * 4;                       // of the hidden layer: rows on all banks
+    // The hidden rows lie in the first three stages, behind what the second layer's stages take of them.
+    constexpr int kPieceRows = (kStage - W2::kBytes) / kPitchB;
+    static_assert(kDepth >= 3 && 3 * kPieceRows >= kRows, "room for the hidden layer");
+    auto hidden_row = [](int r) { return (uint32_t)(r / kPieceRows * kStage + W2::kBytes + r % kPieceRows * kPitchB); };
+    constexpr int kSub = kLatentRows / kRows;                   // workgroups to an entry of the row-block table
+    static_assert((kRows / 32) * (N1 / 32) == 4, "a 32 x 32 block for each wave");
+    extern __shared__ __align__(1024) float smem[];
+    const MlpDev p = blockIdx.y == 0 ? pq : pk;
+    const int32_t code = row_blk[blockIdx.x / kSub];
+    const int head = code >> 24, first = (code & 0xffffff) * kLatentRows + (int)(blockIdx.x % kSub) * kRows;
+    const HeadGeom hg = heads[head];
+    const int rows = hg.n_tiles - first < kRows ? hg.n_tiles - first : kRows;
+    if (rows <= 0) return;
+    const int64_t row0 = (int64_t)blockIdx.z * total_tiles + hg.tile_off + first;
+    const int K = p.in_dim, n1 = K / 16;
+    constexpr int n2 = N1 / 16;
+    const char* x = (const char*)((blockIdx.y == 0 ? zq : zk) + row0 * K);
+    float* y = (blockIdx.y == 0 ? yq : yk) + row0 * N2;
+    const float* w1 = p.w1 + (int64_t)head * K * N1;
+    const float* w2 = p.w2 + (int64_t)head * N1 * N2;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), col = lane & 31, kh = lane >> 5;
+    const int rb = wave / (N1 / 32), cb = wave % (N1 / 32);     // this wave's block of the hidden layer
+    const int rb2 = wave / (N2 / 32), cb2 = wave % (N2 / 32);   // and of the output, if it has one
+    float b1 = p.b1[head * N1 + 32 * cb + col], b2 = p.b2[head * N2 + 32 * cb2 + col];
+    asm volatile("" : "+v"(b1), "+v"(b2));   // have arrived before the loads that are counted
+    const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+    const uint32_t off1 = W1::lane_offset(lane), off2 = W2::lane_offset(lane);
+    const int xq = wave % kXLoads;
+    uint32_t xoff;
+    {
+        const int row = 16 * xq + lane / 4, real = row < rows ? row : rows - 1;
+        xoff = (uint32_t)(real * K * 4 + (((lane & 3) ^ ((row >> 2) & 3)) << 4));
+    }
+    // stages 0 .. n1 - 1 are the first layer's, those after them the second's
+    auto load = [&](int s) __attribute__((always_inline)) {
+        const uint32_t at = base + (uint32_t)(s % kDepth) * kStage;
+        if (s < n1) {
+            W1::load(w1, s, at, wave, off1);
+            dma16_to_lds(at + W1::kBytes + 1024u * xq, x + 64 * s, xoff);
+        } else if (s < n1 + n2) {
+            W2::load(w2, s - n1, at, wave, off2);
+        }
+    };
+    auto meet = []() __attribute__((always_inline)) { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    typedef const __attribute__((address_space(3))) float* lds_f32_ptr;
+    typedef __attribute__((address_space(3))) float* lds_f32_wptr;
+    typedef __attribute__((ext_vector_type(4))) float f4;
+    typedef const __attribute__((address_space(3))) f4* lds_f4_ptr;
+    // 16 terms of the chains: x(m) gives the four inputs 4m .. 4m + 3 of this lane's row
+    auto chain = [&](mlp_f32x16 acc, uint32_t w, int n, int c, auto xs) __attribute__((always_inline)) {
+        const uint32_t wl = w + (uint32_t)(kh * n + ((32 * c + col) ^ (n % 64 == 0 ? kh << 5 : 0))) * 4u;
+        f4 a[4];
+        float b[8];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) a[m] = xs(m);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) b[i] = *(lds_f32_ptr)(uintptr_t)(wl + (uint32_t)(2 * i * n * 4));
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float even = a[i >> 1][2 * (i & 1)], odd = a[i >> 1][2 * (i & 1) + 1];
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kh ? odd : even, b[i], acc, 0, 0, 0);
+        }
+        return acc;
+    };
+#pragma unroll
+    for (int s = 0; s < kDepth - 1; ++s) load(s);
+    mlp_f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = b1;
+    const int xrow = 32 * rb + col;
+    for (int s = 0; s < n1; ++s) {
+        // stage s has landed: only the loads of the kDepth - 2 stages after it are on their way, of which the second layer's
+        // have fewer
+        if (s + kDepth - 2 < n1) wait_vmcnt<(kDepth - 2) * kC1>(); else wait_vmcnt<(kDepth - 2) * kC2>();
+        meet();
+        load(s + kDepth - 1);   // into the place that everybody has left
+        const uint32_t at = base + (uint32_t)(s % kDepth) * kStage;
+        acc = chain(acc, at, N1, cb, [&](int m) __attribute__((always_inline)) {
+            return *(lds_f4_ptr)(uintptr_t)(at + W1::kBytes + xrow * 64 + ((m ^ ((xrow >> 2) & 3)) << 4));
+        });
+    }
+    meet();   // the first layer's stages have been read
+    const bool relu = p.relu != 0;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const float v = (relu && !(acc[r] > 0.0f)) ? 0.0f : acc[r];
+        *(lds_f32_wptr)(uintptr_t)(base + hidden_row(32 * rb + (r & 3) + 8 * (r >> 2) + 4 * kh) + (uint32_t)(32 * cb + col) * 4u) = v;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = b2;
+    const bool has_block = 32 * rb2 < kRows;
+    const uint32_t hrow = base + hidden_row(has_block ? 32 * rb2 + col : 0);
+    for (int s = n1; s < n1 + n2; ++s) {
+        if (s + kDepth - 2 < n1 + n2) wait_vmcnt<(kDepth - 2) * kC2>(); else wait_vmcnt<0>();
+        meet();
+        load(s + kDepth - 1);
+        if (has_block)
+            acc = chain(acc, base + (uint32_t)(s % kDepth) * kStage, N2, cb2, [&](int m) __attribute__((always_inline)) {
+                return *(lds_f4_ptr)(uintptr_t)(hrow + (uint32_t)(16 * (s - n1) + 4 * m) * 4u);
+            });
+    }
+    if (has_block) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int row = 32 * rb2 + (r & 3) + 8 * (r >> 2) + 4 * kh;
+            if (row < rows) y[(int64_t)row * N2 + 32 * cb2 + col] = acc[r];
+        }
+    }
+}
+
+// Both estimators alike in size, and one of the sizes above.
+template <int N1, int N2> static bool staged_sizes(const MlpDev& q, const MlpDev& k, const float* zq, const float* zk) {
+    auto fits = [](const MlpDev& p) {
+        return p.hidden == N1 && p.out_dim == N2 && p.in_dim % 16 == 0 && aligned16(p.w1) && aligned16(p.w2);
+    };
+    return fits(q) && fits(k) && q.in_dim == k.in_dim && aligned16(zq) && aligned16(zk);
+}
+
 constexpr int kSB = 128;      // score block edge
 constexpr int kSC = 32;       // latent coordinates staged per step
 constexpr int kSPitch = 36;   // LDS pitch of one staged latent row (floats): rows stay 16-byte
@@ -441,6 +602,16 @@ veda_status launch_projections(const veda_plan* pl, const veda_mlp* phi_q, const
     MlpDev pq{phi_q->in_dim, phi_q->hidden, phi_q->out_dim, phi_q->act == VEDA_ACT_RELU, phi_q->w1, phi_q->b1, phi_q->w2, phi_q->b2};
     MlpDev pk{phi_k->in_dim, phi_k->hidden, phi_k->out_dim, phi_k->act == VEDA_ACT_RELU, phi_k->w1, phi_k->b1, phi_k->w2, phi_k->b2};
     if (pl->chain_unit() == VEDA_CHAINS_VECTOR) return launch_projections_vector(pl, pq, pk, zq, zk, yq, yk, s);
+#define VEDA_TRY_STAGED(N1, N2, ROWS)                                                                    \
+    if (staged_sizes<N1, N2>(pq, pk, zq, zk)) {                                                          \
+        dim3 sgrid((unsigned)(pl->row_blocks * (kLatentRows / (ROWS))), 2, (unsigned)pl->prob.batch);    \
+        hipLaunchKernelGGL((mlp_staged_kernel<N1, N2, ROWS>), sgrid, dim3(256), kMlpDepth * (16 * (N1) * 4 + (ROWS) * 64), s, \
+                           pl->d_heads, pl->d_row_blk, zq, zk, yq, yk, pq, pk, pl->total_tiles);         \
+        return launch_status("mlp_staged_kernel");                                                       \
+    }
+    VEDA_TRY_STAGED(128, 64, 32)
+    VEDA_TRY_STAGED(64, 32, 64)
+#undef VEDA_TRY_STAGED
     const int max_hidden = phi_q->hidden > phi_k->hidden ? phi_q->hidden : phi_k->hidden;
     // the global route reads the hidden layer back as float4 rows
     if (!hq || !hk || (phi_q->hidden & 3) || (phi_k->hidden & 3)) hq = hk = nullptr;

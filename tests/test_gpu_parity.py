@@ -150,6 +150,40 @@ def test_projection_chains_of_odd_length_keep_signed_zeros():
     assert np.all(yk.cpu().numpy().view(np.uint32) == 0x80000000)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("tiles", [1, 31, 32, 33, 63, 64, 65, 130])
+def test_usual_estimator_sizes_bit_exact(d, tiles):
+    """192 -> 64 -> 32 and 384 -> 128 -> 64, the sizes with a kernel of their own, around the rows a workgroup takes;
+    with weights at other alignments, which the general kernel serves, the same latents."""
+    wl = wlm.custom_workload("usual", 2, d, "f32", (4, 4, 4 * tiles), False, (1, 2), seed=tiles, latent_dim=d // 2, batch=2)
+    dev = torch.device("cuda:0")
+    q, k, _ = wlm.make_qkv(wl, dev)
+    plan = veda.Plan(2, 2, d, wl.grid, wlm.tile_shapes(wl), wl.torch_dtype)
+    _, vm, _, zq = veda.veda_tile_layout_stats(plan, q)
+    _, _, _, zk = veda.veda_tile_layout_stats(plan, k, want_mask=False)
+    rng = np.random.default_rng(tiles)
+    w = [rng.uniform(-0.2, 0.2, s).astype(np.float32) for s in ((2, 3 * d, d), (2, d), (2, d, d // 2), (2, d // 2))]
+    w[2][:, :, 0] = -0.0   # and a column of zeros
+    w[3][:, 0] = -0.0
+    for relu in (True, False):
+        phi = veda.Mlp(*w, relu, dev)
+        odd = veda.Mlp(*w, relu, dev)
+        odd.w1 = torch.cat([torch.zeros(1, device=dev), phi.w1.reshape(-1)])[1:].view(phi.w1.shape)
+        assert odd.w1.data_ptr() % 16 == 4
+        s, ws = veda.veda_tile_score_stats(plan, zq, zk, phi, phi, 1.0)
+        s2, _ = veda.veda_tile_score_stats(plan, zq, zk, odd, odd, 1.0)
+        torch.cuda.synchronize()
+        assert torch.equal(s.view(torch.int32), s2.view(torch.int32))
+        for b in range(2):
+            for h in range(2):
+                args = (w[0][h], w[1][h], w[2][h], w[3][h], relu)
+                lat = [vo.mlp(vo.trippool(hz.to_f32_numpy(x[b, h]), wl.grid, (4, 4, 4)), *args) for x in (q, k)]
+                ref = vo.score(lat[0], lat[1], np.float32(1.0))
+                off = plan.score_offset[h]
+                got = s[b, off:off + tiles * tiles].view(tiles, tiles).cpu().numpy()
+                assert np.array_equal(got.view(np.uint32), ref.view(np.uint32)), (relu, b, h)
+
+
 def test_projection_and_score_chains_in_the_denormal_range():
     """Weights of magnitude 2^-136 (denormal themselves): every product and partial sum of the projection
     chains is a denormal number, and so are the latents; the scores underflow.  Nothing may be flushed to
