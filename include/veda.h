@@ -186,6 +186,11 @@ veda_status veda_tile_score(const veda_plan*, const void* q_tiled, const void* k
  * inputs either way. */
 veda_status veda_tile_layout_stats(const veda_plan*, const void* x, veda_strides sx, void* x_tiled,
                                    uint64_t* valid_mask, int32_t* valid_cnt, float* stats, void* stream);
+/* veda_tile_layout_path = stage 1 of a whole call: veda_tile_layout_stats of q (with the masks) and k and veda_tile_layout of
+ * v in VEDA_CHANNEL_MAJOR order, the same bytes, in one launch.  q_tiled and k_tiled: both or neither. */
+veda_status veda_tile_layout_path(const veda_plan*, const void* q, veda_strides sq, const void* k, veda_strides sk,
+                                  const void* v, veda_strides sv, void* q_tiled, void* k_tiled, void* v_tiled,
+                                  uint64_t* valid_mask, int32_t* valid_cnt, float* stats_q, float* stats_k, void* stream);
 veda_status veda_tile_score_stats(const veda_plan*, const float* stats_q, const float* stats_k,
                                   const veda_mlp* phi_q, const veda_mlp* phi_k, float scale, float* scores,
                                   void* workspace, size_t workspace_bytes, void* stream);

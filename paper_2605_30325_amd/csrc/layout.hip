@@ -41,20 +41,19 @@ __global__ __launch_bounds__(256) void layout_token_major_kernel(
 
 // out tile = [d][64] elements.  The tile is staged in LDS as [64][d] with one pad dword per
 // row so that the column gathers spread over the banks.
+template <typename E, int D> constexpr int kChannelMajorWords = kTile * (D * (int)sizeof(E) / 4 + 1);   // of the stage
+
 template <typename E, int D>
-__global__ __launch_bounds__(256) void layout_channel_major_kernel(
+__device__ __forceinline__ void channel_major_tile(
     const HeadGeom* __restrict__ heads, const uint8_t* __restrict__ tile_head,
     const char* __restrict__ x, int64_t sb, int64_t sh, int64_t sn, char* __restrict__ out,
     int64_t total_tiles, int T, int H, int W,
-    uint64_t* __restrict__ valid_mask, int32_t* __restrict__ valid_cnt) {
+    uint64_t* __restrict__ valid_mask, int32_t* __restrict__ valid_cnt, int g, int b, int* tok, uint32_t* stage) {
     constexpr int kRowBytes = D * (int)sizeof(E);
     constexpr int kRowWords = kRowBytes / 4;
     constexpr int kPitch = kRowWords + 1;   // dwords
     constexpr int kCpr = kRowBytes / 16;
     constexpr int kEpc = 16 / (int)sizeof(E);  // elements per 16-byte output chunk
-    __shared__ int tok[kTile];
-    __shared__ uint32_t stage[kTile * kPitch];
-    const int g = blockIdx.x, b = blockIdx.y;
     const int head = tile_head[g];
     const HeadGeom hg = heads[head];
     const int i = g - hg.tile_off;
@@ -89,6 +88,18 @@ __global__ __launch_bounds__(256) void layout_channel_major_kernel(
         for (int j = 0; j < kEpc; ++j) tmp[j] = se[(l0 + j) * kPitchE + ch];
         *reinterpret_cast<uint4*>(ob + (int64_t)oc * 16) = *reinterpret_cast<const uint4*>(tmp);
     }
+}
+
+template <typename E, int D>
+__global__ __launch_bounds__(256) void layout_channel_major_kernel(
+    const HeadGeom* __restrict__ heads, const uint8_t* __restrict__ tile_head,
+    const char* __restrict__ x, int64_t sb, int64_t sh, int64_t sn, char* __restrict__ out,
+    int64_t total_tiles, int T, int H, int W,
+    uint64_t* __restrict__ valid_mask, int32_t* __restrict__ valid_cnt) {
+    __shared__ int tok[kTile];
+    __shared__ uint32_t stage[kChannelMajorWords<E, D>];
+    channel_major_tile<E, D>(heads, tile_head, x, sb, sh, sn, out, total_tiles, T, H, W, valid_mask, valid_cnt, blockIdx.x,
+                             blockIdx.y, tok, stage);
 }
 
 // 128-token tiles: number of real tokens of a whole tile from the masks of its two halves.
@@ -138,22 +149,23 @@ template <> struct Quad<uint32_t> {
 };
 
 #pragma clang fp contract(off)
+template <int D, int GRP> constexpr int kStatsTok = 256 / (D / 4) * kTile * GRP;   // token numbers of a workgroup's tiles
+
 template <typename E, int D, bool kWrite, int GRP>
-__global__ __launch_bounds__(256) void layout_stats_kernel(
+__device__ __forceinline__ void layout_stats_block(
     const HeadGeom* __restrict__ heads, const uint8_t* __restrict__ tile_head,
     const char* __restrict__ x, int64_t sb, int64_t sh, int64_t sn, char* __restrict__ out,
     float* __restrict__ stats, int64_t total_tiles, int T, int H, int W,
-    uint64_t* __restrict__ valid_mask, int32_t* __restrict__ valid_cnt, RecipTable recip) {
+    uint64_t* __restrict__ valid_mask, int32_t* __restrict__ valid_cnt, const RecipTable& recip, int blk, int b, int* tok_lds) {
     typedef typename Quad<E>::raw raw;
     constexpr int kBatch = kWrite ? Quad<E>::kBatch : Quad<E>::kBatch / 2;
     constexpr int kTpt = D / 4;             // threads per tile
     constexpr int kTiles = 256 / kTpt;      // tiles per workgroup
     constexpr int kRowBytes = D * (int)sizeof(E);
     constexpr int kSlots = kTile * GRP;     // slots of a whole tile
-    __shared__ int tok[kTiles][kSlots];
+    int (*tok)[kSlots] = reinterpret_cast<int (*)[kSlots]>(tok_lds);
     const int64_t whole_tiles = total_tiles / GRP;
-    const int64_t g0 = (int64_t)blockIdx.x * kTiles;
-    const int b = blockIdx.y;
+    const int64_t g0 = (int64_t)blk * kTiles;
     for (int e = threadIdx.x; e < kTiles * kSlots; e += 256) {
         const int tl = e / kSlots, l = e % kSlots;
         const int64_t gi = (g0 + tl) * GRP + l / kTile;   // the 64-slot tile this slot belongs to
@@ -230,6 +242,51 @@ __global__ __launch_bounds__(256) void layout_stats_kernel(
             for (int w = 0; w < GRP; ++w) valid_mask[g * GRP + w] = mask[w];
         }
         if (valid_cnt) valid_cnt[g] = cnt;
+    }
+}
+
+template <typename E, int D, bool kWrite, int GRP>
+__global__ __launch_bounds__(256) void layout_stats_kernel(
+    const HeadGeom* __restrict__ heads, const uint8_t* __restrict__ tile_head,
+    const char* __restrict__ x, int64_t sb, int64_t sh, int64_t sn, char* __restrict__ out,
+    float* __restrict__ stats, int64_t total_tiles, int T, int H, int W,
+    uint64_t* __restrict__ valid_mask, int32_t* __restrict__ valid_cnt, RecipTable recip) {
+    __shared__ int tok[kStatsTok<D, GRP>];
+    layout_stats_block<E, D, kWrite, GRP>(heads, tile_head, x, sb, sh, sn, out, stats, total_tiles, T, H, W, valid_mask, valid_cnt,
+                                          recip, blockIdx.x, blockIdx.y, tok);
+}
+
+// Stage 1 of a whole call in one launch: the descriptors of Q and K (with their tiled copies if asked for) and V channel-major.
+// The three write to memory of their own and none waits for another, so three launches only add their starts and ends:
+// 4 heads of 75 tiles, 2 samples (bf16, d = 64) 29 -> 15 us, 2 fp32 heads of 4 tiles 24 -> 10.5; 12 heads of 624 tiles
+// (bf16, d = 128) 95 -> 79, 40 heads 282 -> 271, 24 heads of 219,600 tokens 1038 -> 1032.
+struct LayoutPathArgs {
+    const char *q, *k, *v;
+    int64_t qb, qh, qn, kb, kh, kn, vb, vh, vn;   // strides in bytes
+    char *q_tiled, *k_tiled, *v_tiled;
+    float *stats_q, *stats_k;
+    uint64_t* valid_mask;
+    int32_t* valid_cnt;
+    int64_t total_tiles;   // of 64 slots
+    int T, H, W;
+    int stats_blocks;      // workgroups of Q, and of K; V's follow
+};
+
+template <typename E, int D, bool kWrite, int GRP>
+__global__ __launch_bounds__(256) void layout_path_kernel(const HeadGeom* __restrict__ heads, const uint8_t* __restrict__ tile_head,
+                                                          LayoutPathArgs a, RecipTable recip) {
+    constexpr int kV = kTile + kChannelMajorWords<E, D>, kS = kStatsTok<D, GRP>;
+    __shared__ uint32_t lds[kV > kS ? kV : kS];
+    const int x = blockIdx.x, b = blockIdx.y;
+    if (x < 2 * a.stats_blocks) {
+        const bool q = x < a.stats_blocks;   // the masks come with Q
+        layout_stats_block<E, D, kWrite, GRP>(heads, tile_head, q ? a.q : a.k, q ? a.qb : a.kb, q ? a.qh : a.kh, q ? a.qn : a.kn,
+                                              q ? a.q_tiled : a.k_tiled, q ? a.stats_q : a.stats_k, a.total_tiles, a.T, a.H, a.W,
+                                              q ? a.valid_mask : nullptr, q ? a.valid_cnt : nullptr, recip,
+                                              q ? x : x - a.stats_blocks, b, (int*)lds);
+    } else {
+        channel_major_tile<E, D>(heads, tile_head, a.v, a.vb, a.vh, a.vn, a.v_tiled, a.total_tiles, a.T, a.H, a.W, nullptr, nullptr,
+                                 x - 2 * a.stats_blocks, b, (int*)lds, lds + kTile);
     }
 }
 
@@ -317,4 +374,53 @@ extern "C" veda_status veda_tile_layout_stats(const veda_plan* pl, const void* x
 #undef VEDA_LAUNCH_LS
 #undef VEDA_LAUNCH_LS2
     return launch_status("veda_tile_layout_stats");
+}
+
+extern "C" veda_status veda_tile_layout_path(const veda_plan* pl, const void* q, veda_strides sq, const void* k, veda_strides sk,
+                                             const void* v, veda_strides sv, void* q_tiled, void* k_tiled, void* v_tiled,
+                                             uint64_t* valid_mask, int32_t* valid_cnt, float* stats_q, float* stats_k, void* stream) {
+    using namespace veda;
+    if (!pl || !q || !k || !v || !v_tiled || !stats_q || !stats_k || !q_tiled != !k_tiled) return VEDA_ERR_INVALID_ARG;
+    const int es = pl->elem_size(), d = pl->prob.head_dim;
+    for (const veda_strides& t : {sq, sk, sv}) {
+        if (t.n < d || t.b < 0 || t.h < 0) return VEDA_ERR_INVALID_ARG;
+        if ((t.b * es) % 16 || (t.h * es) % 16 || (t.n * es) % 16) return VEDA_ERR_UNSUPPORTED;
+    }
+    for (const void* p : {q, k, v, (const void*)q_tiled, (const void*)k_tiled, (const void*)v_tiled, (const void*)stats_q, (const void*)stats_k})
+        if (!aligned16(p)) return VEDA_ERR_UNSUPPORTED;
+    const veda_plan* ip = pl->inner ? pl->inner : pl;
+    RecipTable recip;
+    recip.v[0] = 0.0f;
+    for (int c = 1; c <= 2 * kTile; ++c) recip.v[c] = 1.0f / (float)c;
+    LayoutPathArgs a;
+    a.q = (const char*)q; a.k = (const char*)k; a.v = (const char*)v;
+    a.qb = sq.b * es; a.qh = sq.h * es; a.qn = sq.n * es;
+    a.kb = sk.b * es; a.kh = sk.h * es; a.kn = sk.n * es;
+    a.vb = sv.b * es; a.vh = sv.h * es; a.vn = sv.n * es;
+    a.q_tiled = (char*)q_tiled; a.k_tiled = (char*)k_tiled; a.v_tiled = (char*)v_tiled;
+    a.stats_q = stats_q; a.stats_k = stats_k;
+    a.valid_mask = valid_mask; a.valid_cnt = valid_cnt;
+    a.total_tiles = ip->total_tiles;
+    a.T = pl->prob.T; a.H = pl->prob.H; a.W = pl->prob.W;
+    const int tiles = 256 / (d / 4);   // to a workgroup of the descriptors
+    a.stats_blocks = (int)((pl->total_tiles + tiles - 1) / tiles);
+    dim3 grid((unsigned)(2 * a.stats_blocks + ip->total_tiles), (unsigned)pl->prob.batch);
+    hipStream_t st = (hipStream_t)stream;
+    // Where the descriptors' part needs many registers (tiled copies, 128-token tiles), V's part keeps fewer waves in flight
+    // than in a kernel of its own, which shows once memory is what bounds them: 40 heads of 21x45x80 with 128-token tiles 683 us in one
+    // launch, 637 in three; 8 fp32 heads of 624 tiles (7,500 workgroups) 196 and 193.
+    if ((pl->inner || q_tiled) && (int64_t)grid.x * grid.y > 4096) {
+        veda_status r = veda_tile_layout_stats(pl, q, sq, q_tiled, valid_mask, valid_cnt, stats_q, stream);
+        if (r == VEDA_OK) r = veda_tile_layout_stats(pl, k, sk, k_tiled, nullptr, nullptr, stats_k, stream);
+        return r == VEDA_OK ? veda_tile_layout(pl, v, sv, VEDA_CHANNEL_MAJOR, v_tiled, nullptr, nullptr, stream) : r;
+    }
+    auto launch = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, ip->d_heads, ip->d_tile_head, a, recip);
+        return launch_status("veda_tile_layout_path");
+    };
+#define VEDA_LAUNCH_LP(E, D, GRP) (q_tiled ? launch(layout_path_kernel<E, D, true, GRP>) : launch(layout_path_kernel<E, D, false, GRP>))
+    if (es == 2 && pl->inner) return d == 128 ? VEDA_LAUNCH_LP(uint16_t, 128, 2) : VEDA_LAUNCH_LP(uint16_t, 64, 2);
+    if (es == 2) return d == 128 ? VEDA_LAUNCH_LP(uint16_t, 128, 1) : VEDA_LAUNCH_LP(uint16_t, 64, 1);
+    return d == 128 ? VEDA_LAUNCH_LP(uint32_t, 128, 1) : VEDA_LAUNCH_LP(uint32_t, 64, 1);   // fp32 plans have 64-token tiles
+#undef VEDA_LAUNCH_LP
 }

@@ -30,6 +30,7 @@ EXPORTS = (
     "veda_plan_create", "veda_plan_destroy", "veda_plan_set_option", "veda_plan_chain_unit", "veda_plan_tiles", "veda_plan_tile_offset",
     "veda_plan_score_offset", "veda_plan_total_tiles", "veda_plan_score_elems",
     "veda_plan_workspace_bytes", "veda_plan_workspace_layout", "veda_tile_layout", "veda_tile_score", "veda_tile_layout_stats",
+    "veda_tile_layout_path",
     "veda_tile_score_stats", "veda_tile_score_closed_form", "veda_tile_select", "veda_plan_fused_workspace_bytes",
     "veda_tile_score_select", "veda_tile_score_select_stats", "veda_tile_score_select_stats_noalloc",
     "veda_sparse_attn_fwd", "veda_sparse_attn_fwd_q_tokens",
@@ -103,6 +104,8 @@ def load():
     L.veda_tile_score.restype = C.c_int
     L.veda_tile_layout_stats.argtypes = [vp, vp, veda_strides, vp, vp, vp, vp, vp]
     L.veda_tile_layout_stats.restype = C.c_int
+    L.veda_tile_layout_path.argtypes = [vp, vp, veda_strides, vp, veda_strides, vp, veda_strides] + [vp] * 8
+    L.veda_tile_layout_path.restype = C.c_int
     L.veda_tile_score_stats.argtypes = [vp, vp, vp, C.POINTER(veda_mlp), C.POINTER(veda_mlp), C.c_float, vp, vp,
                                         C.c_size_t, vp]
     L.veda_tile_score_stats.restype = C.c_int
@@ -303,6 +306,28 @@ def veda_tile_layout_stats(plan: Plan, x: torch.Tensor, x_tiled: Optional[torch.
     _check(load().veda_tile_layout_stats(plan.handle, _ptr(x), _strides(x), _ptr(x_tiled), _ptr(valid_mask),
                                          _ptr(valid_cnt), _ptr(stats), _stream()), "veda_tile_layout_stats")
     return x_tiled, valid_mask, valid_cnt, stats
+
+
+def veda_tile_layout_path(plan: Plan, q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, buffers: Optional[dict] = None,
+                          want_tiles: bool = True) -> dict:
+    """Stage 1 of a whole call in one launch: q and k as veda_tile_layout_stats takes them, v channel-major.  Returns
+    {qt, kt, vt, vm, vc, zq, zk} (qt, kt None with want_tiles=False), from `buffers` where it has them."""
+    b, dev = {} if buffers is None else buffers, q.device
+    tiles = (plan.batch, plan.total_tiles, plan.tile_tokens * plan.head_dim)
+
+    def take(name, shape, dtype):
+        t = b.get(name)
+        return torch.empty(shape, dtype=dtype, device=dev) if t is None else t
+
+    r = {"qt": take("qt", tiles, q.dtype) if want_tiles else None, "kt": take("kt", tiles, k.dtype) if want_tiles else None,
+         "vt": take("vt", tiles, v.dtype), "vm": take("vm", plan.total_tiles * plan.mask_words, torch.int64),
+         "vc": take("vc", plan.total_tiles, torch.int32),
+         "zq": take("zq", (plan.batch, plan.total_tiles, 3 * plan.head_dim), torch.float32),
+         "zk": take("zk", (plan.batch, plan.total_tiles, 3 * plan.head_dim), torch.float32)}
+    _check(load().veda_tile_layout_path(plan.handle, _ptr(q), _strides(q), _ptr(k), _strides(k), _ptr(v), _strides(v), _ptr(r["qt"]),
+                                        _ptr(r["kt"]), _ptr(r["vt"]), _ptr(r["vm"]), _ptr(r["vc"]), _ptr(r["zq"]), _ptr(r["zk"]),
+                                        _stream()), "veda_tile_layout_path")
+    return r
 
 
 def veda_tile_score_stats(plan: Plan, stats_q, stats_k, phi_q: Mlp, phi_k: Mlp, scale: float,
@@ -539,15 +564,13 @@ def veda_attention(plan: Plan, q, k, v, phi_q: Mlp, phi_k: Mlp, k_per_head, scor
     if from_tokens and not fused:
         raise ValueError("from_tokens needs fused=True (the descriptors must come from the gathers)")
     if fused:
-        qt, vm, vc, zq = veda_tile_layout_stats(plan, q, bufs.get("qt"), bufs.get("vm"), bufs.get("vc"), bufs.get("zq"),
-                                                want_tiles=not from_tokens)
-        kt, _, _, zk = veda_tile_layout_stats(plan, k, bufs.get("kt"), stats=bufs.get("zk"), want_mask=False,
-                                              want_tiles=not from_tokens)
+        r = veda_tile_layout_path(plan, q, k, v, bufs, want_tiles=not from_tokens)
+        qt, kt, vt, vm, vc, zq, zk = (r[x] for x in ("qt", "kt", "vt", "vm", "vc", "zq", "zk"))
         bufs.update(zq=zq, zk=zk)
     else:
         qt, vm, vc = veda_tile_layout(plan, q, VEDA_TOKEN_MAJOR, bufs.get("qt"), bufs.get("vm"), bufs.get("vc"))
         kt, _, _ = veda_tile_layout(plan, k, VEDA_TOKEN_MAJOR, bufs.get("kt"), want_mask=False)
-    vt, _, _ = veda_tile_layout(plan, v, VEDA_CHANNEL_MAJOR, bufs.get("vt"), want_mask=False)
+        vt, _, _ = veda_tile_layout(plan, v, VEDA_CHANNEL_MAJOR, bufs.get("vt"), want_mask=False)
     if one_call:
         s = None
         if fused:

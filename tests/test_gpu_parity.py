@@ -150,6 +150,32 @@ def test_projection_chains_of_odd_length_keep_signed_zeros():
     assert np.all(yk.cpu().numpy().view(np.uint32) == 0x80000000)
 
 
+@pytest.mark.parametrize("dtype,d,tile_tokens,grid,heads", [
+    ("bf16", 128, 64, (5, 9, 13), 3), ("bf16", 64, 64, (3, 17, 30), 5), ("f32", 128, 64, (6, 7, 9), 3), ("f32", 64, 64, (1, 5, 67), 3),
+    ("bf16", 128, 128, (5, 9, 13), 3), ("bf16", 64, 128, (17, 6, 7), 3),
+    ("f32", 64, 64, (8, 40, 40), 20), ("bf16", 64, 128, (8, 80, 80), 6),   # enough workgroups for three launches
+])
+@pytest.mark.parametrize("want_tiles", [True, False])
+def test_stage_one_in_one_launch_gives_the_same_bytes(dtype, d, tile_tokens, grid, heads, want_tiles):
+    shapes = [(4, 4, 4), (1, 8, 8), (16, 2, 2)]
+    shapes = np.asarray([shapes[h % 3] for h in range(heads)], np.int32) * np.asarray([tile_tokens // 64, 1, 1], np.int32)
+    wl = wlm.custom_workload("one_launch", heads, d, dtype, grid, False, (50, 100), seed=47, batch=2)
+    q, k, v = wlm.make_qkv(wl, torch.device("cuda:0"))
+    k = k.transpose(1, 2).contiguous().transpose(1, 2)   # a stride of its own for each
+    v = torch.cat([v, v], dim=3)[..., :d]
+    plan = veda.Plan(2, heads, d, grid, shapes, wl.torch_dtype, tile_tokens=tile_tokens)
+    r = veda.veda_tile_layout_path(plan, q, k, v, want_tiles=want_tiles)
+    qt, vm, vc, zq = veda.veda_tile_layout_stats(plan, q, want_tiles=want_tiles)
+    kt, _, _, zk = veda.veda_tile_layout_stats(plan, k, want_mask=False, want_tiles=want_tiles)
+    vt, _, _ = veda.veda_tile_layout(plan, v, veda.VEDA_CHANNEL_MAJOR, want_mask=False)
+    torch.cuda.synchronize()
+    for name, want in (("qt", qt), ("kt", kt), ("vt", vt), ("vm", vm), ("vc", vc), ("zq", zq), ("zk", zk)):
+        if want is None:
+            assert r[name] is None
+        else:
+            assert torch.equal(r[name].view(torch.uint8), want.view(torch.uint8)), name
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("tiles", [1, 31, 32, 33, 63, 64, 65, 130])
 def test_usual_estimator_sizes_bit_exact(d, tiles):
