@@ -54,6 +54,7 @@ __global__ __launch_bounds__(256) void select_sampled_kernel(const HeadGeom* __r
 #pragma unroll
             for (int e = 0; e < kSample / 64; ++e) cnt += __popcll(__ballot(sk[e] >= cand));
             if (cnt >= m) pk = cand;
+            if (cnt == m) break;   // as good a pivot
         }
         pivot = __uint_as_float((pk & 0x80000000u) ? (pk ^ 0x80000000u) : ~pk);   // inverse of score_key
         // A float comparison against -inf would miss NaN scores, which rank as -inf.
@@ -132,15 +133,23 @@ veda_status launch_select(const veda_plan* pl, const float* scores, const int32_
     // Otherwise the smallest register-resident instantiation that fits the longest row, else the
     // memory-resident one.
     int items = 0;
-    for (int cand : {4, 16, 32, 64})
+    for (int cand : {2, 4, 6, 8, 10, 12, 14, 16, 24, 32, 48, 64})
         if (max_tiles <= 64 * cand) { items = cand; break; }
 #define VEDA_LAUNCH_SEL(I)                                                                                  \
     hipLaunchKernelGGL((select_kernel<I>), grid, block, 0, s, pl->d_heads, pl->d_tile_head, scores, args,   \
                        row_ptr, col_idx, pl->total_tiles, pl->score_elems, rows)
     switch (items) {
+        case 2: VEDA_LAUNCH_SEL(2); break;
         case 4: VEDA_LAUNCH_SEL(4); break;
+        case 6: VEDA_LAUNCH_SEL(6); break;
+        case 8: VEDA_LAUNCH_SEL(8); break;
+        case 10: VEDA_LAUNCH_SEL(10); break;
+        case 12: VEDA_LAUNCH_SEL(12); break;
+        case 14: VEDA_LAUNCH_SEL(14); break;
         case 16: VEDA_LAUNCH_SEL(16); break;
+        case 24: VEDA_LAUNCH_SEL(24); break;
         case 32: VEDA_LAUNCH_SEL(32); break;
+        case 48: VEDA_LAUNCH_SEL(48); break;
         case 64: VEDA_LAUNCH_SEL(64); break;
         default: VEDA_LAUNCH_SEL(0); break;
     }

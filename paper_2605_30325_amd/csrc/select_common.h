@@ -91,8 +91,9 @@ __device__ __forceinline__ void select_row(const float* __restrict__ srow, int n
             for (int t = 0; t < items; ++t) cnt += __popcll(__ballot(get(t) >= cand));
         }
         if (cnt >= k) thr = cand;
+        if (cnt == k) break;   // a cut between the k-th largest and the next: the bits below would only move it there
     }
-    // thr is now the k-th largest key of the row.
+    // thr is now the k-th largest key of the row, or above the next and not above it.
     int n_gt = 0;
     if (thr == hi) {
         // nothing above the largest
@@ -184,6 +185,7 @@ __device__ __forceinline__ void select_candidates(const uint32_t* ckey, const in
 #pragma unroll
         for (int t = 0; t < NI; ++t) cnt += __popcll(__ballot(key[t] >= cand));
         if (cnt >= k) thr = cand;
+        if (cnt == k) break;   // see select_row
     }
     int n_gt = 0;
 #pragma unroll

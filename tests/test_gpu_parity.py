@@ -255,6 +255,21 @@ def test_projection_and_score_chains_in_the_denormal_range():
     assert np.array_equal(s[0].view(rows, rows).cpu().numpy().view(np.uint32), ref.view(np.uint32))
 
 
+@pytest.mark.parametrize("n", [1, 2, 127, 128, 129, 257, 384, 385, 513, 641, 768, 769, 897, 1023, 1024, 1025, 1537, 2049, 3073, 4097])
+def test_selection_of_every_row_length_class(n):
+    """Row lengths around the registers a row takes; continuous scores (the search stops at the first cut), scores with many
+    ties (it never finds one), one sign, and a few special values."""
+    plan = veda.Plan(1, 1, 64, (4, 4, 4 * n), np.asarray([(4, 4, 4)], np.int32), torch.float32)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    cont = torch.randn((n, n), device="cuda", generator=g)
+    for scores in (cont, (cont * 4).round() / 4, cont.abs() + 1.0, torch.where(cont > 1.0, -0.0, torch.where(cont < -1.5, -math.inf, 0.0 * cont))):
+        key = torch.where(scores == 0.0, 0.0, scores)
+        order = torch.sort(key, dim=1, descending=True, stable=True)[1]
+        for k in sorted({1, max(1, n // 20), max(1, n // 2), n}):
+            _, ci = veda.veda_tile_select(plan, scores.reshape(1, -1).contiguous(), [k])
+            assert torch.equal(ci.view(n, k).long(), torch.sort(order[:, :k], dim=1)[0]), (n, k)
+
+
 def test_zero_sparsity_equals_dense_attention_on_gpu():
     wl = wlm.custom_workload("dense_identity", 3, 128, "bf16", (6, 9, 11), True, (1, 1), seed=13)
     run = hz.run_gpu_path(wl)
