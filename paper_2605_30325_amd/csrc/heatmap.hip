@@ -13,16 +13,15 @@
 // max_v s_uv of pass 1 are kept, 4 bytes per row and key tile where the products of that block read 16 KB, and pass 2
 // only reads those: the same bits without forming the logits again.
 //
-// The same kernel serves bf16 and fp32 (v_mfma_f32_32x32x16_bf16, fp32 operands split into three parts: split_f32.h, with
-// v_mfma_f32_32x32x2_f32 where something is not finite; fp32 accumulation): S^T = K Q^T, so a lane owns a query row and its registers run over keys.  A workgroup holds
+// The same kernel serves bf16 and fp32 (v_mfma_f32_32x32x16_bf16 or v_mfma_f32_32x32x2_f32, fp32
+// accumulation): S^T = K Q^T, so a lane owns a query row and its registers run over keys.  A workgroup holds
 // two query tiles, a wave 32 rows of one.  Pass 1 is bound by its exponentials (one per pair of tokens, with the
 // fused multiply-add before and the addition after it: 48 vector operations per 8 products), pass 2 by the
 // products; the exponentials of one 32-key block are therefore formed behind the products of the next, and the
 // reference of the softmax stays where it is until a sum outgrows it.
 // Measured, the heat map alone, before and after: 12 heads of 624 tiles, bf16, d = 128, 10.0 -> 7.9 ms; one in 16
 // of the query tiles of 40 heads of 21x45x80, mixed shapes, 23.1 -> 11.6 ms (listed tiles used to run one to a
-// workgroup); 8 heads of 144 tiles, fp32, d = 128, 19.1 -> 3.0 ms (on the vector units
-// before), both passes, and 2.4 -> 0.94 ms on average over a search, which forms the sums once, with the products split.  Tried and left out: 64 rows
+// workgroup); 8 heads of 144 tiles, fp32, d = 128, 19.1 -> 3.0 ms (on the vector units before).  Tried and left out: 64 rows
 // per wave, four tiles per workgroup (half the operand reads and loads: 8.3 and 11.7 ms, fp32 3.9), a ring of
 // three or four K tiles (0.5 ms slower: it costs a resident workgroup and the loads are not what is waited for).
 // With scratch, whole calls of the supervision side (gathers, heat map, both top-k, recall), two walks and one: 12 heads
@@ -36,7 +35,6 @@
 
 #include "attn_common.h"
 #include "attn_union.h"
-#include "split_f32.h"
 
 namespace veda {
 
@@ -179,7 +177,7 @@ __device__ inline bool listed_pair(const HeatArgs& a, int item, char* smem, int 
 // kOneWalk: the logits are formed once.  Pass 1 keeps the largest raw logit of every row and key tile in scratch, one
 // place per workgroup and written over for its next work item; pass 2 reads those instead of forming the products again.
 template <typename E, int D, bool kGrouped, bool kListed, bool kOneWalk>
-__global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : D == 64 ? 3 : 2) void tile_heatmap_kernel(HeatArgs a) {
+__global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : 3) void tile_heatmap_kernel(HeatArgs a) {
     typedef HeatFrag<E> F;
     typedef typename F::type frag;
     typedef const __attribute__((address_space(3))) frag* lds_frag_ptr;
@@ -237,11 +235,13 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : D == 64 ? 3 : 2) void til
     const int row = 32 * r + idx, q_rows = __popcll(q_mask);
     bool q_real = row < q_rows;
     const bool active = __builtin_amdgcn_readfirstlane(32 * r < q_rows ? 1 : 0);
+    frag qf[kF];
     float2* row_sums = nullptr;   // where this lane's are kept
-    const char* qrow;
     {
         const int slot = q_real ? nth_bit(q_mask, row) : 0;
-        qrow = a.q + (head_tile0 + (qi >= 0 ? qi : 0)) * kKBytes + slot * kRowB;
+        const char* qrow = a.q + (head_tile0 + (qi >= 0 ? qi : 0)) * kKBytes + slot * kRowB + 16 * hh;
+#pragma unroll
+        for (int f = 0; f < kF; ++f) qf[f] = *reinterpret_cast<const frag*>(qrow + 32 * f);
         if (a.rows && q_real) {
             // a slot without a token has no place there, whatever the mask says of it
             const int token = slot_token(hg, qi, slot, a.T, a.H, a.W);
@@ -250,7 +250,16 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : D == 64 ? 3 : 2) void til
         }
     }
 
+    // global -> LDS copy plan: see the attention kernels.
+    uint32_t k_src[kLoads];
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) {
+        const int krow = (wave * kLoads + j) * (1024 / kRowB) + lane / kKChunks, kpos = lane % kKChunks;
+        k_src[j] = krow * kRowB + ((kpos ^ (krow & (kKChunks - 1))) << 4) - 1024u * (j % kGroup);
+    }
     const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+    const uint32_t wave_lds = smem_base + (uint32_t)wave * (kLoads * 1024);
+    const uint32_t k0 = smem_base + idx * kRowB + ((hh ^ (idx & (kKChunks - 1))) << 4);
     // step_kind of 64 key tiles at a time, one per lane; the next 64 masks are fetched a step before their turn
     // (the wait for the tile loads that ends every step covers them).
     struct Key { int kind; uint32_t lo, hi; };
@@ -267,50 +276,6 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : D == 64 ? 3 : 2) void til
         if ((j & 63) == 62) fetch_masks(j + 2);
         return e;
     };
-    // padded keys of a block: register i is key 8*(i/4) + 4*hh + i%4, or 16*(i/8) + 8*hh + i%8 of split rows
-    auto mask_keys = [&](f32x16& s, uint32_t mask, auto split) __attribute__((always_inline)) {
-        if (mask == ~0u) return;
-        asm volatile("" ::: "memory");   // keeps this a branch, taken at edge tiles only
-        // a register's two keys as a lane mask, on the scalar unit: the vector unit is what pass 1 waits for
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            constexpr int kUp = decltype(split)::value ? 8 : 4;
-            const int bit = decltype(split)::value ? 16 * (i >> 3) + (i & 7) : 8 * (i >> 2) + (i & 3);
-            const uint32_t lo = (uint32_t)((int)(mask << (31 - bit)) >> 31), up = (uint32_t)((int)(mask << (31 - kUp - bit)) >> 31);
-            s[i] = __builtin_amdgcn_inverse_ballot_w64((uint64_t)up << 32 | lo) ? s[i] : -INFINITY;
-        }
-    };
-    // relative to ref, log2 units
-    auto logit = [&](float x, float ref) __attribute__((always_inline)) { return fmaf(x, a.scale_log2, -ref); };
-
-    // whether it holds in any lane of the workgroup; a barrier before and after
-    auto any_wave = [&](bool x) __attribute__((always_inline)) {
-        const bool mine = __any(x);
-        __syncthreads();
-        if (lane == 0) part[wave][0] = mine ? 1.0f : 0.0f;
-        __syncthreads();
-        const bool all = part[0][0] + part[1][0] + part[2][0] + part[3][0] != 0.0f;
-        __syncthreads();
-        return __builtin_amdgcn_readfirstlane(all ? 1 : 0) != 0;
-    };
-    // An item in two passes; split: fp32 products on the bf16 matrix cores (split_f32.h).  False: something is not finite,
-    // and the split products cannot tell what.
-    auto item = [&](auto split_tag) __attribute__((always_inline)) -> bool {
-    constexpr bool kSplit = decltype(split_tag)::value;
-    frag qf[kF];
-    if constexpr (!kSplit) {
-#pragma unroll
-        for (int f = 0; f < kF; ++f) qf[f] = *reinterpret_cast<const frag*>(qrow + 16 * hh + 32 * f);
-    }
-    // global -> LDS copy plan: see the attention kernels.
-    uint32_t k_src[kLoads];
-#pragma unroll
-    for (int j = 0; j < kLoads; ++j) {
-        const int krow = (wave * kLoads + j) * (1024 / kRowB) + lane / kKChunks, kpos = lane % kKChunks;
-        k_src[j] = krow * kRowB + ((kpos ^ (krow & (kKChunks - 1))) << 4) - 1024u * (j % kGroup);
-    }
-    const uint32_t wave_lds = smem_base + (uint32_t)wave * (kLoads * 1024);
-    const uint32_t k0 = smem_base + idx * kRowB + ((hh ^ (idx & (kKChunks - 1))) << 4);
     auto load_k = [&](int j_tile, const Key& e, int sl) __attribute__((always_inline)) {
         if (e.kind == kStepEmpty || (e.kind == kStepHalf && wave >= 2)) return;   // half: only the first 32 rows are read
         const char* src = kt + (int64_t)j_tile * kKBytes;
@@ -330,58 +295,9 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : D == 64 ? 3 : 2) void til
             dma16_group_to_lds<kGroup>(wave_lds + (uint32_t)sl * kKBytes + g * (kGroup * 1024), src, off);
         }
     };
-    // The walk over the key tiles: two K tiles in LDS, loads one step ahead.  Split: two lots of 32 keys as bf16 planes,
-    // the next converted behind the products of the one at hand, the one after that on its way.
-    typedef SplitK<D> K;
-    K ks;
-    bf16x8 qs[3][kSplit ? D / 16 : 1];
-    if constexpr (kSplit) {
-        ks.init(smem_base, smem_base + 2 * K::kPlanes, wave, lane);
-        split_row<D>(reinterpret_cast<const float*>(qrow), hh, 1.0f, qs);
-    }
-    Key e0, e1, e2;
-    uint32_t planes = 0u;
-    auto full = [](const Key& e) __attribute__((always_inline)) { return (e.kind & (kStepWhole | kStepPart)) != 0; };
-    auto load_split = [&](int u, int j, const Key& e, int c) __attribute__((always_inline)) {
-        const uint32_t from = full(e) ? (c ? 0x07060504u : 0x03020100u) : e.kind == kStepHalf ? e.hi : 0x03020100u;
-        ks.load(u, kt + (int64_t)(j < n ? j : 0) * kKBytes, from);
-    };
-    // while 32 keys of tile j are multiplied (block c): place u of the next ones converted and of those after them asked for
-    auto stage = [&](int u, int j, int c) __attribute__((always_inline)) {
-        ks.convert(u, K::kPlanes - planes);
-        if (c == 0 && full(e0)) load_split(u, j + 1, e1, 0);
-        else if (full(e1)) load_split(u, j + 1, e1, 1);
-        else load_split(u, j + 2, e2, 0);
-    };
-    auto block_end = [&]() __attribute__((always_inline)) {
-        planes = K::kPlanes - planes;
-        K::meet();
-    };
-    // a block of tile j by a wave that has no rows
-    auto idle = [&](int j, int c) __attribute__((always_inline)) {
-        if constexpr (kSplit) {
-#pragma unroll
-            for (int u = 0; u < K::kI; ++u) stage(u, j, c);
-            block_end();
-        }
-    };
+    // The walk over the key tiles: two K tiles in LDS, loads one step ahead.
+    Key e0, e1;
     auto walk_begin = [&]() __attribute__((always_inline)) {
-        if constexpr (kSplit) {
-            fetch_masks(0);
-            e0 = key_of(0);
-            e1 = key_of(1);
-            planes = 0u;
-#pragma unroll
-            for (int u = 0; u < K::kI; ++u) load_split(u, 0, e0, 0);
-#pragma unroll
-            for (int u = 0; u < K::kI; ++u) {
-                ks.convert(u, 0u);
-                if (full(e0)) load_split(u, 0, e0, 1);
-                else load_split(u, 1, e1, 0);
-            }
-            K::meet();
-            return;
-        }
         fetch_masks(0);
         e0 = e1 = key_of(0);
         load_k(0, e0, 0);
@@ -389,10 +305,6 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : D == 64 ? 3 : 2) void til
         __syncthreads();
     };
     auto step_begin = [&](int j) __attribute__((always_inline)) {
-        if constexpr (kSplit) {
-            e2 = key_of(j + 2);
-            return;
-        }
         if (j + 1 < n) {
             e1 = key_of(j + 1);
             load_k(j + 1, e1, (j + 1) & 1);
@@ -400,36 +312,20 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : D == 64 ? 3 : 2) void til
     };
     auto step_end = [&]() __attribute__((always_inline)) {
         e0 = e1;
-        if constexpr (kSplit) {
-            e1 = e2;
-            return;
-        }
         wait_vmcnt<0>();
         __syncthreads();
     };
-    auto walk_end = []() __attribute__((always_inline)) {   // nothing lands any more
-        if constexpr (kSplit) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    };
 #define VEDA_KF(block, f) (*(lds_frag_ptr)(uintptr_t)(kx[f] + (block) * (uint32_t)(32 * kRowB)))
 
-    // Raw dot products of this wave's rows with the 32 keys of tile j's block 0 or 1; behind(first, end) is vector work on
-    // those registers of the block before, placed behind some of the products.
+    // Raw dot products of this wave's rows with the 32 keys of the step's block 0 or 1; `behind(f)` is vector work placed
+    // behind the products of fragment f.
     uint32_t kx[kF];   // operand addresses of a step's first block; the second is a constant distance away
     auto addresses = [&](int j) __attribute__((always_inline)) {
         const uint32_t ka = k0 + (uint32_t)((j & 1) * kKBytes);
 #pragma unroll
         for (int f = 0; f < kF; ++f) kx[f] = ka ^ (uint32_t)(f << 5);
     };
-    auto products = [&](f32x16& s, int j, uint32_t block, auto behind) __attribute__((always_inline)) {
-        if constexpr (kSplit) {
-            constexpr int G = D / 16;
-            ks.template products<false>(s, qs, planes, [&](int t) __attribute__((always_inline)) {
-                behind(t * 16 / G, (t + 1) * 16 / G);
-                if (t >= G - K::kI) stage(t - (G - K::kI), j, (int)block);
-            });
-            block_end();
-            return;
-        }
+    auto products = [&](f32x16& s, uint32_t block, auto behind) __attribute__((always_inline)) {
         const f32x16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
         frag kf[kF];
 #pragma unroll
@@ -438,10 +334,24 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : D == 64 ? 3 : 2) void til
         for (int f = 0; f < kF; ++f) {
             if (f + kAhead < kF) kf[f + kAhead] = VEDA_KF(block, f + kAhead);
             s = F::mul(kf[f], qf[f], f == 0 ? zero : s);
-            behind(f * kExps, (f + 1) * kExps);
+            behind(f);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
+    // padded keys of a block: register i is key 8*(i/4) + 4*hh + i%4
+    auto mask_keys = [&](f32x16& s, uint32_t mask) __attribute__((always_inline)) {
+        if (mask == ~0u) return;
+        asm volatile("" ::: "memory");   // keeps this a branch, taken at edge tiles only
+        // a register's two keys as a lane mask, on the scalar unit: the vector unit is what pass 1 waits for
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int bit = 8 * (i >> 2) + (i & 3);
+            const uint32_t lo = (uint32_t)((int)(mask << (31 - bit)) >> 31), up = (uint32_t)((int)(mask << (27 - bit)) >> 31);
+            s[i] = __builtin_amdgcn_inverse_ballot_w64((uint64_t)up << 32 | lo) ? s[i] : -INFINITY;
+        }
+    };
+    // relative to ref, log2 units
+    auto logit = [&](float x, float ref) __attribute__((always_inline)) { return fmaf(x, a.scale_log2, -ref); };
 
     // ---- pass 1: reference (log2 units) and denominator of this lane's row over the keys of its lane half ----
     // The denominator is kept as a finished part and that of the last kHeatFold steps, so that its rounding
@@ -480,43 +390,43 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : D == 64 ? 3 : 2) void til
         f32x16 s0, s1;
         float sum, mx = -INFINITY;
         int last = -1;
-        auto maxima = [&](const f32x16& s, int begin, int end, bool first) __attribute__((always_inline)) {
+        auto maxima = [&](const f32x16& s, int f, bool first) __attribute__((always_inline)) {
             if (!kOneWalk) return;
 #pragma unroll
-            for (int i = begin; i < end; ++i) mx = first && i == 0 ? s[0] : fmaxf(mx, s[i]);
+            for (int i = f * kExps; i < (f + 1) * kExps; ++i) mx = first && i == 0 ? s[0] : fmaxf(mx, s[i]);
         };
         auto keep = [&]() __attribute__((always_inline)) {
             if (!kOneWalk || last < 0) return;
             float* const rows = kept + (int64_t)last * 32;
             rows[idx] = max_with_other_half(mx);   // alike in both halves
         };
-        auto exps = [&](const f32x16& s, int begin, int end) __attribute__((always_inline)) {
-            if (begin == 0) sum = 0.0f;
+        auto exps = [&](const f32x16& s, int f) __attribute__((always_inline)) {
+            if (f == 0) sum = 0.0f;
 #pragma unroll
-            for (int i = begin; i < end; ++i) sum += __builtin_amdgcn_exp2f(logit(s[i], ref));
+            for (int i = f * kExps; i < (f + 1) * kExps; ++i) sum += __builtin_amdgcn_exp2f(logit(s[i], ref));
         };
 #pragma unroll
         for (int i = 0; i < 16; ++i) s1[i] = -INFINITY;
         for (int j = 0; j < n; ++j) {
             step_begin(j);
             addresses(j);
-            if (kSplit || e0.kind != kStepEmpty) {
-                products(s0, j, 0u, [&](int i0, int i1) __attribute__((always_inline)) { exps(s1, i0, i1); maxima(s1, i0, i1, false); });
+            if (e0.kind != kStepEmpty) {
+                products(s0, 0u, [&](int f) __attribute__((always_inline)) { exps(s1, f); maxima(s1, f, false); });
                 asm volatile("" : "+v"(sum), "+v"(mx));   // they stay behind the products: the branches below would take them along
                 keep();
                 last = j;
                 settle(s1, sum);
-                mask_keys(s0, e0.lo, split_tag);
-                if (!full(e0)) {
+                mask_keys(s0, e0.lo);
+                if (e0.kind == kStepHalf) {
                     // moves of this branch alone: as a plain copy the other branch would carry sixteen as well
 #pragma unroll
                     for (int i = 0; i < 16; ++i) s1[i] = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s0[i]), 0xE4, 0xf, 0xf, true));   // quad_perm [0,1,2,3]
                     mx = -INFINITY;
                 } else {
-                    products(s1, j, 1u, [&](int i0, int i1) __attribute__((always_inline)) { exps(s0, i0, i1); maxima(s0, i0, i1, true); });
+                    products(s1, 1u, [&](int f) __attribute__((always_inline)) { exps(s0, f); maxima(s0, f, true); });
                     asm volatile("" : "+v"(sum), "+v"(mx));
                     settle(s0, sum);   // before the mask's branch: the exponentials would move behind it
-                    mask_keys(s1, e0.hi, split_tag);
+                    mask_keys(s1, e0.hi);
                 }
             }
             if ((j & (kHeatFold - 1)) == kHeatFold - 1) {
@@ -525,19 +435,16 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : D == 64 ? 3 : 2) void til
             }
             step_end();
         }
-        exps(s1, 0, 16);
-        maxima(s1, 0, 16, false);
+#pragma unroll
+        for (int f = 0; f < kF; ++f) { exps(s1, f); maxima(s1, f, false); }
         keep();
         settle(s1, sum);
     } else {   // a wave without rows loads and meets the others
         for (int j = 0; j < n; ++j) {
             step_begin(j);
-            idle(j, 0);
-            if (kSplit && full(e0)) idle(j, 1);
             step_end();
         }
     }
-    if (kOneWalk || !a.have_rows) walk_end();
     float inv_l;
     if (!kOneWalk && a.have_rows) {
         const float2 known = row_sums ? *row_sums : make_float2(0.0f, 0.0f);
@@ -546,7 +453,6 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : D == 64 ? 3 : 2) void til
     } else {
         inv_l = 1.0f / sum_with_other_half(l + l_part);   // the lane halves hold different keys
         if (row_sums && hh == 0) *row_sums = make_float2(ref, inv_l);
-        if (kSplit && any_wave(active && q_real && !(inv_l > 0.0f && inv_l < INFINITY))) return false;
     }
 
     // ---- pass 2: block maxima of exp2(s - ref) / l ----
@@ -610,41 +516,33 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : D == 64 ? 3 : 2) void til
             }
             publish(first + 63 < n ? first + 63 : n - 1);
         }
-        return true;
+        return;
     }
-    float odd = 0.0f;   // NaN once a split product is
     walk_begin();
     if (active) {
         for (int j = 0; j < n; ++j) {
             step_begin(j);
             addresses(j);
             float best = 0.0f;
-            if (kSplit || e0.kind != kStepEmpty) {
+            if (e0.kind != kStepEmpty) {
                 f32x16 s0, s1;
-                auto check = [&](const f32x16& s) __attribute__((always_inline)) {
-                    if (!kSplit) return;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) odd = fmaf(s[i], 0.0f, odd);
-                };
-                const bool two = full(e0), empty = e0.kind == kStepEmpty;
-                products(s0, j, 0u, [](int, int) {});
-                check(s0);
-                mask_keys(s0, e0.lo, split_tag);
+                products(s0, 0u, [](int) {});
+                mask_keys(s0, e0.lo);
                 float mx = s0[0];
-                auto maxima = [&](const f32x16& s, int begin, int end) __attribute__((always_inline)) {
+                auto maxima = [&](const f32x16& s, int f) __attribute__((always_inline)) {
 #pragma unroll
-                    for (int i = begin; i < end; ++i) mx = fmaxf(mx, s[i]);
+                    for (int i = f * kExps; i < (f + 1) * kExps; ++i) mx = fmaxf(mx, s[i]);
                 };
-                if (!two) {
+                if (e0.kind == kStepHalf) {
                     s1 = s0;
                 } else {
-                    products(s1, j, 1u, [&](int i0, int i1) __attribute__((always_inline)) { maxima(s0, i0, i1); });
+                    products(s1, 1u, [&](int f) __attribute__((always_inline)) { maxima(s0, f); });
                     asm volatile("" : "+v"(mx));   // the maxima stay behind the products
-                    check(s1);
-                    mask_keys(s1, e0.hi, split_tag);
+                    mask_keys(s1, e0.hi);
                 }
-                maxima(s1, 0, 16);
-                best = empty ? 0.0f : rows_max(q_real ? heat_score<E>(logit(max_with_other_half(mx), ref), inv_l) : 0.0f);
+#pragma unroll
+                for (int f = 0; f < kF; ++f) maxima(s1, f);
+                best = rows_max(q_real ? heat_score<E>(logit(max_with_other_half(mx), ref), inv_l) : 0.0f);
             }
             mine = lane == (j & 63) ? best : mine;
             step_end();
@@ -653,17 +551,10 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : D == 64 ? 3 : 2) void til
     } else {
         for (int j = 0; j < n; ++j) {
             step_begin(j);
-            idle(j, 0);
-            if (kSplit && full(e0)) idle(j, 1);
             step_end();
             publish(j);
         }
     }
-    walk_end();
-    return !(kSplit && any_wave(q_real && odd != 0.0f));
-    };   // item
-    if (sizeof(E) == 4 && item(std::true_type{})) return;
-    item(std::false_type{});
     };   // run
 #undef VEDA_KF
 
@@ -784,8 +675,7 @@ namespace veda {
 // One walk: the workgroups of a launch, each with a place in the scratch.  As many as are resident at once, which their
 // registers decide; a multiple of the dies.
 static int64_t heat_places(const veda_plan* pl) {
-    const bool wide = pl->prob.head_dim == 128;
-    return 256 * (pl->prob.dtype == VEDA_BF16 ? (wide ? 4 : 5) : wide ? 2 : 3);
+    return 256 * (pl->prob.dtype == VEDA_BF16 ? (pl->prob.head_dim == 128 ? 4 : 5) : 3);
 }
 constexpr size_t kHeatTakenBytes = kXcd * kHeatTakenStride * sizeof(uint32_t);   // at the start of the scratch
 
