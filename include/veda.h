@@ -117,8 +117,15 @@ void veda_plan_destroy(veda_plan* plan); /* NULL is allowed */
  * veda_plan_create measures it on the plan's device (both forms on chains with rounding,
  * signed zeros and denormal sums and products, once per device) and uses the matrix cores only
  * if every bit agrees; this option overrides the choice either way.
- * veda_plan_chain_unit tells which unit the plan's next call will use. */
-typedef enum { VEDA_OPT_EXACT_LOGIT_SCALE = 0, VEDA_OPT_ATTN_LIST_WALK = 1, VEDA_OPT_FP32_CHAIN_UNIT = 2 } veda_option;
+ * veda_plan_chain_unit tells which unit the plan's next call will use.
+ * VEDA_OPT_FP32_PRODUCTS (0 = by the length of the lists, the default; VEDA_PRODUCTS_FP32; VEDA_PRODUCTS_SPLIT), fp32
+ * stage 4: products on the fp32 matrix cores, or as six products of exact three-part bf16 splits, which is about
+ * twice as fast and nearer to the exact result (2-norm of the error three quarters).  By default query tiles with
+ * up to 192 kept key tiles take the split products; beyond that the fp32 ones, whose rounding grows with the root of the list,
+ * so that outputs stay within 4e-5 of their root mean square of what those give. */
+typedef enum { VEDA_OPT_EXACT_LOGIT_SCALE = 0, VEDA_OPT_ATTN_LIST_WALK = 1, VEDA_OPT_FP32_CHAIN_UNIT = 2,
+               VEDA_OPT_FP32_PRODUCTS = 3 } veda_option;
+enum { VEDA_PRODUCTS_FP32 = 1, VEDA_PRODUCTS_SPLIT = 2 };
 enum { VEDA_CHAINS_MATRIX = 1, VEDA_CHAINS_VECTOR = 2 };
 veda_status veda_plan_set_option(veda_plan*, veda_option option, int32_t value);
 int32_t veda_plan_chain_unit(const veda_plan*);          /* VEDA_CHAINS_*; -1 on bad args */
@@ -278,8 +285,7 @@ veda_status veda_tile_score_select_stats_noalloc(const veda_plan*, const float* 
  * of two nearest below that factor (exact in bf16) and the logits by the remaining factor in fp32
  * on their way into the exponential: the error no longer depends on the logits' size (max-abs
  * <= 1.7e-2, mean-abs <= 1e-3, lse 1e-5 up to a standard deviation of 16) at about 4 % more time.
- * f32: fp32 arithmetic; products are formed from exact splits of their operands into three bf16 parts and summed in
- * fp32, nearer to the exact sum than fp32 fused multiply-adds in turn. */
+ * f32: fp32 arithmetic (VEDA_OPT_FP32_PRODUCTS). */
 veda_status veda_sparse_attn_fwd(const veda_plan*, const void* q_tiled, const void* k_tiled,
                                  const void* v_tiled, const uint64_t* valid_mask,
                                  const int32_t* row_ptr, const int32_t* col_idx, float softmax_scale,

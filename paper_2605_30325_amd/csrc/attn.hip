@@ -6,6 +6,12 @@
 
 namespace veda {
 
+// Lists up to this long take the fp32 kernel's split products.  Those are nearer to the 64-bit result at any length (8
+// heads of 624 tiles: all kept 2.6e-6 against 3.7e-6, 63 kept 6.5e-7 and 9e-7), but the fp32 chains' rounding grows with
+// the root of the list, and with it how far the two lie apart: 3.9e-5 of the outputs' rms at most after 203 tiles, 4.8e-5
+// after 312, 6.1e-5 after 624 (d = 128, two heads).  Results of this path are compared at 5e-5, so longer lists keep the chains.
+constexpr int kF32SplitTiles = 192;
+
 // Shared by the entry points: q_tiled or (q_tok, sq), k_tiled or (k_tok, sk).
 static veda_status sparse_attn(const veda_plan* pl, const void* q_tiled, const void* q_tok, veda_strides sq,
                                const void* k_tiled, const void* k_tok, veda_strides sk, const void* v_tiled,
@@ -54,6 +60,7 @@ static veda_status sparse_attn(const veda_plan* pl, const void* q_tiled, const v
         a.scale_pow2 = ldexpf(1.0f, ex - 1);
         a.scale_resid = 2.0f * mant;
     }
+    a.split_tiles = pl->fp32_products == VEDA_PRODUCTS_FP32 ? 0 : pl->fp32_products == VEDA_PRODUCTS_SPLIT ? 0x7fffffff : kF32SplitTiles;
     hipStream_t s = (hipStream_t)stream;
     if (pl->prob.dtype == VEDA_BF16) {
         a.xcd_cum = ip->d_xcd_cum_pair;

@@ -39,6 +39,7 @@ struct AttnArgs {
     // logits by scale_resid on their way into the exponential, so no rounding of Q comes between the
     // inputs and the products; without it Q is multiplied by scale_log2 and rounded to bf16 once
     float scale_pow2, scale_resid;
+    int split_tiles;           // fp32 kernel: split products up to this many kept key tiles of a query tile
 };
 
 // Workgroups are dealt round-robin to the 8 dies (XCDs), each with its own L2, all sharing

@@ -18,8 +18,8 @@
 // softmax only so far.  Reading a group of products ahead gave 7 %, rounding pairs once 3 %, V^T rows on all banks 2 %;
 // loads one phase earlier, priorities: 1-2 %.
 //
-// Numbers that are not finite come out of the split products as NaN: a workgroup that finds any in its results walks
-// again on v_mfma_f32_32x32x2_f32.  There a lane owns one query (lane % 32) and one of the two terms of every instruction
+// Long lists (AttnArgs::split_tiles) take v_mfma_f32_32x32x2_f32 instead, and numbers that are not finite come out of the
+// split products as NaN: a workgroup that finds any in its results walks again that way.  There a lane owns one query (lane % 32) and one of the two terms of every instruction
 // (h = lane / 32).  The pairing of the reduction index with h is free as long as both operands agree, and it is
 // chosen so that one 16-byte LDS read feeds four instructions:
 //   S^T, step (m, t):  h supplies channel 8m + 4h + t   (K row: float4 at channel 8m + 4h),
@@ -39,8 +39,9 @@ constexpr float kF32Slack = 8.0f;   // log2 units a row maximum may outgrow the 
 
 // kTable: the steps come from the table in LDS (attn_union.h), as in the bf16 kernel; otherwise the two
 // lists are merged inside the loop (heads above 16384 tiles, VEDA_OPT_ATTN_LIST_WALK).
+// d = 64: three workgroups on a compute unit (42 KB each); with two, 2 heads of 624 tiles, all kept, 7.34 instead of 7.14 ms.
 template <int D, bool kTable>
-__global__ __launch_bounds__(256, 2) void sparse_attn_f32_kernel(AttnArgs a) {
+__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(AttnArgs a) {
     constexpr int kKPitch = D * 4;               // bytes of one K row
     constexpr int kKBytes = kTile * kKPitch;     // K tile
     constexpr int kVPitch = kTile * 4;           // bytes of one V^T row (64 keys)
@@ -166,9 +167,6 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_f32_kernel(AttnArgs a) {
     auto split_walk = [&]() __attribute__((always_inline)) {
         typedef SplitK<D> K;
         constexpr int G = D / 16, kI = K::kI;
-        // Short rows round less often to begin with, so at d = 64 the sums are kept apart (there are registers for it): the
-        // table of the tiling search, squares of differences of two outputs, stayed within 1.2e-8 of the 64-bit one only so.
-        constexpr bool kTight = D == 64;
         constexpr uint32_t kV = K::kPlanes, kRaw = 2 * K::kPlanes;   // V^T planes, landing area: 64 KB (d = 128) in all
         K ks;
         ks.init(smem_base, smem_base + kRaw, wave, lane);
@@ -224,7 +222,9 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_f32_kernel(AttnArgs a) {
             int todo = 1;
             if (mine) {
                 todo = 0;
-                ks.template products<kTight>(s, q, 0u, [&](int t) __attribute__((always_inline)) {
+                // d = 64 has registers for the small products in a sum of their own (the search's table, squares of
+                // differences of outputs, 7.3e-9 -> 5.2e-9 from the 64-bit one; 1 % of the time)
+                ks.template products<D == 64>(s, q, 0u, [&](int t) __attribute__((always_inline)) {
                     if (t >= G - kI) {
                         convert_v(t - (G - kI));
                         load_k(nx, t - (G - kI));
@@ -296,14 +296,7 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_f32_kernel(AttnArgs a) {
                     const bf16x8 y0 = __builtin_bit_cast(bf16x8, u32x4{pw[kk][0][0], pw[kk][0][1], pw[kk][0][2], pw[kk][0][3]});
                     const bf16x8 y1 = __builtin_bit_cast(bf16x8, u32x4{pw[kk][1][0], pw[kk][1][1], pw[kk][1][2], pw[kk][1][3]});
                     const bf16x8 y2 = __builtin_bit_cast(bf16x8, u32x4{pw[kk][2][0], pw[kk][2][1], pw[kk][2][2], pw[kk][2][3]});
-                    if constexpr (kTight) {
-                        f32x16 z;
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) z[i] = 0.0f;
-                        o[nb] += mul6(z, vf[g & 1], y0, y1, y2);
-                    } else {
-                        o[nb] = mul6(o[nb], vf[g & 1], y0, y1, y2);
-                    }
+                    o[nb] = mul6(o[nb], vf[g & 1], y0, y1, y2);
                     if (kk == 0) {
 #pragma unroll
                         for (int e = nb * 4 / NB; e < (nb + 1) * 4 / NB; ++e) prob(1, e);
@@ -510,8 +503,10 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_f32_kernel(AttnArgs a) {
 
     };
 
-    split_walk();
-    {
+    if ((nA > nB ? nA : nB) > a.split_tiles) {
+        exact_walk();
+    } else {
+        split_walk();
         float bad = l_run * 0.0f;   // NaN if anything is not finite
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)

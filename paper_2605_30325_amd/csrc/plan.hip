@@ -217,6 +217,10 @@ veda_status veda_plan_set_option(veda_plan* pl, veda_option option, int32_t valu
             pl->chain_option = value;
             if (pl->inner) pl->inner->chain_option = value;
             return VEDA_OK;
+        case VEDA_OPT_FP32_PRODUCTS:
+            if (value != 0 && value != VEDA_PRODUCTS_FP32 && value != VEDA_PRODUCTS_SPLIT) return VEDA_ERR_INVALID_ARG;
+            pl->fp32_products = value;
+            return VEDA_OK;
     }
     return VEDA_ERR_INVALID_ARG;
 }

@@ -1,4 +1,5 @@
-// fp32 products on the bf16 matrix cores, for the fp32 attention and target-score kernels.
+// fp32 products on the bf16 matrix cores, for the fp32 attention kernel.  (The target scores keep the fp32 chains: a
+// score that moves in its last bits can change places with another in the top-k, and with it the kept lists.)
 //
 // A number is split into three bf16 numbers, each the rounding of what is left: 3 x 8 bits hold fp32's 24, so the sum
 // is exact (of what is finite; below 2^-109 up to half of bf16's smallest subnormal, 2^-133, is lost).  Of the nine products of two split operands the six largest
@@ -8,7 +9,7 @@
 // terms, normal, uniform and log-normal operands, came out 2 to 76 % nearer to the 64-bit result (relative 2-norm; 128
 // normal terms 2.0e-7 -> 1.6e-7).
 // What is not finite does not survive (an infinity's remainder is NaN, and its products with remainders of either
-// sign cancel): every such product is NaN, the kernels find that in their results and form them again on fp32 matrix cores.
+// sign cancel): every such product is NaN; the kernel finds that in its results and forms them again on fp32 matrix cores.
 #pragma once
 
 #include "attn_common.h"

@@ -63,6 +63,7 @@ struct veda_plan {
     int device = -1;
     bool exact_logit_scale = false;     // VEDA_OPT_EXACT_LOGIT_SCALE (bf16 attention kernel)
     bool attn_list_walk = false;        // VEDA_OPT_ATTN_LIST_WALK (attention kernels)
+    int fp32_products = 0;              // VEDA_OPT_FP32_PRODUCTS (fp32 attention kernel)
     // Where the fixed-order fp32 chains of stage 2 run: chain_probe is what probe_chain_unit found on
     // this plan's device, chain_option what VEDA_OPT_FP32_CHAIN_UNIT asks for (0 = as probed).
     int chain_probe = VEDA_CHAINS_MATRIX, chain_option = 0;

@@ -48,6 +48,9 @@ def tiling_search(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, grid: Seque
     for c, shape in enumerate(candidates):
         shapes = np.tile(np.asarray(shape, np.int32), (heads, 1))
         plan = veda.Plan(samples, heads, d, grid, shapes, q.dtype, tile_tokens=tile_tokens)
+        # The table sums squares over all tokens: split products serve lists of any length (the table moves by 1e-8).  With
+        # every tile kept it would hold nothing but their rounding, so there the plain fp32 products stay.
+        plan.set_option(veda.VEDA_OPT_FP32_PRODUCTS, veda.VEDA_PRODUCTS_FP32 if keep[0] >= keep[1] else veda.VEDA_PRODUCTS_SPLIT)
         qt, vm, _ = veda.veda_tile_layout(plan, q, veda.VEDA_TOKEN_MAJOR)
         kt, _, _ = veda.veda_tile_layout(plan, k, veda.VEDA_TOKEN_MAJOR, want_mask=False)
         vt, _, _ = veda.veda_tile_layout(plan, v, veda.VEDA_CHANNEL_MAJOR, want_mask=False)

@@ -24,6 +24,8 @@ VEDA_TOKEN_MAJOR, VEDA_CHANNEL_MAJOR = 0, 1
 VEDA_OPT_EXACT_LOGIT_SCALE = 0
 VEDA_OPT_ATTN_LIST_WALK = 1
 VEDA_OPT_FP32_CHAIN_UNIT = 2
+VEDA_OPT_FP32_PRODUCTS = 3
+VEDA_PRODUCTS_FP32, VEDA_PRODUCTS_SPLIT = 1, 2
 VEDA_CHAINS_MATRIX, VEDA_CHAINS_VECTOR = 1, 2
 
 EXPORTS = (

@@ -1321,6 +1321,109 @@ def test_heatmap_with_and_without_scratch(dtype, d, tile_tokens, grid, heads):
         assert torch.equal(heats[0].view(torch.int32), heats[2].view(torch.int32))
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("where,value", [("k", -math.inf), ("k", math.inf), ("k", math.nan), ("k", 3.4e38), ("q", -math.inf),
+                                         ("v", math.inf), ("v", math.nan), ("v", 3.4e38), ("q", 1e-30), ("v", 1e-35)])
+def test_fp32_kernels_on_numbers_a_split_does_not_hold(d, where, value):
+    """Numbers that do not survive the split into bf16 parts (not finite, or rounded to infinity) or whose parts are
+    subnormal: outputs and target scores are those of the formulas, not finite exactly where those are not."""
+    grid, heads = (4, 9, 22), 2
+    wl = wlm.custom_workload("odd_numbers", heads, d, "f32", grid, False, (50, 100), seed=43)
+    dev = torch.device("cuda:0")
+    q, k, v = wlm.make_qkv(wl, dev)
+    x = {"q": q, "k": k, "v": v}[where]
+    if abs(value) < 1.0:
+        x *= value
+    else:
+        x[0, 0, 100, 5] = value   # head 1 stays as it is
+        x[0, 0, 333, d - 1] = value
+    shape = (4, 4, 4)
+    plan = veda.Plan(1, heads, d, grid, np.asarray([shape] * heads, np.int32), torch.float32)
+    qt, vm, _ = veda.veda_tile_layout(plan, q)
+    kt, _, _ = veda.veda_tile_layout(plan, k, want_mask=False)
+    vt, _, _ = veda.veda_tile_layout(plan, v, veda.VEDA_CHANNEL_MAJOR, want_mask=False)
+    n, scale = plan.tiles[0], 1.0 / math.sqrt(d)
+    keep = torch.rand((heads * n, n), generator=torch.Generator().manual_seed(3)).argsort(dim=1)[:, :n // 2].sort(dim=1)[0]
+    rp = (torch.arange(heads * n + 1, dtype=torch.int32) * (n // 2)).to(dev)
+    out, _ = veda.veda_sparse_attn_fwd(plan, qt, kt, vt, vm, rp, keep.reshape(-1).to(torch.int32).to(dev), scale)
+    heat = veda.veda_tile_heatmap(plan, qt, kt, vm, scale).cpu().view(heads, n, n)
+    kept, sums = veda.veda_tile_heatmap_rows(plan, qt, kt, vm, scale)
+    again, _ = veda.veda_tile_heatmap_rows(plan, qt, kt, vm, scale, sums)
+    assert torch.equal(kept.cpu().view(heads, n, n).nan_to_num(-1.0), heat.nan_to_num(-1.0))
+    assert torch.equal(again.cpu().view(heads, n, n).nan_to_num(-1.0), heat.nan_to_num(-1.0))
+    out, q, k, v = (t[0].cpu() for t in (out, q, k, v))
+    slots = _tile_tokens(shape, grid)
+    for h in range(heads):
+        # logits as fp32 has them (a product of finite numbers may leave its range; the attention scales the queries, the
+        # target scores the products), the rest in 64 bits
+        log2e = 1.4426950408889634
+        s = ((q[h].double() * (scale * log2e)) @ k[h].double().T).float().double() / log2e
+        full = torch.softmax((q[h].double() @ k[h].double().T).float().double() * scale, dim=1)
+        for i in range(n):
+            rows = slots[i][slots[i] >= 0]
+            cols = slots[keep[h * n + i]].reshape(-1)
+            cols = cols[cols >= 0]
+            p = torch.softmax(s[rows][:, cols], dim=1)
+            ref = p @ v[h][cols].double()
+            got = out[h][rows].double()
+            assert torch.equal(torch.isfinite(got), torch.isfinite(ref.float())), (h, i)
+            ok = torch.isfinite(ref.float())
+            # a sum of up to 384 products, each with a weight off by the error of its logit, itself a sum of d: below
+            # (384 + 2 * 8 * d) * 2^-24 of the sum of |p v| for logits up to 8, and half a subnormal for each
+            bound = 2.0 ** -24 * (384 + 16 * d) * (p @ v[h][cols].double().abs()) + 384 * 2.0 ** -150
+            assert ((got - ref).abs() <= bound)[ok].all(), (h, i)
+            block = torch.stack([full[rows][:, t[t >= 0]].nan_to_num(-1.0).amax() for t in slots])
+            if torch.isfinite(full[rows]).all():
+                assert ((heat[h, i] - block).abs() <= 2e-5 * block + 1e-30).all(), (h, i)
+
+
+def _tile_tokens(shape, grid):
+    """Token of every slot of every tile, -1 for padding: [tiles, 64]."""
+    ax = [torch.where(torch.arange(-(-n // e) * e) < n, torch.arange(-(-n // e) * e), -10 ** 6).view(-1, e) for e, n in zip(shape, grid)]
+    t = (ax[0][:, None, None, :, None, None] * grid[1] + ax[1][None, :, None, None, :, None]) * grid[2] + ax[2][None, None, :, None, None, :]
+    return t.clamp(min=-1).reshape(-1, shape[0] * shape[1] * shape[2])
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("walk", [0, 1])
+def test_fp32_products_by_list_length(d, walk):
+    """Lists on both sides of the length at which the split products end, in one call: the rows of short lists have the
+    bits of VEDA_PRODUCTS_SPLIT, those of pairs with a longer one the bits of VEDA_PRODUCTS_FP32, and all lie within the fp32
+    bar of the formulas."""
+    grid, heads, n = (4, 4, 4 * 231), 1, 231
+    wl = wlm.custom_workload("lengths", heads, d, "f32", grid, False, (50, 100), seed=53)
+    dev = torch.device("cuda:0")
+    q, k, v = wlm.make_qkv(wl, dev)
+    plan = veda.Plan(1, heads, d, grid, np.asarray([(4, 4, 4)], np.int32), torch.float32)
+    plan.set_option(veda.VEDA_OPT_ATTN_LIST_WALK, walk)
+    qt, vm, _ = veda.veda_tile_layout(plan, q)
+    kt, _, _ = veda.veda_tile_layout(plan, k, want_mask=False)
+    vt, _, _ = veda.veda_tile_layout(plan, v, veda.VEDA_CHANNEL_MAJOR, want_mask=False)
+    g = torch.Generator().manual_seed(5)
+    lengths = [(1, 2, 63, 64, 129, 191, 192, 193, 194, 230, 231)[i % 11] for i in range(n)]
+    lists = [torch.randperm(n, generator=g)[:m].sort()[0] for m in lengths]
+    rp = torch.tensor([0] + list(np.cumsum(lengths)), dtype=torch.int32, device=dev)
+    ci = torch.cat(lists).to(torch.int32).to(dev)
+    outs = {}
+    for option in (0, veda.VEDA_PRODUCTS_FP32, veda.VEDA_PRODUCTS_SPLIT):
+        plan.set_option(veda.VEDA_OPT_FP32_PRODUCTS, option)
+        outs[option], _ = veda.veda_sparse_attn_fwd(plan, qt, kt, vt, vm, rp, ci, 1.0 / math.sqrt(d))
+        outs[option] = outs[option][0, 0].cpu()
+    with pytest.raises(veda.VedaError):
+        plan.set_option(veda.VEDA_OPT_FP32_PRODUCTS, 3)
+    slots = _tile_tokens((4, 4, 4), grid)
+    s = (q[0, 0].double() @ k[0, 0].double().T).cpu() / math.sqrt(d)
+    assert not torch.equal(outs[1], outs[2])
+    for i in range(n):
+        pair = [j for j in (i, i ^ 1) if j < n]   # tiles of a row of tiles pair up along it
+        want = 1 if max(lengths[j] for j in pair) > 192 else 2
+        assert torch.equal(outs[0][slots[i]], outs[want][slots[i]]), (i, lengths[i])
+        cols = slots[lists[i]].reshape(-1)
+        ref = torch.softmax(s[slots[i]][:, cols], dim=1) @ v[0, 0].cpu()[cols].double()
+        for option in (1, 2):
+            assert (outs[option][slots[i]].double() - ref).abs().max() <= 1e-4
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_row_sums_have_no_place_for_padded_slots(dtype):
     """A mask that calls padded slots real: their rows have no token, so no sums are kept for them (what lies around
