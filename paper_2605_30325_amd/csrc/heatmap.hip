@@ -25,8 +25,8 @@
 // per wave, four tiles per workgroup (half the operand reads and loads: 8.3 and 11.7 ms, fp32 3.9), a ring of
 // three or four K tiles (0.5 ms slower: it costs a resident workgroup and the loads are not what is waited for).
 // With scratch, whole calls of the supervision side (gathers, heat map, both top-k, recall), two walks and one: 12 heads
-// of 624 tiles 8.0 -> 5.0 ms, one in 16 tiles of 40 heads of 21x45x80 13.4 -> 8.8 ms.  Pass 1 then stands at 79 % vector
-// issue (85 instructions per 8 products; 48 of them are the exponentials' three, 8 the maximum) and 45 % matrix pipe; of that, masks
+// of 624 tiles 8.0 -> 5.0 ms, one in 16 tiles of 40 heads of 21x45x80 13.4 -> 8.8 ms.  While a compute unit is busy pass 1 then stands at 79 % vector
+// issue (85 instructions per 8 products; 48 of them are the exponentials' three, 8 the maximum) and 45 % matrix pipe; of the gain, masks
 // on the scalar unit, operand addresses formed once per step and no register copies at the ends of branches gave a fifth,
 // handing work items out as asked for 12 % of the second case.
 // Padding: a tile's real rows come first (a wave runs only the blocks that hold any), and key tiles with few

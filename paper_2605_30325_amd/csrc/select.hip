@@ -59,6 +59,12 @@ __global__ __launch_bounds__(256) void select_sampled_kernel(const HeadGeom* __r
         pivot = __uint_as_float((pk & 0x80000000u) ? (pk ^ 0x80000000u) : ~pk);   // inverse of score_key
         // A float comparison against -inf would miss NaN scores, which rank as -inf.
         ok = pivot > -INFINITY;
+        // More than fit are to be expected where the pivot's value fills the row (target rows nobody asked for): no pass
+        // to find that out.  40 heads of 1344 tiles, fifteen such rows in sixteen, 286 -> 156 us; none, 167 and 167.
+        int at_least = 0;
+#pragma unroll
+        for (int e = 0; e < kSample / 64; ++e) at_least += __popcll(__ballot(sk[e] >= pk));
+        ok = ok && (int64_t)at_least * n < (int64_t)kCandCap * kSample;
     }
     int m_cand = 0;
     if (ok) {

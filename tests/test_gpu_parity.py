@@ -595,6 +595,26 @@ def _lists_of(plan, stats_q, stats_k, pq, pk, sscale, kph):
     return (rp, ci), (rp2, ci2)
 
 
+@pytest.mark.parametrize("hw", [(32, 32), (41, 25), (53, 29)])
+def test_select_rows_whose_sample_is_one_value(hw):
+    """Rows of 1024 tiles and more whose sampled columns are all alike skip the candidates: all equal, lower or higher
+    in between, and the one value the lowest there is."""
+    nt = hw[0] * hw[1]
+    plan = veda.Plan(1, 1, 64, (1, 8 * hw[0], 8 * hw[1]), np.asarray([[1, 8, 8]], np.int32), torch.float32)
+    sampled = np.arange(256) * nt // 256
+    x = np.random.default_rng(nt).standard_normal((4, nt)).astype(np.float32)
+    x[0] = 0.25
+    x[1], x[2] = 0.25 - np.abs(x[1]), 0.25 + np.abs(x[2])
+    x[:3, sampled] = 0.25
+    x[3, sampled] = -np.inf
+    s = torch.as_tensor(x[np.arange(nt) % 4]).reshape(1, -1).cuda()
+    for k in (1, nt // 40, nt // 20):
+        _say(f"[parity] select of {nt} tiles, one value sampled, k {k}")
+        _, ci = veda.veda_tile_select(plan, s, [k])
+        torch.cuda.synchronize()
+        assert np.array_equal(ci.cpu().numpy().reshape(nt, k), vo.select(x, k)[np.arange(nt) % 4]), (nt, k)
+
+
 def test_score_select_in_one_call_long_rows():
     # rows of 1260 - 1840 tiles at a 5 % budget: every score is compared with its row's pivot as it
     # is formed and never written.  Lists must equal the two-stage route's (which the other tests
