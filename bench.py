@@ -35,7 +35,8 @@ PEAK_HBM_GBPS = 8000.0
 # copy kernel of known size.  A record is used only if it names the workload, tile size, keep
 # fraction and Q/K route of this run AND the hash of the attention kernel's sources as they are now;
 # otherwise traffic is null and traffic_source says why.
-KERNEL_SOURCES = ("attn_pair.hip", "attn_step.h", "attn_union.h", "attn_common.h", "attn.hip", "veda_internal.h", "geometry.h")
+KERNEL_SOURCES = ("attn_pair.hip", "attn_step.h", "attn_union.h", "attn_common.h", "direct_load.h", "attn.hip", "veda_internal.h",
+                  "geometry.h")
 
 
 def kernel_source_sha() -> str:
