@@ -10,6 +10,8 @@
 //              with 1/count rounded once on the host; max/min by plain comparisons.
 //   phi      : per output, one fmaf chain over ascending input index started from the bias.
 //   score    : per (i,j), one fmaf chain over ascending latent index from +0, then * scale.
+#include <type_traits>
+
 #include "direct_load.h"
 #include "score_common.h"
 
@@ -433,6 +435,8 @@ constexpr int kSPitch = 36;   // LDS pitch of one staged latent row (floats): ro
 // the fmaf chain).  Wave w holds rows 32w..32w+31 x all 128 columns in four 32x32 accumulators:
 // register r of lane (col = lane%32, kh = lane/32) is row (r%4) + 8(r/4) + 4kh, column 32cb + col.
 // Latent rows are staged row-major in LDS, 32 coordinates at a time.
+// Rows and columns past the head's last tile are not multiplied, 32 at a time: a short row's time is that of its own
+// products.  Loading the second 32 coordinates behind the first's products spills (20 -> 24..40 us for 12 heads of 624 tiles).
 __device__ __forceinline__ void score_block_128(const HeadGeom& hg, int bi, int bj, int64_t b, float* qs, float* ks,
                                                 const float* __restrict__ yq, const float* __restrict__ yk,
                                                 float* __restrict__ scores, int dp, float scale,
@@ -446,38 +450,52 @@ __device__ __forceinline__ void score_block_128(const HeadGeom& hg, int bi, int 
     for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[cb][r] = 0.0f;
-    for (int c0 = 0; c0 < dp; c0 += kSC) {
-        const int cn = dp - c0 < kSC ? dp - c0 : kSC;   // multiple of 4
-        __syncthreads();
-        for (int t = threadIdx.x; t < kSB * (kSC / 4); t += 256) {
-            const int r = t / (kSC / 4), c4 = (t % (kSC / 4)) * 4;
-            float4 qv = make_float4(0.f, 0.f, 0.f, 0.f), kv = qv;
-            if (c4 < cn) {
-                if (bi * kSB + r < nT) qv = *reinterpret_cast<const float4*>(qbase + (int64_t)(bi * kSB + r) * dp + c0 + c4);
-                if (bj * kSB + r < nT) kv = *reinterpret_cast<const float4*>(kbase + (int64_t)(bj * kSB + r) * dp + c0 + c4);
+    constexpr int kPer = kSB * (kSC / 4) / 256;   // float4s of each side per thread and stage
+    float4 qv[kPer], kv[kPer];
+    auto fetch = [&](int c0) {
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int t = threadIdx.x + 256 * u, r = t / (kSC / 4), c4 = (t % (kSC / 4)) * 4;
+            qv[u] = kv[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (c0 + c4 < dp) {   // dp is a multiple of 4
+                if (bi * kSB + r < nT) qv[u] = *reinterpret_cast<const float4*>(qbase + (int64_t)(bi * kSB + r) * dp + c0 + c4);
+                if (bj * kSB + r < nT) kv[u] = *reinterpret_cast<const float4*>(kbase + (int64_t)(bj * kSB + r) * dp + c0 + c4);
             }
-            *reinterpret_cast<float4*>(qs + r * kSPitch + c4) = qv;
-            *reinterpret_cast<float4*>(ks + r * kSPitch + c4) = kv;
         }
-        __syncthreads();
-        const float* qa = qs + (32 * wave + col) * kSPitch + kh;   // A: q[row = col][c + kh]
-        const float* kb = ks + col * kSPitch + kh;                  // B: k[column = col][c + kh]
+    };
+    const float* qa = qs + (32 * wave + col) * kSPitch + kh;   // A: q[row = col][c + kh]
+    const float* kb = ks + col * kSPitch + kh;                  // B: k[column = col][c + kh]
+    auto products = [&](auto blocks, int cn) {
+        auto step = [&](int c) {
+            const float a = qa[c];
+#pragma unroll
+            for (int cb = 0; cb < decltype(blocks)::value; ++cb)
+                acc[cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, kb[32 * cb * kSPitch + c], acc[cb], 0, 0, 0);
+        };
         if (cn == kSC) {
 #pragma unroll
-            for (int c = 0; c < kSC; c += 2) {
-                const float a = qa[c];
-#pragma unroll
-                for (int cb = 0; cb < 4; ++cb)
-                    acc[cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, kb[32 * cb * kSPitch + c], acc[cb], 0, 0, 0);
-            }
+            for (int c = 0; c < kSC; c += 2) step(c);
         } else {
-            for (int c = 0; c < cn; c += 2) {
-                const float a = qa[c];
-#pragma unroll
-                for (int cb = 0; cb < 4; ++cb)
-                    acc[cb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, kb[32 * cb * kSPitch + c], acc[cb], 0, 0, 0);
-            }
+            for (int c = 0; c < cn; c += 2) step(c);
         }
+    };
+    const int first_row = __builtin_amdgcn_readfirstlane(bi * kSB + 32 * wave);
+    const int col_blocks = first_row < nT ? (nT - bj * kSB + 31) / 32 : 0;   // that hold any column
+    for (int c0 = 0; c0 < dp; c0 += kSC) {
+        const int cn = dp - c0 < kSC ? dp - c0 : kSC;
+        fetch(c0);
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int t = threadIdx.x + 256 * u, r = t / (kSC / 4), c4 = (t % (kSC / 4)) * 4;
+            *reinterpret_cast<float4*>(qs + r * kSPitch + c4) = qv[u];
+            *reinterpret_cast<float4*>(ks + r * kSPitch + c4) = kv[u];
+        }
+        __syncthreads();
+        if (col_blocks >= 4) products(std::integral_constant<int, 4>(), cn);
+        else if (col_blocks == 3) products(std::integral_constant<int, 3>(), cn);
+        else if (col_blocks == 2) products(std::integral_constant<int, 2>(), cn);
+        else if (col_blocks == 1) products(std::integral_constant<int, 1>(), cn);
     }
     float* sbase = scores + b * score_elems + hg.score_off;
 #pragma unroll
@@ -493,18 +511,20 @@ __device__ __forceinline__ void score_block_128(const HeadGeom& hg, int bi, int 
 }
 
 // All score blocks, one workgroup each.
+// The head is counted with one load per 64 heads; a search was six, each waiting for the one before.  With that and the blocks
+// left out: 2 heads of 4 tiles 5.0 -> 3.9 us, 4 of 75 (2 samples) 7.7 -> 6.9, 12 of 624 20.7 -> 19.3, 40 of 624 51.5 -> 47.0.
 __global__ __launch_bounds__(256, 3) void score_kernel(const HeadGeom* __restrict__ heads, int n_heads,
                                                     const float* __restrict__ yq, const float* __restrict__ yk,
                                                     float* __restrict__ scores, int dp, float scale,
                                                     int64_t total_tiles, int64_t score_elems) {
     __shared__ __align__(16) float qs[kSB * kSPitch];
     __shared__ __align__(16) float ks[kSB * kSPitch];
-    int lo = 0, hi = n_heads - 1;   // last head whose first block is <= blockIdx.x
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if ((int)blockIdx.x >= heads[mid].score_blk_off) lo = mid; else hi = mid - 1;
+    int head = -1;   // the last head whose first block is <= blockIdx.x
+    for (int h0 = 0; h0 < n_heads; h0 += 64) {
+        const int h = h0 + (threadIdx.x & 63);
+        head += __popcll(__ballot(h < n_heads && (int)blockIdx.x >= heads[h < n_heads ? h : 0].score_blk_off));
     }
-    const HeadGeom hg = heads[lo];
+    const HeadGeom hg = heads[head];
     const int blk = blockIdx.x - hg.score_blk_off;
     const int bi = blk / hg.score_blk_dim, bj = blk - bi * hg.score_blk_dim;
     score_block_128(hg, bi, bj, blockIdx.y, qs, ks, yq, yk, scores, dp, scale, total_tiles, score_elems);

@@ -210,6 +210,26 @@ def test_usual_estimator_sizes_bit_exact(d, tiles):
                 assert np.array_equal(got.view(np.uint32), ref.view(np.uint32)), (relu, b, h)
 
 
+@pytest.mark.parametrize("heads", [1, 63, 64, 65])
+def test_scores_of_many_heads_on_either_unit(heads):
+    """A score block finds its head among 64 at a time; heads of 160, 224 and 140 tiles, whose last blocks hold one or three
+    times 32 columns, whole and not; the scores on the matrix cores are those on the vector units."""
+    grid, dev = (5, 28, 64), torch.device("cuda:0")
+    shapes = np.asarray([[[1, 8, 8], [4, 4, 4], [1, 1, 64]][h % 3] for h in range(heads)], np.int32)
+    plan = veda.Plan(1, heads, 64, grid, shapes, torch.float32)
+    gen = torch.Generator(device=dev).manual_seed(heads)
+    z = torch.randn(plan.total_tiles, 192, device=dev, generator=gen)
+    rng = np.random.default_rng(heads)
+    phi = veda.Mlp(*[rng.uniform(-0.2, 0.2, x).astype(np.float32) for x in ((heads, 192, 64), (heads, 64), (heads, 64, 36), (heads, 36))],
+                   True, dev)
+    got = []
+    for unit in (veda.VEDA_CHAINS_MATRIX, veda.VEDA_CHAINS_VECTOR):
+        plan.set_option(veda.VEDA_OPT_FP32_CHAIN_UNIT, unit)
+        got.append(veda.veda_tile_score_stats(plan, z, z, phi, phi, 0.5)[0].view(torch.int32))
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], got[1])
+
+
 def test_projection_and_score_chains_in_the_denormal_range():
     """Weights of magnitude 2^-136 (denormal themselves): every product and partial sum of the projection
     chains is a denormal number, and so are the latents; the scores underflow.  Nothing may be flushed to
