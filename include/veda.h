@@ -122,7 +122,9 @@ void veda_plan_destroy(veda_plan* plan); /* NULL is allowed */
  * stage 4: products on the fp32 matrix cores, or as six products of exact three-part bf16 splits, which is about
  * twice as fast and nearer to the exact result (2-norm of the error three quarters).  By default query tiles with
  * up to 192 kept key tiles take the split products; beyond that the fp32 ones, whose rounding grows with the root of the list,
- * so that outputs stay within 4e-5 of their root mean square of what those give. */
+ * so that outputs stay within 4e-5 of their root mean square of what those give.  Whatever the option, work items (two query tiles) with
+ * a result that is not finite, or too small for its parts (|q * scale| or |logit| of 2^48, sums of p * v outside 2^-48 .. 2^32), are formed
+ * again on the fp32 matrix cores. */
 typedef enum { VEDA_OPT_EXACT_LOGIT_SCALE = 0, VEDA_OPT_ATTN_LIST_WALK = 1, VEDA_OPT_FP32_CHAIN_UNIT = 2,
                VEDA_OPT_FP32_PRODUCTS = 3 } veda_option;
 enum { VEDA_PRODUCTS_FP32 = 1, VEDA_PRODUCTS_SPLIT = 2 };

@@ -19,8 +19,8 @@
 // loads one phase earlier, priorities: 1-2 %.
 //
 // Long lists (AttnArgs::split_tiles) take v_mfma_f32_32x32x2_f32 instead, and numbers that are not finite come out of the
-// split products as NaN: a workgroup that finds any in its results walks again that way.  There a lane owns one query (lane % 32) and one of the two terms of every instruction
-// (h = lane / 32).  The pairing of the reduction index with h is free as long as both operands agree, and it is
+// split products as NaN: a workgroup that finds any in its results, or one too small for its parts (kF32Small), walks again
+// that way.  There a lane owns one query (lane % 32) and one of the two terms of every instruction (h = lane / 32).  The pairing of the reduction index with h is free as long as both operands agree, and it is
 // chosen so that one 16-byte LDS read feeds four instructions:
 //   S^T, step (m, t):  h supplies channel 8m + 4h + t   (K row: float4 at channel 8m + 4h),
 //   O^T, step (c, j, t): h supplies key 32c + 8j + 4h + t, which is exactly register 4j + t of the
@@ -36,6 +36,12 @@ namespace veda {
 
 constexpr int kF32Chunk = 128;   // step-table entries filled at a time
 constexpr float kF32Slack = 8.0f;   // log2 units a row maximum may outgrow the softmax reference
+
+// The split walk multiplies Q by 2^80 and V by 2^96, so that their parts hold every fp32 number (bf16 ends at 2^-133);
+// what outgrows the range that leaves, |q| and |logit| of 2^48 and sums of 2^32, comes out not finite and walks again.
+// Parts of K below 2^-133 move a logit by 2^-79 at most.  Those of a probability below 2^-102 are the rest: next to an
+// output of 2^48 or more in this scale they are below 2^-25 of it for lists of a million keys; a smaller one that is not zero walks again.
+constexpr float kF32QScale = 0x1p80f, kF32VScale = 0x1p96f, kF32Small = 0x1p48f;
 
 // kTable: the steps come from the table in LDS (attn_union.h), as in the bf16 kernel; otherwise the two
 // lists are merged inside the loop (heads above 16384 tiles, VEDA_OPT_ATTN_LIST_WALK).
@@ -171,7 +177,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
         K ks;
         ks.init(smem_base, smem_base + kRaw, wave, lane);
         bf16x8 q[3][G];
-        split_row<D>(qrow, h, a.scale_log2, q);
+        split_row<D>(qrow, h, a.scale_log2 * kF32QScale, q);
         struct Sub { int j, fl, c; uint32_t mask, hi, from; };   // 32 keys of a step: c-th half of key tile j, or a half step
         // K and V^T take turns in the landing area.  Past the end the loads go on, from key tile 0.
         auto load_k = [&](const Sub& e, int j) __attribute__((always_inline)) { ks.load(j, kt + (int64_t)e.j * kKBytes, e.from); };
@@ -183,7 +189,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
         };
         const int v_row = (D / 4) * wave + (lane >> 3), v_c = lane & 7;
         const uint32_t vw = smem_base + kV + v_row * 64 + (((v_c >> 1) ^ ((v_row >> 2) & 3)) << 4) + (v_c & 1) * 8;
-        auto convert_v = [&](int j) __attribute__((always_inline)) { ks.put(j, (vw ^ (uint32_t)((j & 1) << 5)) + (uint32_t)(j * 8 * 64)); };
+        auto convert_v = [&](int j) __attribute__((always_inline)) { ks.put(j, (vw ^ (uint32_t)((j & 1) << 5)) + (uint32_t)(j * 8 * 64), kF32VScale); };
         const uint32_t vr = smem_base + kV + idx * 64 + ((h ^ ((idx >> 2) & 3)) << 4);
         auto of_step = [&](Sub& n) __attribute__((always_inline)) {
             Step e;
@@ -193,7 +199,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
             n.hi = (uint32_t)(e.vm >> 32);
             n.from = e.fl & kStepHalf ? n.hi : 0x03020100u;
         };
-        float thr = -INFINITY, ref = 0.0f;   // a row maximum above thr moves the reference
+        float thr = -INFINITY, ref = 0.0f;   // a row maximum above thr (in the products' scale) moves the reference
         begin_rows();
         begin_walk();
         Sub cur, nx;
@@ -260,11 +266,11 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
                 for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
                 if (__any(mx > thr)) {
                     asm volatile("" ::: "memory");
-                    m_run = fmaxf(m_run, max_with_other_half(mx));
+                    m_run = fmaxf(m_run, max_with_other_half(mx) * (1.0f / kF32QScale));
                     const float use = m_run == -INFINITY ? 0.0f : m_run;
                     const float alpha = thr == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(ref - use);
                     ref = use;
-                    thr = m_run + kF32Slack;
+                    thr = (m_run + kF32Slack) * kF32QScale;
                     l_run *= alpha;
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb)
@@ -274,7 +280,8 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
                 float psum = 0.0f;
                 uint32_t pw[2][3][4];
                 auto prob = [&](int kk, int e) __attribute__((always_inline)) {   // registers 8*kk + 2e, +1
-                    const float p0 = __builtin_amdgcn_exp2f(s[8 * kk + 2 * e] - ref), p1 = __builtin_amdgcn_exp2f(s[8 * kk + 2 * e + 1] - ref);
+                    const float p0 = __builtin_amdgcn_exp2f(fmaf(s[8 * kk + 2 * e], 1.0f / kF32QScale, -ref));
+                    const float p1 = __builtin_amdgcn_exp2f(fmaf(s[8 * kk + 2 * e + 1], 1.0f / kF32QScale, -ref));
                     psum += p0;
                     psum += p1;
                     uint32_t p[3];
@@ -334,7 +341,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
         __syncthreads();
     };
 
-    // The walk on fp32 matrix cores, where a number is not finite.
+    // The walk on fp32 matrix cores.
     auto exact_walk = [&]() __attribute__((always_inline)) {
         // Q operand: lane (query 32r + idx, half h) holds channels 8m + 4h + t, scaled by softmax_scale*log2(e).
         float qreg[D / 2];
@@ -503,28 +510,35 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
 
     };
 
-    if ((nA > nB ? nA : nB) > a.split_tiles) {
-        exact_walk();
-    } else {
+    bool chains = (nA > nB ? nA : nB) > a.split_tiles;
+    float unscale = 1.0f;
+    if (!chains) {
         split_walk();
         float bad = l_run * 0.0f;   // NaN if anything is not finite
+        uint32_t least = ~0u;       // 2 |o| - 1 in bits: zeros are the largest
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) bad = fmaf(o[nb][i], 0.0f, bad);
+            for (int i = 0; i < 16; ++i) {
+                bad = fmaf(o[nb][i], 0.0f, bad);
+                least = min(least, (__float_as_uint(o[nb][i]) << 1) - 1u);
+            }
         uint32_t* flag = reinterpret_cast<uint32_t*>(smem);   // the planes are done with
-        const bool any_bad = __any(bad != 0.0f);
+        const bool any_bad = __any(bad != 0.0f || least < (__float_as_uint(kF32Small) << 1) - 1u);
         if (lane == 0) flag[wave] = any_bad ? 1u : 0u;
         __syncthreads();
-        if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)(flag[0] | flag[1] | flag[2] | flag[3])), 0)) {
-            __syncthreads();
-            exact_walk();
-        }
+        chains = __builtin_amdgcn_readfirstlane((int)(flag[0] | flag[1] | flag[2] | flag[3])) != 0;
+        unscale = 1.0f / kF32VScale;
+        __syncthreads();
+    }
+    if (chains) {
+        exact_walk();
+        unscale = 1.0f;
     }
 
     // Normalise, transpose through LDS ([2 tiles][64 rows][D] fp32) and scatter the real rows.
     const float l_all = l_run + __shfl_xor(l_run, 32);
-    const float inv = l_all > 0.0f ? 1.0f / l_all : 0.0f;
+    const float inv = l_all > 0.0f ? unscale / l_all : 0.0f;
     __syncthreads();   // nobody fills the step table any more
     float* obuf = reinterpret_cast<float*>(smem);
     float* lse_s = obuf + 2 * kTile * D;

@@ -2,7 +2,8 @@
 // score that moves in its last bits can change places with another in the top-k, and with it the kept lists.)
 //
 // A number is split into three bf16 numbers, each the rounding of what is left: 3 x 8 bits hold fp32's 24, so the sum
-// is exact (of what is finite; below 2^-109 up to half of bf16's smallest subnormal, 2^-133, is lost).  Of the nine products of two split operands the six largest
+// is exact of what is finite and not below 2^-109 (there up to 2^-134, half of bf16's smallest subnormal, is lost: the kernel
+// scales its operands away from it, see kF32QScale).  Of the nine products of two split operands the six largest
 // are formed, each by v_mfma_f32_32x32x16_bf16 with fp32 accumulation; the three left out are below 2^-26 of the
 // product, an eighth of its rounding to fp32.  Six such instructions take 192 cycles where v_mfma_f32_32x32x2_f32 takes
 // 512 for the same 16 terms, and they round the running sum 6 times where it rounds 16: dot products of 64 to 32768
@@ -101,20 +102,20 @@ template <int D> struct SplitK {
         else asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
         static_assert(kI == 4 || kI == 2, "the counts above");
     }
-    // Four numbers of the j-th load to their places in three planes at `to`.
-    __device__ __forceinline__ void put(int j, uint32_t to) const {
+    // Four numbers of the j-th load, times `scale`, to their places in three planes at `to`.
+    __device__ __forceinline__ void put(int j, uint32_t to, float scale) const {
         landed();
         const f32x4 x = lds_read_f32x4(raw_lane + 1024u * j);
         uint32_t p0[3], p1[3];
-        split2(x[0], x[1], p0);
-        split2(x[2], x[3], p1);
+        split2(x[0] * scale, x[1] * scale, p0);
+        split2(x[2] * scale, x[3] * scale, p1);
         typedef __attribute__((address_space(3))) u32x2* lds_u32x2_ptr;
 #pragma unroll
         for (int u = 0; u < 3; ++u) *(lds_u32x2_ptr)(uintptr_t)(to + u * kPlane) = u32x2{p0[u], p1[u]};
     }
     __device__ __forceinline__ void convert(int j, uint32_t planes = 0u) const {
         constexpr int kRows = 1024 / kRowB;   // rows of a load
-        put(j, planes + (kw ^ (uint32_t)((rho(j * kRows) & (kPc - 1)) << 4)) + (uint32_t)(j * kRows * D * 2));
+        put(j, planes + (kw ^ (uint32_t)((rho(j * kRows) & (kPc - 1)) << 4)) + (uint32_t)(j * kRows * D * 2), 1.0f);
     }
     static __device__ __forceinline__ bf16x8 frag(uint32_t at, int u) {
         typedef const __attribute__((address_space(3))) bf16x8* lds_bf16x8_ptr;

@@ -1425,6 +1425,46 @@ def _tile_tokens(shape, grid):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("qs,ks,vs,gap,same", [
+    (1.0, 1.0, 1e-34, False, True), (1.0, 1.0, 1e-35, False, True), (1.0, 1.0, 1e-37, False, True), (1.0, 1.0, 1e-41, False, True),
+    (1e-36, 1e36, 1.0, False, False), (1e-33, 1e33, 1.0, False, False), (1e36, 1e-36, 1.0, False, True), (1e10, 1e-10, 1.0, False, False),
+    (1.0, 1.0, 1.0, True, True), (1.0, 1.0, 1e12, True, True),
+    (1.0, 1.0, 1e-3, False, False), (1.0, 1.0, 1e3, False, False),
+])
+def test_fp32_splits_lose_nothing_of_small_numbers(d, qs, ks, vs, gap, same):
+    """Operands and probabilities with parts below what bf16 holds (2^-133), and ordinary ones beside them: the split products
+    are no further from 64 bits than the fp32 ones, and where they cannot say so the result is that of the fp32 ones."""
+    grid, n = (4, 4, 72), 18
+    wl = wlm.custom_workload("small_numbers", 1, d, "f32", grid, False, (50, 100), seed=61)
+    q, k, v = wlm.make_qkv(wl, torch.device("cuda:0"))
+    q *= qs
+    k *= ks
+    v *= vs
+    if gap:   # all weight on one key without a value, the others' weights around 2^-121
+        k *= 0.01
+        q[..., 0], k[..., 0] = math.sqrt(d), 0.0
+        k[0, 0, 7, 0], v[0, 0, 7] = 84.0, 0.0
+    plan = veda.Plan(1, 1, d, grid, np.asarray([(4, 4, 4)], np.int32), torch.float32)
+    qt, vm, _ = veda.veda_tile_layout(plan, q)
+    kt, _, _ = veda.veda_tile_layout(plan, k, want_mask=False)
+    vt, _, _ = veda.veda_tile_layout(plan, v, veda.VEDA_CHANNEL_MAJOR, want_mask=False)
+    rp = torch.arange(n + 1, dtype=torch.int32, device="cuda") * n
+    ci = torch.arange(n, dtype=torch.int32, device="cuda").repeat(n)
+    scale, outs = 1.0 / math.sqrt(d), {}
+    for form in (veda.VEDA_PRODUCTS_FP32, 0, veda.VEDA_PRODUCTS_SPLIT):
+        plan.set_option(veda.VEDA_OPT_FP32_PRODUCTS, form)
+        outs[form] = [t[0, 0].cpu() for t in veda.veda_sparse_attn_fwd(plan, qt, kt, vt, vm, rp, ci, scale, want_lse=True)]
+    s = (q[0, 0].double() @ k[0, 0].double().T).cpu() * scale
+    ref = torch.softmax(s, dim=1) @ v[0, 0].cpu().double()
+    err = {f: ((o.double() - ref).norm() / ref.norm()).item() for f, (o, _) in outs.items()}
+    _say(f"[parity] fp32 products d {d} q {qs} k {ks} v {vs} gap {gap}: from 64 bits {err}")
+    for form in (0, veda.VEDA_PRODUCTS_SPLIT):
+        assert err[form] <= err[veda.VEDA_PRODUCTS_FP32]
+        assert torch.equal(outs[form][0], outs[veda.VEDA_PRODUCTS_FP32][0]) == same
+        assert (outs[form][1].double() - torch.logsumexp(s, dim=1)).abs().max() <= 1e-5 * max(1.0, s.abs().max().item())
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("walk", [0, 1])
 def test_fp32_products_by_list_length(d, walk):
     """Lists on both sides of the length at which the split products end, in one call: the rows of short lists have the
