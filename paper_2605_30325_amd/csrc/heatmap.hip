@@ -198,6 +198,7 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : 3) void tile_heatmap_kern
     const int idx = lane & 31, hh = lane >> 5;
     const int which = wave >> 1, r = wave & 1;   // this wave's tile and 32-row block
 
+    const uint32_t block = blockIdx.y * gridDim.x + blockIdx.x;
     // A work item is up to two query tiles of one head.
     auto run = [&](uint32_t work) __attribute__((always_inline)) {
     const int64_t b = work / a.items;
@@ -381,7 +382,7 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : 3) void tile_heatmap_kern
         l_part += sum;
     };
     // One walk: the largest raw logits of this wave's rows, [key tile][32 rows], nothing for tiles without a real key.
-    float* const kept = kOneWalk ? a.maxima + ((int64_t)blockIdx.x * 4 + wave) * a.max_tiles * 32 : nullptr;
+    float* const kept = kOneWalk ? a.maxima + ((int64_t)block * 4 + wave) * a.max_tiles * 32 : nullptr;
     if (!kOneWalk && a.have_rows) {
         // nothing to do
     } else if (walk_begin(); active) {
@@ -561,9 +562,9 @@ __global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : 3) void tile_heatmap_kern
     // With more items than places in the scratch a workgroup goes on with the next one of its die.  Handed out as they
     // are asked for: a fixed share each left a quarter of the chip idle at the end where tiles differ (one in 16 of 40
     // heads of 21x45x80, mixed shapes).
-    const uint32_t die = blockIdx.x % kXcd;
+    const uint32_t die = block % kXcd;
     uint32_t* const next = reinterpret_cast<uint32_t*>(part + 4);
-    for (uint32_t work = blockIdx.x;;) {
+    for (uint32_t work = block;;) {
         run(work);
         if (!kOneWalk || a.taken == nullptr) return;
         if (tid == 0) *next = (gridDim.x / kXcd + atomicAdd(a.taken + die * kHeatTakenStride, 1u)) * kXcd + die;
@@ -745,7 +746,9 @@ static veda_status target_heatmap(const veda_plan* pl, const void* q_tiled, cons
             hipLaunchKernelGGL(heat_taken_clear_kernel, dim3(1), dim3(kXcd), 0, s, a.taken);
         }
     }
+    // a dimension holds fewer than 2^32 threads: samples of many padding workgroups go along the second
     dim3 grid((unsigned)blocks), block(256);
+    if (blocks >= (int64_t)1 << 24) grid = dim3((unsigned)items, (unsigned)pl->prob.batch);
     const size_t smem = (size_t)2 * kTile * d * pl->elem_size() + 4 * 64 * sizeof(float) + 16;
     auto launch = [&](auto kern) {
         if (smem > 64 * 1024)

@@ -409,7 +409,8 @@ extern "C" veda_status veda_tile_layout_path(const veda_plan* pl, const void* q,
     // Where the descriptors' part needs many registers (tiled copies, 128-token tiles), V's part keeps fewer waves in flight
     // than in a kernel of its own, which shows once memory is what bounds them: 40 heads of 21x45x80 with 128-token tiles 683 us in one
     // launch, 637 in three; 8 fp32 heads of 624 tiles (7,500 workgroups) 196 and 193.
-    if ((pl->inner || q_tiled) && (int64_t)grid.x * grid.y > 4096) {
+    // (And a grid's dimension holds fewer than 2^32 threads.)
+    if (((pl->inner || q_tiled) && (int64_t)grid.x * grid.y > 4096) || grid.x >= 1u << 24) {
         veda_status r = veda_tile_layout_stats(pl, q, sq, q_tiled, valid_mask, valid_cnt, stats_q, stream);
         if (r == VEDA_OK) r = veda_tile_layout_stats(pl, k, sk, k_tiled, nullptr, nullptr, stats_k, stream);
         return r == VEDA_OK ? veda_tile_layout(pl, v, sv, VEDA_CHANNEL_MAJOR, v_tiled, nullptr, nullptr, stream) : r;

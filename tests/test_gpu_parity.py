@@ -1417,6 +1417,27 @@ def test_fp32_kernels_on_numbers_a_split_does_not_hold(d, where, value):
                 assert ((heat[h, i] - block).abs() <= 2e-5 * block + 1e-30).all(), (h, i)
 
 
+def test_heatmap_of_many_small_samples():
+    """128 heads of one tile: eight workgroups for each (every head's pair falls to the first die), so that 16384 samples are
+    2^24 of them, more than a grid's first dimension takes."""
+    heads, batch, dev = 128, 16384, torch.device("cuda:0")
+    plan = veda.Plan(batch, heads, 64, (4, 4, 4), np.asarray([(4, 4, 4)] * heads, np.int32), torch.bfloat16)
+    x = torch.zeros((batch, heads, 64 * 64), dtype=torch.bfloat16, device=dev)
+    for b in (0, 1, batch // 2, batch - 1):
+        x[b] = torch.randn((heads, 64 * 64), device=dev, generator=torch.Generator(device=dev).manual_seed(b)).bfloat16()
+    vm = torch.full((heads,), -1, dtype=torch.int64, device=dev)
+    heat = torch.full((batch, heads), -7.0, device=dev)
+    stream = torch.cuda.current_stream().cuda_stream
+    assert veda.load().veda_tile_heatmap(plan.handle, x.data_ptr(), x.data_ptr(), vm.data_ptr(), 0.125, None, 0, heat.data_ptr(),
+                                         stream) == veda.VEDA_OK
+    assert torch.equal(heat, veda.veda_tile_heatmap(plan, x, x, vm, 0.125))
+    assert bool((heat[2] == 1.0 / 64).all())
+    for b in (0, 1, batch // 2, batch - 1):
+        t = x[b].view(heads, 64, 64).float()
+        ref = torch.softmax(torch.bmm(t, t.transpose(1, 2).contiguous()) * 0.125, dim=2).amax(dim=(1, 2))
+        assert ((heat[b] - ref).abs() <= 1e-5 * ref).all()
+
+
 def _tile_tokens(shape, grid):
     """Token of every slot of every tile, -1 for padding: [tiles, 64]."""
     ax = [torch.where(torch.arange(-(-n // e) * e) < n, torch.arange(-(-n // e) * e), -10 ** 6).view(-1, e) for e, n in zip(shape, grid)]
