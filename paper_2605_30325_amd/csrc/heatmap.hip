@@ -172,12 +172,21 @@ __device__ inline bool listed_pair(const HeatArgs& a, int item, char* smem, int 
     return any;
 }
 
+// Workgroups on a compute unit: two K tiles of fp32 at d = 128 are 65 KB of LDS, elsewhere the registers decide.  One walk
+// keeps a place for each (three where two fit: 8.12 instead of 8.10 ms for 12 heads of 288 tiles, a third of them listed 3.68 instead
+// of 3.56; bf16 at d = 64, five where four fit: 12 heads of 624, a third listed, 1.23 instead of 1.18 ms).
+// fp32 at d = 64: a fourth fits where all tiles are asked for, and is slower (12 heads of 624 tiles 17.6 -> 18.2 ms).
+constexpr int heat_resident(bool bf16, int d, bool grouped, bool listed) {
+    if (!bf16) return d == 128 ? 2 : 3;
+    return d == 128 || (listed && !grouped) ? 4 : 5;
+}
+
 // kGrouped: 128-token tiles.  The geometry in `a` is that of the 64-slot halves; a whole tile is a
 // workgroup and two consecutive key steps, and its block maximum the maximum over them.
 // kOneWalk: the logits are formed once.  Pass 1 keeps the largest raw logit of every row and key tile in scratch, one
 // place per workgroup and written over for its next work item; pass 2 reads those instead of forming the products again.
 template <typename E, int D, bool kGrouped, bool kListed, bool kOneWalk>
-__global__ __launch_bounds__(256, sizeof(E) == 2 ? 4 : 3) void tile_heatmap_kernel(HeatArgs a) {
+__global__ __launch_bounds__(256, heat_resident(sizeof(E) == 2, D, kGrouped, kListed)) void tile_heatmap_kernel(HeatArgs a) {
     typedef HeatFrag<E> F;
     typedef typename F::type frag;
     typedef const __attribute__((address_space(3))) frag* lds_frag_ptr;
@@ -673,10 +682,9 @@ __global__ void recall_finish_kernel(const HeadGeom* __restrict__ heads, RecallA
 
 namespace veda {
 
-// One walk: the workgroups of a launch, each with a place in the scratch.  As many as are resident at once, which their
-// registers decide; a multiple of the dies.
-static int64_t heat_places(const veda_plan* pl) {
-    return 256 * (pl->prob.dtype == VEDA_BF16 ? (pl->prob.head_dim == 128 ? 4 : 5) : 3);
+// One walk: the workgroups of a launch, each with a place in the scratch: as many as are resident at once.
+static int64_t heat_places(const veda_plan* pl, bool listed) {
+    return 256 * heat_resident(pl->prob.dtype == VEDA_BF16, pl->prob.head_dim, pl->inner != nullptr, listed);
 }
 constexpr size_t kHeatTakenBytes = kXcd * kHeatTakenStride * sizeof(uint32_t);   // at the start of the scratch
 
@@ -736,7 +744,7 @@ static veda_status target_heatmap(const veda_plan* pl, const void* q_tiled, cons
     if (blocks > 0x7fffffff) return VEDA_ERR_UNSUPPORTED;
     if (workspace) {
         if (reinterpret_cast<uintptr_t>(workspace) & 15u) return VEDA_ERR_UNSUPPORTED;
-        const int64_t places = heat_places(pl);
+        const int64_t places = heat_places(pl, query_tiles != nullptr);
         const bool share = blocks > places;
         blocks = share ? places : blocks;
         if (workspace_bytes < kHeatTakenBytes + (size_t)(blocks * a.max_tiles) * 128 * sizeof(float)) return VEDA_ERR_WORKSPACE;
@@ -770,7 +778,7 @@ static veda_status target_heatmap(const veda_plan* pl, const void* q_tiled, cons
 extern "C" size_t veda_plan_heatmap_workspace_bytes(const veda_plan* pl, int64_t n_query_tiles) {
     using namespace veda;
     if (!pl || n_query_tiles < 0 || n_query_tiles > pl->total_tiles) return 0;
-    const int64_t blocks = heat_items(pl, n_query_tiles) * pl->prob.batch, places = heat_places(pl);
+    const int64_t blocks = heat_items(pl, n_query_tiles) * pl->prob.batch, places = heat_places(pl, n_query_tiles > 0);
     return kHeatTakenBytes + (size_t)((blocks < places ? blocks : places) * heat_max_tiles(pl)) * 128 * sizeof(float);
 }
 

@@ -1417,6 +1417,20 @@ def test_fp32_kernels_on_numbers_a_split_does_not_hold(d, where, value):
                 assert ((heat[h, i] - block).abs() <= 2e-5 * block + 1e-30).all(), (h, i)
 
 
+@pytest.mark.parametrize("dtype,d,tile_tokens,all_tiles,listed", [
+    ("bf16", 128, 64, 4, 4), ("bf16", 128, 128, 4, 4), ("bf16", 64, 64, 5, 4), ("bf16", 64, 128, 5, 5), ("f32", 128, 64, 2, 2), ("f32", 64, 64, 3, 3)])
+def test_heatmap_scratch_is_that_of_the_resident_workgroups(dtype, d, tile_tokens, all_tiles, listed):
+    """Workgroups on a compute unit as hipOccupancyMaxActiveBlocksPerMultiprocessor gives them (fp32, d = 64: one fewer), 256
+    compute units."""
+    shape = (4, 4, tile_tokens // 16)
+    plan = veda.Plan(3, 40, d, (20, 20, 400), np.asarray([shape] * 40, np.int32), torch.bfloat16 if dtype == "bf16" else torch.float32, tile_tokens=tile_tokens)
+    halves = plan.tiles[0] * tile_tokens // 64
+    need = veda.load().veda_plan_heatmap_workspace_bytes
+    assert need(plan.handle, 0) == 512 + 512 * halves * 256 * all_tiles
+    assert need(plan.handle, plan.total_tiles) == 512 + 512 * halves * 256 * listed
+    assert need(plan.handle, 16) <= 512 + 512 * halves * 64
+
+
 def test_heatmap_of_many_small_samples():
     """128 heads of one tile: eight workgroups for each (every head's pair falls to the first die), so that 16384 samples are
     2^24 of them, more than a grid's first dimension takes."""
