@@ -340,8 +340,8 @@ veda_status veda_tile_heatmap_rows(const veda_plan*, const void* q_tiled, const 
  * block maxima are kept there, and the second pass over the key tiles falls away.
  * row_sums  optional: written as by veda_tile_heatmap_rows with have_row_sums = 0.
  * workspace device, 16-byte aligned, at least veda_plan_heatmap_workspace_bytes(), which grows with the tiles of the largest
- *           head (128 floats per key tile for each workgroup that can be resident, up to 1280, and 512 bytes); contents
- *           undefined after. */
+ *           head (128 floats per key tile for each workgroup that can be resident, up to 1280, and 512 bytes; from 2 GiB on
+ *           for fewer workgroups, down to half of them); contents undefined after. */
 size_t veda_plan_heatmap_workspace_bytes(const veda_plan*, int64_t n_query_tiles);
 veda_status veda_tile_heatmap_ws(const veda_plan*, const void* q_tiled, const void* k_tiled, const uint64_t* valid_mask,
                                  float softmax_scale, const int32_t* query_tiles, int64_t n_query_tiles, float* row_sums,

@@ -682,10 +682,6 @@ __global__ void recall_finish_kernel(const HeadGeom* __restrict__ heads, RecallA
 
 namespace veda {
 
-// One walk: the workgroups of a launch, each with a place in the scratch: as many as are resident at once.
-static int64_t heat_places(const veda_plan* pl, bool listed) {
-    return 256 * heat_resident(pl->prob.dtype == VEDA_BF16, pl->prob.head_dim, pl->inner != nullptr, listed);
-}
 constexpr size_t kHeatTakenBytes = kXcd * kHeatTakenStride * sizeof(uint32_t);   // at the start of the scratch
 
 static int64_t heat_items(const veda_plan* pl, int64_t n_listed) {
@@ -698,6 +694,15 @@ static int64_t heat_max_tiles(const veda_plan* pl) {
     int64_t n = 0;
     for (const HeadGeom& g : ip->heads) n = g.n_tiles > n ? g.n_tiles : n;
     return n;
+}
+
+// One walk: the workgroups of a launch, each with a place in the scratch.  As many as are resident at once, fewer where their
+// scratch would pass 2 GiB, down to half (a head of 8192 tiles in bf16: 76.8 ms on 1024 places, 4.3 GB; 90.6 on 512; 132 in two walks
+// without scratch).
+static int64_t heat_places(const veda_plan* pl, bool listed) {
+    const int64_t all = 256 * heat_resident(pl->prob.dtype == VEDA_BF16, pl->prob.head_dim, pl->inner != nullptr, listed);
+    const int64_t fit = (((int64_t)2 << 30) - (int64_t)kHeatTakenBytes) / (heat_max_tiles(pl) * 128 * (int64_t)sizeof(float)) / kXcd * kXcd;
+    return fit >= all ? all : fit > all / 2 ? fit : all / 2;
 }
 
 }  // namespace veda

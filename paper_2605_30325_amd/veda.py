@@ -479,20 +479,28 @@ def veda_tile_heatmap(plan: Plan, q_tiled, k_tiled, valid_mask, softmax_scale: f
     return heat
 
 
+HEATMAP_SCRATCH_BYTES = 2 << 30   # what veda_plan_heatmap_workspace_bytes asks for up to about 8000 tiles a head
+
+
 def _heatmap_ws(plan, q_tiled, k_tiled, valid_mask, softmax_scale, query_tiles, n_qt, row_sums, heat, what):
     """One walk over the keys, with scratch from torch's allocator (taken on every call: no state that calls on other
-    streams or threads could share); two walks without scratch where there is no memory left for it."""
+    streams or threads could share); two walks without scratch, the same bits in about 1.6 times the time, where that
+    would be more than HEATMAP_SCRATCH_BYTES or there is no memory left for it."""
     args = (plan.handle, _ptr(q_tiled), _ptr(k_tiled), _ptr(valid_mask), C.c_float(softmax_scale))
     need = int(load().veda_plan_heatmap_workspace_bytes(plan.handle, n_qt))
-    try:
-        ws = torch.empty(need, dtype=torch.uint8, device=q_tiled.device)
-    except torch.cuda.OutOfMemoryError:
-        if row_sums is None:
-            _check(load().veda_tile_heatmap(*args, _ptr(query_tiles), n_qt, _ptr(heat), _stream()), what)
-        else:
-            _check(load().veda_tile_heatmap_rows(*args, _ptr(row_sums), 0, _ptr(heat), _stream()), what)
-        return
-    _check(load().veda_tile_heatmap_ws(*args, _ptr(query_tiles), n_qt, _ptr(row_sums), _ptr(heat), _ptr(ws), need, _stream()), what)
+    ws = None
+    if need <= HEATMAP_SCRATCH_BYTES:
+        try:
+            ws = torch.empty(need, dtype=torch.uint8, device=q_tiled.device)
+        except torch.cuda.OutOfMemoryError:
+            pass
+    if ws is not None:
+        status = load().veda_tile_heatmap_ws(*args, _ptr(query_tiles), n_qt, _ptr(row_sums), _ptr(heat), _ptr(ws), need, _stream())
+    elif row_sums is None:
+        status = load().veda_tile_heatmap(*args, _ptr(query_tiles), n_qt, _ptr(heat), _stream())
+    else:
+        status = load().veda_tile_heatmap_rows(*args, _ptr(row_sums), 0, _ptr(heat), _stream())
+    _check(status, what)
 
 
 def veda_tile_heatmap_rows(plan: Plan, q_tiled, k_tiled, valid_mask, softmax_scale: float, row_sums: Optional[torch.Tensor] = None,

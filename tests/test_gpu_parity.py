@@ -1431,6 +1431,41 @@ def test_heatmap_scratch_is_that_of_the_resident_workgroups(dtype, d, tile_token
     assert need(plan.handle, 16) <= 512 + 512 * halves * 64
 
 
+@pytest.mark.parametrize("tiles,places,bounded", [(3840, 1024, False), (4352, 960, False), (8256, 512, True)])
+def test_heatmap_scratch_has_an_upper_bound(tiles, places, bounded):
+    """Heads whose scratch would pass 2 GiB get by with fewer places, and from half of them on with none, with the same bits."""
+    grid, dev = (16, 4 * 16, 4 * (tiles // 64)), torch.device("cuda:0")
+    wl = wlm.custom_workload("large_heads", 1, 128, "bf16", grid, False, (50, 100), seed=67)
+    q, k, _ = wlm.make_qkv(wl, dev)
+    plan = veda.Plan(1, 1, 128, grid, np.asarray([(4, 4, 4)], np.int32), torch.bfloat16)
+    assert plan.total_tiles == tiles
+    qt, vm, _ = veda.veda_tile_layout(plan, q)
+    kt, _, _ = veda.veda_tile_layout(plan, k, want_mask=False)
+    heats = [torch.empty((1, plan.score_elems), device=dev) for _ in range(3)]
+    need = int(veda.load().veda_plan_heatmap_workspace_bytes(plan.handle, 0))
+    assert need == 512 + 512 * tiles * places and (need > veda.HEATMAP_SCRATCH_BYTES) == bounded
+    scale, stream = 1.0 / math.sqrt(128), torch.cuda.current_stream().cuda_stream
+
+    def grows(f):
+        torch.cuda.empty_cache()
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        r = f()
+        torch.cuda.synchronize()
+        return r, torch.cuda.max_memory_allocated() - before
+
+    _, used = grows(lambda: veda.veda_tile_heatmap(plan, qt, kt, vm, scale, None, heats[0]))
+    assert used == 0 if bounded else used >= need
+    (heat, sums), used = grows(lambda: veda.veda_tile_heatmap_rows(plan, qt, kt, vm, scale))
+    assert used - (heat.numel() + sums.numel()) * 4 < (2 ** 20 if bounded else need + 2 ** 22)
+    ws = torch.empty(need, dtype=torch.uint8, device=dev)
+    assert veda.load().veda_tile_heatmap_ws(plan.handle, qt.data_ptr(), kt.data_ptr(), vm.data_ptr(), scale, None, 0, None,
+                                            heats[1].data_ptr(), ws.data_ptr(), need, stream) == veda.VEDA_OK
+    assert veda.load().veda_tile_heatmap(plan.handle, qt.data_ptr(), kt.data_ptr(), vm.data_ptr(), scale, None, 0, heats[2].data_ptr(),
+                                         stream) == veda.VEDA_OK
+    assert torch.equal(heats[0], heats[1]) and torch.equal(heats[0], heats[2]) and torch.equal(heats[0], heat)
+
+
 def test_heatmap_of_many_small_samples():
     """128 heads of one tile: eight workgroups for each (every head's pair falls to the first die), so that 16384 samples are
     2^24 of them, more than a grid's first dimension takes."""
