@@ -1325,12 +1325,23 @@ def test_fp32_target_scores_below_the_smallest_normal_number(d):
     ("f32", 64, 64, (1, 5, 67), 5),
 ])
 def test_heatmap_with_and_without_scratch(dtype, d, tile_tokens, grid, heads):
+    _with_and_without_scratch(dtype, d, tile_tokens, grid, heads, 1)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_heatmap_of_whole_tiles_with_more_items_than_places(d):
+    """128-token tiles, all 6720 and 5042 listed ones of two samples: more than the 1024 or 1280 places, so that a workgroup goes on
+    with its scratch and its LDS as the tile before left them."""
+    _with_and_without_scratch("bf16", d, 128, (8, 66, 64), 12, 2)
+
+
+def _with_and_without_scratch(dtype, d, tile_tokens, grid, heads, batch):
     """The logits formed once (with scratch) or twice: the same bits, all rows and listed ones, with rows and keys that
     are not finite among them, and nothing outside the scratch is touched."""
     shapes = [(4, 4, 4), (1, 8, 8), (16, 2, 2), (64, 1, 1), (1, 1, 64)]
     shapes = [(2 * a, b, c) for a, b, c in shapes] if tile_tokens == 128 else shapes
     shapes = np.asarray([shapes[h % 5] for h in range(heads)] if heads < 12 else [shapes[h % 2] for h in range(heads)], np.int32)
-    wl = wlm.custom_workload("one_walk", heads, d, dtype, grid, False, (50, 100), seed=37)
+    wl = wlm.custom_workload("one_walk", heads, d, dtype, grid, False, (50, 100), seed=37, batch=batch)
     dev = torch.device("cuda:0")
     q, k, _ = wlm.make_qkv(wl, dev)
     n_tok = q.shape[2]
@@ -1338,7 +1349,7 @@ def test_heatmap_with_and_without_scratch(dtype, d, tile_tokens, grid, heads):
     q[0, 1, :n_tok // 2] = float("inf")
     k[0, 2, 5] = float("-inf")
     k[0, 3, n_tok // 3:n_tok // 2] = float("nan")
-    plan = veda.Plan(1, heads, d, grid, shapes, wl.torch_dtype, tile_tokens=tile_tokens)
+    plan = veda.Plan(batch, heads, d, grid, shapes, wl.torch_dtype, tile_tokens=tile_tokens)
     qt, vm, _ = veda.veda_tile_layout(plan, q, veda.VEDA_TOKEN_MAJOR)
     kt, _, _ = veda.veda_tile_layout(plan, k, veda.VEDA_TOKEN_MAJOR, want_mask=False)
     lib, scale, stream = veda.load(), 1.0 / math.sqrt(d), torch.cuda.current_stream().cuda_stream
@@ -1346,7 +1357,7 @@ def test_heatmap_with_and_without_scratch(dtype, d, tile_tokens, grid, heads):
     for rows in (None, listed.to(torch.int32).to(dev)):
         n = 0 if rows is None else rows.numel()
         ptr = None if rows is None else rows.data_ptr()
-        heats = [torch.full((1, plan.score_elems), -7.0, device=dev) for _ in range(3)]
+        heats = [torch.full((batch, plan.score_elems), -7.0, device=dev) for _ in range(3)]
         need = int(lib.veda_plan_heatmap_workspace_bytes(plan.handle, n))
         around = torch.full((need + 512,), 77, dtype=torch.uint8, device=dev)
         args = (plan.handle, qt.data_ptr(), kt.data_ptr(), vm.data_ptr(), scale, ptr, n)
@@ -1532,6 +1543,79 @@ def test_fp32_splits_lose_nothing_of_small_numbers(d, qs, ks, vs, gap, same):
         assert err[form] <= err[veda.VEDA_PRODUCTS_FP32]
         assert torch.equal(outs[form][0], outs[veda.VEDA_PRODUCTS_FP32][0]) == same
         assert (outs[form][1].double() - torch.logsumexp(s, dim=1)).abs().max() <= 1e-5 * max(1.0, s.abs().max().item())
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("walk", [0, 1])
+def test_fp32_second_walk_after_a_long_first(d, walk):
+    """Work items whose unions outgrow the step table's ring (256 entries), walked again for numbers that are not finite: the bits of
+    VEDA_PRODUCTS_FP32, and for the others those of the same call without such numbers."""
+    n = 400
+    grid = (4, 4, 4 * n)
+    wl = wlm.custom_workload("again", 1, d, "f32", grid, False, (50, 100), seed=71)
+    q, k, v = wlm.make_qkv(wl, torch.device("cuda:0"))
+    plan = veda.Plan(1, 1, d, grid, np.asarray([(4, 4, 4)], np.int32), torch.float32)
+    plan.set_option(veda.VEDA_OPT_ATTN_LIST_WALK, walk)
+    g = torch.Generator().manual_seed(6)
+    keep = torch.stack([torch.randperm(n, generator=g)[:200].sort()[0] for _ in range(n)])
+    for i in range(0, n, 2):
+        assert len(set(keep[i].tolist()) | set(keep[i + 1].tolist())) > 256
+    rp = (torch.arange(n + 1, dtype=torch.int32) * 200).cuda()
+    ci = keep.reshape(-1).to(torch.int32).cuda()
+    slots = _tile_tokens((4, 4, 4), grid)
+    hit = (keep == 390).any(dim=1)   # the tile of the infinity in V, kept late in the walk
+    hit[37] = True                   # and the one of the NaN in Q
+    hit = hit.view(-1, 2).any(dim=1).repeat_interleave(2)
+    assert 0 < int(hit.sum()) < n
+    outs = []
+    for odd, form in ((False, veda.VEDA_PRODUCTS_SPLIT), (True, veda.VEDA_PRODUCTS_SPLIT), (True, veda.VEDA_PRODUCTS_FP32)):
+        if odd:
+            v[0, 0, slots[390, 5], 3] = math.inf
+            q[0, 0, slots[37, 63], 0] = math.nan
+        plan.set_option(veda.VEDA_OPT_FP32_PRODUCTS, form)
+        qt, vm, _ = veda.veda_tile_layout(plan, q)
+        kt, _, _ = veda.veda_tile_layout(plan, k, want_mask=False)
+        vt, _, _ = veda.veda_tile_layout(plan, v, veda.VEDA_CHANNEL_MAJOR, want_mask=False)
+        outs.append(veda.veda_sparse_attn_fwd(plan, qt, kt, vt, vm, rp, ci, 1.0 / math.sqrt(d))[0][0, 0].cpu()[slots])
+    clean, again, chains = outs
+    assert torch.equal(again[~hit], clean[~hit]) and not torch.equal(chains[~hit], clean[~hit])
+    assert torch.equal(again[hit].isnan(), chains[hit].isnan()) and torch.equal(again[hit].nan_to_num(7.0), chains[hit].nan_to_num(7.0))
+    assert bool(again[hit].isinf().any()) and bool(again[37, 63].isnan().all())
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("recipe", ["unit", "amp"])
+@pytest.mark.parametrize("kept", [16, 63, 192, 193, 400])
+def test_fp32_products_against_64_bits(d, recipe, kept):
+    """The split products are nearer to 64 bits than the fp32 ones at every length and at larger logits ("amp"), and the default form
+    stays within the fp32 bar, 1e-4 of the outputs' root mean square, of the fp32 ones (seen: up to 5.8e-5, after 192 tiles)."""
+    n = 400
+    grid = (4, 4, 4 * n)
+    wl = wlm.custom_workload("nearness", 1, d, "f32", grid, False, (50, 100), seed=73, recipe=recipe)
+    q, k, v = wlm.make_qkv(wl, torch.device("cuda:0"))
+    plan = veda.Plan(1, 1, d, grid, np.asarray([(4, 4, 4)], np.int32), torch.float32)
+    qt, vm, _ = veda.veda_tile_layout(plan, q)
+    kt, _, _ = veda.veda_tile_layout(plan, k, want_mask=False)
+    vt, _, _ = veda.veda_tile_layout(plan, v, veda.VEDA_CHANNEL_MAJOR, want_mask=False)
+    keep = torch.rand((n, n), generator=torch.Generator().manual_seed(7)).argsort(dim=1)[:, :kept].sort(dim=1)[0]
+    rp = (torch.arange(n + 1, dtype=torch.int32) * kept).cuda()
+    ci, scale, outs = keep.reshape(-1).to(torch.int32).cuda(), 1.0 / math.sqrt(d), {}
+    slots = _tile_tokens((4, 4, 4), grid)
+    for form in (0, veda.VEDA_PRODUCTS_FP32, veda.VEDA_PRODUCTS_SPLIT):
+        plan.set_option(veda.VEDA_OPT_FP32_PRODUCTS, form)
+        outs[form] = veda.veda_sparse_attn_fwd(plan, qt, kt, vt, vm, rp, ci, scale)[0][0, 0][slots.cuda()].double()
+    assert torch.equal(outs[0], outs[veda.VEDA_PRODUCTS_SPLIT if kept <= 192 else veda.VEDA_PRODUCTS_FP32])
+    ref = torch.empty_like(outs[0])
+    order = slots.cuda()
+    q64, k64, v64 = q[0, 0].double(), k[0, 0].double(), v[0, 0].double()
+    for i in range(n):
+        cols = order[keep[i].cuda()].reshape(-1)
+        ref[i] = torch.softmax((q64[order[i]] @ k64[cols].T) * scale, dim=1) @ v64[cols]
+    err = {f: ((o - ref).norm() / ref.norm()).item() for f, o in outs.items()}
+    apart = ((outs[0] - outs[veda.VEDA_PRODUCTS_FP32]).abs().max() / ref.square().mean().sqrt()).item()
+    _say(f"[parity] fp32 products d {d} {recipe} kept {kept}: from 64 bits {err}, the default and the fp32 form apart by {apart:.2e}")
+    assert err[veda.VEDA_PRODUCTS_SPLIT] < err[veda.VEDA_PRODUCTS_FP32]
+    assert apart <= 1e-4
 
 
 @pytest.mark.parametrize("d", [64, 128])
