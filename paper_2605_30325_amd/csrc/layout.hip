@@ -407,10 +407,13 @@ extern "C" veda_status veda_tile_layout_path(const veda_plan* pl, const void* q,
     dim3 grid((unsigned)(2 * a.stats_blocks + ip->total_tiles), (unsigned)pl->prob.batch);
     hipStream_t st = (hipStream_t)stream;
     // Where the descriptors' part needs many registers (tiled copies, 128-token tiles), V's part keeps fewer waves in flight
-    // than in a kernel of its own, which shows once memory is what bounds them: 40 heads of 21x45x80 with 128-token tiles 683 us in one
-    // launch, 637 in three; 8 fp32 heads of 624 tiles (7,500 workgroups) 196 and 193.
+    // than in a kernel of its own, which shows once memory is what bounds them.  8 heads, one launch and three: tiled copies, fp32 at
+    // d = 128, 3200 workgroups 118 and 132 us, 6000 212 and 214, 7680 268 and 256 (bf16 120 and 129 at 6000, 148 and 144 at 7680);
+    // of 128-token tiles 5400 120 and 137, 10,116 210 and 217, 18,000 353 and 320; their descriptors alone 10,116 130 and 149,
+    // 18,000 220 and 222, 31,500 366 and 363, 54,000 615 and 601.  Descriptors of 64-token tiles: level at 93,750 (958 and 951).
     // (And a grid's dimension holds fewer than 2^32 threads.)
-    if (((pl->inner || q_tiled) && (int64_t)grid.x * grid.y > 4096) || grid.x >= 1u << 24) {
+    const int64_t one_launch = pl->inner ? (q_tiled ? 12288 : 24576) : q_tiled ? 6144 : INT64_MAX;
+    if ((int64_t)grid.x * grid.y > one_launch || grid.x >= 1u << 24) {
         veda_status r = veda_tile_layout_stats(pl, q, sq, q_tiled, valid_mask, valid_cnt, stats_q, stream);
         if (r == VEDA_OK) r = veda_tile_layout_stats(pl, k, sk, k_tiled, nullptr, nullptr, stats_k, stream);
         return r == VEDA_OK ? veda_tile_layout(pl, v, sv, VEDA_CHANNEL_MAJOR, v_tiled, nullptr, nullptr, stream) : r;
