@@ -799,7 +799,8 @@ extern "C" veda_status veda_tile_heatmap_ws(const veda_plan* pl, const void* q_t
                                             const uint64_t* valid_mask, float softmax_scale, const int32_t* query_tiles,
                                             int64_t n_query_tiles, float* row_sums, float* heat, void* workspace,
                                             size_t workspace_bytes, void* stream) {
-    if (!pl) return VEDA_ERR_INVALID_ARG;
+    // a list that has no size of scratch is a bad list, not too little scratch
+    if (!pl || (query_tiles ? n_query_tiles < 1 || n_query_tiles > pl->total_tiles : n_query_tiles != 0)) return VEDA_ERR_INVALID_ARG;
     if (!workspace) return VEDA_ERR_WORKSPACE;
     if (reinterpret_cast<uintptr_t>(row_sums) & 7u) return VEDA_ERR_UNSUPPORTED;
     return target_heatmap(pl, q_tiled, k_tiled, valid_mask, softmax_scale, query_tiles, n_query_tiles,

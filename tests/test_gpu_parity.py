@@ -1477,6 +1477,20 @@ def test_heatmap_scratch_has_an_upper_bound(tiles, places, bounded):
     assert torch.equal(heats[0], heats[1]) and torch.equal(heats[0], heats[2]) and torch.equal(heats[0], heat)
 
 
+def test_heatmap_refuses_lists_longer_than_the_tiles():
+    """As an invalid argument, with and without scratch: no scratch is said to be needed for them."""
+    plan = veda.Plan(1, 1, 64, (4, 4, 16), np.asarray([(4, 4, 4)], np.int32), torch.bfloat16)
+    x, vm = torch.zeros((1, 4, 64 * 64), dtype=torch.bfloat16, device="cuda"), torch.full((4,), -1, dtype=torch.int64, device="cuda")
+    listed = torch.arange(5, dtype=torch.int32, device="cuda") % 4
+    heat = torch.empty((1, 16), device="cuda")
+    for call in (lambda: veda.veda_tile_heatmap(plan, x, x, vm, 0.125, listed, heat),
+                 lambda: veda._check(veda.load().veda_tile_heatmap(plan.handle, x.data_ptr(), x.data_ptr(), vm.data_ptr(), 0.125, listed.data_ptr(), 5,
+                                                                   heat.data_ptr(), None), "veda_tile_heatmap")):
+        with pytest.raises(veda.VedaError) as e:
+            call()
+        assert e.value.status == veda.VEDA_ERR_INVALID_ARG
+
+
 def test_heatmap_of_many_small_samples():
     """128 heads of one tile: eight workgroups for each (every head's pair falls to the first die), so that 16384 samples are
     2^24 of them, more than a grid's first dimension takes."""
