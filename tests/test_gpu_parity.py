@@ -816,6 +816,44 @@ def test_whole_path_replayed_from_a_hip_graph():
         assert torch.equal(bufs["out"].view(torch.int16), want), rep
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_target_scores_replayed_from_a_hip_graph(dtype):
+    """1920 work items on at most 1024 places: the counters they are drawn from are cleared by every replay, and the scratch, taken
+    while the graph was recorded, stays the graph's own."""
+    mk = lambda i: wlm.make_qkv(wlm.custom_workload("target_graph", 20, 128, dtype, (9, 32, 32), False, (25, 100), seed=17 + i), dev)[:2]
+    dev, scale = torch.device("cuda:0"), 1.0 / math.sqrt(128)
+    inputs = [mk(i) for i in range(3)]
+    plan = veda.Plan(1, 20, 128, (9, 32, 32), np.asarray([(4, 4, 4)] * 20, np.int32), inputs[0][0].dtype)
+    q, k = (x.clone() for x in inputs[0])
+    qt, vm, vc = veda.veda_tile_layout(plan, q)
+    kt, _, _ = veda.veda_tile_layout(plan, k, want_mask=False)
+    heat = torch.zeros((1, plan.score_elems), device=dev)
+    rp, ci = veda.veda_tile_select(plan, heat, [40] * 20)
+
+    def step():
+        veda.veda_tile_layout(plan, q, veda.VEDA_TOKEN_MAJOR, qt, vm, vc)
+        veda.veda_tile_layout(plan, k, veda.VEDA_TOKEN_MAJOR, kt, want_mask=False)
+        veda.veda_tile_heatmap(plan, qt, kt, vm, scale, None, heat)
+        veda.veda_tile_select(plan, heat, [40] * 20, rp, ci)
+
+    step()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    for rep, (qi, ki) in enumerate(inputs[1:] + inputs):
+        q.copy_(qi); k.copy_(ki)
+        step()
+        want, want_ci = heat.clone(), ci.clone()
+        other = torch.full((64 << 20,), 7.0, device=dev)   # would land in scratch that was given back
+        heat.fill_(float("nan")); ci.zero_()
+        graph.replay()
+        other.add_(1.0)
+        torch.cuda.synchronize()
+        assert torch.equal(heat, want) and torch.equal(ci, want_ci), rep
+        del other
+
+
 @pytest.mark.parametrize("d,tile_tokens", [(128, 64), (64, 64), (128, 128)])
 def test_attention_with_q_in_token_order(d, tile_tokens):
     # the attention kernel gathering Q itself (no tiled copy of Q): same bits as with the tiled Q; and
