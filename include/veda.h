@@ -120,11 +120,15 @@ void veda_plan_destroy(veda_plan* plan); /* NULL is allowed */
  * veda_plan_chain_unit tells which unit the plan's next call will use.
  * VEDA_OPT_FP32_PRODUCTS (0 = by the length of the lists, the default; VEDA_PRODUCTS_FP32; VEDA_PRODUCTS_SPLIT), fp32
  * stage 4: products on the fp32 matrix cores, or as six products of exact three-part bf16 splits, which is about
- * twice as fast and nearer to the exact result (2-norm of the error three quarters).  By default query tiles with
- * up to 192 kept key tiles take the split products; beyond that the fp32 ones, whose rounding grows with the root of the list,
- * so that outputs stay within 4e-5 of their root mean square of what those give.  Whatever the option, work items (two query tiles) with
- * a result that is not finite, or too small for its parts (|q * scale| or |logit| of 2^48, sums of p * v outside 2^-48 .. 2^32), are formed
- * again on the fp32 matrix cores. */
+ * twice as fast and nearer to the exact result at every length (2-norm of the error 0.6 to 0.85 of the fp32 products').
+ * By default query tiles with up to 192 kept key tiles take the split products and longer lists the fp32 ones: a line
+ * that keeps long lists' results near those of the fp32 products, not one of speed or exactness.  (Largest difference
+ * of the two forms over the outputs' root mean square, as measured with 400 tiles a head: 1.3e-5 ... 1.7e-5 after 16
+ * kept tiles, 2.2e-5 ... 3.1e-5 after 63, 4.1e-5 ... 5.8e-5 after 192, most of it the fp32 products' rounding, which grows with
+ * the root of the list.)  Whatever the option, results that are not finite or too small for their parts (|q * scale| or
+ * |logit| of 2^48, sums of p * v outside 2^-48 .. 2^32) are formed again on the fp32 matrix cores.  A workgroup holds
+ * two adjacent query tiles and takes one form for both: the longer list decides, and a result of either that has to be
+ * formed again, so that the last bits of a row can depend on its neighbour tile. */
 typedef enum { VEDA_OPT_EXACT_LOGIT_SCALE = 0, VEDA_OPT_ATTN_LIST_WALK = 1, VEDA_OPT_FP32_CHAIN_UNIT = 2,
                VEDA_OPT_FP32_PRODUCTS = 3 } veda_option;
 enum { VEDA_PRODUCTS_FP32 = 1, VEDA_PRODUCTS_SPLIT = 2 };

@@ -6,10 +6,11 @@
 
 namespace veda {
 
-// Lists up to this long take the fp32 kernel's split products.  Those are nearer to the 64-bit result at any length (8
-// heads of 624 tiles: all kept 2.6e-6 against 3.7e-6, 63 kept 6.5e-7 and 9e-7), but the fp32 chains' rounding grows with
-// the root of the list, and with it how far the two lie apart: 3.9e-5 of the outputs' rms at most after 203 tiles, 4.8e-5
-// after 312, 6.1e-5 after 624 (d = 128, two heads).  Results of this path are compared at 5e-5, so longer lists keep the chains.
+// Lists up to this long take the fp32 kernel's split products.  Those are faster and nearer to the 64-bit result at any length
+// (8 heads of 624 tiles: all kept 2.6e-6 against 3.7e-6, 63 kept 6.5e-7 and 9e-7); the line only keeps long lists' results
+// near those of the fp32 chains, whose rounding grows with the root of the list and makes most of the difference: 4.1e-5 of the
+// outputs' rms at most at d = 128 and 5.8e-5 at d = 64 after 192 tiles (one head of 400), 6.1e-5 at d = 128 after 624, which is
+// more than the 5e-5 that results of this path are compared at.
 constexpr int kF32SplitTiles = 192;
 
 // Shared by the entry points: q_tiled or (q_tok, sq), k_tiled or (k_tok, sk).

@@ -15,7 +15,8 @@
 // Measured, whole calls: 8 heads of 624 tiles, 10 % kept, 5.9 -> 3.3 ms (the products on fp32 matrix cores at 93 % of their
 // rate before); 1.1 PFLOP/s of bf16 products, matrix pipes 52 % busy.  What is left: a fifth of the wave-steps belong
 // to waves whose query tile does not keep the key tile, and two waves on a SIMD cover each other's
-// softmax only so far.  Reading a group of products ahead gave 7 %, rounding pairs once 3 %, V^T rows on all banks 2 %;
+// softmax only so far.  d = 64 (168 registers) reloads one spilled fragment of Q per 32 keys, which waits for every load in
+// flight; d = 128 spills nothing inside its steps since the two forms share one body of the chains.  Reading a group of products ahead gave 7 %, rounding pairs once 3 %, V^T rows on all banks 2 %;
 // loads one phase earlier, priorities: 1-2 %.
 //
 // Long lists (AttnArgs::split_tiles) take v_mfma_f32_32x32x2_f32 instead, and numbers that are not finite come out of the

@@ -137,7 +137,8 @@ veda_status launch_select(const veda_plan* pl, const float* scores, const int32_
         return launch_status("select_sampled_kernel");
     }
     // Otherwise the smallest register-resident instantiation that fits the longest row, else the
-    // memory-resident one.
+    // memory-resident one.  Half kept, in the class below and in that of 4, 16, 32 or 64: 24 heads of 300 tiles 19 and
+    // 26 us, 450 26 and 34, 600 34 and 40, 700 41 and 46, 850 50 and 53, 1400 139 and 155, 13 of 2900 415 and 573.
     int items = 0;
     for (int cand : {2, 4, 6, 8, 10, 12, 14, 16, 24, 32, 48, 64})
         if (max_tiles <= 64 * cand) { items = cand; break; }

@@ -105,7 +105,7 @@ __device__ __forceinline__ void select_row(const float* __restrict__ srow, int n
     } else {
         for (int t = 0; t < items; ++t) n_gt += __popcll(__ballot(get(t) > thr));
     }
-    int ties_left = k - n_gt;   // >= 1
+    int ties_left = k - n_gt;   // 0 after a stop between two keys
     int written = 0;
     const uint64_t below = (1ull << lane) - 1ull;
     auto emit = [&](int t, uint32_t kv) {
