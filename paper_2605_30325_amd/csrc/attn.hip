@@ -47,6 +47,8 @@ static veda_status sparse_attn(const veda_plan* pl, const void* q_tiled, const v
     a.k_tok = (const char*)k_tok;
     a.sk_b = sk.b * es; a.sk_h = sk.h * es; a.sk_n = sk.n * es;
     a.tile_n0 = ip->d_tile_n0;
+    a.tile_real = ip->d_tile_real;
+    a.items = ip->d_attn_items;
     a.valid_mask = valid_mask; a.row_ptr = row_ptr; a.col_idx = col_idx;
     a.out = (char*)out; a.lse = lse;
     a.total_tiles = ip->total_tiles;

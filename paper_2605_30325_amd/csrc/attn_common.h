@@ -15,7 +15,9 @@ constexpr float kLn2 = 0.6931471805599453f;
 struct AttnArgs {
     const HeadGeom* heads;
     const uint8_t* tile_head;
-    const int32_t* xcd_cum;
+    const int32_t* xcd_cum;    // pair items, walk mode
+    const AttnItem* items;     // items of the table mode, by workgroup
+    const uint64_t* tile_real; // real slots of every tile (plan table)
     const char* q;             // tiled Q, or null when q_tok is given
     const char* q_tok;         // Q in token order (bf16 kernel only): gathered by the kernel itself
     int64_t sq_b, sq_h, sq_n;  // its strides in bytes
@@ -82,6 +84,31 @@ __device__ inline void pair_tiles(const HeadGeom& g, int p, int& qiA, int& qiB, 
         qiA = 2 * tt2 * plane + rest; qiB = qiA + plane; hasB = 2 * tt2 + 1 < g.nt;
     }
     if (!hasB) qiB = qiA;
+}
+
+// What this workgroup computes, or false for nothing: its entry of the plan's table, or (walk mode: two lists at most) the
+// pair that xcd_work gives it.
+template <bool kTable> __device__ __forceinline__ bool attn_work(const AttnArgs& a, AttnItem& it) {
+    if constexpr (kTable) {
+        typedef const __attribute__((address_space(4))) int32_t* const_i32_t;
+        const const_i32_t src = (const_i32_t)(uintptr_t)(a.items + blockIdx.x);   // scalar loads
+        it.head = src[0];
+        it.n_tiles = src[1];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) it.tile[t] = src[2 + t];
+        it.waves = (uint32_t)src[6];
+        return it.head >= 0;
+    } else {
+        int pair;
+        bool hasB;
+        if (!xcd_work(a.xcd_cum, a.heads, a.n_heads, blockIdx.x, it.head, pair)) return false;
+        pair_tiles(a.heads[it.head], pair, it.tile[0], it.tile[1], hasB);
+        it.n_tiles = hasB ? 2 : 1;
+        it.tile[2] = it.tile[3] = it.tile[0];
+        const uint32_t b = hasB ? 1u : kItemIdle;
+        it.waves = kItemSecond << 8 | b << 16 | (b | kItemSecond) << 24;
+        return true;
+    }
 }
 
 // Position of the n-th set bit (from 0) of m; n < popcount(m).

@@ -1,9 +1,9 @@
 // Stage 4, fp32 (Eq. 2; Sec. 3.1 masked form; Sec. 4.3 tile skipping; Alg. 1 "UnTile"): the
 // accuracy path (1e-4 against the double-precision definition), fp32 products on the bf16 matrix cores.
 //
-// Same work split as the bf16 kernel: a workgroup of four wavefronts owns a pair of partner query
-// tiles and walks the union of their two kept lists; waves 0,1 hold rows 0-31 / 32-63 of tile A,
-// waves 2,3 those of tile B.  Padding is handled as in the bf16 kernel (real query rows first; half steps, attn_union.h).
+// Same work split as the bf16 kernel: a workgroup of four wavefronts of 32 rows owns a pair of partner query
+// tiles, or four thin ones, and walks the union of their kept lists (8 heads of 21x30x52, 10 % kept, thin tiles in fours
+// instead of twos: whole call 3.07 -> 2.93 ms; 2 x 4 heads of 9x24x32, all kept, 5 %).  Padding is handled as in the bf16 kernel (real query rows first; half steps, attn_union.h).
 // Every operand is split into three bf16 parts and a product is six bf16 ones (split_f32.h: why that is no less exact),
 // 32 keys at a time:
 //   S^T = K Q^T from the K planes, in the shadow of its last products V^T converted (landing area -> registers -> planes)
@@ -44,6 +44,12 @@ constexpr float kF32Slack = 8.0f;   // log2 units a row maximum may outgrow the 
 // output of 2^48 or more in this scale they are below 2^-25 of it for lists of a million keys; a smaller one that is not zero walks again.
 constexpr float kF32QScale = 0x1p80f, kF32VScale = 0x1p96f, kF32Small = 0x1p48f;
 
+// LDS: a K tile and a V^T tile, then the step table and the rows' tokens; at the end the output rows and their softmax sums
+// lie over all but the tokens.
+typedef UnionLds<4, kF32Chunk> F32Table;
+template <int D, bool kTable>
+constexpr size_t kF32Tokens = (size_t)2 * kTile * D * 4 + (kTable ? sizeof(F32Table) : 4 * 32 * sizeof(float));
+
 // kTable: the steps come from the table in LDS (attn_union.h), as in the bf16 kernel; otherwise the two
 // lists are merged inside the loop (heads above 16384 tiles, VEDA_OPT_ATTN_LIST_WALK).
 // d = 64: three workgroups on a compute unit (42 KB each); with two, 2 heads of 624 tiles, all kept, 7.34 instead of 7.14 ms.
@@ -58,40 +64,47 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
     constexpr int kGroups = kLoads / 4;
     constexpr int NB = D / 32;                   // 32-channel blocks of O^T
     constexpr int kM = D / 8;                    // 16-byte K reads per key block and lane
+    constexpr int kLists = kTable ? 4 : 2;       // kept lists of a workgroup, at most
     extern __shared__ __align__(1024) char smem[];
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int which = wave >> 1, r = (wave ^ __popc(blockIdx.x >> 3)) & 1;   // see the bf16 kernel
     const int idx = lane & 31, h = lane >> 5;
 
-    int head, pair;
-    if (!xcd_work(a.xcd_cum, a.heads, a.n_heads, blockIdx.x, head, pair)) return;
+    AttnItem it;   // see the bf16 kernel
+    if (!attn_work<kTable>(a, it)) return;
+    const int head = it.head;
     const HeadGeom hg = a.heads[head];
     const int64_t b = blockIdx.y;
-    int qiA, qiB;
-    bool hasB;
-    pair_tiles(hg, pair, qiA, qiB, hasB);
-    const int qi = which ? qiB : qiA;
+    const uint32_t place = it.waves >> (8 * wave);
+    const int which = place & 3u, r = place & kItemSecond ? 1 : 0;
+    const int qi = which == 0 ? it.tile[0] : which == 1 ? it.tile[1] : which == 2 ? it.tile[2] : it.tile[3];
     const int64_t head_tile0 = b * a.total_tiles + hg.tile_off;
-    const int64_t rowA = head_tile0 + qiA, rowB = head_tile0 + qiB;
-    const int begA = a.row_ptr[rowA], nA = a.row_ptr[rowA + 1] - begA;
-    const int begB = a.row_ptr[rowB], nB = hasB ? a.row_ptr[rowB + 1] - begB : 0;
+    int beg[kLists], cnt[kLists];
+#pragma unroll
+    for (int t = 0; t < kLists; ++t) {
+        beg[t] = a.row_ptr[head_tile0 + it.tile[t]];
+        cnt[t] = t < it.n_tiles ? a.row_ptr[head_tile0 + it.tile[t] + 1] - beg[t] : 0;
+    }
     typedef const __attribute__((address_space(4))) int32_t* const_i32_t;
     typedef const __attribute__((address_space(4))) uint64_t* const_u64_t;
-    const const_i32_t colsA = (const_i32_t)(uintptr_t)(a.col_idx + begA);
-    const const_i32_t colsB = (const_i32_t)(uintptr_t)(a.col_idx + begB);
+    const const_i32_t colsA = (const_i32_t)(uintptr_t)(a.col_idx + beg[0]);
+    const const_i32_t colsB = (const_i32_t)(uintptr_t)(a.col_idx + beg[1]);
+    const int nA = cnt[0], nB = cnt[1];   // walk mode: two lists
     const const_u64_t vmask = (const_u64_t)(uintptr_t)(a.valid_mask + hg.tile_off);
     const char* kt = a.k + head_tile0 * kKBytes;
     const char* vt = a.v + head_tile0 * kVBytes;
 
     // Row 32r + idx is the tile's real slot of that rank; rows beyond the real slots read slot 0 and are not written.
-    const uint64_t q_real = __ballot(slot_token(hg, qi, lane, a.T, a.H, a.W) >= 0);
-    const int q_rows = __popcll(q_real);
+    const uint64_t q_real = ((const_u64_t)(uintptr_t)(a.tile_real + hg.tile_off))[qi];
+    const int q_rows = place & kItemIdle ? 0 : __popcll(q_real);
     const float* qrow;
+    int* tok_s = reinterpret_cast<int*>(smem + kF32Tokens<D, kTable>);   // [4][32] token of each row, -1 = none
     {
+        const bool real = 32 * r + idx < q_rows;
         int slot = 32 * r + idx;
-        if (q_real != ~0ull) slot = slot < q_rows ? nth_bit(q_real, slot) : 0;
+        if (q_real != ~0ull) slot = real ? nth_bit(q_real, slot) : 0;
+        if (h == 0) tok_s[wave * 32 + idx] = real ? token_from(hg, a.tile_n0[hg.tile_off + qi], slot, a.H, a.W) : -1;
         qrow = reinterpret_cast<const float*>(a.q + (head_tile0 + qi) * kKBytes + slot * kKPitch);
     }
     f32x16 o[NB];
@@ -108,29 +121,29 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
     const uint32_t smem_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
     const uint32_t wave_lds = smem_base + (uint32_t)wave * (kLoads * 1024);
     struct Step { int j, fl; uint64_t vm; };   // vm: the mask, or step_kind's lo | hi << 32 (half steps)
-    constexpr int kKeepers = 3;
+    constexpr int kKeepers = 15;
     // The steps: the union of the two kept lists.  Table mode: laid out in LDS before the loop; walk mode:
     // merged with scalar loads as the loop goes (32-bit integers on the scalar unit; see the bf16 kernel).
     constexpr int kEnd = 0x7fffffff;
     int ia = 0, ib = 0;
     int rawA = 0, rawB = 0, okA = 0, okB = 0;
-    typedef UnionLds<2, kF32Chunk> Table;
-    Table& u = *reinterpret_cast<Table*>(smem + kKBytes + kVBytes);
+    F32Table& u = *reinterpret_cast<F32Table*>(smem + kKBytes + kVBytes);
     const uint32_t tab_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)&u.tab[0];
     const uint64_t* vmask_g = a.valid_mask + hg.tile_off;
     const int32_t* n0s_g = a.tile_n0 + hg.tile_off;
     i32x4 raw_next = {0, 0, 0, 0};
     int s_read = 0, s_done = 0, total = 0;
     if constexpr (kTable) {
-        const int32_t* lists[2] = {a.col_idx + begA, a.col_idx + begB};
-        const int counts[2] = {nA, nB};
-        total = union_build<2, 256, kF32Chunk>(u, lists, counts, hg.n_tiles, tid);
+        const int32_t* cols[kLists];
+#pragma unroll
+        for (int t = 0; t < kLists; ++t) cols[t] = a.col_idx + beg[t];
+        total = union_build<kLists, 256, kF32Chunk>(u, cols, cnt, it.n_tiles, hg.n_tiles, tid);
     }
     // to the first step; ends with a barrier
     auto begin_walk = [&]() __attribute__((always_inline)) {
         s_done = 0;
         if constexpr (kTable) {
-            union_fill<2, 256, kF32Chunk, false, 2 * kF32Chunk>(u, 0, total, hg.n_tiles, vmask_g, n0s_g, tid);   // the whole ring
+            union_fill<4, 256, kF32Chunk, false, 2 * kF32Chunk>(u, 0, total, hg.n_tiles, vmask_g, n0s_g, tid);   // the whole ring
             __syncthreads();
             raw_next = union_read<kF32Chunk>(tab_lds, 0);
             s_read = 1;
@@ -333,7 +346,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
                 if (nx.c == 0) {
                     ++s_done;
                     if ((s_done & (kF32Chunk - 1)) == 0)
-                        union_fill<2, 256, kF32Chunk, false>(u, s_done + kF32Chunk, total, hg.n_tiles, vmask_g, n0s_g, tid);
+                        union_fill<4, 256, kF32Chunk, false>(u, s_done + kF32Chunk, total, hg.n_tiles, vmask_g, n0s_g, tid);
                 }
             }
             cur = nx;
@@ -505,13 +518,16 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
             if constexpr (kTable) {   // the table's other half has been left behind: refill it
                 ++s_done;
                 if ((s_done & (kF32Chunk - 1)) == 0)
-                    union_fill<2, 256, kF32Chunk, false>(u, s_done + kF32Chunk, total, hg.n_tiles, vmask_g, n0s_g, tid);
+                    union_fill<4, 256, kF32Chunk, false>(u, s_done + kF32Chunk, total, hg.n_tiles, vmask_g, n0s_g, tid);
             }
         }
 
     };
 
-    bool chains = (nA > nB ? nA : nB) > a.split_tiles;
+    int longest = 0;
+#pragma unroll
+    for (int t = 0; t < kLists; ++t) longest = cnt[t] > longest ? cnt[t] : longest;
+    bool chains = longest > a.split_tiles;
     float unscale = 1.0f;
     if (!chains) {
         split_walk();
@@ -537,22 +553,14 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
         unscale = 1.0f;
     }
 
-    // Normalise, transpose through LDS ([2 tiles][64 rows][D] fp32) and scatter the real rows.
+    // Normalise, transpose through LDS ([4 wavefronts][32 rows][D] fp32) and scatter the real rows.
     const float l_all = l_run + __shfl_xor(l_run, 32);
     const float inv = l_all > 0.0f ? unscale / l_all : 0.0f;
     __syncthreads();   // nobody fills the step table any more
     float* obuf = reinterpret_cast<float*>(smem);
-    float* lse_s = obuf + 2 * kTile * D;
-    int* tok_s = reinterpret_cast<int*>(lse_s + 2 * kTile);
-    if (tid < 2 * kTile) {   // row c is the c-th real slot of its tile
-        const int slot = tid % kTile, base = tid - slot;
-        const int n = slot_token(hg, base ? qiB : qiA, slot, a.T, a.H, a.W);
-        const uint64_t real = __ballot(n >= 0);
-        if (slot >= __popcll(real)) tok_s[tid] = -1;
-        if (n >= 0) tok_s[base + __popcll(real & ((1ull << slot) - 1ull))] = n;
-    }
+    float* lse_s = obuf + 4 * 32 * D;
     {
-        float* orow = obuf + (which * kTile + 32 * r + idx) * D;
+        float* orow = obuf + (wave * 32 + idx) * D;
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -562,19 +570,18 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
                 for (int t = 0; t < 4; ++t) v[t] = o[nb][4 * j + t] * inv;
                 *reinterpret_cast<f32x4*>(orow + 32 * nb + 8 * j + 4 * h) = v;
             }
-        if (h == 0) lse_s[which * kTile + 32 * r + idx] = (m_run + __log2f(l_all)) * kLn2;
+        if (h == 0) lse_s[wave * 32 + idx] = (m_run + __log2f(l_all)) * kLn2;
     }
     __syncthreads();
     char* ob = a.out + b * a.so_b + head * a.so_h;
-    const int n_tiles = hasB ? 2 : 1;
-    for (int cid = tid; cid < n_tiles * kTile * kKChunks; cid += 256) {
+    for (int cid = tid; cid < 4 * 32 * kKChunks; cid += 256) {
         const int row = cid / kKChunks, ch = cid % kKChunks;
         const int n = tok_s[row];
         if (n >= 0)
             *reinterpret_cast<uint4*>(ob + (int64_t)n * a.so_n + ch * 16) =
                 *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(obuf) + row * kKPitch + ch * 16);
     }
-    if (a.lse && tid < n_tiles * kTile) {
+    if (a.lse && tid < 4 * 32) {
         const int n = tok_s[tid];
         if (n >= 0) a.lse[(b * a.n_heads + head) * a.tokens + n] = lse_s[tid];
     }
@@ -582,17 +589,13 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
 
 veda_status launch_sparse_attn_f32(const veda_plan* pl, const AttnArgs& a, bool walk, hipStream_t s) {
     const int d = pl->prob.head_dim;
-    dim3 grid((unsigned)(kXcd * pl->xcd_max_pairs), (unsigned)pl->prob.batch), block(256);
     bool table = !walk;   // the step table's bitmaps cover 16384 tiles per head
     for (const HeadGeom& g : pl->heads) table = table && g.n_tiles <= kUnionMaxTiles;
-    // a K tile and a V^T tile, then the step table; at the end, over all of them, the two output tiles with
-    // their softmax sums and token numbers
-    const size_t tiles = (size_t)2 * kTile * d * 4, out = tiles + 2 * kTile * (sizeof(float) + sizeof(int));
-    const size_t with_table = tiles + (table ? sizeof(UnionLds<2, kF32Chunk>) : 0);
-    const size_t smem = with_table > out ? with_table : out;
+    dim3 grid((unsigned)(table ? pl->attn_blocks : kXcd * pl->xcd_max_pairs), (unsigned)pl->prob.batch), block(256);
 #define VEDA_LAUNCH_F32(DD, TT)                                                                          \
     do {                                                                                                 \
         auto kern = sparse_attn_f32_kernel<DD, TT>;                                                      \
+        constexpr size_t smem = kF32Tokens<DD, TT> + 4 * 32 * sizeof(int);                               \
         if (smem > 64 * 1024)                                                                            \
             VEDA_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem)); \
         hipLaunchKernelGGL(kern, grid, block, smem, s, a);                                               \

@@ -7,16 +7,21 @@
 // along the axis in which the head's tile shape is thinnest: pair_tiles()) and walks the union
 // of their two kept lists: a key tile kept by both is loaded once and used twice.
 //
-// Four wavefronts: waves 0,1 hold rows 0-31 / 32-63 of query tile A, waves 2,3 those of its
-// partner B.  Every wave attends to all 64 slots of a key tile, so it needs no merge with
-// another wave at the end.  A wave whose query tile does not keep the current key tile skips
-// the step and only meets the others at the barrier; the matrix cores it leaves idle go to the
+// Four wavefronts of 32 query rows: two for each of the two tiles, or one for each of FOUR neighbouring thin tiles (32
+// real rows or fewer, at the ragged edges of a grid: geometry.h, attn_items).  Every wave attends to all 64 slots of a
+// key tile, so it needs no merge with another wave at the end.  A wave whose query tile does not keep the current key
+// tile skips the step and only meets the others at the barrier; the matrix cores it leaves idle go to the
 // second workgroup resident on the compute unit.
 //
 // Padding costs little: a query tile's real rows come first, so a wave beyond them idles, and a key tile
 // with few real keys is a half step (attn_union.h).  The attention call alone, repeated, in turn on one box: on a
 // 21 x 30 x 52 grid with 4x4x4 tiles, where 27 % of the tiles are such, 12 heads with every tile kept 7.9 -> 6.9 ms and
 // with 10 % kept 0.98 -> 0.81; on 61 x 45 x 80, with few of them, 24 heads at 5 % kept 32.5 -> 32.15 ms.
+// Thin tiles used to run two to a workgroup with half its waves idle.  Four together walk 1.3-2.0 times their list's length
+// instead of 2 x 1.2-1.4, and their workgroups, the longest, start first and are spread evenly over the dies (left in
+// raster order all of a head's last layer fell to one or two dies: 12 heads of 21x30x52 5 % slower than in twos).
+// Whole calls, in turn on one box: 40 heads of 21x45x80 at 20 % kept (28 % of the tiles are thin) 33.0 -> 29.5 ms, of
+// 21x30x52 at 5 % 2.05 -> 1.89; 12 heads of 21x30x52 at 10 % 0.943 -> 0.907, all kept 6.95 -> 6.44.
 //
 // The products are formed transposed (S^T = K Q^T, O^T = V^T P^T): a lane owns one query, its
 // accumulator registers run over keys, P^T in registers already is the B operand of the second
@@ -37,30 +42,19 @@
 
 namespace veda {
 
-// After the last step: normalise, transpose through LDS and scatter the real rows of the
-// workgroup's two query tiles to token order.  obuf: [2 tiles][64 rows][D] bf16, then lse_s and tok_s.
+// After the last step: normalise, transpose through LDS and scatter the real rows of the workgroup's four
+// wavefronts to token order.  obuf: [4 wavefronts][32 rows][D] bf16, then lse_s; tok_s: token of each row, -1 = none.
 template <int D>
-__device__ __forceinline__ void finish_pair(const PairState<D>& st, const AttnArgs& a, const HeadGeom& hg, char* smem,
-                                            int head, int qiA, int qiB, bool hasB, int64_t b, int tid, int which,
-                                            int r, int lq, int hh) {
+__device__ __forceinline__ void finish_pair(const PairState<D>& st, const AttnArgs& a, const int* tok_s, char* smem,
+                                            int head, int64_t b, int tid, int wave, int lq, int hh) {
     constexpr int kRowB = D * 2, kKChunks = kRowB / 16;
     const float l_all = st.l_run + __shfl_xor(st.l_run, 32);
     const float inv = l_all > 0.0f ? 1.0f / l_all : 0.0f;
     char* obuf = smem;
-    float* lse_s = reinterpret_cast<float*>(smem + 2 * kTile * kRowB);   // [2][64]
-    int* tok_s = reinterpret_cast<int*>(lse_s + 2 * kTile);              // [2][64] token of each row, -1 = padding
+    float* lse_s = reinterpret_cast<float*>(smem + 4 * 32 * kRowB);   // [4][32]
     __syncthreads();
-    // the slot -> token map costs a handful of integer divisions: once per row, not once per chunk
-    // (row c is the c-th real slot of its tile; rows beyond the real slots have no token)
-    if (tid < 2 * kTile) {
-        const int slot = tid % kTile, base = tid - slot;
-        const int n = slot_token(hg, base ? qiB : qiA, slot, a.T, a.H, a.W);
-        const uint64_t real = __ballot(n >= 0);
-        if (slot >= __popcll(real)) tok_s[tid] = -1;
-        if (n >= 0) tok_s[base + __popcll(real & ((1ull << slot) - 1ull))] = n;
-    }
     {
-        char* orow = obuf + (which * kTile + 32 * r + lq) * kRowB;
+        char* orow = obuf + (wave * 32 + lq) * kRowB;
 #pragma unroll
         for (int nb = 0; nb < D / 32; ++nb)
 #pragma unroll
@@ -72,19 +66,18 @@ __device__ __forceinline__ void finish_pair(const PairState<D>& st, const AttnAr
                 for (int t = 0; t < 4; ++t) pk[t] = (__bf16)(st.o[nb][4 * j + t] * inv);
                 *reinterpret_cast<bf16x4*>(orow + d0 * 2) = pk;
             }
-        if (hh == 0) lse_s[which * kTile + 32 * r + lq] = (st.ref * st.resid + __log2f(l_all)) * kLn2;
+        if (hh == 0) lse_s[wave * 32 + lq] = (st.ref * st.resid + __log2f(l_all)) * kLn2;
     }
     __syncthreads();
     char* ob = a.out + b * a.so_b + head * a.so_h;
-    const int n_tiles = hasB ? 2 : 1;
-    for (int cid = tid; cid < n_tiles * kTile * kKChunks; cid += 256) {
+    for (int cid = tid; cid < 4 * 32 * kKChunks; cid += 256) {
         const int row = cid / kKChunks, ch = cid % kKChunks;
         const int n = tok_s[row];
         if (n >= 0)
             *reinterpret_cast<uint4*>(ob + (int64_t)n * a.so_n + ch * 16) =
                 *reinterpret_cast<const uint4*>(obuf + row * kRowB + ch * 16);
     }
-    if (a.lse && tid < n_tiles * kTile) {
+    if (a.lse && tid < 4 * 32) {
         const int n = tok_s[tid];
         if (n >= 0) a.lse[(b * a.n_heads + head) * a.tokens + n] = lse_s[tid];
     }
@@ -117,35 +110,39 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     constexpr int kKChunks = kRowB / 16;         // 16-byte chunks per K row
     constexpr int kLoads = kKBytes / 1024 / 4;   // direct-load instructions per wave per tile (K; same for V)
     constexpr int G = D / 16, NB = D / 32;
+    constexpr int kLists = kGrouped ? 1 : kTable ? 4 : 2;   // kept lists of a workgroup, at most
+    typedef UnionLds<kLists, kPairChunk> Table;
     extern __shared__ __align__(1024) char smem[];   // base bits 4-9 clear: see PairAddr
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // The wave that a query tile with 32 or fewer real rows leaves idle (r = 1) is not on the same SIMD in
-    // every workgroup: half of them deal their rows the other way round (40 heads of 21x45x80 at 20 % kept, whole call
-    // 33.2 -> 33.1 ms; no difference on 21x30x52).
-    const int which = wave >> 1, r = (wave ^ __popc(blockIdx.x >> 3)) & 1;
     const int lq = lane & 31, hh = lane >> 5;
 
-    int head, pair;
-    if (!xcd_work(a.xcd_cum, a.heads, a.n_heads, blockIdx.x, head, pair)) return;
+    AttnItem it;
+    if (!attn_work<kTable>(a, it)) return;
+    const int head = it.head;
     const HeadGeom hg = a.heads[head];
     const int64_t b = blockIdx.y;
-    int qiA, qiB;
-    bool hasB;
-    pair_tiles(hg, pair, qiA, qiB, hasB);
-    const int qi = which ? qiB : qiA;
+    const uint32_t place = it.waves >> (8 * wave);
+    const int which = place & 3u, r = place & kItemSecond ? 1 : 0;
+    const int qi = which == 0 ? it.tile[0] : which == 1 ? it.tile[1] : which == 2 ? it.tile[2] : it.tile[3];
     const int64_t row0 = kGrouped ? b * (a.total_tiles / 2) + hg.tile_off / 2 : b * a.total_tiles + hg.tile_off;
-    const int64_t rowA = row0 + (kGrouped ? pair : qiA), rowB = row0 + (kGrouped ? pair : qiB);
-    const int begA = a.row_ptr[rowA], nA = a.row_ptr[rowA + 1] - begA;
-    const int begB = a.row_ptr[rowB], nB = hasB ? a.row_ptr[rowB + 1] - begB : 0;
+    const int lists = kGrouped ? 1 : it.n_tiles;
+    int beg[kLists], cnt[kLists];
+#pragma unroll
+    for (int t = 0; t < kLists; ++t) {
+        const int64_t row = row0 + (kGrouped ? it.tile[0] >> 1 : it.tile[t]);
+        beg[t] = a.row_ptr[row];
+        cnt[t] = t < lists ? a.row_ptr[row + 1] - beg[t] : 0;
+    }
     // The kept lists and the validity masks are read-only for the whole launch and indexed
     // uniformly: reading them through the constant address space makes them scalar loads, so
     // no vector-memory counter waits of the compiler's own end up inside the main loop.
     typedef const __attribute__((address_space(4))) int32_t* const_i32_t;
     typedef const __attribute__((address_space(4))) uint64_t* const_u64_t;
-    const const_i32_t colsA = (const_i32_t)(uintptr_t)(a.col_idx + begA);
-    const const_i32_t colsB = (const_i32_t)(uintptr_t)(a.col_idx + begB);
+    const const_i32_t colsA = (const_i32_t)(uintptr_t)(a.col_idx + beg[0]);
+    const const_i32_t colsB = (const_i32_t)(uintptr_t)(a.col_idx + beg[kLists == 2 ? 1 : 0]);
+    const int nA = cnt[0], nB = kLists == 2 ? cnt[kLists == 2 ? 1 : 0] : 0;   // walk mode
     const const_u64_t vmask = (const_u64_t)(uintptr_t)(a.valid_mask + hg.tile_off);
     const int64_t head_tile0 = b * a.total_tiles + hg.tile_off;
     const char* kt = kTokK ? a.k_tok + b * a.sk_b + head * a.sk_h : a.k + head_tile0 * kKBytes;
@@ -156,16 +153,18 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     // Rows are the real slots of the query tile in order: with padding among its 64 slots a tile at a ragged
     // edge fills fewer rows, and a wave whose 32 rows are all beyond the real ones has nothing to compute.
     PairState<D> st;
-    const uint64_t q_real = __ballot(slot_token(hg, qi, lane, a.T, a.H, a.W) >= 0);
-    const int q_rows = __popcll(q_real);
+    const uint64_t q_real = ((const_u64_t)(uintptr_t)(a.tile_real + hg.tile_off))[qi];
+    const int q_rows = place & kItemIdle ? 0 : __popcll(q_real);
+    int* tok_s = reinterpret_cast<int*>(smem + 2 * kSlot + (kTable ? sizeof(Table) : 0));   // [4][32] token of each row, -1 = none
     {
         // from the tiled tensor, or straight from token order
         const char* qrow;
         const bool real = 32 * r + lq < q_rows;
         int slot = 32 * r + lq;
         if (q_real != ~0ull) slot = real ? nth_bit(q_real, slot) : 0;
+        const int n = real ? token_from(hg, n0s[qi], slot, a.H, a.W) : 0;
+        if (hh == 0) tok_s[wave * 32 + lq] = real ? n : -1;
         if (a.q_tok) {
-            const int n = real ? slot_token(hg, qi, slot, a.T, a.H, a.W) : 0;
             qrow = a.q_tok + b * a.sq_b + head * a.sq_h + (int64_t)n * a.sq_n + 16 * hh;
         } else {
             qrow = a.q + (head_tile0 + qi) * kKBytes + slot * kRowB + 16 * hh;
@@ -206,8 +205,7 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
         k_row[j] = krow;
         k_src0[j] = chunk + kBias - 1024u * j;
         if (kTokK) {   // byte offset of the row's token from the tile's anchor token (host checked: fits 32 bits)
-            const int lw = krow % hg.pw, lh = (krow / hg.pw) % hg.ph, lt = krow / (hg.pw * hg.ph);
-            k_src[j] = (uint32_t)((((int64_t)lt * a.H + lh) * a.W + lw) * a.sk_n) + chunk + kBias - 1024u * j;
+            k_src[j] = (uint32_t)(token_from(hg, 0, krow, a.H, a.W) * a.sk_n) + chunk + kBias - 1024u * j;
         } else {
             k_src[j] = krow * kRowB + chunk - 1024u * j;
         }
@@ -222,8 +220,8 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     uint32_t k_chunk[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-        const int sl = 8 << i, lw = sl % hg.pw, lh = (sl / hg.pw) % hg.ph, lt = sl / (hg.pw * hg.ph);
-        k_chunk[i] = kTokK ? (uint32_t)((((int64_t)lt * a.H + lh) * a.W + lw) * a.sk_n) : (uint32_t)(sl * kRowB);
+        const int sl = 8 << i;
+        k_chunk[i] = kTokK ? (uint32_t)(token_from(hg, 0, sl, a.H, a.W) * a.sk_n) : (uint32_t)(sl * kRowB);
     }
     const int v_c = (lane & 7) ^ ((lane >> 4) & 3) ^ (((lane >> 3) & 1) << 2);
     auto chunk_off = [&](uint32_t c) __attribute__((always_inline)) {
@@ -299,7 +297,6 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     int gh = 0;         // grouped walk: which half of the current entry comes next
     int ta = 0, tb = 0; // this step consumes the head of list A / B
     // table mode: the raw entry read one step ahead of its use, the next entry to read, steps done
-    typedef UnionLds<2, kPairChunk> Table;
     Table& u = *reinterpret_cast<Table*>(smem + 2 * kSlot);
     const uint32_t tab_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)&u.tab[0];
     i32x4 raw_next = {0, 0, 0, 0};
@@ -308,10 +305,11 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     const uint64_t* vmask_g = a.valid_mask + hg.tile_off;
     const int32_t* n0s_g = a.tile_n0 + hg.tile_off;
     if constexpr (kTable) {
-        const int32_t* lists[2] = {a.col_idx + begA, a.col_idx + begB};
-        const int counts[2] = {nA, kGrouped ? 0 : nB};
-        total = union_build<2, 256, kPairChunk>(u, lists, counts, list_range, tid) * (kGrouped ? 2 : 1);
-        union_fill<2, 256, kPairChunk, kGrouped, 2 * kPairChunk>(u, 0, total, list_range, vmask_g, n0s_g, tid);   // the whole ring
+        const int32_t* cols[kLists];
+#pragma unroll
+        for (int t = 0; t < kLists; ++t) cols[t] = a.col_idx + beg[t];
+        total = union_build<kLists, 256, kPairChunk>(u, cols, cnt, lists, list_range, tid) * (kGrouped ? 2 : 1);
+        union_fill<kLists, 256, kPairChunk, kGrouped, 2 * kPairChunk>(u, 0, total, list_range, vmask_g, n0s_g, tid);   // the whole ring
         __syncthreads();
     } else {
         rawA = colsA[0];
@@ -369,13 +367,13 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
         if constexpr (kTable) {
             ++s_done;
             if ((s_done & (kPairChunk - 1)) == 0)
-                union_fill<2, 256, kPairChunk, kGrouped>(u, s_done + kPairChunk, total, list_range, vmask_g, n0s_g, tid);
+                union_fill<kLists, 256, kPairChunk, kGrouped>(u, s_done + kPairChunk, total, list_range, vmask_g, n0s_g, tid);
         }
     };
     if constexpr (kTable) next_advance();   // entry 0 on its way
 
     // Step s (P = s & 1) computes on slot P while the tiles of step s+1 land in slot P^1.
-    const int my_bit = 32 * r < q_rows ? 1 << which : 128;   // 128: a bit no step has
+    const int my_bit = 32 * r < q_rows ? (kGrouped ? 1 : 1 << which) : 128;   // 128: a bit no step has
     MergedStep e0, e1, e2;
     next_head(e0);
     next_advance();
@@ -426,18 +424,19 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
 #undef VEDA_STEP
 #undef VEDA_LOADS_DONE_BARRIER
 
-    finish_pair<D>(st, a, hg, smem, head, qiA, qiB, hasB, b, tid, which, r, lq, hh);
+    finish_pair<D>(st, a, tok_s, smem, head, b, tid, wave, lq, hh);
 }
 
 veda_status launch_sparse_attn_bf16_pair(const veda_plan* pl, const AttnArgs& a, bool grouped, bool exact, bool walk,
                                          hipStream_t s) {
     const int d = pl->prob.head_dim;
-    dim3 grid((unsigned)(kXcd * pl->xcd_max_pairs), (unsigned)pl->prob.batch), block(256);
     // the step table needs a bitmap over the tiles the lists may name
     bool table = !walk;
     for (const HeadGeom& g : pl->heads) table = table && (grouped ? g.n_tiles / 2 : g.n_tiles) <= kUnionMaxTiles;
-    // two slots of (K tile + V^T tile), then the step table
-    const size_t smem = (size_t)2 * 2 * kTile * d * 2 + (table ? sizeof(UnionLds<2, kPairChunk>) : 0);
+    dim3 grid((unsigned)(table ? pl->attn_blocks : kXcd * pl->xcd_max_pairs), (unsigned)pl->prob.batch), block(256);
+    // two slots of (K tile + V^T tile), then the step table and the rows' tokens
+    const size_t tables = grouped ? sizeof(UnionLds<1, kPairChunk>) : sizeof(UnionLds<4, kPairChunk>);
+    const size_t smem = (size_t)2 * 2 * kTile * d * 2 + (table ? tables : 0) + 4 * 32 * sizeof(int);
 #define VEDA_LAUNCH_PAIR_T(DD, GG, KK, EE, TT)                                                           \
     do {                                                                                                 \
         auto kern = sparse_attn_bf16_pair_kernel<DD, GG, KK, EE, TT>;                                    \

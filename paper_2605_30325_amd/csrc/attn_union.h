@@ -88,20 +88,23 @@ template <int N, int kChunk> struct UnionLds {
 // one go took 40 heads of 21x30x52 at one kept tile from 371 to 364 us.
 // Steps 1 and 2.  cols[t], n[t]: list t (global memory).  All threads of the workgroup call it;
 // it ends with a barrier.  Returns the number of steps.
-// n_tiles: the range of the list entries.
+// n_tiles: the range of the list entries; lists: how many of the N there are.
 template <int N, int kThreads, int kChunk>
-__device__ inline int union_build(UnionLds<N, kChunk>& u, const int32_t* const (&cols)[N], const int (&n)[N], int n_tiles, int tid) {
+__device__ inline int union_build(UnionLds<N, kChunk>& u, const int32_t* const (&cols)[N], const int (&n)[N], int lists, int n_tiles, int tid) {
     static_assert(kUnionMaxWords % kThreads == 0, "whole words per thread");
     constexpr int kPer = kUnionMaxWords / kThreads;
     const int words = (n_tiles + 31) >> 5;
     // the first entries are on their way while the bitmaps are cleared
     int early[N];
 #pragma unroll
-    for (int t = 0; t < N; ++t) early[t] = tid < n[t] ? cols[t][tid] : -1;
-    for (int i = tid; i < N * kUnionMaxWords; i += kThreads) (&u.bm[0][0])[i] = 0u;
+    for (int t = 0; t < N; ++t) early[t] = t < lists && tid < n[t] ? cols[t][tid] : -1;
+    for (int w = tid; w < words; w += kThreads)
+#pragma unroll
+        for (int t = 0; t < N; ++t) u.bm[t][w] = 0u;
     __syncthreads();
 #pragma unroll
     for (int t = 0; t < N; ++t) {
+        if (t >= lists) break;
         auto mark = [&](int j) {
             if ((unsigned)j < (unsigned)n_tiles) atomicOr(&u.bm[t][j >> 5], 1u << (j & 31));
         };

@@ -5,6 +5,9 @@
 
 #include <stdint.h>
 
+#include <algorithm>
+#include <vector>
+
 namespace veda {
 
 // Per-head geometry, one entry per head, in device memory (plan->d_heads).
@@ -26,12 +29,13 @@ struct HeadGeom {
     int32_t ot, oh, ow;      // extents of a whole tile
     int32_t ht, hh, hw;      // token offset of the second half inside a whole tile
     int32_t grp;             // 64-slot tiles per whole tile: 1 or 2
-    // Query tiles are processed two at a time by the bf16 attention and heat-map kernels.  Partners
+    // Full query tiles are processed two at a time by the attention and heat-map kernels.  Partners
     // are neighbours along pair_ax (0 = t, 1 = h, 2 = w: the axis along which a tile is thinnest, so
     // its neighbour is the closest one and keeps the most similar key tiles); a last layer without a
-    // partner is processed alone.  pair_ax = 3: the two halves of a 128-token tile.
+    // partner is processed alone (heat map, merged lists) or with the next lines' (attn_items).  pair_ax = 3: the two halves of a 128-token tile.
     int32_t pair_ax;
     int32_t n_pairs;         // work items (pairs and partnerless tiles) of this head
+    int32_t log_pw, log_phw; // log2 of pw and of ph*pw (extents multiply to 64, so each is a power of two)
 };
 
 // Extents and tile grid of one head: shape = (p_t,p_h,p_w) of a whole tile, grp = 1 or 2.
@@ -46,6 +50,8 @@ inline void head_extents(HeadGeom& g, const int32_t* shape, int grp, int T, int 
         else if (g.oh > 1) { g.ph = g.oh / 2; g.hh = g.ph; }
         else { g.pw = g.ow / 2; g.hw = g.pw; }
     }
+    for (g.log_pw = 0; (1 << g.log_pw) < g.pw; ++g.log_pw) {}
+    for (g.log_phw = g.log_pw; (1 << g.log_phw) < g.ph * g.pw; ++g.log_phw) {}
     g.nt = (T + g.ot - 1) / g.ot;
     g.nh = (H + g.oh - 1) / g.oh;
     g.nw = (W + g.ow - 1) / g.ow;
@@ -64,6 +70,134 @@ inline int32_t tile_anchor_token(const HeadGeom& g, int32_t i, int T, int H, int
             w = (int64_t)tw * g.ow + half * g.hw;
     if (t >= T || h >= H || w >= W) { t -= half * g.ht; h -= half * g.hh; w -= half * g.hw; }
     return (int32_t)((t * H + h) * W + w);
+}
+
+// Real slots of 64-slot tile i: bit l is set if slot l lies inside the grid.
+inline uint64_t tile_real_slots(const HeadGeom& g, int32_t i, int T, int H, int W) {
+    const int o = g.grp == 2 ? i >> 1 : i, half = g.grp == 2 ? (i & 1) : 0;
+    const int tw = o % g.nw, th = (o / g.nw) % g.nh, tt = o / (g.nw * g.nh);
+    auto inside = [](int first, int extent, int size) { return std::max(0, std::min(extent, size - first)); };
+    const int rt = inside(tt * g.ot + half * g.ht, g.pt, T), rh = inside(th * g.oh + half * g.hh, g.ph, H),
+              rw = inside(tw * g.ow + half * g.hw, g.pw, W);
+    if (rt == g.pt && rh == g.ph && rw == g.pw) return ~0ull;
+    uint64_t mask = 0;
+    for (int t = 0; rw > 0 && t < rt; ++t)
+        for (int h = 0; h < rh; ++h) mask |= (rw == 64 ? ~0ull : (1ull << rw) - 1ull) << ((t * g.ph + h) * g.pw);
+    return mask;
+}
+
+// What a workgroup of the attention kernels (four wavefronts of 32 query rows) computes: up to four query tiles of one
+// head, visited together.  A tile with more than 32 real rows takes two wavefronts, a thin one at a ragged edge of the
+// grid (32 rows or fewer: its second wavefront would have none) takes one, so four thin tiles share a workgroup where two full
+// ones do.  Built once per plan: which tiles share depends on the geometry alone.
+struct AttnItem {
+    int32_t head;      // -1: nothing to do (a die with fewer items than others)
+    int32_t n_tiles;   // 1..4
+    int32_t tile[4];   // head-local query tiles; places beyond n_tiles repeat the first
+    uint32_t waves;    // byte w: wavefront w's place in tile[] | kItemSecond | kItemIdle
+    int32_t unused;
+};
+constexpr uint32_t kItemSecond = 4u;   // rows 32-63 of its tile, not 0-31
+constexpr uint32_t kItemIdle = 8u;     // no rows
+
+// Appends head h's items: those of more than two tiles, which have the most steps, before the others, each kind ordered by
+// its first tile.  Returns the number of the former.  Full tiles are paired along pair_ax (line by line; the odd ones out
+// with those of the next lines), thin ones taken four at a time by 2x2x2 blocks of the tile grid, so that tiles that share a
+// workgroup are neighbours, whose kept lists agree most.  At most two items of a head have wavefronts to spare.
+inline size_t attn_items_of_head(const HeadGeom& g, int32_t h, int T, int H, int W, std::vector<AttnItem>& items) {
+    const size_t first = items.size();
+    auto add = [&](const int32_t* tiles, int n, int full) {   // the first `full` of them take two wavefronts
+        AttnItem it = {h, n, {0, 0, 0, 0}, 0u, 0};
+        for (int t = 0; t < 4; ++t) it.tile[t] = tiles[t < n ? t : 0];
+        // which of a tile's wavefronts comes first alternates: the second one of an edge tile has less to do, and is then
+        // not on the same SIMD in every workgroup
+        uint32_t place[4] = {kItemIdle, kItemIdle, kItemIdle, kItemIdle};
+        int w = 0;
+        const uint32_t flip = (items.size() - first) & 1;
+        for (int t = 0; t < n; ++t) {
+            if (t < full) {
+                place[w++] = (uint32_t)t | (flip ? kItemSecond : 0u);
+                place[w++] = (uint32_t)t | (flip ? 0u : kItemSecond);
+            } else {
+                place[w++] = (uint32_t)t;
+            }
+        }
+        for (w = 0; w < 4; ++w) it.waves |= place[w] << (8 * w);
+        items.push_back(it);
+    };
+    if (g.pair_ax == 3) {   // the two halves of a 128-token tile keep one list between them
+        for (int32_t o = 0; o < g.n_tiles / 2; ++o) {
+            const int32_t both[2] = {2 * o, 2 * o + 1};
+            add(both, 2, 2);
+        }
+        return 0;
+    }
+    const int cnt[3] = {g.nt, g.nh, g.nw}, stride[3] = {g.nh * g.nw, g.nw, 1}, ax = g.pair_ax;
+    std::vector<int32_t> odd, thin;
+    for (int32_t i = 0; i < g.n_tiles; ++i) {
+        if (i / stride[ax] % cnt[ax] != 0) continue;
+        int32_t held = -1;
+        for (int c = 0; c < cnt[ax]; ++c) {
+            const int32_t t = i + c * stride[ax];
+            if (__builtin_popcountll(tile_real_slots(g, t, T, H, W)) <= 32) {
+                thin.push_back(t);
+            } else if (held < 0) {
+                held = t;
+            } else {
+                const int32_t pair[2] = {held, t};
+                add(pair, 2, 2);
+                held = -1;
+            }
+        }
+        if (held >= 0) odd.push_back(held);
+    }
+    for (size_t i = 0; i + 1 < odd.size(); i += 2) add(&odd[i], 2, 2);
+    auto block = [&](int32_t i) {
+        const int64_t w = i % g.nw, hh = i / g.nw % g.nh, t = i / (g.nw * g.nh);
+        return ((((t / 2) * g.nh + hh / 2) * g.nw + w / 2) * 2 + t % 2) * 4 + hh % 2 * 2 + w % 2;
+    };
+    std::sort(thin.begin(), thin.end(), [&](int32_t a, int32_t b) { return block(a) < block(b); });
+    if (odd.size() % 2) {   // a last full tile takes along what would not fill a workgroup
+        int32_t tiles[3] = {odd.back(), 0, 0};
+        int n = 1;
+        for (size_t over = thin.size() % 4 < 3 ? thin.size() % 4 : 0; over > 0; --over) {
+            tiles[n++] = thin.back();
+            thin.pop_back();
+        }
+        add(tiles, n, 1);
+    }
+    for (size_t i = 0; i < thin.size(); i += 4) add(&thin[i], (int)std::min<size_t>(4, thin.size() - i), 0);
+    std::sort(items.begin() + first, items.end(), [](const AttnItem& a, const AttnItem& b) {
+        return (a.n_tiles > 2) != (b.n_tiles > 2) ? a.n_tiles > 2 : a.tile[0] < b.tile[0];
+    });
+    return (size_t)std::count_if(items.begin() + first, items.end(), [](const AttnItem& a) { return a.n_tiles > 2; });
+}
+
+// The launch table: workgroup i runs on die i % dies, and die x takes the x-th part of every head's items of either kind, heads
+// in order (all dies then work on the same head at the same time, whose K and V stay in the memory-side cache, and the
+// workgroups that share an L2 hold neighbouring query tiles).  Dies with fewer items end with empty ones.
+inline std::vector<AttnItem> attn_items(const std::vector<HeadGeom>& heads, int T, int H, int W, int dies) {
+    std::vector<std::vector<AttnItem>> per(dies);
+    std::vector<AttnItem> items;
+    size_t most = 0;
+    for (size_t h = 0; h < heads.size(); ++h) {
+        items.clear();
+        const size_t many = attn_items_of_head(heads[h], (int32_t)h, T, H, W, items), n[2] = {many, items.size() - many};
+        size_t at = 0;
+        for (int kind = 0; kind < 2; ++kind)
+            for (int i = 0; i < dies; ++i) {
+                const int x = kind ? i : dies - 1 - i;   // the odd ones of one kind go to the last dies, of the other to the first
+                const size_t share = n[kind] / dies + ((size_t)i < n[kind] % dies ? 1 : 0);
+                per[x].insert(per[x].end(), items.begin() + at, items.begin() + at + share);
+                at += share;
+                most = std::max(most, per[x].size());
+            }
+    }
+    const AttnItem none = {-1, 0, {0, 0, 0, 0}, 0u, 0};
+    std::vector<AttnItem> table(most * dies, none);
+    for (int x = 0; x < dies; ++x)
+        for (size_t i = 0; i < per[x].size(); ++i) table[i * dies + x] = per[x][i];
+    return table;
 }
 
 // Work split of the target scores over a list of n query tiles, in any order: two entries of one head, the next two in

@@ -108,6 +108,12 @@ static veda_status build_plan(const veda_problem* p, const int32_t* shapes, int 
         }
     }
 
+    std::vector<uint64_t> tile_real((size_t)toff);
+    for (const HeadGeom& g : pl->heads)
+        for (int32_t i = 0; i < g.n_tiles; ++i) tile_real[(size_t)g.tile_off + i] = veda::tile_real_slots(g, i, p->T, p->H, p->W);
+    const std::vector<veda::AttnItem> items = veda::attn_items(pl->heads, p->T, p->H, p->W, veda::kXcd);
+    pl->attn_blocks = (int32_t)items.size();
+
     std::vector<int32_t> row_blk;
     for (int h = 0; h < p->heads; ++h)
         for (int32_t i = 0; i < (pl->heads[h].n_tiles + 63) / 64; ++i) row_blk.push_back((int32_t)((uint32_t)h << 24 | (uint32_t)i));
@@ -142,6 +148,12 @@ static veda_status build_plan(const veda_problem* p, const int32_t* shapes, int 
     if (e == hipSuccess) e = hipMalloc((void**)&pl->d_tile_n0, tile_n0.size() * sizeof(int32_t));
     if (e == hipSuccess)
         e = hipMemcpy(pl->d_tile_n0, tile_n0.data(), tile_n0.size() * sizeof(int32_t), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMalloc((void**)&pl->d_tile_real, tile_real.size() * sizeof(uint64_t));
+    if (e == hipSuccess)
+        e = hipMemcpy(pl->d_tile_real, tile_real.data(), tile_real.size() * sizeof(uint64_t), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMalloc((void**)&pl->d_attn_items, items.size() * sizeof(veda::AttnItem));
+    if (e == hipSuccess)
+        e = hipMemcpy(pl->d_attn_items, items.data(), items.size() * sizeof(veda::AttnItem), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMalloc((void**)&pl->d_row_blk, row_blk.size() * sizeof(int32_t));
     if (e == hipSuccess) e = hipMalloc((void**)&pl->d_xcd_cum_pair, xcd_cum_pair.size() * sizeof(int32_t));
     if (e == hipSuccess)
@@ -196,6 +208,8 @@ void veda_plan_destroy(veda_plan* pl) {
     if (pl->d_heads) (void)hipFree(pl->d_heads);
     if (pl->d_tile_head) (void)hipFree(pl->d_tile_head);
     if (pl->d_tile_n0) (void)hipFree(pl->d_tile_n0);
+    if (pl->d_tile_real) (void)hipFree(pl->d_tile_real);
+    if (pl->d_attn_items) (void)hipFree(pl->d_attn_items);
     if (pl->d_row_blk) (void)hipFree(pl->d_row_blk);
     if (pl->d_xcd_cum_pair) (void)hipFree(pl->d_xcd_cum_pair);
     delete pl;

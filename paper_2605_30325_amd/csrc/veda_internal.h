@@ -40,6 +40,12 @@ template <> struct Chunk<uint32_t> {  // fp32: 4 channels per 16 bytes
     }
 };
 
+// Token of slot l of a tile whose slot 0 is token n0 (a real slot).
+__device__ __forceinline__ int token_from(const HeadGeom& g, int n0, int l, int H, int W) {
+    const int lw = l & (g.pw - 1), lh = (l >> g.log_pw) & (g.ph - 1), lt = l >> g.log_phw;
+    return n0 + (lt * H + lh) * W + lw;
+}
+
 // Token index of slot l of tile i of a head, or -1 for a padded slot.  Tiles and slots are
 // both raster order with time slowest (App. A.5: temporal neighbours p_h*p_w slots apart).
 __device__ inline int slot_token(const HeadGeom& g, int i, int l, int T, int H, int W) {
@@ -74,11 +80,14 @@ struct veda_plan {
     veda::HeadGeom* d_heads = nullptr;  // device [heads]
     uint8_t* d_tile_head = nullptr;     // device [total_tiles]: head of each global tile
     int32_t* d_tile_n0 = nullptr;       // device [total_tiles]: anchor token of each tile (tile_anchor_token: always a real token)
+    uint64_t* d_tile_real = nullptr;    // device [total_tiles]: tile_real_slots of each tile
+    veda::AttnItem* d_attn_items = nullptr;   // device [attn_blocks]: work of the attention kernels, by workgroup
+    int32_t attn_blocks = 0;
     // Blocks of 64 consecutive tiles that never straddle two heads (the projection kernel's work
     // items): d_row_blk[x] = head << 24 | block index inside the head.
     int32_t* d_row_blk = nullptr;       // device [row_blocks]
     int64_t row_blocks = 0;
-    // Work split of the attention and heat-map launches: die x takes the x-th eighth of every head's pair work
+    // Work split of the heat-map launches, and of the attention's where its lists are merged inside the loop: die x takes the x-th eighth of every head's pair work
     // items (HeadGeom::n_pairs), heads in order, so all dies work on the same head at the same time.
     // d_xcd_cum_pair[x*(heads+1) + h] = number of items die x owns in heads < h.
     int32_t* d_xcd_cum_pair = nullptr;  // device [8][heads+1]

@@ -118,3 +118,72 @@ def test_workgroups_over_a_list_of_query_tiles(tmp_path):
         pairs = [int(((np.bincount(p, minlength=heads) + 1) // 2).sum()) for p in parts]
         rooms = [(len(p) + min(heads, len(p))) // 2 for p in parts]                  # of each window, one after the other
         assert blocks == sum(rooms) and all(a <= b <= a + heads // 2 for a, b in zip(pairs, rooms)), (heads, len(l))
+
+
+ITEMS_PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "geometry.h"
+int main(int argc, char** argv) {
+    const int T = atoi(argv[1]), H = atoi(argv[2]), W = atoi(argv[3]), grp = atoi(argv[4]), dies = atoi(argv[5]);
+    std::vector<veda::HeadGeom> heads;
+    for (int i = 6; i + 3 < argc; i += 4) {
+        const int32_t shape[3] = {atoi(argv[i]), atoi(argv[i + 1]), atoi(argv[i + 2])};
+        veda::HeadGeom g;
+        veda::head_extents(g, shape, grp, T, H, W);
+        g.pair_ax = atoi(argv[i + 3]);
+        heads.push_back(g);
+    }
+    for (const veda::HeadGeom& g : heads) {
+        printf("%d", g.n_tiles);
+        for (int i = 0; i < g.n_tiles; ++i) printf(" %llx", (unsigned long long)veda::tile_real_slots(g, i, T, H, W));
+        printf("\n");
+    }
+    for (const veda::AttnItem& it : veda::attn_items(heads, T, H, W, dies)) printf("%d %d %d %d %d %d %u\n", it.head, it.n_tiles, it.tile[0], it.tile[1], it.tile[2], it.tile[3], it.waves);
+    return 0;
+}
+"""
+
+
+@pytest.mark.parametrize("grp", [1, 2])
+@pytest.mark.parametrize("grid", [(1, 1, 1), (1, 2, 3), (5, 9, 13), (17, 6, 7), (21, 30, 52), (4, 57, 32), (9, 18, 18)])
+def test_every_wavefront_of_rows_is_in_one_work_item(tmp_path, grid, grp):
+    """The attention kernels' launch table: every 32-row part of a query tile that holds real rows belongs to exactly one
+    wavefront, at most two workgroups of a head have wavefronts to spare, and no die has more than one item of either kind over its share."""
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no C++ compiler")
+    (tmp_path / "items.cc").write_text(ITEMS_PROGRAM)
+    subprocess.check_call([gxx, "-std=c++17", "-O1", "-Wall", "-Werror", f"-I{CSRC}", str(tmp_path / "items.cc"), "-o", str(tmp_path / "items")])
+    grow = grp
+    shapes = [(4 * grow, 4, 4), (grow, 8, 8), (16 * grow, 2, 2), (grow, 1, 64)]
+    axes = [3] if grp == 2 else [0, 1, 2]
+    heads = [(s, ax) for s in shapes for ax in axes]
+    args = [str(x) for s, ax in heads for x in (*s, ax)]
+    lines = subprocess.run([str(tmp_path / "items"), *map(str, grid), str(grp), "8", *args], capture_output=True, text=True, check=True).stdout.splitlines()
+    real = []
+    for (s, _), line in zip(heads, lines):
+        masks = [int(x, 16) for x in line.split()[1:]]
+        slots = np.asarray([[(m >> l) & 1 for l in range(64)] for m in masks], bool).reshape(-1, 64 * grp)
+        tile_of = vo.token_tile_map(grid, s).reshape(-1)
+        assert (slots.sum(1) == np.bincount(tile_of, minlength=len(slots))).all()
+        real.append([bin(m).count("1") for m in masks])
+    items = [[int(x) for x in l.split()] for l in lines[len(heads):]]
+    assert len(items) % 8 == 0
+    for h, rows in enumerate(real):
+        seen, spare = [], 0
+        dies = np.zeros((2, 8), int)
+        for i, (head, n, *tiles, waves) in enumerate(items):
+            if head != h:
+                continue
+            assert 1 <= n <= 4 and len(set(tiles[:n])) == n and all(t == tiles[0] for t in tiles[n:])
+            dies[int(n > 2), i % 8] += 1
+            places = [(waves >> (8 * w)) & 255 for w in range(4)]
+            live = [p for p in places if not p & 8]
+            assert all((p & 3) < n for p in live)
+            seen += [(tiles[p & 3], (p >> 2) & 1) for p in live]
+            spare += len(live) < 4
+        want = [(t, r) for t, m in enumerate(rows) for r in (0, 1) if grp == 2 or r == 0 or m > 32]
+        assert sorted(seen) == want, (h, len(seen), len(want))
+        assert spare <= (0 if grp == 2 else 1 if sum(m > 32 for m in rows) % 2 == 0 else 2), (h, spare)
+        assert (dies.max(1) - dies.min(1)).max() <= 1
