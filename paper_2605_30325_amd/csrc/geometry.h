@@ -200,12 +200,55 @@ inline std::vector<AttnItem> attn_items(const std::vector<HeadGeom>& heads, int 
     return table;
 }
 
-// Work split of the target scores over a list of n query tiles, in any order: two entries of one head, the next two in
-// the list, share a workgroup, and workgroup p takes the p-th pair, head by head.  Pairs are formed inside windows of
+// What a workgroup of the target scores computes where all query tiles are asked for: consecutive query tiles of one head, as
+// many as have 128 real rows between them (four wavefronts of 32, packed: a wavefront may hold rows of several tiles).
+constexpr int kHeatTiles = 8;   // at most
+struct HeatItem {
+    int32_t head, first, n;   // n = 0: nothing to do (a die with fewer items than others)
+};
+inline std::vector<HeatItem> heat_items(const std::vector<HeadGeom>& heads, int T, int H, int W, int dies) {
+    std::vector<std::vector<HeatItem>> per(dies);
+    std::vector<HeatItem> items;
+    size_t most = 0;
+    for (size_t h = 0; h < heads.size(); ++h) {
+        const HeadGeom& g = heads[h];
+        items.clear();
+        int rows = 0;
+        for (int32_t i = 0; i < g.n_tiles; ++i) {
+            const int more = __builtin_popcountll(tile_real_slots(g, i, T, H, W));
+            const bool fits = g.grp == 2 ? i % 2 == 1 : rows + more <= 128 && !items.empty() && items.back().n < kHeatTiles;
+            if (fits) {
+                ++items.back().n;
+                rows += more;
+            } else {
+                items.push_back({(int32_t)h, i, 1});
+                rows = more;
+            }
+        }
+        const size_t n = items.size();
+        size_t at = 0;
+        for (int x = 0; x < dies; ++x) {
+            const size_t share = n / dies + ((size_t)x < n % dies ? 1 : 0);
+            per[x].insert(per[x].end(), items.begin() + at, items.begin() + at + share);
+            at += share;
+            most = std::max(most, per[x].size());
+        }
+    }
+    std::vector<HeatItem> table(most * dies, HeatItem{0, 0, 0});
+    for (int x = 0; x < dies; ++x)
+        for (size_t i = 0; i < per[x].size(); ++i) table[i * dies + x] = per[x][i];
+    return table;
+}
+
+// Work split of the target scores over a list of n query tiles, in any order: entries of one head, the next in
+// the list, share a workgroup: two full tiles, four thin ones (32 real rows or fewer), or a last full one and two thin ones;
+// workgroup p takes the p-th such item, head by head.  Items are formed inside windows of
 // kListWindow entries, so that a workgroup's look at the list is bounded (a longer list loses at most one partner per
 // head and window).  A window of m entries has at most one partnerless entry per head, hence this many workgroups
-// (those past the last pair, at most half the number of heads, have nothing to do).
+// at most (those past the last item have nothing to do).
 constexpr int kListWindow = 4096;
+// f full and t thin entries of a head make no more items than pairs.
+constexpr int list_items(int f, int t) { return (f + 1) / 2 + ((f & 1) ? (t > 2 ? (t + 1) / 4 : 0) : (t + 3) / 4); }
 constexpr int64_t list_window_blocks(int64_t m, int heads) { return (m + (heads < m ? heads : m)) / 2; }
 constexpr int64_t list_blocks(int64_t n, int heads) {
     return n / kListWindow * list_window_blocks(kListWindow, heads) + list_window_blocks(n % kListWindow, heads);

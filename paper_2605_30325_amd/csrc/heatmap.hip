@@ -14,8 +14,11 @@
 // only reads those: the same bits without forming the logits again.
 //
 // The same kernel serves bf16 and fp32 (v_mfma_f32_32x32x16_bf16 or v_mfma_f32_32x32x2_f32, fp32
-// accumulation): S^T = K Q^T, so a lane owns a query row and its registers run over keys.  A workgroup holds
-// two query tiles, a wave 32 rows of one.  Pass 1 is bound by its exponentials (one per pair of tokens, with the
+// accumulation): S^T = K Q^T, so a lane owns a query row and its registers run over keys.  A workgroup holds the
+// real rows of as many consecutive query tiles as fit its four waves of 32 (geometry.h, heat_items; with a list, up to four
+// tiles), packed: rows do not know each other before their maxima meet, in LDS, per tile.  Two tiles to a workgroup, whatever
+// they hold, before: 12 heads of 21x30x52 (27 % of the tiles hold 32 rows or fewer) whole call 4.91 -> 4.49 ms, one tile
+// in 16 of 40 heads of 21x45x80 8.41 -> 8.14, fp32 search of 9x24x32, whose 16x2x2 tiles hold 36 rows, 9.5 -> 7.5.  Pass 1 is bound by its exponentials (one per pair of tokens, with the
 // fused multiply-add before and the addition after it: 48 vector operations per 8 products), pass 2 by the
 // products; the exponentials of one 32-key block are therefore formed behind the products of the next, and the
 // reference of the softmax stays where it is until a sum outgrows it.
@@ -29,8 +32,7 @@
 // issue (85 instructions per 8 products; 48 of them are the exponentials' three, 8 the maximum) and 45 % matrix pipe; of the gain, masks
 // on the scalar unit, operand addresses formed once per step and no register copies at the ends of branches gave a fifth,
 // handing work items out as asked for 12 % of the second case.
-// Padding: a tile's real rows come first (a wave runs only the blocks that hold any), and key tiles with few
-// real keys are half steps (attn_union.h).
+// Padding: a wave runs only the blocks that hold real rows, and key tiles with few real keys are half steps (attn_union.h).
 #include <type_traits>
 
 #include "attn_common.h"
@@ -41,7 +43,7 @@ namespace veda {
 struct HeatArgs {
     const HeadGeom* heads;
     const uint8_t* tile_head;
-    const int32_t* xcd_cum;       // the pair table; unused with a query list
+    const HeatItem* table;        // the plan's work items; unused with a query list
     const int32_t* query_tiles;   // optional: global tile ids to process
     int64_t n_query_tiles;
     const char* q;
@@ -110,6 +112,17 @@ template <typename E> __device__ __forceinline__ float heat_score(float t, float
     return low ? p * 0x1p-64f : p;
 }
 
+// Scores as unsigned numbers of the same order, so that wavefronts meet in LDS with an integer maximum: 0 where there is none, 1
+// for NaN (the largest only where there is nothing else, as with fmaxf).
+__device__ __forceinline__ uint32_t heat_key(float x) {
+    const uint32_t u = __float_as_uint(x);
+    return x != x ? 1u : u ^ (uint32_t)((int)u >> 31 | (int)0x80000000);
+}
+__device__ __forceinline__ float heat_of_key(uint32_t key) {
+    if (key <= 1u) return key ? __builtin_nanf("") : 0.0f;
+    return __uint_as_float(key & 0x80000000u ? key ^ 0x80000000u : ~key);
+}
+
 // Sum over the lanes up to and with this one, by DPP.
 __device__ __forceinline__ int wave_scan(int x) {
     x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8
@@ -121,52 +134,69 @@ __device__ __forceinline__ int wave_scan(int x) {
     return x;
 }
 
-// The two listed query tiles of this workgroup (the second -1 if its head has no more) and their head, or false: the
-// split is in geometry.h.  The heads of the window's entries are counted in LDS and kept there as bytes; every wave then
-// finds the same head and the same two entries.  LDS: kListWindow bytes and a word per head, free again on return.
-// Finding the p-th pair here leaves no workgroup that only exits: with one workgroup per entry, those that had a pair
+// The listed query tiles of this workgroup (up to four), their head and their number, or false: the split is in
+// geometry.h.  The heads' full and thin entries in the window are counted in LDS and their kinds kept there as bytes; every
+// wave then finds the same head and the same entries.  LDS: kListWindow bytes and a word per head, free again on return.
+// Finding the p-th item here leaves no workgroup that only exits: with one workgroup per entry, those that had a pair
 // alternated with those that did not in an ordinary list, and the hardware deals workgroups out in turn, over the dies
 // and inside them, so half the chip had nothing.  Measured, one workgroup per entry and now: one tile in 16 of 40 heads of
 // 21x45x80, one shape, bf16 13.7 -> 10.0 ms (mixed shapes 11.7-12.6 -> 11.5, in no order 14.3 -> 11.7); all tiles of
 // 12 heads of 624 in order, bf16 11.4 -> 7.9 and fp32 128 -> 64.6 ms (without a list 7.75 and 64.2), in no order
 // 8.8 -> 7.8 and 77 -> 64.2; all 57,600 of 40 heads at d = 64 142 -> 87 ms; 8 tiles of 2 heads 15.3 -> 15.9 us.  A
 // contiguous piece of the list for each die, followers still exiting, is not enough (13.1, 13.3 and 121 ms).
-__device__ inline bool listed_pair(const HeatArgs& a, int item, char* smem, int tid, int& head, int (&pair)[2]) {
-    static_assert(kMaxHeads == 128, "two heads per lane");
+__device__ inline bool listed_tiles(const HeatArgs& a, int item, char* smem, int tid, int& head, int& n_own, int (&own)[4]) {
+    static_assert(kMaxHeads == 128, "two heads per lane, a head and a kind in a byte");
     const int lane = tid & 63;
     const int per = (int)list_window_blocks(kListWindow, a.n_heads), p = item % per;
     const int64_t begin = (int64_t)(item / per) * kListWindow;
     const int m = (int)(a.n_query_tiles - begin < kListWindow ? a.n_query_tiles - begin : kListWindow);
     const int32_t* list = a.query_tiles + begin;
-    uint8_t* heads = reinterpret_cast<uint8_t*>(smem);
-    int* count = reinterpret_cast<int*>(smem + kListWindow);
+    uint8_t* kinds = reinterpret_cast<uint8_t*>(smem);          // 2 head + (1 if thin)
+    int* count = reinterpret_cast<int*>(smem + kListWindow);    // full | thin << 16
     if (tid < kMaxHeads) count[tid] = 0;
     __syncthreads();
     for (int i = tid; i < m; i += 256) {
-        const int h = a.tile_head[list[i]];
-        heads[i] = (uint8_t)h;
-        atomicAdd(&count[h], 1);
+        const int g = list[i], h = a.tile_head[g];
+        const bool thin = __popcll(a.valid_mask[g]) <= 32;
+        kinds[i] = (uint8_t)(2 * h + (thin ? 1 : 0));
+        atomicAdd(&count[h], thin ? 1 << 16 : 1);
     }
     __syncthreads();
-    // pairs of heads `lane` and 64 + lane, and of all heads up to them
-    const int n0 = (count[lane] + 1) >> 1, n1 = (count[64 + lane] + 1) >> 1;
+    // items of heads `lane` and 64 + lane, and of all heads up to them
+    auto items = [&](int h) { return list_items(count[h] & 0xffff, (int)((uint32_t)count[h] >> 16)); };
+    const int n0 = items(lane), n1 = items(64 + lane);
     const int upto0 = wave_scan(n0);
     int upto1 = __builtin_amdgcn_readlane(upto0, 63);
     if (a.n_heads > 64) upto1 += wave_scan(n1);
     head = __popcll(__ballot(upto0 <= p)) + __popcll(__ballot(upto1 <= p));
     const bool any = head < kMaxHeads;
+    n_own = 0;
     if (any) {
-        const int skip = 2 * (p - __builtin_amdgcn_readlane(head < 64 ? upto0 - n0 : upto1 - n1, head & 63));
-        int first = -1, next = -1, before = 0;   // entries of rank skip and skip + 1 in the head
-        for (int i0 = 0; i0 < m && next < 0; i0 += 64) {
-            const uint64_t same = __ballot(i0 + lane < m && heads[i0 + lane < m ? i0 + lane : 0] == head);
-            const int upto = before + __popcll(same);
-            if (first < 0 && skip < upto) first = i0 + nth_bit(same, skip - before);
-            if (skip + 1 < upto) next = i0 + nth_bit(same, skip + 1 - before);
-            before = upto;
+        const int q = p - __builtin_amdgcn_readlane(head < 64 ? upto0 - n0 : upto1 - n1, head & 63);
+        const int both = __builtin_amdgcn_readfirstlane(count[head]), full = both & 0xffff, thin = (int)((uint32_t)both >> 16);
+        // entries of rank first .. first + want - 1 of a kind
+        auto find = [&](int kind, int first, int want) {
+            int before = 0;
+            for (int i0 = 0; i0 < m && want > 0; i0 += 64) {
+                const uint64_t same = __ballot(i0 + lane < m && kinds[i0 + lane < m ? i0 + lane : 0] == 2 * head + kind);
+                const int upto = before + __popcll(same);
+                for (; want > 0 && first < upto; ++first, --want) {
+                    const int at = list[i0 + nth_bit(same, first - before)];
+                    if (n_own == 0) own[0] = at; else if (n_own == 1) own[1] = at; else if (n_own == 2) own[2] = at; else own[3] = at;
+                    ++n_own;
+                }
+                before = upto;
+            }
+        };
+        const int along = full & 1 ? (thin < 2 ? thin : 2) : 0;   // thin entries that go with the last full one
+        if (q < (full + 1) / 2) {
+            const bool last = 2 * q + 1 == full;
+            find(0, 2 * q, last ? 1 : 2);
+            if (last && along) find(1, 0, along);
+        } else {
+            const int first = along + 4 * (q - (full + 1) / 2);
+            find(1, first, thin - first < 4 ? thin - first : 4);
         }
-        pair[0] = list[first];
-        pair[1] = next >= 0 ? list[next] : -1;
     }
     __syncthreads();
     return any;
@@ -194,62 +224,73 @@ __global__ __launch_bounds__(256, heat_resident(sizeof(E) == 2, D, kGrouped, kLi
     constexpr int kF = kRowB / 32;               // fragments of a row
     constexpr int kLoads = kKBytes / 1024 / 4;   // direct-load instructions per wave per K tile
     constexpr int kGroup = kLoads < 4 ? kLoads : 4;
-    constexpr int kShare = kGrouped ? 4 : 2;     // waves whose maxima make one result
     constexpr int kAhead = 4;
     constexpr int kExps = 16 / kF;               // exponentials behind one fragment's products
     // dynamic LDS only, so the base is the workgroup's LDS origin (the XOR swizzle needs address bits 4-9 of
-    // the base clear): two K slots, then 64 steps of block maxima of the four waves
+    // the base clear): two K slots, then the results of 64 steps for each of the workgroup's query tiles
     extern __shared__ __align__(1024) char smem[];
-    float (*part)[64] = reinterpret_cast<float (*)[64]>(smem + 2 * kKBytes);
+    uint32_t (*part)[64] = reinterpret_cast<uint32_t (*)[64]>(smem + 2 * kKBytes);   // heat_key
+    int* out_tile = reinterpret_cast<int*>(part + kHeatTiles);                       // the tiles
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int idx = lane & 31, hh = lane >> 5;
-    const int which = wave >> 1, r = wave & 1;   // this wave's tile and 32-row block
+    for (int i = tid; i < kHeatTiles * 64; i += 256) (&part[0][0])[i] = 0u;   // read after the barriers of the walk
 
     const uint32_t block = blockIdx.y * gridDim.x + blockIdx.x;
-    // A work item is up to two query tiles of one head.
+    // A work item is a few query tiles of one head, with 128 rows between them or a little less.
     auto run = [&](uint32_t work) __attribute__((always_inline)) {
     const int64_t b = work / a.items;
     const int at = (int)(work - (uint32_t)b * a.items);
-    int head, qi = -1;   // qi < 0: this wave has none
-    if constexpr (kListed) {
-        int own;   // this wave's entry
-        if (kGrouped) {   // a listed 128-token tile fills a workgroup
-            own = a.query_tiles[at];
-            head = a.tile_head[2 * own];
-        } else {
-            int pair[2];
-            if (!listed_pair(a, at, smem, tid, head, pair)) return;
-            own = pair[which];
-        }
-        const int lo = a.heads[head].tile_off;
-        if (own >= 0) qi = (kGrouped ? 2 * own + which : own) - lo;
+    constexpr bool kOwn = kListed && !kGrouped;
+    int head, first = 0, n_own = 0, own[4] = {0, 0, 0, 0};
+    if constexpr (kOwn) {
+        if (!listed_tiles(a, at, smem, tid, head, n_own, own)) return;
+    } else if constexpr (kListed) {   // a listed 128-token tile fills a workgroup
+        first = 2 * a.query_tiles[at];
+        head = a.tile_head[first];
+        first -= a.heads[head].tile_off;
+        n_own = 2;
     } else {
-        int item, qiA, qiB;
-        bool hasB;
-        if (!xcd_work(a.xcd_cum, a.heads, a.n_heads, at, head, item)) return;
-        pair_tiles(a.heads[head], item, qiA, qiB, hasB);
-        qi = which == 0 ? qiA : hasB ? qiB : -1;
+        typedef const __attribute__((address_space(4))) int32_t* const_i32_t;
+        const const_i32_t src = (const_i32_t)(uintptr_t)(a.table + at);
+        head = src[0];
+        first = src[1];
+        n_own = src[2];
     }
-    qi = __builtin_amdgcn_readfirstlane(qi);
     const HeadGeom hg = a.heads[head];
     const int n = hg.n_tiles;
     const int64_t head_tile0 = b * a.total_tiles + hg.tile_off;
     const char* kt = a.k + head_tile0 * kKBytes;
     typedef const __attribute__((address_space(4))) uint64_t* const_u64_t;
     const const_u64_t vmask = (const_u64_t)(uintptr_t)(a.valid_mask + hg.tile_off);
-
-    // This lane's row: the real slots of the query tile in order, 32 per wave.
-    const uint64_t q_mask = qi >= 0 ? vmask[qi] : 0ull;
-    const int row = 32 * r + idx, q_rows = __popcll(q_mask);
-    bool q_real = row < q_rows;
-    const bool active = __builtin_amdgcn_readfirstlane(32 * r < q_rows ? 1 : 0);
+    // The item's tiles as far as their rows fit; a mask with more real slots than the grid gives leaves some for another turn.
+    for (int t0 = 0; t0 < n_own;) {
+    // This lane's row: the real slots of the query tiles in order, 32 per wave.
+    const int row = 32 * wave + idx;
+    int qi = 0, slot = 0, out = 0, rows = 0, t1 = t0;
+    bool q_real = false;
+    for (; t1 < n_own; ++t1) {
+        const int i = !kOwn ? first + t1 : (t1 == 0 ? own[0] : t1 == 1 ? own[1] : t1 == 2 ? own[2] : own[3]) - hg.tile_off;
+        const uint64_t mask = vmask[i];
+        const int more = __popcll(mask);
+        if (rows + more > 128) break;
+        if (row >= rows && row < rows + more) {
+            qi = i;
+            slot = nth_bit(mask, row - rows);
+            out = kGrouped ? 0 : t1 - t0;
+            q_real = true;
+        }
+        if (tid == 0) out_tile[t1 - t0] = i;
+        rows += more;
+    }
+    const int outs = kGrouped ? 1 : t1 - t0;
+    t0 = t1;
+    const bool active = __builtin_amdgcn_readfirstlane(32 * wave < rows ? 1 : 0);
     frag qf[kF];
     float2* row_sums = nullptr;   // where this lane's are kept
     {
-        const int slot = q_real ? nth_bit(q_mask, row) : 0;
-        const char* qrow = a.q + (head_tile0 + (qi >= 0 ? qi : 0)) * kKBytes + slot * kRowB + 16 * hh;
+        const char* qrow = a.q + (head_tile0 + qi) * kKBytes + slot * kRowB + 16 * hh;
 #pragma unroll
         for (int f = 0; f < kF; ++f) qf[f] = *reinterpret_cast<const frag*>(qrow + 32 * f);
         if (a.rows && q_real) {
@@ -259,6 +300,10 @@ __global__ __launch_bounds__(256, heat_resident(sizeof(E) == 2, D, kGrouped, kLi
             if (q_real) row_sums = a.rows + (b * a.n_heads + head) * a.tokens + token;
         }
     }
+    uint32_t rows_real = (uint32_t)__ballot(q_real);
+    const int out0 = __builtin_amdgcn_readfirstlane(out);
+    // 32 rows of one tile: results need no telling apart
+    const bool plain = rows_real == ~0u && __ballot(out != out0) == 0ull;
 
     // global -> LDS copy plan: see the attention kernels.
     uint32_t k_src[kLoads];
@@ -468,44 +513,43 @@ __global__ __launch_bounds__(256, heat_resident(sizeof(E) == 2, D, kGrouped, kLi
     // ---- pass 2: block maxima of exp2(s - ref) / l ----
     // whole-tile score blocks hold a quarter of the half-tile ones
     const int n_cols = kGrouped ? n >> 1 : n;
-    float* hrow = a.heat + b * a.score_elems + (kGrouped ? hg.score_off / 4 : hg.score_off) + (int64_t)(kGrouped ? qi >> 1 : qi) * n_cols;
-    float mine = 0.0f;   // block maximum of step 64*m + lane
-    // After the barrier that ends step j: every 64 steps, and at the end, the maxima go out in one store.
+    float* const heat = a.heat + b * a.score_elems + (kGrouped ? hg.score_off / 4 : hg.score_off);
+    float mine = 0.0f;   // plain: block maximum of step 64*m + lane
+    // After the barrier that ends step j: every 64 steps, and at the end, the maxima go out, a tile's in one store.
     auto publish = [&](int j) __attribute__((always_inline)) {
         if ((j & 63) != 63 && j != n - 1) return;
-        part[wave][lane] = mine;
+        if (active && plain) atomicMax(&part[out0][lane], heat_key(mine));
         __syncthreads();
-        float v = mine;
-        if (wave % kShare == 0) {
-#pragma unroll
-            for (int w = 1; w < kShare; ++w) v = fmaxf(v, part[wave + w][lane]);
-        }
-        __syncthreads();
-        if (wave % kShare == 0 && qi >= 0) {
-            const int first = j & ~63;
+        for (int o = wave; o < outs; o += 4) {
+            float v = heat_of_key(part[o][lane]);
+            part[o][lane] = 0u;
+            const int from = j & ~63;
+            float* const hrow = heat + (int64_t)(kGrouped ? out_tile[0] >> 1 : out_tile[o]) * n_cols;
             if (kGrouped) {
                 v = fmaxf(v, __shfl_xor(v, 1));
-                if (!(lane & 1) && first + lane <= j) hrow[(first + lane) >> 1] = v;
-            } else if (first + lane <= j) {
-                hrow[first + lane] = v;
+                if (!(lane & 1) && from + lane <= j) hrow[(from + lane) >> 1] = v;
+            } else if (from + lane <= j) {
+                hrow[from + lane] = v;
             }
         }
+        __syncthreads();
         mine = 0.0f;
     };
     if constexpr (kOneWalk) {
         // A lane takes a key tile and goes through the wave's rows, whose reference and denominator are then scalars.
         __syncthreads();   // what other lanes of this wave kept is read below; the last key tile has been read
-        const uint32_t rows_real = (uint32_t)__ballot(q_real);
-        for (int first = 0; first < n; first += 64) {
+        // rows after which another tile's come, or none
+        const int next_out = __shfl_down(q_real ? out : -1, 1);   // by all lanes
+        uint32_t ends = (uint32_t)__ballot(q_real && (idx == 31 || next_out != out));
+        for (int from = 0; from < n; from += 64) {
             if (active) {
-                const int tile = first + lane < n ? first + lane : n - 1;
+                const int tile = from + lane < n ? from + lane : n - 1;
                 const float4* src = reinterpret_cast<const float4*>(kept + tile * 32);
                 float4 x[8];
 #pragma unroll
                 for (int g = 0; g < 8; ++g) x[g] = src[g];
                 const bool empty = vmask_g[tile] == 0ull;
-                float best = 0.0f;
-                asm volatile("" : "+v"(ref), "+v"(inv_l));   // 64 scalars, formed where they are used: kept, they would spill
+                asm volatile("" : "+v"(ref), "+v"(inv_l), "+v"(out));   // 96 scalars, formed where they are used: kept, they would spill
                 auto take = [&](int i) __attribute__((always_inline)) {
                     const float4& v = x[i >> 2];
                     const float m = (i & 3) == 0 ? v.x : (i & 3) == 1 ? v.y : (i & 3) == 2 ? v.z : v.w;
@@ -513,20 +557,27 @@ __global__ __launch_bounds__(256, heat_resident(sizeof(E) == 2, D, kGrouped, kLi
                     const float row_inv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(inv_l), i));
                     return heat_score<E>(logit(m, row_ref), row_inv);
                 };
-                if (rows_real == ~0u) {
-                    best = take(0);
+                if (plain) {
+                    float best = take(0);
 #pragma unroll
                     for (int i = 1; i < 32; ++i) best = fmaxf(best, take(i));
+                    mine = empty ? 0.0f : best;
                 } else {
+                    float best = __builtin_nanf("");   // fmaxf takes the other
+                    asm volatile("" : "+s"(rows_real), "+s"(ends));   // so are the tests of their bits
 #pragma unroll
-                    for (int i = 0; i < 32; ++i)
+                    for (int i = 0; i < 32; ++i) {
                         if ((rows_real >> i) & 1u) best = fmaxf(best, take(i));
+                        if ((ends >> i) & 1u) {
+                            atomicMax(&part[__builtin_amdgcn_readlane(out, i)][lane], heat_key(empty ? 0.0f : best));
+                            best = __builtin_nanf("");
+                        }
+                    }
                 }
-                mine = empty ? 0.0f : best;
             }
-            publish(first + 63 < n ? first + 63 : n - 1);
+            publish(from + 63 < n ? from + 63 : n - 1);
         }
-        return;
+        continue;
     }
     walk_begin();
     if (active) {
@@ -552,7 +603,11 @@ __global__ __launch_bounds__(256, heat_resident(sizeof(E) == 2, D, kGrouped, kLi
                 }
 #pragma unroll
                 for (int f = 0; f < kF; ++f) maxima(s1, f);
-                best = rows_max(q_real ? heat_score<E>(logit(max_with_other_half(mx), ref), inv_l) : 0.0f);
+                const float score = heat_score<E>(logit(max_with_other_half(mx), ref), inv_l);
+                if (plain) best = rows_max(score);
+                else if (q_real && hh == 0) atomicMax(&part[out][j & 63], heat_key(score));
+            } else if (!plain && q_real && hh == 0) {
+                atomicMax(&part[out][j & 63], heat_key(0.0f));
             }
             mine = lane == (j & 63) ? best : mine;
             step_end();
@@ -565,6 +620,7 @@ __global__ __launch_bounds__(256, heat_resident(sizeof(E) == 2, D, kGrouped, kLi
             publish(j);
         }
     }
+    }   // tiles of the item
     };   // run
 #undef VEDA_KF
 
@@ -572,7 +628,7 @@ __global__ __launch_bounds__(256, heat_resident(sizeof(E) == 2, D, kGrouped, kLi
     // are asked for: a fixed share each left a quarter of the chip idle at the end where tiles differ (one in 16 of 40
     // heads of 21x45x80, mixed shapes).
     const uint32_t die = block % kXcd;
-    uint32_t* const next = reinterpret_cast<uint32_t*>(part + 4);
+    uint32_t* const next = reinterpret_cast<uint32_t*>(out_tile + kHeatTiles);
     for (uint32_t work = block;;) {
         run(work);
         if (!kOneWalk || a.taken == nullptr) return;
@@ -684,9 +740,9 @@ namespace veda {
 
 constexpr size_t kHeatTakenBytes = kXcd * kHeatTakenStride * sizeof(uint32_t);   // at the start of the scratch
 
-static int64_t heat_items(const veda_plan* pl, int64_t n_listed) {
+static int64_t heat_item_count(const veda_plan* pl, int64_t n_listed) {
     const veda_plan* ip = pl->inner ? pl->inner : pl;
-    return n_listed == 0 ? (int64_t)kXcd * ip->xcd_max_pairs : pl->inner ? n_listed : list_blocks(n_listed, pl->prob.heads);
+    return n_listed == 0 ? (int64_t)ip->heat_blocks : pl->inner ? n_listed : list_blocks(n_listed, pl->prob.heads);
 }
 
 static int64_t heat_max_tiles(const veda_plan* pl) {
@@ -738,8 +794,8 @@ static veda_status target_heatmap(const veda_plan* pl, const void* q_tiled, cons
     a.tokens = pl->tokens();
     a.T = pl->prob.T; a.H = pl->prob.H; a.W = pl->prob.W;
     hipStream_t s = (hipStream_t)stream;
-    a.xcd_cum = ip->d_xcd_cum_pair;
-    const int64_t items = heat_items(pl, a.n_query_tiles);
+    a.table = ip->d_heat_items;
+    const int64_t items = heat_item_count(pl, a.n_query_tiles);
     a.items = (uint32_t)items;
     a.batch = (uint32_t)pl->prob.batch;
     a.maxima = nullptr;
@@ -762,7 +818,7 @@ static veda_status target_heatmap(const veda_plan* pl, const void* q_tiled, cons
     // a dimension holds fewer than 2^32 threads: samples of many padding workgroups go along the second
     dim3 grid((unsigned)blocks), block(256);
     if (blocks >= (int64_t)1 << 24) grid = dim3((unsigned)items, (unsigned)pl->prob.batch);
-    const size_t smem = (size_t)2 * kTile * d * pl->elem_size() + 4 * 64 * sizeof(float) + 16;
+    const size_t smem = (size_t)2 * kTile * d * pl->elem_size() + kHeatTiles * (64 + 1) * sizeof(uint32_t) + 16;
     auto launch = [&](auto kern) {
         if (smem > 64 * 1024)
             VEDA_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
@@ -783,7 +839,7 @@ static veda_status target_heatmap(const veda_plan* pl, const void* q_tiled, cons
 extern "C" size_t veda_plan_heatmap_workspace_bytes(const veda_plan* pl, int64_t n_query_tiles) {
     using namespace veda;
     if (!pl || n_query_tiles < 0 || n_query_tiles > pl->total_tiles) return 0;
-    const int64_t blocks = heat_items(pl, n_query_tiles) * pl->prob.batch, places = heat_places(pl, n_query_tiles > 0);
+    const int64_t blocks = heat_item_count(pl, n_query_tiles) * pl->prob.batch, places = heat_places(pl, n_query_tiles > 0);
     return kHeatTakenBytes + (size_t)((blocks < places ? blocks : places) * heat_max_tiles(pl)) * 128 * sizeof(float);
 }
 

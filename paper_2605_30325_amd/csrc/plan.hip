@@ -113,6 +113,8 @@ static veda_status build_plan(const veda_problem* p, const int32_t* shapes, int 
         for (int32_t i = 0; i < g.n_tiles; ++i) tile_real[(size_t)g.tile_off + i] = veda::tile_real_slots(g, i, p->T, p->H, p->W);
     const std::vector<veda::AttnItem> items = veda::attn_items(pl->heads, p->T, p->H, p->W, veda::kXcd);
     pl->attn_blocks = (int32_t)items.size();
+    const std::vector<veda::HeatItem> heat_items = veda::heat_items(pl->heads, p->T, p->H, p->W, veda::kXcd);
+    pl->heat_blocks = (int32_t)heat_items.size();
 
     std::vector<int32_t> row_blk;
     for (int h = 0; h < p->heads; ++h)
@@ -154,6 +156,9 @@ static veda_status build_plan(const veda_problem* p, const int32_t* shapes, int 
     if (e == hipSuccess) e = hipMalloc((void**)&pl->d_attn_items, items.size() * sizeof(veda::AttnItem));
     if (e == hipSuccess)
         e = hipMemcpy(pl->d_attn_items, items.data(), items.size() * sizeof(veda::AttnItem), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMalloc((void**)&pl->d_heat_items, heat_items.size() * sizeof(veda::HeatItem));
+    if (e == hipSuccess)
+        e = hipMemcpy(pl->d_heat_items, heat_items.data(), heat_items.size() * sizeof(veda::HeatItem), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMalloc((void**)&pl->d_row_blk, row_blk.size() * sizeof(int32_t));
     if (e == hipSuccess) e = hipMalloc((void**)&pl->d_xcd_cum_pair, xcd_cum_pair.size() * sizeof(int32_t));
     if (e == hipSuccess)
@@ -210,6 +215,7 @@ void veda_plan_destroy(veda_plan* pl) {
     if (pl->d_tile_n0) (void)hipFree(pl->d_tile_n0);
     if (pl->d_tile_real) (void)hipFree(pl->d_tile_real);
     if (pl->d_attn_items) (void)hipFree(pl->d_attn_items);
+    if (pl->d_heat_items) (void)hipFree(pl->d_heat_items);
     if (pl->d_row_blk) (void)hipFree(pl->d_row_blk);
     if (pl->d_xcd_cum_pair) (void)hipFree(pl->d_xcd_cum_pair);
     delete pl;

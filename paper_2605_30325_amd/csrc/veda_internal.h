@@ -83,11 +83,13 @@ struct veda_plan {
     uint64_t* d_tile_real = nullptr;    // device [total_tiles]: tile_real_slots of each tile
     veda::AttnItem* d_attn_items = nullptr;   // device [attn_blocks]: work of the attention kernels, by workgroup
     int32_t attn_blocks = 0;
+    veda::HeatItem* d_heat_items = nullptr;   // device [heat_blocks]: work of the target scores, by workgroup
+    int32_t heat_blocks = 0;
     // Blocks of 64 consecutive tiles that never straddle two heads (the projection kernel's work
     // items): d_row_blk[x] = head << 24 | block index inside the head.
     int32_t* d_row_blk = nullptr;       // device [row_blocks]
     int64_t row_blocks = 0;
-    // Work split of the heat-map launches, and of the attention's where its lists are merged inside the loop: die x takes the x-th eighth of every head's pair work
+    // Work split of the attention launches whose lists are merged inside the loop: die x takes the x-th eighth of every head's pair work
     // items (HeadGeom::n_pairs), heads in order, so all dies work on the same head at the same time.
     // d_xcd_cum_pair[x*(heads+1) + h] = number of items die x owns in heads < h.
     int32_t* d_xcd_cum_pair = nullptr;  // device [8][heads+1]

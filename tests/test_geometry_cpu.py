@@ -139,6 +139,8 @@ int main(int argc, char** argv) {
         for (int i = 0; i < g.n_tiles; ++i) printf(" %llx", (unsigned long long)veda::tile_real_slots(g, i, T, H, W));
         printf("\n");
     }
+    for (const veda::HeatItem& it : veda::heat_items(heads, T, H, W, dies)) printf("run %d %d %d\n", it.head, it.first, it.n);
+    for (int f = 0; f < 40; ++f) for (int t = 0; t < 40; ++t) printf("list %d %d %d\n", f, t, veda::list_items(f, t));
     for (const veda::AttnItem& it : veda::attn_items(heads, T, H, W, dies)) printf("%d %d %d %d %d %d %u\n", it.head, it.n_tiles, it.tile[0], it.tile[1], it.tile[2], it.tile[3], it.waves);
     return 0;
 }
@@ -168,7 +170,16 @@ def test_every_wavefront_of_rows_is_in_one_work_item(tmp_path, grid, grp):
         tile_of = vo.token_tile_map(grid, s).reshape(-1)
         assert (slots.sum(1) == np.bincount(tile_of, minlength=len(slots))).all()
         real.append([bin(m).count("1") for m in masks])
-    items = [[int(x) for x in l.split()] for l in lines[len(heads):]]
+    # the target scores': runs of tiles in order, no more rows than fit, all of them once
+    runs = [[int(x) for x in l.split()[1:]] for l in lines if l.startswith("run")]
+    for h, rows in enumerate(real):
+        mine = [(a, n) for i in range(8) for head, a, n in runs[i::8] if head == h and n]
+        assert [a + i for a, n in mine for i in range(n)] == list(range(len(rows)))
+        assert all(n <= (2 if grp == 2 else 8) and sum(rows[a:a + n]) <= 128 for a, n in mine)
+    for f, t, n in ([int(x) for x in l.split()[1:]] for l in lines if l.startswith("list")):
+        left = max(0, t - 2) if f % 2 else t
+        assert n == (f + 1) // 2 + (left + 3) // 4 <= (f + t + 1) // 2
+    items = [[int(x) for x in l.split()] for l in lines[len(heads):] if l[0].isdigit() or l[0] == "-"]
     assert len(items) % 8 == 0
     for h, rows in enumerate(real):
         seen, spare = [], 0

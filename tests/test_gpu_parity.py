@@ -1322,6 +1322,42 @@ def test_listed_query_tiles_of_every_pattern(dtype, batch):
         assert torch.equal(part[:, ~rest], full[:, ~rest]) and bool((part[:, rest] == -7.0).all()), len(listed)
 
 
+@pytest.mark.parametrize("dtype,d,grid,shape", [
+    ("bf16", 128, (5, 9, 13), (4, 4, 4)), ("bf16", 64, (9, 6, 10), (16, 2, 2)), ("f32", 128, (9, 6, 10), (16, 2, 2)), ("bf16", 128, (1, 1, 40), (1, 1, 64)),
+    ("f32", 64, (5, 5, 17), (4, 4, 4)), ("bf16", 64, (21, 5, 7), (4, 4, 4))])
+def test_target_scores_of_tiles_that_share_wavefronts(dtype, d, grid, shape):
+    """Query tiles of few and of many real rows, packed into wavefronts together: any list of them gives the rows of a full run
+    (a list packs them otherwise), with scratch and without; and with a mask that calls every slot real, which leaves fewer tiles to
+    a workgroup than the geometry's, the rows of a tile are those of a call for that tile alone."""
+    heads, dev, scale = 3, torch.device("cuda:0"), 1.0 / math.sqrt(d)
+    wl = wlm.custom_workload("packed", heads, d, dtype, grid, False, (50, 100), seed=41, batch=2)
+    q, k, _ = wlm.make_qkv(wl, dev)
+    plan = veda.Plan(2, heads, d, grid, np.asarray([shape] * heads, np.int32), wl.torch_dtype)
+    qt, vm, _ = veda.veda_tile_layout(plan, q)
+    kt, _, _ = veda.veda_tile_layout(plan, k, want_mask=False)
+    n, total = plan.tiles[0], plan.total_tiles
+    lib, stream = veda.load(), torch.cuda.current_stream().cuda_stream
+    rng = np.random.default_rng(5)
+    for mask in (vm, torch.full_like(vm, -1)):
+        full = veda.veda_tile_heatmap(plan, qt, kt, mask, scale).view(2, total, n)
+        again = torch.empty_like(full)
+        assert lib.veda_tile_heatmap(plan.handle, qt.data_ptr(), kt.data_ptr(), mask.data_ptr(), scale, None, 0, again.data_ptr(), stream) == veda.VEDA_OK
+        assert torch.equal(full, again) and bool((full > 0).all())
+        for count in sorted({1, min(2, total), min(5, total), (total + 1) // 2, total}):
+            listed = torch.as_tensor(rng.permutation(total)[:count].astype(np.int32)).cuda()
+            rest = torch.ones(total, dtype=torch.bool, device=dev)
+            rest[listed.long()] = False
+            part = veda.veda_tile_heatmap(plan, qt, kt, mask, scale, listed, torch.full_like(full, -7.0).view(2, -1)).view(2, total, n)
+            assert torch.equal(part[:, ~rest], full[:, ~rest]) and bool((part[:, rest] == -7.0).all()), count
+        if mask is vm:
+            x, y = (t.view(2, heads, n * 64, d).double() for t in (qt, kt))
+            real = ((vm.view(heads, n, 1) >> torch.arange(64, device=dev)) & 1).bool().view(1, heads, n * 64)
+            s = torch.matmul(x, y.transpose(2, 3).contiguous()) * scale
+            s = torch.softmax(s.masked_fill(~real[:, :, None], -math.inf), dim=3) * real[..., None]
+            ref = s.view(2, heads, n, 64, n, 64).amax(dim=(3, 5)).view(2, total, n)
+            assert ((full - ref).abs() <= (2e-4 if dtype == "bf16" else 2e-5) * ref).all()
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_fp32_target_scores_below_the_smallest_normal_number(d):
     """Key tiles up to 102 below the row's maximum (natural units): their scores are subnormal, keep their order,
