@@ -137,7 +137,8 @@ __device__ __forceinline__ void both_halves(float x, float& lo, float& hi) {
 __device__ __forceinline__ float max_with_other_half(float x) {
     float lo, hi;
     both_halves(x, lo, hi);
-    return fmaxf(lo, hi);
+    asm("v_max_f32 %0, %0, %1" : "+v"(lo) : "v"(hi));   // fmaxf would quiet both first
+    return lo;
 }
 __device__ __forceinline__ float sum_with_other_half(float x) {
     float lo, hi;

@@ -30,8 +30,10 @@
 // With scratch, whole calls of the supervision side (gathers, heat map, both top-k, recall), two walks and one: 12 heads
 // of 624 tiles 8.0 -> 5.0 ms, one in 16 tiles of 40 heads of 21x45x80 13.4 -> 8.8 ms.  While a compute unit is busy pass 1 then stands at 79 % vector
 // issue (85 instructions per 8 products; 48 of them are the exponentials' three, 8 the maximum) and 45 % matrix pipe; of the gain, masks
-// on the scalar unit, operand addresses formed once per step and no register copies at the ends of branches gave a fifth,
-// handing work items out as asked for 12 % of the second case.
+// on the scalar unit and no register copies at the ends of branches gave a fifth,
+// handing work items out as asked for 12 % of the second case.  Operand addresses that never change (two steps to a turn of the
+// loop, the slot a constant) and maxima that quiet no NaN first (61 vector instructions per 8 products): 4.49 -> 4.15 ms and
+// 8.14 -> 7.72.  Tried: the additions on the matrix pipe (v_mfma_f32_4x4x1, one a lane), 5.25 ms: they queue behind the products.
 // Padding: a wave runs only the blocks that hold real rows, and key tiles with few real keys are half steps (attn_union.h).
 #include <type_traits>
 
@@ -370,15 +372,21 @@ __global__ __launch_bounds__(256, heat_resident(sizeof(E) == 2, D, kGrouped, kLi
         wait_vmcnt<0>();
         __syncthreads();
     };
-#define VEDA_KF(block, f) (*(lds_frag_ptr)(uintptr_t)(kx[f] + (block) * (uint32_t)(32 * kRowB)))
+#define VEDA_KF(block, f) (*(lds_frag_ptr)(uintptr_t)(kx[f] + (block) * (uint32_t)(32 * kRowB)))   // block 2P, 2P + 1: of slot P
 
-    // Raw dot products of this wave's rows with the 32 keys of the step's block 0 or 1; `behind(f)` is vector work placed
+    // Raw dot products of this wave's rows with the 32 keys of an LDS block; `behind(f)` is vector work placed
     // behind the products of fragment f.
-    uint32_t kx[kF];   // operand addresses of a step's first block; the second is a constant distance away
-    auto addresses = [&](int j) __attribute__((always_inline)) {
-        const uint32_t ka = k0 + (uint32_t)((j & 1) * kKBytes);
+    uint32_t kx[kF];   // operand addresses of slot 0's first block; the others are constant distances away
 #pragma unroll
-        for (int f = 0; f < kF; ++f) kx[f] = ka ^ (uint32_t)(f << 5);
+    for (int f = 0; f < kF; ++f) kx[f] = k0 ^ (uint32_t)(f << 5);
+    // body(j, P) for every key tile j, its slot P = j % 2 a constant
+    auto walk = [&](auto body) __attribute__((always_inline)) {
+        for (int j = 0;;) {
+            body(j, std::integral_constant<uint32_t, 0u>{});
+            if (++j == n) break;
+            body(j, std::integral_constant<uint32_t, 1u>{});
+            if (++j == n) break;
+        }
     };
     auto products = [&](f32x16& s, uint32_t block, auto behind) __attribute__((always_inline)) {
         const f32x16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
@@ -448,7 +456,7 @@ __global__ __launch_bounds__(256, heat_resident(sizeof(E) == 2, D, kGrouped, kLi
         auto maxima = [&](const f32x16& s, int f, bool first) __attribute__((always_inline)) {
             if (!kOneWalk) return;
 #pragma unroll
-            for (int i = f * kExps; i < (f + 1) * kExps; ++i) mx = first && i == 0 ? s[0] : fmaxf(mx, s[i]);
+            for (int i = f * kExps; i < (f + 1) * kExps; ++i) mx = fmaxf(first && i == 0 ? -INFINITY : mx, s[i]);
         };
         auto keep = [&]() __attribute__((always_inline)) {
             if (!kOneWalk || last < 0) return;
@@ -456,17 +464,18 @@ __global__ __launch_bounds__(256, heat_resident(sizeof(E) == 2, D, kGrouped, kLi
             rows[idx] = max_with_other_half(mx);   // alike in both halves
         };
         auto exps = [&](const f32x16& s, int f) __attribute__((always_inline)) {
-            if (f == 0) sum = 0.0f;
 #pragma unroll
-            for (int i = f * kExps; i < (f + 1) * kExps; ++i) sum += __builtin_amdgcn_exp2f(logit(s[i], ref));
+            for (int i = f * kExps; i < (f + 1) * kExps; ++i) {
+                const float p = __builtin_amdgcn_exp2f(logit(s[i], ref));
+                sum = i == 0 ? p : sum + p;
+            }
         };
 #pragma unroll
         for (int i = 0; i < 16; ++i) s1[i] = -INFINITY;
-        for (int j = 0; j < n; ++j) {
+        walk([&](int j, auto P) __attribute__((always_inline)) {
             step_begin(j);
-            addresses(j);
             if (e0.kind != kStepEmpty) {
-                products(s0, 0u, [&](int f) __attribute__((always_inline)) { exps(s1, f); maxima(s1, f, false); });
+                products(s0, 2u * P, [&](int f) __attribute__((always_inline)) { exps(s1, f); maxima(s1, f, false); });
                 asm volatile("" : "+v"(sum), "+v"(mx));   // they stay behind the products: the branches below would take them along
                 keep();
                 last = j;
@@ -478,7 +487,7 @@ __global__ __launch_bounds__(256, heat_resident(sizeof(E) == 2, D, kGrouped, kLi
                     for (int i = 0; i < 16; ++i) s1[i] = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(s0[i]), 0xE4, 0xf, 0xf, true));   // quad_perm [0,1,2,3]
                     mx = -INFINITY;
                 } else {
-                    products(s1, 1u, [&](int f) __attribute__((always_inline)) { exps(s0, f); maxima(s0, f, true); });
+                    products(s1, 2u * P + 1u, [&](int f) __attribute__((always_inline)) { exps(s0, f); maxima(s0, f, true); });
                     asm volatile("" : "+v"(sum), "+v"(mx));
                     settle(s0, sum);   // before the mask's branch: the exponentials would move behind it
                     mask_keys(s1, e0.hi);
@@ -489,7 +498,7 @@ __global__ __launch_bounds__(256, heat_resident(sizeof(E) == 2, D, kGrouped, kLi
                 l_part = 0.0f;
             }
             step_end();
-        }
+        });
 #pragma unroll
         for (int f = 0; f < kF; ++f) { exps(s1, f); maxima(s1, f, false); }
         keep();
@@ -581,13 +590,12 @@ __global__ __launch_bounds__(256, heat_resident(sizeof(E) == 2, D, kGrouped, kLi
     }
     walk_begin();
     if (active) {
-        for (int j = 0; j < n; ++j) {
+        walk([&](int j, auto P) __attribute__((always_inline)) {
             step_begin(j);
-            addresses(j);
             float best = 0.0f;
             if (e0.kind != kStepEmpty) {
                 f32x16 s0, s1;
-                products(s0, 0u, [](int) {});
+                products(s0, 2u * P, [](int) {});
                 mask_keys(s0, e0.lo);
                 float mx = s0[0];
                 auto maxima = [&](const f32x16& s, int f) __attribute__((always_inline)) {
@@ -597,7 +605,7 @@ __global__ __launch_bounds__(256, heat_resident(sizeof(E) == 2, D, kGrouped, kLi
                 if (e0.kind == kStepHalf) {
                     s1 = s0;
                 } else {
-                    products(s1, 1u, [&](int f) __attribute__((always_inline)) { maxima(s0, f); });
+                    products(s1, 2u * P + 1u, [&](int f) __attribute__((always_inline)) { maxima(s0, f); });
                     asm volatile("" : "+v"(mx));   // the maxima stay behind the products
                     mask_keys(s1, e0.hi);
                 }
@@ -612,7 +620,7 @@ __global__ __launch_bounds__(256, heat_resident(sizeof(E) == 2, D, kGrouped, kLi
             mine = lane == (j & 63) ? best : mine;
             step_end();
             publish(j);
-        }
+        });
     } else {
         for (int j = 0; j < n; ++j) {
             step_begin(j);
