@@ -6,13 +6,6 @@
 
 namespace veda {
 
-// Lists up to this long take the fp32 kernel's split products.  Those are faster and nearer to the 64-bit result at any length
-// (8 heads of 624 tiles: all kept 2.6e-6 against 3.7e-6, 63 kept 6.5e-7 and 9e-7); the line only keeps long lists' results
-// near those of the fp32 chains, whose rounding grows with the root of the list and makes most of the difference: 4.1e-5 of the
-// outputs' rms at most at d = 128 and 5.8e-5 at d = 64 after 192 tiles (one head of 400), 6.1e-5 at d = 128 after 624, which is
-// more than the 5e-5 that results of this path are compared at.
-constexpr int kF32SplitTiles = 192;
-
 // Shared by the entry points: q_tiled or (q_tok, sq), k_tiled or (k_tok, sk).
 static veda_status sparse_attn(const veda_plan* pl, const void* q_tiled, const void* q_tok, veda_strides sq,
                                const void* k_tiled, const void* k_tok, veda_strides sk, const void* v_tiled,

@@ -100,11 +100,15 @@ struct AttnItem {
 constexpr uint32_t kItemSecond = 4u;   // rows 32-63 of its tile, not 0-31
 constexpr uint32_t kItemIdle = 8u;     // no rows
 
+// How many full tiles, or thin ones, share a workgroup.  The more do, the fewer key tiles are loaded and the more steps a
+// workgroup's walk has (1.1-1.3 times a list's length for two full tiles, 1.3-2.0 for four thin ones).
+struct AttnShare { int full, thin; };
+
 // Appends head h's items: those of more than two tiles, which have the most steps, before the others, each kind ordered by
 // its first tile.  Returns the number of the former.  Full tiles are paired along pair_ax (line by line; the odd ones out
 // with those of the next lines), thin ones taken four at a time by 2x2x2 blocks of the tile grid, so that tiles that share a
 // workgroup are neighbours, whose kept lists agree most.  At most two items of a head have wavefronts to spare.
-inline size_t attn_items_of_head(const HeadGeom& g, int32_t h, int T, int H, int W, std::vector<AttnItem>& items) {
+inline size_t attn_items_of_head(const HeadGeom& g, int32_t h, int T, int H, int W, AttnShare share, std::vector<AttnItem>& items) {
     const size_t first = items.size();
     auto add = [&](const int32_t* tiles, int n, int full) {   // the first `full` of them take two wavefronts
         AttnItem it = {h, n, {0, 0, 0, 0}, 0u, 0};
@@ -141,6 +145,8 @@ inline size_t attn_items_of_head(const HeadGeom& g, int32_t h, int T, int H, int
             const int32_t t = i + c * stride[ax];
             if (__builtin_popcountll(tile_real_slots(g, t, T, H, W)) <= 32) {
                 thin.push_back(t);
+            } else if (share.full == 1) {
+                add(&t, 1, 1);
             } else if (held < 0) {
                 held = t;
             } else {
@@ -160,13 +166,13 @@ inline size_t attn_items_of_head(const HeadGeom& g, int32_t h, int T, int H, int
     if (odd.size() % 2) {   // a last full tile takes along what would not fill a workgroup
         int32_t tiles[3] = {odd.back(), 0, 0};
         int n = 1;
-        for (size_t over = thin.size() % 4 < 3 ? thin.size() % 4 : 0; over > 0; --over) {
+        for (size_t over = share.thin == 4 && thin.size() % 4 < 3 ? thin.size() % 4 : 0; over > 0; --over) {
             tiles[n++] = thin.back();
             thin.pop_back();
         }
         add(tiles, n, 1);
     }
-    for (size_t i = 0; i < thin.size(); i += 4) add(&thin[i], (int)std::min<size_t>(4, thin.size() - i), 0);
+    for (size_t i = 0; i < thin.size(); i += share.thin) add(&thin[i], (int)std::min<size_t>(share.thin, thin.size() - i), 0);
     std::sort(items.begin() + first, items.end(), [](const AttnItem& a, const AttnItem& b) {
         return (a.n_tiles > 2) != (b.n_tiles > 2) ? a.n_tiles > 2 : a.tile[0] < b.tile[0];
     });
@@ -176,13 +182,13 @@ inline size_t attn_items_of_head(const HeadGeom& g, int32_t h, int T, int H, int
 // The launch table: workgroup i runs on die i % dies, and die x takes the x-th part of every head's items of either kind, heads
 // in order (all dies then work on the same head at the same time, whose K and V stay in the memory-side cache, and the
 // workgroups that share an L2 hold neighbouring query tiles).  Dies with fewer items end with empty ones.
-inline std::vector<AttnItem> attn_items(const std::vector<HeadGeom>& heads, int T, int H, int W, int dies) {
+inline std::vector<AttnItem> attn_items(const std::vector<HeadGeom>& heads, int T, int H, int W, int dies, AttnShare sharing) {
     std::vector<std::vector<AttnItem>> per(dies);
     std::vector<AttnItem> items;
     size_t most = 0;
     for (size_t h = 0; h < heads.size(); ++h) {
         items.clear();
-        const size_t many = attn_items_of_head(heads[h], (int32_t)h, T, H, W, items), n[2] = {many, items.size() - many};
+        const size_t many = attn_items_of_head(heads[h], (int32_t)h, T, H, W, sharing, items), n[2] = {many, items.size() - many};
         size_t at = 0;
         for (int kind = 0; kind < 2; ++kind)
             for (int i = 0; i < dies; ++i) {
@@ -196,7 +202,16 @@ inline std::vector<AttnItem> attn_items(const std::vector<HeadGeom>& heads, int 
     const AttnItem none = {-1, 0, {0, 0, 0, 0}, 0u, 0};
     std::vector<AttnItem> table(most * dies, none);
     for (int x = 0; x < dies; ++x)
-        for (size_t i = 0; i < per[x].size(); ++i) table[i * dies + x] = per[x][i];
+        for (size_t i = 0; i < per[x].size(); ++i) {
+            AttnItem it = per[x][i];
+            // Workgroups 32 apart on a die tend to share a compute unit: where two wavefronts or fewer have rows they are not
+            // the same ones, so not on the same SIMDs, in both.
+            int live = 0;
+            for (int w = 0; w < 4; ++w) live += (it.waves >> (8 * w) & kItemIdle) == 0u;
+            const uint32_t turn = live <= 2 ? (uint32_t)(i / 32 * live % 4) * 8u : 0u;
+            if (turn) it.waves = it.waves << turn | it.waves >> (32u - turn);
+            table[i * dies + x] = it;
+        }
     return table;
 }
 
@@ -206,7 +221,7 @@ constexpr int kHeatTiles = 8;   // at most
 struct HeatItem {
     int32_t head, first, n;   // n = 0: nothing to do (a die with fewer items than others)
 };
-inline std::vector<HeatItem> heat_items(const std::vector<HeadGeom>& heads, int T, int H, int W, int dies) {
+inline std::vector<HeatItem> heat_items(const std::vector<HeadGeom>& heads, int T, int H, int W, int dies, int most_tiles) {
     std::vector<std::vector<HeatItem>> per(dies);
     std::vector<HeatItem> items;
     size_t most = 0;
@@ -216,7 +231,7 @@ inline std::vector<HeatItem> heat_items(const std::vector<HeadGeom>& heads, int 
         int rows = 0;
         for (int32_t i = 0; i < g.n_tiles; ++i) {
             const int more = __builtin_popcountll(tile_real_slots(g, i, T, H, W));
-            const bool fits = g.grp == 2 ? i % 2 == 1 : rows + more <= 128 && !items.empty() && items.back().n < kHeatTiles;
+            const bool fits = g.grp == 2 ? i % 2 == 1 : rows + more <= 128 && !items.empty() && items.back().n < most_tiles;
             if (fits) {
                 ++items.back().n;
                 rows += more;

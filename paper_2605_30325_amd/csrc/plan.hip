@@ -111,9 +111,30 @@ static veda_status build_plan(const veda_problem* p, const int32_t* shapes, int 
     std::vector<uint64_t> tile_real((size_t)toff);
     for (const HeadGeom& g : pl->heads)
         for (int32_t i = 0; i < g.n_tiles; ++i) tile_real[(size_t)g.tile_off + i] = veda::tile_real_slots(g, i, p->T, p->H, p->W);
-    const std::vector<veda::AttnItem> items = veda::attn_items(pl->heads, p->T, p->H, p->W, veda::kXcd);
+    // With few tiles, workgroups of one tile each: no key tile is walked that the tile does not keep, and a second workgroup on a
+    // compute unit still finds room.  With more, pairs of either kind, then thin tiles in fours.  The attention alone, us, by
+    // tiles of the call, alone / pairs / fours: bf16 d = 64, 9x18x18, 25 % kept 75: 20 24 29, 474: 36 41 40, 636: 53 45 42, 954: 68 56 47;
+    // d = 128, 8x16x32, 10 % 320: 21 26 32, 512: 26 28 32, 704: 39 32 34, 1344: 64 53 41; 17x30x52, 5 % 520: 68 55 69,
+    // 1300: 132 120 111; fp32 d = 128, 9x18x18 75: 86 120 155, 318: 131 149 168, 474: 161 164 188, 636: 259 197 194.
+    // Short lists share little (19 heads of 4x15x23 at 5 tiles kept, 444 pairs: fours 5 % slower over the whole call).
+    constexpr int64_t kAlone = 512, kPairs = 512;   // workgroups, all samples
+    int32_t most_tiles = 0;
+    for (const HeadGeom& g : pl->heads) most_tiles = std::max(most_tiles, g.n_tiles);
+    // fp32 tiles that share a workgroup share the form of their products, which lists longer than kF32SplitTiles decide: where
+    // such lists can be, tiles stay with their partners.
+    const bool alone = toff * p->batch <= kAlone && (p->dtype == VEDA_BF16 || most_tiles <= veda::kF32SplitTiles);
+    std::vector<veda::AttnItem> items;
+    for (const veda::AttnShare share : {veda::AttnShare{1, 1}, veda::AttnShare{2, 2}, veda::AttnShare{2, 4}}) {
+        if (share.full == 1 && !alone) continue;
+        if (share.full == 2 && share.thin == 2 && toff * p->batch > 4 * kPairs) continue;   // more pairs than kPairs in any case
+        items = veda::attn_items(pl->heads, p->T, p->H, p->W, veda::kXcd, share);
+        int64_t busy = 0;
+        for (const veda::AttnItem& it : items) busy += it.head >= 0;
+        if (share.full == 1 || busy * p->batch <= kPairs) break;
+    }
     pl->attn_blocks = (int32_t)items.size();
-    const std::vector<veda::HeatItem> heat_items = veda::heat_items(pl->heads, p->T, p->H, p->W, veda::kXcd);
+    // With no more than two workgroups of two tiles on a compute unit, packing more of them together gains nothing.
+    const std::vector<veda::HeatItem> heat_items = veda::heat_items(pl->heads, p->T, p->H, p->W, veda::kXcd, toff * p->batch <= 1024 ? 2 : veda::kHeatTiles);
     pl->heat_blocks = (int32_t)heat_items.size();
 
     std::vector<int32_t> row_blk;

@@ -125,9 +125,9 @@ ITEMS_PROGRAM = r"""
 #include <cstdlib>
 #include "geometry.h"
 int main(int argc, char** argv) {
-    const int T = atoi(argv[1]), H = atoi(argv[2]), W = atoi(argv[3]), grp = atoi(argv[4]), dies = atoi(argv[5]);
+    const int T = atoi(argv[1]), H = atoi(argv[2]), W = atoi(argv[3]), grp = atoi(argv[4]), dies = atoi(argv[5]), full = atoi(argv[6]), thin = atoi(argv[7]);
     std::vector<veda::HeadGeom> heads;
-    for (int i = 6; i + 3 < argc; i += 4) {
+    for (int i = 8; i + 3 < argc; i += 4) {
         const int32_t shape[3] = {atoi(argv[i]), atoi(argv[i + 1]), atoi(argv[i + 2])};
         veda::HeadGeom g;
         veda::head_extents(g, shape, grp, T, H, W);
@@ -139,17 +139,17 @@ int main(int argc, char** argv) {
         for (int i = 0; i < g.n_tiles; ++i) printf(" %llx", (unsigned long long)veda::tile_real_slots(g, i, T, H, W));
         printf("\n");
     }
-    for (const veda::HeatItem& it : veda::heat_items(heads, T, H, W, dies)) printf("run %d %d %d\n", it.head, it.first, it.n);
+    for (const veda::HeatItem& it : veda::heat_items(heads, T, H, W, dies, 2 * thin)) printf("run %d %d %d\n", it.head, it.first, it.n);
     for (int f = 0; f < 40; ++f) for (int t = 0; t < 40; ++t) printf("list %d %d %d\n", f, t, veda::list_items(f, t));
-    for (const veda::AttnItem& it : veda::attn_items(heads, T, H, W, dies)) printf("%d %d %d %d %d %d %u\n", it.head, it.n_tiles, it.tile[0], it.tile[1], it.tile[2], it.tile[3], it.waves);
+    for (const veda::AttnItem& it : veda::attn_items(heads, T, H, W, dies, {full, thin})) printf("%d %d %d %d %d %d %u\n", it.head, it.n_tiles, it.tile[0], it.tile[1], it.tile[2], it.tile[3], it.waves);
     return 0;
 }
 """
 
 
-@pytest.mark.parametrize("grp", [1, 2])
+@pytest.mark.parametrize("grp,full,thin", [(1, 1, 1), (1, 2, 2), (1, 2, 4), (2, 2, 4)])
 @pytest.mark.parametrize("grid", [(1, 1, 1), (1, 2, 3), (5, 9, 13), (17, 6, 7), (21, 30, 52), (4, 57, 32), (9, 18, 18)])
-def test_every_wavefront_of_rows_is_in_one_work_item(tmp_path, grid, grp):
+def test_every_wavefront_of_rows_is_in_one_work_item(tmp_path, grid, grp, full, thin):
     """The attention kernels' launch table: every 32-row part of a query tile that holds real rows belongs to exactly one
     wavefront, at most two workgroups of a head have wavefronts to spare, and no die has more than one item of either kind over its share."""
     gxx = shutil.which("g++")
@@ -162,7 +162,7 @@ def test_every_wavefront_of_rows_is_in_one_work_item(tmp_path, grid, grp):
     axes = [3] if grp == 2 else [0, 1, 2]
     heads = [(s, ax) for s in shapes for ax in axes]
     args = [str(x) for s, ax in heads for x in (*s, ax)]
-    lines = subprocess.run([str(tmp_path / "items"), *map(str, grid), str(grp), "8", *args], capture_output=True, text=True, check=True).stdout.splitlines()
+    lines = subprocess.run([str(tmp_path / "items"), *map(str, grid), str(grp), "8", str(full), str(thin), *args], capture_output=True, text=True, check=True).stdout.splitlines()
     real = []
     for (s, _), line in zip(heads, lines):
         masks = [int(x, 16) for x in line.split()[1:]]
@@ -175,7 +175,7 @@ def test_every_wavefront_of_rows_is_in_one_work_item(tmp_path, grid, grp):
     for h, rows in enumerate(real):
         mine = [(a, n) for i in range(8) for head, a, n in runs[i::8] if head == h and n]
         assert [a + i for a, n in mine for i in range(n)] == list(range(len(rows)))
-        assert all(n <= (2 if grp == 2 else 8) and sum(rows[a:a + n]) <= 128 for a, n in mine)
+        assert all(n <= (2 if grp == 2 else 2 * thin) and sum(rows[a:a + n]) <= 128 for a, n in mine)
     for f, t, n in ([int(x) for x in l.split()[1:]] for l in lines if l.startswith("list")):
         left = max(0, t - 2) if f % 2 else t
         assert n == (f + 1) // 2 + (left + 3) // 4 <= (f + t + 1) // 2
@@ -187,7 +187,7 @@ def test_every_wavefront_of_rows_is_in_one_work_item(tmp_path, grid, grp):
         for i, (head, n, *tiles, waves) in enumerate(items):
             if head != h:
                 continue
-            assert 1 <= n <= 4 and len(set(tiles[:n])) == n and all(t == tiles[0] for t in tiles[n:])
+            assert 1 <= n <= max(full, thin) and len(set(tiles[:n])) == n and all(t == tiles[0] for t in tiles[n:])
             dies[int(n > 2), i % 8] += 1
             places = [(waves >> (8 * w)) & 255 for w in range(4)]
             live = [p for p in places if not p & 8]
@@ -196,5 +196,5 @@ def test_every_wavefront_of_rows_is_in_one_work_item(tmp_path, grid, grp):
             spare += len(live) < 4
         want = [(t, r) for t, m in enumerate(rows) for r in (0, 1) if grp == 2 or r == 0 or m > 32]
         assert sorted(seen) == want, (h, len(seen), len(want))
-        assert spare <= (0 if grp == 2 else 1 if sum(m > 32 for m in rows) % 2 == 0 else 2), (h, spare)
+        assert thin < 4 or spare <= (0 if grp == 2 else 1 if sum(m > 32 for m in rows) % 2 == 0 else 2), (h, spare)
         assert (dies.max(1) - dies.min(1)).max() <= 1
