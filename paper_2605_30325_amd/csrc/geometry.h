@@ -104,6 +104,11 @@ constexpr uint32_t kItemIdle = 8u;     // no rows
 // workgroup's walk has (1.1-1.3 times a list's length for two full tiles, 1.3-2.0 for four thin ones).
 struct AttnShare { int full, thin; };
 
+// Whether two heads' tiles are the same ones.
+inline bool same_tiles(const HeadGeom& a, const HeadGeom& b) {
+    return a.ot == b.ot && a.oh == b.oh && a.ow == b.ow && a.grp == b.grp && a.pair_ax == b.pair_ax;
+}
+
 // Appends head h's items: those of more than two tiles, which have the most steps, before the others, each kind ordered by
 // its first tile.  Returns the number of the former.  Full tiles are paired along pair_ax (line by line; the odd ones out
 // with those of the next lines), thin ones taken four at a time by 2x2x2 blocks of the tile grid, so that tiles that share a
@@ -185,10 +190,15 @@ inline size_t attn_items_of_head(const HeadGeom& g, int32_t h, int T, int H, int
 inline std::vector<AttnItem> attn_items(const std::vector<HeadGeom>& heads, int T, int H, int W, int dies, AttnShare sharing) {
     std::vector<std::vector<AttnItem>> per(dies);
     std::vector<AttnItem> items;
-    size_t most = 0;
+    size_t most = 0, many = 0;
     for (size_t h = 0; h < heads.size(); ++h) {
-        items.clear();
-        const size_t many = attn_items_of_head(heads[h], (int32_t)h, T, H, W, sharing, items), n[2] = {many, items.size() - many};
+        if (h > 0 && same_tiles(heads[h], heads[h - 1])) {
+            for (AttnItem& it : items) it.head = (int32_t)h;
+        } else {
+            items.clear();
+            many = attn_items_of_head(heads[h], (int32_t)h, T, H, W, sharing, items);
+        }
+        const size_t n[2] = {many, items.size() - many};
         size_t at = 0;
         for (int kind = 0; kind < 2; ++kind)
             for (int i = 0; i < dies; ++i) {
@@ -227,19 +237,21 @@ inline std::vector<HeatItem> heat_items(const std::vector<HeadGeom>& heads, int 
     size_t most = 0;
     for (size_t h = 0; h < heads.size(); ++h) {
         const HeadGeom& g = heads[h];
-        items.clear();
+        const bool same = h > 0 && same_tiles(g, heads[h - 1]);
+        if (!same) items.clear();
         int rows = 0;
-        for (int32_t i = 0; i < g.n_tiles; ++i) {
+        for (int32_t i = 0; i < g.n_tiles && !same; ++i) {
             const int more = __builtin_popcountll(tile_real_slots(g, i, T, H, W));
             const bool fits = g.grp == 2 ? i % 2 == 1 : rows + more <= 128 && !items.empty() && items.back().n < most_tiles;
             if (fits) {
                 ++items.back().n;
                 rows += more;
             } else {
-                items.push_back({(int32_t)h, i, 1});
+                items.push_back({0, i, 1});
                 rows = more;
             }
         }
+        for (HeatItem& it : items) it.head = (int32_t)h;
         const size_t n = items.size();
         size_t at = 0;
         for (int x = 0; x < dies; ++x) {

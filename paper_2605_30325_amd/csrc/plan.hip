@@ -1,6 +1,7 @@
 // Plan object: validates a problem, derives every head's ceil-padded tile grid (Sec. 3.1 tiles
 // of size B; Sec. 4.2 per-head shapes from Omega, Eq. 7) and uploads the per-head table.
 #include <algorithm>
+#include <cstring>
 #include <new>
 
 #include "veda_internal.h"
@@ -109,8 +110,12 @@ static veda_status build_plan(const veda_problem* p, const int32_t* shapes, int 
     }
 
     std::vector<uint64_t> tile_real((size_t)toff);
-    for (const HeadGeom& g : pl->heads)
-        for (int32_t i = 0; i < g.n_tiles; ++i) tile_real[(size_t)g.tile_off + i] = veda::tile_real_slots(g, i, p->T, p->H, p->W);
+    for (int h = 0; h < p->heads; ++h) {
+        const HeadGeom& g = pl->heads[h];
+        uint64_t* const real = tile_real.data() + g.tile_off;
+        if (h > 0 && veda::same_tiles(g, pl->heads[h - 1])) std::copy(real - g.n_tiles, real, real);
+        else for (int32_t i = 0; i < g.n_tiles; ++i) real[i] = veda::tile_real_slots(g, i, p->T, p->H, p->W);
+    }
     // With few tiles, workgroups of one tile each: no key tile is walked that the tile does not keep, and a second workgroup on a
     // compute unit still finds room.  With more, pairs of either kind, then thin tiles in fours.  The attention alone, us, by
     // tiles of the call, alone / pairs / fours: bf16 d = 64, 9x18x18, 25 % kept 75: 20 24 29, 474: 36 41 40, 636: 53 45 42, 954: 68 56 47;
@@ -166,31 +171,29 @@ static veda_status build_plan(const veda_problem* p, const int32_t* shapes, int 
             return ns;
         }
     }
-    if (e == hipSuccess) e = hipMalloc((void**)&pl->d_heads, sizeof(HeadGeom) * p->heads);
-    if (e == hipSuccess) e = hipMalloc((void**)&pl->d_tile_head, tile_head.size());
-    if (e == hipSuccess) e = hipMalloc((void**)&pl->d_tile_n0, tile_n0.size() * sizeof(int32_t));
-    if (e == hipSuccess)
-        e = hipMemcpy(pl->d_tile_n0, tile_n0.data(), tile_n0.size() * sizeof(int32_t), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc((void**)&pl->d_tile_real, tile_real.size() * sizeof(uint64_t));
-    if (e == hipSuccess)
-        e = hipMemcpy(pl->d_tile_real, tile_real.data(), tile_real.size() * sizeof(uint64_t), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc((void**)&pl->d_attn_items, items.size() * sizeof(veda::AttnItem));
-    if (e == hipSuccess)
-        e = hipMemcpy(pl->d_attn_items, items.data(), items.size() * sizeof(veda::AttnItem), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc((void**)&pl->d_heat_items, heat_items.size() * sizeof(veda::HeatItem));
-    if (e == hipSuccess)
-        e = hipMemcpy(pl->d_heat_items, heat_items.data(), heat_items.size() * sizeof(veda::HeatItem), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMalloc((void**)&pl->d_row_blk, row_blk.size() * sizeof(int32_t));
-    if (e == hipSuccess) e = hipMalloc((void**)&pl->d_xcd_cum_pair, xcd_cum_pair.size() * sizeof(int32_t));
-    if (e == hipSuccess)
-        e = hipMemcpy(pl->d_xcd_cum_pair, xcd_cum_pair.data(), xcd_cum_pair.size() * sizeof(int32_t),
-                      hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-        e = hipMemcpy(pl->d_row_blk, row_blk.data(), row_blk.size() * sizeof(int32_t), hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-        e = hipMemcpy(pl->d_heads, pl->heads.data(), sizeof(HeadGeom) * p->heads, hipMemcpyHostToDevice);
-    if (e == hipSuccess)
-        e = hipMemcpy(pl->d_tile_head, tile_head.data(), tile_head.size(), hipMemcpyHostToDevice);
+    // All tables in one allocation and one copy.  The tiling search makes a plan per candidate: with eight of each, and plans made
+    // between launches, the search of 3 heads of 5x8x9 took 1.15 ms, now 0.65; 2 x 4 heads of 9x24x32 7.6 and 6.9 ms.
+    std::vector<char> tables;
+    auto put = [&tables](const auto& v) {   // offset of a table
+        const size_t at = (tables.size() + 255) / 256 * 256;
+        tables.resize(at + v.size() * sizeof(v[0]));
+        std::memcpy(tables.data() + at, v.data(), v.size() * sizeof(v[0]));
+        return at;
+    };
+    const size_t at_heads = put(pl->heads), at_head = put(tile_head), at_n0 = put(tile_n0), at_real = put(tile_real),
+                 at_items = put(items), at_heat = put(heat_items), at_blk = put(row_blk), at_pair = put(xcd_cum_pair);
+    if (e == hipSuccess) e = hipMalloc((void**)&pl->d_tables, tables.size());
+    if (e == hipSuccess) e = hipMemcpy(pl->d_tables, tables.data(), tables.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess) {
+        pl->d_heads = reinterpret_cast<HeadGeom*>(pl->d_tables + at_heads);
+        pl->d_tile_head = reinterpret_cast<uint8_t*>(pl->d_tables + at_head);
+        pl->d_tile_n0 = reinterpret_cast<int32_t*>(pl->d_tables + at_n0);
+        pl->d_tile_real = reinterpret_cast<uint64_t*>(pl->d_tables + at_real);
+        pl->d_attn_items = reinterpret_cast<veda::AttnItem*>(pl->d_tables + at_items);
+        pl->d_heat_items = reinterpret_cast<veda::HeatItem*>(pl->d_tables + at_heat);
+        pl->d_row_blk = reinterpret_cast<int32_t*>(pl->d_tables + at_blk);
+        pl->d_xcd_cum_pair = reinterpret_cast<int32_t*>(pl->d_tables + at_pair);
+    }
     if (e != hipSuccess) {
         veda_status st = veda::hip_fail(e, "veda_plan_create");
         veda_plan_destroy(pl);
@@ -231,14 +234,7 @@ veda_status veda_plan_create(const veda_problem* p, veda_plan** out) {
 void veda_plan_destroy(veda_plan* pl) {
     if (!pl) return;
     veda_plan_destroy(pl->inner);
-    if (pl->d_heads) (void)hipFree(pl->d_heads);
-    if (pl->d_tile_head) (void)hipFree(pl->d_tile_head);
-    if (pl->d_tile_n0) (void)hipFree(pl->d_tile_n0);
-    if (pl->d_tile_real) (void)hipFree(pl->d_tile_real);
-    if (pl->d_attn_items) (void)hipFree(pl->d_attn_items);
-    if (pl->d_heat_items) (void)hipFree(pl->d_heat_items);
-    if (pl->d_row_blk) (void)hipFree(pl->d_row_blk);
-    if (pl->d_xcd_cum_pair) (void)hipFree(pl->d_xcd_cum_pair);
+    if (pl->d_tables) (void)hipFree(pl->d_tables);
     delete pl;
 }
 

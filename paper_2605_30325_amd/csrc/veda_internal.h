@@ -84,6 +84,7 @@ struct veda_plan {
     // 128-token tiles: this plan describes the whole tiles (stages 2 and 3 work on them); `inner`
     // describes their 64-slot halves, in the order 2o, 2o+1 (stages 1 and 4 work on those).
     veda_plan* inner = nullptr;
+    char* d_tables = nullptr;           // device: the one allocation of all tables below
     veda::HeadGeom* d_heads = nullptr;  // device [heads]
     uint8_t* d_tile_head = nullptr;     // device [total_tiles]: head of each global tile
     int32_t* d_tile_n0 = nullptr;       // device [total_tiles]: anchor token of each tile (tile_anchor_token: always a real token)

@@ -23,15 +23,10 @@ def keep_budget(n_tiles: Sequence[int], keep: Tuple[int, int]) -> np.ndarray:
 
 def _dense_output(plan: veda.Plan, qt, kt, vt, vm, softmax_scale: float) -> torch.Tensor:
     """Full attention through the sparse kernel with every key tile kept."""
-    dev = qt.device
-    rows = []
-    for n in plan.tiles:
-        rows.append(torch.arange(n, dtype=torch.int32, device=dev).repeat(n))
-    cols = torch.cat(rows).repeat(plan.batch)
-    counts = torch.tensor([n for _ in range(plan.batch) for n in plan.tiles for _ in range(n)], dtype=torch.int64)
-    row_ptr = torch.zeros(plan.batch * plan.total_tiles + 1, dtype=torch.int64)
-    row_ptr[1:] = torch.cumsum(counts, 0)
-    out, _ = veda.veda_sparse_attn_fwd(plan, qt, kt, vt, vm, row_ptr.to(torch.int32).to(dev), cols, softmax_scale)
+    n, rows = plan.tiles[0], plan.batch * plan.total_tiles   # one shape for all heads
+    cols = torch.arange(n, dtype=torch.int32, device=qt.device).repeat(rows)
+    row_ptr = torch.arange(rows + 1, dtype=torch.int32, device=qt.device) * n
+    out, _ = veda.veda_sparse_attn_fwd(plan, qt, kt, vt, vm, row_ptr, cols, softmax_scale)
     return out
 
 
@@ -45,9 +40,10 @@ def tiling_search(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, grid: Seque
     scale = 1.0 / math.sqrt(d) if softmax_scale is None else float(softmax_scale)
     errors = torch.zeros((heads, len(candidates)), dtype=torch.float64, device=q.device)
     o_full = row_sums = None
-    for c, shape in enumerate(candidates):
-        shapes = np.tile(np.asarray(shape, np.int32), (heads, 1))
-        plan = veda.Plan(samples, heads, d, grid, shapes, q.dtype, tile_tokens=tile_tokens)
+    # All plans before the first launch: making one, and giving its memory back, waits for the GPU.
+    plans = [veda.Plan(samples, heads, d, grid, np.tile(np.asarray(shape, np.int32), (heads, 1)), q.dtype, tile_tokens=tile_tokens)
+             for shape in candidates]
+    for c, plan in enumerate(plans):
         # The table sums squares over all tokens: split products serve lists of any length (the table moves by 1e-8).  With
         # every tile kept it would hold nothing but their rounding, so there the plain fp32 products stay.
         plan.set_option(veda.VEDA_OPT_FP32_PRODUCTS, veda.VEDA_PRODUCTS_FP32 if keep[0] >= keep[1] else veda.VEDA_PRODUCTS_SPLIT)
@@ -64,7 +60,8 @@ def tiling_search(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, grid: Seque
         o_sp, _ = veda.veda_sparse_attn_fwd(plan, qt, kt, vt, vm, row_ptr, col_idx, scale)
         err = veda.veda_output_sqerr(plan, o_full, o_sp)          # [samples, heads]
         errors[:, c] = err.sum(dim=0)
-        plan.close()
     table = errors.cpu().numpy()
+    for plan in plans:
+        plan.close()
     best = np.asarray([candidates[int(j)] for j in table.argmin(axis=1)], np.int32)
     return best, table
