@@ -111,6 +111,17 @@ template <bool kTable> __device__ __forceinline__ bool attn_work(const AttnArgs&
     }
 }
 
+// Sum over the lanes up to and with this one, by DPP.
+__device__ __forceinline__ int wave_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15, 31
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+
 // Position of the n-th set bit (from 0) of m; n < popcount(m).
 __device__ inline int nth_bit(uint64_t m, int n) {
     int pos = 0;

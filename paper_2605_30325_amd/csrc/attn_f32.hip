@@ -133,18 +133,25 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
     const int32_t* n0s_g = a.tile_n0 + hg.tile_off;
     i32x4 raw_next = {0, 0, 0, 0};
     int s_read = 0, s_done = 0, total = 0;
+    bool filled = false;   // the ring holds the first steps
     if constexpr (kTable) {
         const int32_t* cols[kLists];
 #pragma unroll
         for (int t = 0; t < kLists; ++t) cols[t] = a.col_idx + beg[t];
-        total = union_build<kLists, 256, kF32Chunk>(u, cols, cnt, it.n_tiles, hg.n_tiles, tid);
+        UnionEarly<kLists, 256, false> early;
+        early.ask(cols, cnt, it.n_tiles, hg.n_tiles, vmask_g, n0s_g, tid);
+        total = union_table<kLists, 256, kF32Chunk, false>(u, early, cols, cnt, it.n_tiles, hg.n_tiles, vmask_g, n0s_g, tid);
+        filled = true;
     }
     // to the first step; ends with a barrier
     auto begin_walk = [&]() __attribute__((always_inline)) {
         s_done = 0;
         if constexpr (kTable) {
-            union_fill<4, 256, kF32Chunk, false, 2 * kF32Chunk>(u, 0, total, hg.n_tiles, vmask_g, n0s_g, tid);   // the whole ring
-            __syncthreads();
+            if (!filled) {
+                union_fill<4, 256, kF32Chunk, false, 2 * kF32Chunk>(u, 0, total, hg.n_tiles, vmask_g, n0s_g, tid);   // the whole ring
+                __syncthreads();
+            }
+            filled = false;
             raw_next = union_read<kF32Chunk>(tab_lds, 0);
             s_read = 1;
         } else {

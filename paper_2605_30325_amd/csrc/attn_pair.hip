@@ -149,6 +149,18 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     const char* vt = a.v + head_tile0 * kVBytes;
     const const_i32_t n0s = (const_i32_t)(uintptr_t)(a.tile_n0 + hg.tile_off);
 
+    const int list_range = kGrouped ? hg.n_tiles / 2 : hg.n_tiles;
+    const uint64_t* vmask_g = a.valid_mask + hg.tile_off;
+    const int32_t* n0s_g = a.tile_n0 + hg.tile_off;
+    UnionEarly<kLists, 256, kGrouped> early;
+    const int32_t* cols[kLists];
+    if constexpr (kTable) {
+#pragma unroll
+        for (int t = 0; t < kLists; ++t) cols[t] = a.col_idx + beg[t];
+        early.ask(cols, cnt, lists, list_range, vmask_g, n0s_g, tid);
+        __builtin_amdgcn_sched_barrier(0);   // before Q's rows: loads return in order, and the table is what is waited for
+    }
+
     // Q operand (B matrix of S^T = K Q^T): lane holds query row 32r+lq, channels 16t+8hh..+8.
     // Rows are the real slots of the query tile in order: with padding among its 64 slots a tile at a ragged
     // edge fills fewer rows, and a wave whose 32 rows are all beyond the real ones has nothing to compute.
@@ -156,10 +168,10 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     const uint64_t q_real = ((const_u64_t)(uintptr_t)(a.tile_real + hg.tile_off))[qi];
     const int q_rows = place & kItemIdle ? 0 : __popcll(q_real);
     int* tok_s = reinterpret_cast<int*>(smem + 2 * kSlot + (kTable ? sizeof(Table) : 0));   // [4][32] token of each row, -1 = none
+    const bool real = 32 * r + lq < q_rows;
     {
         // from the tiled tensor, or straight from token order
         const char* qrow;
-        const bool real = 32 * r + lq < q_rows;
         int slot = 32 * r + lq;
         if (q_real != ~0ull) slot = real ? nth_bit(q_real, slot) : 0;
         const int n = real ? token_from(hg, n0s[qi], slot, a.H, a.W) : 0;
@@ -170,12 +182,15 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
             qrow = a.q + (head_tile0 + qi) * kKBytes + slot * kRowB + 16 * hh;
         }
 #pragma unroll
-        for (int t = 0; t < G; ++t) {
-            const bf16x8 raw = *reinterpret_cast<const bf16x8*>(qrow + 32 * t);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) st.qf[t][e] = real ? (__bf16)((float)raw[e] * (kExact ? a.scale_pow2 : a.scale_log2)) : (__bf16)0.0f;
-        }
+        for (int t = 0; t < G; ++t) st.qf[t] = *reinterpret_cast<const bf16x8*>(qrow + 32 * t);
     }
+    auto scale_q = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < G; ++t)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                st.qf[t][e] = real ? (__bf16)((float)st.qf[t][e] * (kExact ? a.scale_pow2 : a.scale_log2)) : (__bf16)0.0f;
+    };
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -301,16 +316,8 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     const uint32_t tab_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)&u.tab[0];
     i32x4 raw_next = {0, 0, 0, 0};
     int s_read = 0, s_done = 0, total = 0;
-    const int list_range = kGrouped ? hg.n_tiles / 2 : hg.n_tiles;
-    const uint64_t* vmask_g = a.valid_mask + hg.tile_off;
-    const int32_t* n0s_g = a.tile_n0 + hg.tile_off;
     if constexpr (kTable) {
-        const int32_t* cols[kLists];
-#pragma unroll
-        for (int t = 0; t < kLists; ++t) cols[t] = a.col_idx + beg[t];
-        total = union_build<kLists, 256, kPairChunk>(u, cols, cnt, lists, list_range, tid) * (kGrouped ? 2 : 1);
-        union_fill<kLists, 256, kPairChunk, kGrouped, 2 * kPairChunk>(u, 0, total, list_range, vmask_g, n0s_g, tid);   // the whole ring
-        __syncthreads();
+        total = union_table<kLists, 256, kPairChunk, kGrouped>(u, early, cols, cnt, lists, list_range, vmask_g, n0s_g, tid) * (kGrouped ? 2 : 1);
     } else {
         rawA = colsA[0];
         rawB = colsB[0];
@@ -381,6 +388,7 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     next_advance();
     load_tile(e0, 0, 0);
     load_tile(e0, 0, 1);
+    scale_q();
     VEDA_LOADS_DONE_BARRIER();   // also the Q loads: nothing vector-memory is pending below
 
     // One step.  A wave whose query tile keeps the current key tile does its housekeeping (loads of

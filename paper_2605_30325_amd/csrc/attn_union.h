@@ -79,38 +79,41 @@ template <int N, int kChunk> struct UnionLds {
     uint32_t bm[N][kUnionMaxWords];
     int32_t prefix[kUnionMaxWords];
     int32_t wave_sum[16];
-    int32_t total;
 };
 
-// What comes before the first product of a workgroup is a chain of loads and barriers, about 14 us for one kept
-// tile: 15 % of a call at 32 kept tiles, 10 % at 63 (the second resident workgroup computes meanwhile).  Finding
-// the head by ballot (xcd_work), asking for the lists before the bitmaps are cleared and filling the whole ring in
-// one go took 40 heads of 21x30x52 at one kept tile from 371 to 364 us.
-// Steps 1 and 2.  cols[t], n[t]: list t (global memory).  All threads of the workgroup call it;
-// it ends with a barrier.  Returns the number of steps.
-// n_tiles: the range of the list entries; lists: how many of the N there are.
-template <int N, int kThreads, int kChunk>
-__device__ inline int union_build(UnionLds<N, kChunk>& u, const int32_t* const (&cols)[N], const int (&n)[N], int lists, int n_tiles, int tid) {
-    static_assert(kUnionMaxWords % kThreads == 0, "whole words per thread");
-    constexpr int kPer = kUnionMaxWords / kThreads;
-    const int words = (n_tiles + 31) >> 5;
-    // the first entries are on their way while the bitmaps are cleared
-    int early[N];
-#pragma unroll
-    for (int t = 0; t < N; ++t) early[t] = t < lists && tid < n[t] ? cols[t][tid] : -1;
-    for (int w = tid; w < words; w += kThreads)
-#pragma unroll
-        for (int t = 0; t < N; ++t) u.bm[t][w] = 0u;
-    __syncthreads();
+// What comes before the first product of a workgroup is a chain of loads and barriers: 15 % of a call at 32 kept
+// tiles, 10 % at 63 (the second resident workgroup computes meanwhile).  Finding the head by ballot (xcd_work), asking
+// for the lists before the bitmaps are cleared and filling the whole ring in one go took 40 heads of 21x30x52 at
+// one kept tile from 371 to 364 us; union_table after that: 4 heads of 9x18x18, 2 samples, 25 % kept (d = 64, whole call)
+// 73.9 -> 72.4 us, 40 heads of 21x30x52 at 5 % 1906 -> 1895.
+
+// The lists' entries into their bitmaps, which are clear.  early: the first kThreads of each.
+template <int N, int kThreads>
+__device__ __forceinline__ void union_mark(uint32_t (&bm)[N][kUnionMaxWords], const int32_t* const (&cols)[N], const int (&n)[N],
+                                           const int (&early)[N], int lists, int n_tiles, int tid) {
 #pragma unroll
     for (int t = 0; t < N; ++t) {
         if (t >= lists) break;
         auto mark = [&](int j) {
-            if ((unsigned)j < (unsigned)n_tiles) atomicOr(&u.bm[t][j >> 5], 1u << (j & 31));
+            if ((unsigned)j < (unsigned)n_tiles) atomicOr(&bm[t][j >> 5], 1u << (j & 31));
         };
         mark(early[t]);
         for (int i = tid + kThreads; i < n[t]; i += kThreads) mark(cols[t][i]);
     }
+}
+
+// Steps 1 and 2 over many key tiles (kUnionDirectTiles).  All threads of the workgroup call it; it ends with a barrier.  Returns the number of kept key tiles.
+template <int N, int kThreads, int kChunk>
+__device__ inline int union_build(UnionLds<N, kChunk>& u, const int32_t* const (&cols)[N], const int (&n)[N], const int (&early)[N],
+                                  int lists, int n_tiles, int tid) {
+    static_assert(kUnionMaxWords % kThreads == 0, "whole words per thread");
+    constexpr int kPer = kUnionMaxWords / kThreads;
+    const int words = (n_tiles + 31) >> 5;
+    for (int w = tid; w < words; w += kThreads)
+#pragma unroll
+        for (int t = 0; t < N; ++t) u.bm[t][w] = 0u;
+    __syncthreads();
+    union_mark<N, kThreads>(u.bm, cols, n, early, lists, n_tiles, tid);
     __syncthreads();
     // exclusive prefix sum of the words' population counts: kPer consecutive words per thread
     int cnt[kPer], mine = 0;
@@ -147,7 +150,6 @@ __device__ inline int union_build(UnionLds<N, kChunk>& u, const int32_t* const (
         u.prefix[tid * kPer + p] = run;
         run += cnt[p];
     }
-    if (tid == 0) u.total = total;
     __syncthreads();
     return total;
 }
@@ -191,6 +193,98 @@ __device__ inline void union_fill(UnionLds<N, kChunk>& u, int first, int total, 
         }
         u.tab[step & (2 * kChunk - 1)] = e;
     }
+}
+
+// Lists over few key tiles: the whole table at once.  A thread stands for a key tile (of every kThreads-th) instead of a step, so
+// the tiles' masks and anchors are asked for before the lists have come and neither a search nor a second trip to memory
+// follows them; a bitmap word to a lane of a wavefront, so that every wavefront numbers the steps for itself.
+constexpr int kUnionDirectTiles = 2048;
+
+template <int N, int kThreads, bool kGrouped> struct UnionEarly {
+    static constexpr int kTurns = kUnionDirectTiles / kThreads, kHalves = kGrouped ? 2 : 1;
+    int col[N];                     // the thread's first entry of every list, or -1
+    uint64_t vm[kTurns][kHalves];   // its key tiles'
+    int32_t n0[kTurns][kHalves];
+
+    __device__ __forceinline__ void ask(const int32_t* const (&cols)[N], const int (&n)[N], int lists, int n_tiles,
+                                        const uint64_t* __restrict__ vmask, const int32_t* __restrict__ n0s, int tid) {
+#pragma unroll
+        for (int t = 0; t < N; ++t) col[t] = t < lists && tid < n[t] ? cols[t][tid] : -1;
+#pragma unroll
+        for (int i = 0; i < kTurns; ++i) {
+            if (i * kThreads >= n_tiles || n_tiles > kUnionDirectTiles) break;
+            const int j = i * kThreads + tid < n_tiles ? i * kThreads + tid : n_tiles - 1;
+#pragma unroll
+            for (int h = 0; h < kHalves; ++h) {
+                vm[i][h] = vmask[kHalves * j + h];
+                n0[i][h] = n0s[kHalves * j + h];
+            }
+        }
+    }
+};
+
+// Steps 1 and 2, and step 3 for the whole ring.  cols[t], n[t]: list t (global memory).  n_tiles: the range of the list entries; lists: how
+// many of the N there are.  All threads of the workgroup call it; it ends with a barrier.  Returns the number of
+// kept key tiles; with kGrouped each makes two steps.
+template <int N, int kThreads, int kChunk, bool kGrouped>
+__device__ inline int union_table(UnionLds<N, kChunk>& u, const UnionEarly<N, kThreads, kGrouped>& early, const int32_t* const (&cols)[N],
+                                  const int (&n)[N], int lists, int n_tiles, const uint64_t* __restrict__ vmask,
+                                  const int32_t* __restrict__ n0s, int tid) {
+    if (n_tiles > kUnionDirectTiles) {
+        const int total = union_build<N, kThreads, kChunk>(u, cols, n, early.col, lists, n_tiles, tid);
+        union_fill<N, kThreads, kChunk, kGrouped, 2 * kChunk>(u, 0, kGrouped ? 2 * total : total, n_tiles, vmask, n0s, tid);
+        __syncthreads();
+        return total;
+    }
+    constexpr int kWords = kUnionDirectTiles / 32, kRing = 2 * kChunk, kHalves = kGrouped ? 2 : 1;
+    static_assert(kWords == 64 && kThreads % 64 == 0, "a word to a lane");
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (int i = tid; i < N * kWords; i += kThreads) u.bm[i / kWords][i % kWords] = 0u;
+    for (int i = tid; i < kRing; i += kThreads) u.tab[i] = UnionEntry{0, 0, 0u, 0u};
+    __syncthreads();
+    union_mark<N, kThreads>(u.bm, cols, n, early.col, lists, n_tiles, tid);
+    __syncthreads();
+    uint32_t word = 0u;
+#pragma unroll
+    for (int t = 0; t < N; ++t) word |= u.bm[t][lane];
+    const int upto = wave_scan(__popc(word)), before = upto - __popc(word), total = __builtin_amdgcn_readlane(upto, 63);
+    if (wave == 0) u.prefix[lane] = before;   // for union_fill
+#pragma unroll
+    for (int i = 0; i < UnionEarly<N, kThreads, kGrouped>::kTurns; ++i) {
+        if (i * kThreads >= n_tiles) break;
+        const int at = i * (kThreads / 32) + 2 * wave;   // word of lanes 0-31
+        const bool up = lane >= 32;
+        const uint32_t w0 = (uint32_t)__builtin_amdgcn_readlane((int)word, at), w1 = (uint32_t)__builtin_amdgcn_readlane((int)word, at + 1);
+        const int s0 = __builtin_amdgcn_readlane(before, at), s1 = __builtin_amdgcn_readlane(before, at + 1);
+        const uint32_t w = up ? w1 : w0;
+        const int bit = lane & 31, s = (up ? s1 : s0) + __popc(w & ((1u << bit) - 1u));
+        if (((w >> bit) & 1u) && kHalves * s < kRing) {
+            int fl = 0;
+            if (kGrouped) {
+                fl = (1 << N) - 1;
+            } else {
+#pragma unroll
+                for (int t = 0; t < N; ++t) fl |= (int)((u.bm[t][at + (up ? 1 : 0)] >> bit) & 1u) << t;
+            }
+#pragma unroll
+            for (int h = 0; h < kHalves; ++h) {
+                const int j = kHalves * (i * kThreads + tid) + h;
+                u.tab[kHalves * s + h] = UnionEntry{j | fl << 16, early.n0[i][h], (uint32_t)early.vm[i][h], (uint32_t)(early.vm[i][h] >> 32)};
+            }
+        }
+    }
+    __syncthreads();
+    // the kinds, a step to a thread: above, few threads of a turn have one
+    for (int i = tid; i < kRing; i += kThreads) {
+        if (i >= kHalves * total) break;
+        UnionEntry e = u.tab[i];
+        const uint64_t vm = (uint64_t)e.w << 32 | e.z;
+        const int kind = step_kind(vm, e.z, e.w);
+        e.x = kind == kStepEmpty ? (e.x & 0xffff) | kind << 16 : e.x | kind << 16;
+        u.tab[i] = e;
+    }
+    __syncthreads();
+    return total;
 }
 
 // One step as the main loop holds it (all fields wave-uniform, in scalar registers).

@@ -125,17 +125,6 @@ __device__ __forceinline__ float heat_of_key(uint32_t key) {
     return __uint_as_float(key & 0x80000000u ? key ^ 0x80000000u : ~key);
 }
 
-// Sum over the lanes up to and with this one, by DPP.
-__device__ __forceinline__ int wave_scan(int x) {
-    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1, 2, 4, 8
-    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15, 31
-    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
-    return x;
-}
-
 // The listed query tiles of this workgroup (up to four), their head and their number, or false: the split is in
 // geometry.h.  The heads' full and thin entries in the window are counted in LDS and their kinds kept there as bytes; every
 // wave then finds the same head and the same entries.  LDS: kListWindow bytes and a word per head, free again on return.
