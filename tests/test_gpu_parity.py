@@ -323,6 +323,69 @@ def test_attention_on_hand_made_lists(dtype, d, walk):
     _hand_made_lists(dtype, d, 1.0, 1.0, walk=walk)
 
 
+@pytest.mark.parametrize("exact_scale", [False, True])
+@pytest.mark.parametrize("d,rows,cols", [(128, 16, 16), (128, 1, 257), (64, 16, 32), (64, 27, 19), (64, 1, 3)])
+def test_lists_shared_by_the_wavefronts_of_a_tile(d, rows, cols, exact_scale):
+    """256 tiles of a call at d = 128 and 512 at d = 64, up to which two halves of a workgroup share a tile's list, and one more;
+    lists of one tile, around the eight that stay whole, odd ones, and all tiles (more steps than the table holds), one
+    of them with an infinite key: against float64 softmax (bars of the bf16 path, logits of deviation 1), and the bits of the
+    lists merged inside the loop."""
+    dev, rng = torch.device("cuda:0"), np.random.default_rng(43)
+    n, grid = rows * cols, (1, 8 * rows, 8 * cols - 3)   # the last column of tiles is ragged
+    tokens = int(np.prod(grid))
+    q, k, v = (torch.as_tensor(rng.standard_normal((1, 1, tokens, d), np.float32)).to(dev, torch.bfloat16) for _ in range(3))
+    k[0, 0, -1, 3] = float("inf")   # of the last tile
+    plan = veda.Plan(1, 1, d, grid, np.asarray([(1, 8, 8)], np.int32), torch.bfloat16)
+    if exact_scale:
+        plan.set_option(veda.VEDA_OPT_EXACT_LOGIT_SCALE, 1)
+    vt, vm, _ = veda.veda_tile_layout(plan, v, veda.VEDA_CHANNEL_MAJOR)
+    sizes = [min(s, n) for s in (1, 2, 7, 8, 9, 10, 33, n)]
+    lists = [np.sort(rng.choice(n if i % 8 == 7 else max(1, n - 1), min(sizes[i % 8], n if i % 8 == 7 else n - 1), replace=False)) for i in range(n)]
+    row_ptr = torch.as_tensor(np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int32)).to(dev)
+    col_idx = torch.as_tensor(np.concatenate(lists).astype(np.int32)).to(dev)
+    outs, scale = [], 1.0 / math.sqrt(d)
+    for walk in (0, 1):
+        plan.set_option(veda.VEDA_OPT_ATTN_LIST_WALK, walk)
+        outs.append(veda.veda_sparse_attn_fwd(plan, None, None, vt, vm, row_ptr, col_idx, scale, want_lse=True, q_tokens=q, k_tokens=k))
+        torch.cuda.synchronize()
+    (out, lse), (out2, lse2) = outs
+    assert torch.equal(out.view(torch.int16), out2.view(torch.int16)) and torch.equal(lse.view(torch.int32), lse2.view(torch.int32))
+    h, w = torch.meshgrid(torch.arange(grid[1]), torch.arange(grid[2]), indexing="ij")
+    tile_of = ((h // 8) * cols + w // 8).reshape(-1).to(dev)
+    for i in list(range(min(n, 16))) + [n - 1]:
+        rows_i, kept = (tile_of == i).nonzero()[:, 0], torch.isin(tile_of, torch.as_tensor(lists[i]).to(dev))
+        s = (q[0, 0, rows_i].double() @ k[0, 0, kept].double().T) * scale
+        want, want_lse = torch.softmax(s, dim=1) @ v[0, 0, kept].double(), torch.logsumexp(s, dim=1)
+        err, fine = (out[0, 0, rows_i].double() - want).abs(), torch.isfinite(want_lse)
+        assert bool((torch.isfinite(out[0, 0, rows_i].float()).all(dim=1) == fine).all()), i
+        assert float(err[fine].max()) <= hz.BF16_MAX_ABS and float(err[fine].mean()) <= hz.BF16_MEAN_ABS, i
+        assert float((lse[0, 0, rows_i].double() - want_lse)[fine].abs().max()) <= 2e-2, i
+
+
+@pytest.mark.parametrize("tile_tokens,rows,cols", [(64, 32, 64), (64, 3, 683), (128, 32, 64), (128, 3, 683)])
+def test_step_table_up_to_and_past_a_word_a_lane(tile_tokens, rows, cols):
+    """2048 tiles of a head, a bitmap word to each lane of a wavefront, and 2049, beyond it, with lists of one tile, of the
+    last ones, and of more steps than the table holds at a time: the bits of the lists merged inside the loop."""
+    grow = tile_tokens // 64
+    grid, n, d = (grow, 8 * rows, 8 * cols - 3), rows * cols, 64   # the last column of tiles is ragged
+    dev, rng = torch.device("cuda:0"), np.random.default_rng(41)
+    q, k, v = (torch.as_tensor(rng.standard_normal((1, 1, int(np.prod(grid)), d), np.float32)).to(dev, torch.bfloat16) for _ in range(3))
+    plan = veda.Plan(1, 1, d, grid, np.asarray([(grow, 8, 8)], np.int32), torch.bfloat16, tile_tokens=tile_tokens)
+    vt, vm, _ = veda.veda_tile_layout(plan, v, veda.VEDA_CHANNEL_MAJOR)
+    sizes = np.where(np.arange(n) % 97 == 0, 300, rng.integers(1, 6, n))
+    lists = [np.sort(rng.choice(n, s, replace=False)) for s in sizes]
+    lists[1], lists[2] = np.asarray([n - 1]), np.asarray([0, n - 2, n - 1])
+    row_ptr = torch.as_tensor(np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int32)).to(dev)
+    col_idx = torch.as_tensor(np.concatenate(lists).astype(np.int32)).to(dev)
+    outs = []
+    for walk in (0, 1):
+        plan.set_option(veda.VEDA_OPT_ATTN_LIST_WALK, walk)
+        outs.append(veda.veda_sparse_attn_fwd(plan, None, None, vt, vm, row_ptr, col_idx, 0.125, want_lse=True, q_tokens=q, k_tokens=k))
+        torch.cuda.synchronize()
+    assert bool(torch.isfinite(outs[0][0].float()).all())
+    assert torch.equal(outs[0][0].view(torch.int16), outs[1][0].view(torch.int16)) and torch.equal(outs[0][1], outs[1][1])
+
+
 def test_attention_with_large_logits_fp32():
     # Queries six times larger: logits spread over +-40 in log2 units, so the running softmax
     # reference moves on many steps and a stale one would overflow or flush rows to zero.
