@@ -1,11 +1,11 @@
 // Stage 2's fixed-order fp32 chains in the form that defines them (Eq. 5): every projection output
 // and every score is ONE chain of scalar fmaf over ascending index, on the vector units.
 //
-// The kernels in score.hip issue the same chains as v_mfma_f32_32x32x2_f32, which is twice as
-// fast and gives the same bits on gfx950 -- a measured property of that instruction (its two
-// products are added to the accumulator one after the other, each rounded like an fma, denormals
+// The kernels in score.hip issue the same chains as v_mfma_f32_32x32x2_f32 (or, where few rows wait for one chain,
+// v_mfma_f32_16x16x4_f32), which is twice as fast and gives the same bits on gfx950 -- a measured property of those
+// instructions (their products are added to the accumulator one after the other, each rounded like an fma, denormals
 // kept), not one the instruction set promises.  So the measurement is part of the library:
-// probe_chain_unit() runs both forms on chains that exercise rounding, signed zeros and the
+// probe_chain_unit() runs all forms on chains that exercise rounding, signed zeros and the
 // denormal range, once per device (veda_plan_create makes the call), and a plan uses the matrix
 // cores only where every bit agreed.  The kernels here are what it uses otherwise, and what
 // VEDA_OPT_FP32_CHAIN_UNIT = VEDA_CHAINS_VECTOR selects on any device.  They are written to be
@@ -108,11 +108,12 @@ __global__ __launch_bounds__(256) void score_vector_kernel(const HeadGeom* __res
 }
 
 // The probe: 128 threads x 16 chains of 64 terms, each computed as a chain of
-// v_mfma_f32_32x32x2_f32 and as the fmaf chain it stands for; mismatch[thread] = chains whose
-// bits differ.  Inputs come from a counter hash; `kinds` gives each of the two waves one of four
+// v_mfma_f32_32x32x2_f32, as one of v_mfma_f32_16x16x4_f32 and as the fmaf chain they stand for; mismatch[thread] =
+// chains whose bits differ.  Inputs come from a counter hash; `kinds` gives each of the two waves one of four
 // recipes: ordinary magnitudes (products that round), sums in the denormal range, denormal
 // products with signed zeros among the terms, large terms that cancel.
 typedef __attribute__((ext_vector_type(16))) float probe_f32x16;
+typedef __attribute__((ext_vector_type(4))) float probe_f32x4;
 
 __device__ inline uint32_t probe_hash(uint32_t x) {
     x ^= x >> 16; x *= 0x7feb352du; x ^= x >> 15; x *= 0x846ca68bu; x ^= x >> 16;
@@ -150,6 +151,20 @@ __global__ __launch_bounds__(128) void chain_probe_kernel(int32_t* __restrict__ 
         float ref = start;
         for (int k = 0; k < 64; ++k) ref = __builtin_fmaf(xa[wave][row][k], wb[wave][k][col], ref);
         bad += __float_as_uint(ref) != __float_as_uint(acc[r]) ? 1 : 0;
+    }
+    // the 16 x 16 x 4 form, quarter by quarter: register r of lane l is row 4 (l / 16) + r, column l % 16
+    const int c16 = lane & 15, h16 = lane >> 4;
+    for (int quarter = 0; quarter < 4; ++quarter) {
+        const int row0 = 16 * (quarter >> 1), col0 = 16 * (quarter & 1);
+        probe_f32x4 part = {start, start, start, start};
+        for (int k = 0; k < 64; k += 4)
+            part = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[wave][row0 + c16][k + h16], wb[wave][k + h16][col0 + c16], part, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float ref = start;
+            for (int k = 0; k < 64; ++k) ref = __builtin_fmaf(xa[wave][row0 + 4 * h16 + r][k], wb[wave][k][col0 + c16], ref);
+            bad += __float_as_uint(ref) != __float_as_uint(part[r]) ? 1 : 0;
+        }
     }
     mismatch[threadIdx.x] = bad;
 }

@@ -416,6 +416,173 @@ __global__ __launch_bounds__(256) void mlp_staged_kernel(const HeadGeom* __restr
     }
 }
 
+// The same for few rows, where the time is that of one workgroup's chain: v_mfma_f32_16x16x4_f32 takes four terms of a chain in
+// 32 cycles where the 32 x 32 form takes two in 64 (the same bits: chain_probe_kernel), so a workgroup has 16 rows, its wavefronts
+// a quarter of the columns each, and a stage's operands are read behind the products of the one before.
+// LDS stages: weights [16][N], the 64-byte blocks of row k exchanged by k % 4 (N = 32: by k / 2 % 2), so that the four rows an
+// instruction takes lie on all banks; inputs [16][16], 16-byte chunk ^ row / 4.  The hidden layer has a place of its own.
+template <int N> struct MlpStage16 {
+    static constexpr int kBytes = 16 * N * 4, kLoads = kBytes / 1024, kRowChunks = N / 4;
+    static constexpr int kPer = kLoads >= 4 ? kLoads / 4 : 1;   // loads per wave; two loads: waves 2, 3 repeat those of 0, 1
+    static_assert(N == 128 || N == 64 || N == 32, "rows to a load, loads to a wave");
+    static __device__ __forceinline__ uint32_t lane_offset(int lane) {
+        const int row = lane / kRowChunks, c = lane % kRowChunks;
+        return (uint32_t)(row * kRowChunks + (c ^ (N == 32 ? (row >> 1 & 1) << 2 : (row & 3) << 2))) * 16u;
+    }
+    static __device__ __forceinline__ void load(const float* w, int stage, uint32_t lds, int wave, uint32_t lane_off) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int q = kLoads >= 4 ? wave * kPer + i : wave & 1;
+            // N = 128: two rows to a load, every second load the rows 2 and 3 of four
+            dma16_to_lds(lds + 1024u * q, (const char*)w + (int64_t)stage * kBytes + 1024 * q, N == 128 && (i & 1) ? lane_off ^ 128u : lane_off);
+        }
+    }
+    // of row 4i + h, columns 16c .. 16c + 15
+    static __device__ __forceinline__ uint32_t at(int i, int h, int c) {
+        return (uint32_t)((4 * i + h) * N * 4 + (c ^ (N == 32 ? h >> 1 : h)) * 64);
+    }
+};
+
+// Measured, whole calls with the kernel above and this one: 75 tiles (192 -> 64 -> 32) 50.1 -> 45.4 us, 4 heads of 75, 2 samples
+// 76.4 -> 71.8; 3 heads of 64 (384 -> 128 -> 64) 52.5 -> 48.3, 8 heads of 624 403 -> 398, 12 heads of 624 892 -> 899 (936
+// workgroups; at 192 -> 64 -> 32 384 -> 381), 40 heads of 624 1911 -> 1923: this one up to as many workgroups as are resident.
+constexpr int64_t kRows16Most = 768;   // three to a compute unit (45 KB)
+
+template <int N1, int N2>
+constexpr int kMlp16Lds = kMlpDepth * (MlpStage16<N1>::kBytes + 1024) + 16 * (N1 + 4) * 4;
+
+template <int N1, int N2>
+__global__ __launch_bounds__(256) void mlp_rows16_kernel(const HeadGeom* __restrict__ heads, const int32_t* __restrict__ row_blk,
+                                                            const float* __restrict__ zq, const float* __restrict__ zk,
+                                                            float* __restrict__ yq, float* __restrict__ yk, MlpDev pq, MlpDev pk,
+                                                            int64_t total_tiles) {
+    typedef MlpStage16<N1> W1;
+    typedef MlpStage16<N2> W2;
+    constexpr int kRows = 16, kSub = kLatentRows / kRows, kDepth = kMlpDepth;
+    constexpr int kStage = W1::kBytes + 1024, kHidden = kDepth * kStage, kPitchB = (N1 + 4) * 4;
+    constexpr int kC1 = W1::kPer + 1, kC2 = W2::kPer;   // loads per wave and stage
+    static_assert(kDepth == 4 && kC2 <= kC1, "the waits below");
+    constexpr int kCols = N1 / 64;                      // blocks of 16 columns of a wavefront
+    extern __shared__ __align__(1024) float smem[];
+    const MlpDev p = blockIdx.y == 0 ? pq : pk;
+    const int32_t code = row_blk[blockIdx.x / kSub];
+    const int head = code >> 24, first = (code & 0xffffff) * kLatentRows + (int)(blockIdx.x % kSub) * kRows;
+    const HeadGeom hg = heads[head];
+    const int rows = hg.n_tiles - first < kRows ? hg.n_tiles - first : kRows;
+    if (rows <= 0) return;
+    const int64_t row0 = (int64_t)blockIdx.z * total_tiles + hg.tile_off + first;
+    const int K = p.in_dim, n1 = K / 16;
+    constexpr int n2 = N1 / 16;
+    const char* x = (const char*)((blockIdx.y == 0 ? zq : zk) + row0 * K);
+    float* y = (blockIdx.y == 0 ? yq : yk) + row0 * N2;
+    const float* w1 = p.w1 + (int64_t)head * K * N1;
+    const float* w2 = p.w2 + (int64_t)head * N1 * N2;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), col = lane & 15, h = lane >> 4;
+    const bool has_block = 16 * wave < N2;              // of the output
+    float b1[kCols], b2 = p.b2[head * N2 + (has_block ? 16 * wave : 0) + col];
+#pragma unroll
+    for (int c = 0; c < kCols; ++c) {
+        b1[c] = p.b1[head * N1 + 16 * (kCols * wave + c) + col];
+        asm volatile("" : "+v"(b1[c]));   // have arrived before the loads that are counted
+    }
+    asm volatile("" : "+v"(b2));
+    const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)smem;
+    const uint32_t off1 = W1::lane_offset(lane), off2 = W2::lane_offset(lane);
+    uint32_t xoff;
+    {
+        const int row = lane / 4, real = row < rows ? row : rows - 1;
+        xoff = (uint32_t)(real * K * 4 + (((lane & 3) ^ ((row >> 2) & 3)) << 4));
+    }
+    // stages 0 .. n1 - 1 are the first layer's, those after them the second's
+    auto load = [&](int s) __attribute__((always_inline)) {
+        const uint32_t at = base + (uint32_t)(s % kDepth) * kStage;
+        if (s < n1) {
+            W1::load(w1, s, at, wave, off1);
+            dma16_to_lds(at + W1::kBytes, x + 64 * s, xoff);   // by all four: the same count for each
+        } else if (s < n1 + n2) {
+            W2::load(w2, s - n1, at, wave, off2);
+        }
+    };
+    // Stage s has landed everywhere: of the loads only those of the two stages after it are on their way (the second layer's are fewer).
+    auto landed = [&](int s) __attribute__((always_inline)) {
+        if (s + 2 < n1) wait_vmcnt<2 * kC1>();
+        else if (s + 2 < n1 + n2) wait_vmcnt<2 * kC2>();
+        else wait_vmcnt<0>();
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    };
+    typedef const __attribute__((address_space(3))) float* lds_f32_ptr;
+    typedef __attribute__((address_space(3))) float* lds_f32_wptr;
+    typedef __attribute__((ext_vector_type(4))) float f4;
+    struct Frag { float a[4], b[kCols][4]; };   // term 4i + h of this lane's row, and of its columns
+    auto read1 = [&](Frag& f, int s) __attribute__((always_inline)) {
+        const uint32_t at = base + (uint32_t)(s % kDepth) * kStage, xr = at + W1::kBytes + (uint32_t)(col * 64 + h * 4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            f.a[i] = *(lds_f32_ptr)(uintptr_t)(xr + (uint32_t)((i ^ (col >> 2)) << 4));
+#pragma unroll
+            for (int c = 0; c < kCols; ++c) f.b[c][i] = *(lds_f32_ptr)(uintptr_t)(at + W1::at(i, h, kCols * wave + c) + col * 4u);
+        }
+    };
+    auto read2 = [&](Frag& f, int s) __attribute__((always_inline)) {
+        const uint32_t at = base + (uint32_t)(s % kDepth) * kStage, hr = base + kHidden + (uint32_t)(col * kPitchB + (16 * (s - n1) + h) * 4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            f.a[i] = *(lds_f32_ptr)(uintptr_t)(hr + 16u * i);
+            f.b[0][i] = *(lds_f32_ptr)(uintptr_t)(at + W2::at(i, h, has_block ? wave : 0) + col * 4u);
+        }
+    };
+#pragma unroll
+    for (int s = 0; s < kDepth - 1; ++s) load(s);
+    f4 acc[kCols];
+#pragma unroll
+    for (int c = 0; c < kCols; ++c) acc[c] = f4{b1[c], b1[c], b1[c], b1[c]};
+    Frag f, next;
+    landed(0);
+    read1(f, 0);
+    for (int s = 0; s < n1; ++s) {
+        load(s + kDepth - 1);   // into the place of stage s - 1, read before everybody met for stage s
+        if (s + 1 < n1) {
+            landed(s + 1);
+            read1(next, s + 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int c = 0; c < kCols; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.a[i], f.b[c][i], acc[c], 0, 0, 0);
+        f = next;
+    }
+    const bool relu = p.relu != 0;
+#pragma unroll
+    for (int c = 0; c < kCols; ++c)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float v = (relu && !(acc[c][r] > 0.0f)) ? 0.0f : acc[c][r];
+            *(lds_f32_wptr)(uintptr_t)(base + kHidden + (uint32_t)((4 * h + r) * kPitchB + (16 * (kCols * wave + c) + col) * 4)) = v;
+        }
+    f4 out = {b2, b2, b2, b2};
+    landed(n1);   // and the hidden layer is written
+    read2(f, n1);
+    for (int s = n1; s < n1 + n2; ++s) {
+        load(s + kDepth - 1);
+        if (s + 1 < n1 + n2) {
+            landed(s + 1);
+            read2(next, s + 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (has_block) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) out = __builtin_amdgcn_mfma_f32_16x16x4f32(f.a[i], f.b[0][i], out, 0, 0, 0);
+        }
+        f = next;
+    }
+    if (has_block) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (4 * h + r < rows) y[(int64_t)(4 * h + r) * N2 + 16 * wave + col] = out[r];
+    }
+}
+
 // Both estimators alike in size, and one of the sizes above.
 template <int N1, int N2> static bool staged_sizes(const MlpDev& q, const MlpDev& k, const float* zq, const float* zk) {
     auto fits = [](const MlpDev& p) {
@@ -622,9 +789,17 @@ veda_status launch_projections(const veda_plan* pl, const veda_mlp* phi_q, const
     MlpDev pq{phi_q->in_dim, phi_q->hidden, phi_q->out_dim, phi_q->act == VEDA_ACT_RELU, phi_q->w1, phi_q->b1, phi_q->w2, phi_q->b2};
     MlpDev pk{phi_k->in_dim, phi_k->hidden, phi_k->out_dim, phi_k->act == VEDA_ACT_RELU, phi_k->w1, phi_k->b1, phi_k->w2, phi_k->b2};
     if (pl->chain_unit() == VEDA_CHAINS_VECTOR) return launch_projections_vector(pl, pq, pk, zq, zk, yq, yk, s);
+    int64_t blocks16 = 0;   // workgroups of 16 rows
+    for (const HeadGeom& g : pl->heads) blocks16 += (g.n_tiles + 15) / 16;
+    const bool rows16 = 2 * blocks16 * pl->prob.batch <= kRows16Most;
 #define VEDA_TRY_STAGED(N1, N2, ROWS)                                                                    \
     if (staged_sizes<N1, N2>(pq, pk, zq, zk)) {                                                          \
         dim3 sgrid((unsigned)(pl->row_blocks * (kLatentRows / (ROWS))), 2, (unsigned)pl->prob.batch);    \
+        if (rows16) {                                                                                    \
+            hipLaunchKernelGGL((mlp_rows16_kernel<N1, N2>), dim3((unsigned)(pl->row_blocks * (kLatentRows / 16)), 2, (unsigned)pl->prob.batch), \
+                               dim3(256), (kMlp16Lds<N1, N2>), s, pl->d_heads, pl->d_row_blk, zq, zk, yq, yk, pq, pk, pl->total_tiles); \
+            return launch_status("mlp_rows16_kernel");                                                   \
+        }                                                                                                \
         hipLaunchKernelGGL((mlp_staged_kernel<N1, N2, ROWS>), sgrid, dim3(256), kMlpDepth * (16 * (N1) * 4 + (ROWS) * 64), s, \
                            pl->d_heads, pl->d_row_blk, zq, zk, yq, yk, pq, pk, pl->total_tiles);         \
         return launch_status("mlp_staged_kernel");                                                       \

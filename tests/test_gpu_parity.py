@@ -210,6 +210,23 @@ def test_usual_estimator_sizes_bit_exact(d, tiles):
                 assert np.array_equal(got.view(np.uint32), ref.view(np.uint32)), (relu, b, h)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads,tiles", [(64, 33), (65, 33), (97, 17)])
+def test_usual_estimator_sizes_of_many_heads(d, heads, tiles):
+    """768 workgroups of 16 rows, and more, from where a workgroup takes 32 or 64: the latents' scores are those of the general kernel,
+    which serves weights at other alignments."""
+    dev, batch = torch.device("cuda:0"), 2
+    plan = veda.Plan(batch, heads, d, (4, 4, 4 * tiles), np.asarray([(4, 4, 4)] * heads, np.int32), torch.float32)
+    gen = torch.Generator(device=dev).manual_seed(tiles)
+    z = torch.randn(batch * plan.total_tiles, 3 * d, device=dev, generator=gen)
+    phi, odd = (veda.Mlp(*[np.random.default_rng(heads).uniform(-0.2, 0.2, x).astype(np.float32)
+                           for x in ((heads, 3 * d, d), (heads, d), (heads, d, d // 2), (heads, d // 2))], True, dev) for _ in range(2))
+    odd.w1 = torch.cat([torch.zeros(1, device=dev), phi.w1.reshape(-1)])[1:].view(phi.w1.shape)
+    got = [veda.veda_tile_score_stats(plan, z, z, e, e, 0.5)[0].view(torch.int32) for e in (phi, odd)]
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], got[1])
+
+
 @pytest.mark.parametrize("heads", [1, 63, 64, 65])
 def test_scores_of_many_heads_on_either_unit(heads):
     """A score block finds its head among 64 at a time; heads of 160, 224 and 140 tiles, whose last blocks hold one or three
