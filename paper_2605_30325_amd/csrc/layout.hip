@@ -43,11 +43,22 @@ __global__ __launch_bounds__(256) void layout_token_major_kernel(
 // row so that the column gathers spread over the banks.
 template <typename E, int D> constexpr int kChannelMajorWords = kTile * (D * (int)sizeof(E) / 4 + 1);   // of the stage
 
+// The plan's tables of the 64-slot tiles: what slot_token divides for.  With V's rows asked for together (channel_major_tile), whole calls
+// before and after: 75 tiles (bf16, d = 64) 45.5 -> 44.5 us, 384 tiles 43.0 -> 41.9, 12 heads of 624 (d = 128) 560 -> 553.  Tried: all 64 rows
+// of a tile asked for at once where few workgroups leave the registers, 1 % slower (longer code, fetched anew by every call).
+struct TileTables {
+    const int32_t* n0;       // anchor token
+    const uint64_t* real;    // slots inside the grid
+    __device__ __forceinline__ int token(const HeadGeom& hg, int64_t g, int l, int H, int W) const {
+        return (real[g] >> l) & 1ull ? token_from(hg, n0[g], l, H, W) : -1;
+    }
+};
+
 template <typename E, int D>
 __device__ __forceinline__ void channel_major_tile(
-    const HeadGeom* __restrict__ heads, const uint8_t* __restrict__ tile_head,
+    const HeadGeom* __restrict__ heads, const uint8_t* __restrict__ tile_head, const TileTables tables,
     const char* __restrict__ x, int64_t sb, int64_t sh, int64_t sn, char* __restrict__ out,
-    int64_t total_tiles, int T, int H, int W,
+    int64_t total_tiles, int H, int W,
     uint64_t* __restrict__ valid_mask, int32_t* __restrict__ valid_cnt, int g, int b, int* tok, uint32_t* stage) {
     constexpr int kRowBytes = D * (int)sizeof(E);
     constexpr int kRowWords = kRowBytes / 4;
@@ -56,9 +67,8 @@ __device__ __forceinline__ void channel_major_tile(
     constexpr int kEpc = 16 / (int)sizeof(E);  // elements per 16-byte output chunk
     const int head = tile_head[g];
     const HeadGeom hg = heads[head];
-    const int i = g - hg.tile_off;
     if (threadIdx.x < kTile) {
-        const int n = slot_token(hg, i, threadIdx.x, T, H, W);
+        const int n = tables.token(hg, g, threadIdx.x, H, W);
         tok[threadIdx.x] = n;
         const uint64_t m = __ballot(n >= 0);
         if (threadIdx.x == 0 && b == 0) {
@@ -68,13 +78,19 @@ __device__ __forceinline__ void channel_major_tile(
     }
     __syncthreads();
     const char* xb = x + b * sb + head * sh;
-    for (int c = threadIdx.x; c < kTile * kCpr; c += 256) {
-        const int l = c / kCpr, ch = c - l * kCpr;
-        const int n = tok[l];
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (n >= 0) v = *reinterpret_cast<const uint4*>(xb + (int64_t)n * sn + ch * 16);
+    constexpr int kPer = kTile * kCpr / 256;   // 16-byte chunks of a thread, all asked for before the first is put down; padded rows read token 0
+    uint4 v[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int c = threadIdx.x + 256 * i, l = c / kCpr, ch = c - l * kCpr, n = tok[l];
+        v[i] = *reinterpret_cast<const uint4*>(xb + (int64_t)(n >= 0 ? n : 0) * sn + ch * 16);
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int c = threadIdx.x + 256 * i, l = c / kCpr, ch = c - l * kCpr;
+        const bool real = tok[l] >= 0;
         uint32_t* s = stage + l * kPitch + ch * 4;
-        s[0] = v.x; s[1] = v.y; s[2] = v.z; s[3] = v.w;
+        s[0] = real ? v[i].x : 0u; s[1] = real ? v[i].y : 0u; s[2] = real ? v[i].z : 0u; s[3] = real ? v[i].w : 0u;
     }
     __syncthreads();
     const E* se = reinterpret_cast<const E*>(stage);
@@ -92,13 +108,13 @@ __device__ __forceinline__ void channel_major_tile(
 
 template <typename E, int D>
 __global__ __launch_bounds__(256) void layout_channel_major_kernel(
-    const HeadGeom* __restrict__ heads, const uint8_t* __restrict__ tile_head,
+    const HeadGeom* __restrict__ heads, const uint8_t* __restrict__ tile_head, TileTables tables,
     const char* __restrict__ x, int64_t sb, int64_t sh, int64_t sn, char* __restrict__ out,
-    int64_t total_tiles, int T, int H, int W,
+    int64_t total_tiles, int H, int W,
     uint64_t* __restrict__ valid_mask, int32_t* __restrict__ valid_cnt) {
     __shared__ int tok[kTile];
     __shared__ uint32_t stage[kChannelMajorWords<E, D>];
-    channel_major_tile<E, D>(heads, tile_head, x, sb, sh, sn, out, total_tiles, T, H, W, valid_mask, valid_cnt, blockIdx.x,
+    channel_major_tile<E, D>(heads, tile_head, tables, x, sb, sh, sn, out, total_tiles, H, W, valid_mask, valid_cnt, blockIdx.x,
                              blockIdx.y, tok, stage);
 }
 
@@ -153,9 +169,9 @@ template <int D, int GRP> constexpr int kStatsTok = 256 / (D / 4) * kTile * GRP;
 
 template <typename E, int D, bool kWrite, int GRP>
 __device__ __forceinline__ void layout_stats_block(
-    const HeadGeom* __restrict__ heads, const uint8_t* __restrict__ tile_head,
+    const HeadGeom* __restrict__ heads, const uint8_t* __restrict__ tile_head, const TileTables tables,
     const char* __restrict__ x, int64_t sb, int64_t sh, int64_t sn, char* __restrict__ out,
-    float* __restrict__ stats, int64_t total_tiles, int T, int H, int W,
+    float* __restrict__ stats, int64_t total_tiles, int H, int W,
     uint64_t* __restrict__ valid_mask, int32_t* __restrict__ valid_cnt, const RecipTable& recip, int blk, int b, int* tok_lds) {
     typedef typename Quad<E>::raw raw;
     constexpr int kBatch = kWrite ? Quad<E>::kBatch : Quad<E>::kBatch / 2;
@@ -172,7 +188,7 @@ __device__ __forceinline__ void layout_stats_block(
         int n = -1;
         if (g0 + tl < whole_tiles) {
             const HeadGeom hg = heads[tile_head[gi]];
-            n = slot_token(hg, (int)(gi - hg.tile_off), l % kTile, T, H, W);
+            n = tables.token(hg, gi, l % kTile, H, W);
         }
         tok[tl][l] = n;
     }
@@ -247,12 +263,12 @@ __device__ __forceinline__ void layout_stats_block(
 
 template <typename E, int D, bool kWrite, int GRP>
 __global__ __launch_bounds__(256) void layout_stats_kernel(
-    const HeadGeom* __restrict__ heads, const uint8_t* __restrict__ tile_head,
+    const HeadGeom* __restrict__ heads, const uint8_t* __restrict__ tile_head, const TileTables tables,
     const char* __restrict__ x, int64_t sb, int64_t sh, int64_t sn, char* __restrict__ out,
-    float* __restrict__ stats, int64_t total_tiles, int T, int H, int W,
+    float* __restrict__ stats, int64_t total_tiles, int H, int W,
     uint64_t* __restrict__ valid_mask, int32_t* __restrict__ valid_cnt, RecipTable recip) {
     __shared__ int tok[kStatsTok<D, GRP>];
-    layout_stats_block<E, D, kWrite, GRP>(heads, tile_head, x, sb, sh, sn, out, stats, total_tiles, T, H, W, valid_mask, valid_cnt,
+    layout_stats_block<E, D, kWrite, GRP>(heads, tile_head, tables, x, sb, sh, sn, out, stats, total_tiles, H, W, valid_mask, valid_cnt,
                                           recip, blockIdx.x, blockIdx.y, tok);
 }
 
@@ -268,24 +284,24 @@ struct LayoutPathArgs {
     uint64_t* valid_mask;
     int32_t* valid_cnt;
     int64_t total_tiles;   // of 64 slots
-    int T, H, W;
+    int H, W;
     int stats_blocks;      // workgroups of Q, and of K; V's follow
 };
 
 template <typename E, int D, bool kWrite, int GRP>
-__global__ __launch_bounds__(256) void layout_path_kernel(const HeadGeom* __restrict__ heads, const uint8_t* __restrict__ tile_head,
+__global__ __launch_bounds__(256) void layout_path_kernel(const HeadGeom* __restrict__ heads, const uint8_t* __restrict__ tile_head, TileTables tables,
                                                           LayoutPathArgs a, RecipTable recip) {
     constexpr int kV = kTile + kChannelMajorWords<E, D>, kS = kStatsTok<D, GRP>;
     __shared__ uint32_t lds[kV > kS ? kV : kS];
     const int x = blockIdx.x, b = blockIdx.y;
     if (x < 2 * a.stats_blocks) {
         const bool q = x < a.stats_blocks;   // the masks come with Q
-        layout_stats_block<E, D, kWrite, GRP>(heads, tile_head, q ? a.q : a.k, q ? a.qb : a.kb, q ? a.qh : a.kh, q ? a.qn : a.kn,
-                                              q ? a.q_tiled : a.k_tiled, q ? a.stats_q : a.stats_k, a.total_tiles, a.T, a.H, a.W,
+        layout_stats_block<E, D, kWrite, GRP>(heads, tile_head, tables, q ? a.q : a.k, q ? a.qb : a.kb, q ? a.qh : a.kh, q ? a.qn : a.kn,
+                                              q ? a.q_tiled : a.k_tiled, q ? a.stats_q : a.stats_k, a.total_tiles, a.H, a.W,
                                               q ? a.valid_mask : nullptr, q ? a.valid_cnt : nullptr, recip,
                                               q ? x : x - a.stats_blocks, b, (int*)lds);
     } else {
-        channel_major_tile<E, D>(heads, tile_head, a.v, a.vb, a.vh, a.vn, a.v_tiled, a.total_tiles, a.T, a.H, a.W, nullptr, nullptr,
+        channel_major_tile<E, D>(heads, tile_head, tables, a.v, a.vb, a.vh, a.vn, a.v_tiled, a.total_tiles, a.H, a.W, nullptr, nullptr,
                                  x - 2 * a.stats_blocks, b, (int*)lds, lds + kTile);
     }
 }
@@ -318,8 +334,8 @@ extern "C" veda_status veda_tile_layout(const veda_plan* pl, const void* x, veda
     } else {
 #define VEDA_LAUNCH_CM(E, D)                                                                           \
     hipLaunchKernelGGL((layout_channel_major_kernel<E, D>), grid, dim3(256), 0, st, ip->d_heads,        \
-                       ip->d_tile_head, (const char*)x, sb, sh, sn, (char*)x_tiled, ip->total_tiles, T, \
-                       H, W, valid_mask, cnt_arg)
+                       ip->d_tile_head, TileTables{ip->d_tile_n0, ip->d_tile_real}, (const char*)x, sb, sh, sn, (char*)x_tiled, \
+                       ip->total_tiles, H, W, valid_mask, cnt_arg)
         if (es == 2 && d == 128) VEDA_LAUNCH_CM(uint16_t, 128);
         else if (es == 2 && d == 64) VEDA_LAUNCH_CM(uint16_t, 64);
         else if (es == 4 && d == 128) VEDA_LAUNCH_CM(uint32_t, 128);
@@ -345,7 +361,7 @@ extern "C" veda_status veda_tile_layout_stats(const veda_plan* pl, const void* x
         return VEDA_ERR_UNSUPPORTED;
     hipStream_t st = (hipStream_t)stream;
     const int64_t sb = sx.b * es, sh = sx.h * es, sn = sx.n * es;
-    const int T = pl->prob.T, H = pl->prob.H, W = pl->prob.W;
+    const int H = pl->prob.H, W = pl->prob.W;
     RecipTable recip;
     recip.v[0] = 0.0f;
     for (int c = 1; c <= 2 * kTile; ++c) recip.v[c] = 1.0f / (float)c;
@@ -353,7 +369,7 @@ extern "C" veda_status veda_tile_layout_stats(const veda_plan* pl, const void* x
     const veda_plan* ip = pl->inner ? pl->inner : pl;
 #define VEDA_LAUNCH_LS2(E, D, WR, GRP)                                                                    \
     hipLaunchKernelGGL((layout_stats_kernel<E, D, WR, GRP>), grid, dim3(256), 0, st, ip->d_heads,         \
-                       ip->d_tile_head, (const char*)x, sb, sh, sn, (char*)x_tiled, stats, ip->total_tiles, T, H, W, \
+                       ip->d_tile_head, TileTables{ip->d_tile_n0, ip->d_tile_real}, (const char*)x, sb, sh, sn, (char*)x_tiled, stats, ip->total_tiles, H, W, \
                        valid_mask, valid_cnt, recip)
 #define VEDA_LAUNCH_LS(E, D)                                                                              \
     do {                                                                                                  \
@@ -401,7 +417,7 @@ extern "C" veda_status veda_tile_layout_path(const veda_plan* pl, const void* q,
     a.stats_q = stats_q; a.stats_k = stats_k;
     a.valid_mask = valid_mask; a.valid_cnt = valid_cnt;
     a.total_tiles = ip->total_tiles;
-    a.T = pl->prob.T; a.H = pl->prob.H; a.W = pl->prob.W;
+    a.H = pl->prob.H; a.W = pl->prob.W;
     const int tiles = 256 / (d / 4);   // to a workgroup of the descriptors
     a.stats_blocks = (int)((pl->total_tiles + tiles - 1) / tiles);
     dim3 grid((unsigned)(2 * a.stats_blocks + ip->total_tiles), (unsigned)pl->prob.batch);
@@ -419,7 +435,7 @@ extern "C" veda_status veda_tile_layout_path(const veda_plan* pl, const void* q,
         return r == VEDA_OK ? veda_tile_layout(pl, v, sv, VEDA_CHANNEL_MAJOR, v_tiled, nullptr, nullptr, stream) : r;
     }
     auto launch = [&](auto kern) {
-        hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, ip->d_heads, ip->d_tile_head, a, recip);
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, st, ip->d_heads, ip->d_tile_head, TileTables{ip->d_tile_n0, ip->d_tile_real}, a, recip);
         return launch_status("veda_tile_layout_path");
     };
 #define VEDA_LAUNCH_LP(E, D, GRP) (q_tiled ? launch(layout_path_kernel<E, D, true, GRP>) : launch(layout_path_kernel<E, D, false, GRP>))
