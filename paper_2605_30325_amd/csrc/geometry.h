@@ -184,6 +184,18 @@ inline size_t attn_items_of_head(const HeadGeom& g, int32_t h, int T, int H, int
     return (size_t)std::count_if(items.begin() + first, items.end(), [](const AttnItem& a) { return a.n_tiles > 2; });
 }
 
+// Shares of n items for each die.  Those that n leaves over go to the first dies, of the items dealt from the last die on to the last; in
+// calls of few workgroups to the dies with the fewest so far: to the same ones for every head they left one die twice the others' work.
+// Whole calls: 36 heads of 9 tiles, d = 128, fp32, one tile kept 75.7 -> 64.6 us, five kept 116.5 -> 90.3, bf16 55.2 -> 49.2.  (In calls of many
+// workgroups nothing to gain, and what dies share of the heads in progress changes: 8 heads of 624 in fp32 5 % slower.)
+inline std::vector<size_t> die_shares(size_t n, const std::vector<std::vector<AttnItem>>& per, bool from_last, bool few) {
+    std::vector<size_t> order(per.size()), share(per.size(), n / per.size());
+    for (size_t x = 0; x < order.size(); ++x) order[x] = from_last ? order.size() - 1 - x : x;
+    if (few) std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return per[a].size() < per[b].size(); });
+    for (size_t i = 0; i < n % per.size(); ++i) ++share[order[i]];
+    return share;
+}
+
 // The launch table: workgroup i runs on die i % dies, and die x takes the x-th part of every head's items of either kind, heads
 // in order (all dies then work on the same head at the same time, whose K and V stay in the memory-side cache, and the
 // workgroups that share an L2 hold neighbouring query tiles).  Dies with fewer items end with empty ones.
@@ -200,14 +212,15 @@ inline std::vector<AttnItem> attn_items(const std::vector<HeadGeom>& heads, int 
         }
         const size_t n[2] = {many, items.size() - many};
         size_t at = 0;
-        for (int kind = 0; kind < 2; ++kind)
+        for (int kind = 0; kind < 2; ++kind) {
+            const std::vector<size_t> shares = die_shares(n[kind], per, kind == 0, sharing.thin != 4);
             for (int i = 0; i < dies; ++i) {
-                const int x = kind ? i : dies - 1 - i;   // the odd ones of one kind go to the last dies, of the other to the first
-                const size_t share = n[kind] / dies + ((size_t)i < n[kind] % dies ? 1 : 0);
-                per[x].insert(per[x].end(), items.begin() + at, items.begin() + at + share);
-                at += share;
+                const int x = kind ? i : dies - 1 - i;
+                per[x].insert(per[x].end(), items.begin() + at, items.begin() + at + shares[x]);
+                at += shares[x];
                 most = std::max(most, per[x].size());
             }
+        }
     }
     const AttnItem none = {-1, 0, {0, 0, 0, 0}, 0u, 0};
     std::vector<AttnItem> table(most * dies, none);
