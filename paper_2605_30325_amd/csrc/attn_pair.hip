@@ -83,41 +83,6 @@ __device__ __forceinline__ void finish_pair(const PairState<D>& st, const AttnAr
     }
 }
 
-// Split walks: group 1's sums go to group 0, row by row on the larger of the two references.  A group whose exponentials are all zero
-// (or that had no step) has no reference.  LDS: [2 wavefronts][32 rows][D] floats, then [2][64 lanes] sums and references.
-template <int D, bool kExact>
-__device__ __forceinline__ void merge_split(PairState<D>& st, char* smem, int group, int w, int lane) {
-    float4* o = reinterpret_cast<float4*>(smem + w * (32 * D * 4)) + lane;
-    float* sums = reinterpret_cast<float*>(smem + 2 * 32 * D * 4) + w * 64 + lane;
-    const float mine = sum_with_other_half(st.l_run) == 0.0f ? -INFINITY : st.ref;
-    if (group) {
-#pragma unroll
-        for (int i = 0; i < D / 8; ++i) {
-            const f32x16& b = st.o[i / 4];
-            o[64 * i] = make_float4(b[4 * (i % 4)], b[4 * (i % 4) + 1], b[4 * (i % 4) + 2], b[4 * (i % 4) + 3]);
-        }
-        sums[0] = st.l_run;
-        sums[128] = mine;
-    }
-    __syncthreads();
-    if (group == 0) {
-        const float other = sums[128], ref = fmaxf(mine, other);
-        auto weight = [&](float x) { return x == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(kExact ? (x - ref) * st.resid : x - ref); };
-        const float f0 = weight(mine), f1 = weight(other);
-#pragma unroll
-        for (int i = 0; i < D / 8; ++i) {
-            const float4 x = o[64 * i];
-            f32x16& b = st.o[i / 4];
-            b[4 * (i % 4)] = b[4 * (i % 4)] * f0 + x.x * f1;
-            b[4 * (i % 4) + 1] = b[4 * (i % 4) + 1] * f0 + x.y * f1;
-            b[4 * (i % 4) + 2] = b[4 * (i % 4) + 2] * f0 + x.z * f1;
-            b[4 * (i % 4) + 3] = b[4 * (i % 4) + 3] * f0 + x.w * f1;
-        }
-        st.l_run = st.l_run * f0 + sums[0] * f1;
-        st.ref = ref == -INFINITY ? 0.0f : ref;
-    }
-}
-
 // One step of the merged walk over the kept lists of the two query tiles of a workgroup.
 struct MergedStep {
     int j;         // key tile (head-local)
@@ -134,14 +99,9 @@ struct MergedStep {
 // instead (any finite or non-finite value will do: their logits are overwritten with -inf).
 // kTable: the steps come from a table in LDS built before the main loop (attn_union.h; heads of up
 // to 16384 whole tiles); otherwise the lists are walked with scalar loads as the loop goes.
-// kSplit: few query tiles (plan.hip, attn_split), one to a workgroup.  Its steps go by twos: wavefronts 0 and 1 take the first of them,
-// 2 and 3, which would have no rows, the second, for the same rows; at the end the two halves' sums meet (merge_split).
-// Lists of up to kSplitLeast tiles are not shared: bringing the sums together takes as long as the steps it saves (2 kept
-// tiles 36.0 -> 38.8 us with shared lists, 7 level, 13 gain 2.4).
-constexpr int kSplitLeast = 8;
 constexpr int kPairChunk = 128;   // step-table entries filled at a time
 
-template <int D, bool kGrouped, bool kTokK, bool kExact, bool kTable, bool kSplit>
+template <int D, bool kGrouped, bool kTokK, bool kExact, bool kTable>
 __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs a) {
     constexpr int kRowB = D * 2;                 // bytes of one K row
     constexpr int kKBytes = kTile * kRowB;       // K tile
@@ -150,8 +110,7 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     constexpr int kKChunks = kRowB / 16;         // 16-byte chunks per K row
     constexpr int kLoads = kKBytes / 1024 / 4;   // direct-load instructions per wave per tile (K; same for V)
     constexpr int G = D / 16, NB = D / 32;
-    constexpr int kSlots = kSplit ? 4 : 2;       // LDS slots
-    constexpr int kLists = kGrouped || kSplit ? 1 : kTable ? 4 : 2;   // kept lists of a workgroup, at most
+    constexpr int kLists = kGrouped ? 1 : kTable ? 4 : 2;   // kept lists of a workgroup, at most
     typedef UnionLds<kLists, kPairChunk> Table;
     extern __shared__ __align__(1024) char smem[];   // base bits 4-9 clear: see PairAddr
 
@@ -160,13 +119,11 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     const int lq = lane & 31, hh = lane >> 5;
 
     AttnItem it;
-    if (!attn_work<kTable || kSplit>(a, it)) return;
+    if (!attn_work<kTable>(a, it)) return;
     const int head = it.head;
     const HeadGeom hg = a.heads[head];
     const int64_t b = blockIdx.y;
-    // split: a thin tile's second wavefronts have nothing to do; not on the same SIMDs in workgroups that tend to share a compute unit
-    const uint32_t place = kSplit ? ((wave ^ (blockIdx.x / (kXcd * 32))) & 1 ? kItemSecond : 0u) : it.waves >> (8 * wave);
-    const int group = kSplit ? wave >> 1 : 0;
+    const uint32_t place = it.waves >> (8 * wave);
     const int which = place & 3u, r = place & kItemSecond ? 1 : 0;
     const int qi = which == 0 ? it.tile[0] : which == 1 ? it.tile[1] : which == 2 ? it.tile[2] : it.tile[3];
     const int64_t row0 = kGrouped ? b * (a.total_tiles / 2) + hg.tile_off / 2 : b * a.total_tiles + hg.tile_off;
@@ -210,7 +167,7 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     PairState<D> st;
     const uint64_t q_real = ((const_u64_t)(uintptr_t)(a.tile_real + hg.tile_off))[qi];
     const int q_rows = place & kItemIdle ? 0 : __popcll(q_real);
-    int* tok_s = reinterpret_cast<int*>(smem + kSlots * kSlot + (kTable ? sizeof(Table) : 0));   // [4][32] token of each row, -1 = none
+    int* tok_s = reinterpret_cast<int*>(smem + 2 * kSlot + (kTable ? sizeof(Table) : 0));   // [4][32] token of each row, -1 = none
     const bool real = 32 * r + lq < q_rows;
     {
         // from the tiled tensor, or straight from token order
@@ -218,7 +175,7 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
         int slot = 32 * r + lq;
         if (q_real != ~0ull) slot = real ? nth_bit(q_real, slot) : 0;
         const int n = real ? token_from(hg, n0s[qi], slot, a.H, a.W) : 0;
-        if (hh == 0) tok_s[wave * 32 + lq] = real && group == 0 ? n : -1;
+        if (hh == 0) tok_s[wave * 32 + lq] = real ? n : -1;
         if (a.q_tok) {
             qrow = a.q_tok + b * a.sq_b + head * a.sq_h + (int64_t)n * a.sq_n + 16 * hh;
         } else {
@@ -355,7 +312,7 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     int gh = 0;         // grouped walk: which half of the current entry comes next
     int ta = 0, tb = 0; // this step consumes the head of list A / B
     // table mode: the raw entry read one step ahead of its use, the next entry to read, steps done
-    Table& u = *reinterpret_cast<Table*>(smem + kSlots * kSlot);
+    Table& u = *reinterpret_cast<Table*>(smem + 2 * kSlot);
     const uint32_t tab_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)&u.tab[0];
     i32x4 raw_next = {0, 0, 0, 0};
     int s_read = 0, s_done = 0, total = 0;
@@ -424,40 +381,13 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
 
     // Step s (P = s & 1) computes on slot P while the tiles of step s+1 land in slot P^1.
     const int my_bit = 32 * r < q_rows ? (kGrouped ? 1 : 1 << which) : 128;   // 128: a bit no step has
-    // Split: steps 2s and 2s + 1 (e0, e1) on slots 2P and 2P + 1 while the next two (f0, f1) land in the others.
-    MergedStep e0, e1, e2, f0, f1;
+    MergedStep e0, e1, e2;
     next_head(e0);
     next_advance();
     next_head(e1);
     next_advance();
-    // Short lists stay with the first two wavefronts: e1 and f1 are no steps.
-    const bool solo = kSplit && cnt[0] <= kSplitLeast;
-    auto next_second = [&](MergedStep& e) __attribute__((always_inline)) {
-        e.j = e.fl = e.n0 = 0;
-        e.vm = 0;
-        if (!solo) {
-            next_head(e);
-            next_advance();
-        }
-    };
-    if constexpr (kSplit) {
-        if (solo) {
-            f0 = e1;
-            e1.fl = 0;
-        } else {
-            next_head(f0);
-            next_advance();
-        }
-        next_second(f1);
-        fa.k0 += (uint32_t)group * kSlot;
-        fa.v0 += (uint32_t)group * kSlot;
-    }
     load_tile(e0, 0, 0);
     load_tile(e0, 0, 1);
-    if constexpr (kSplit) {
-        load_tile(e1, 1, 0);
-        load_tile(e1, 1, 1);
-    }
     scale_q();
     VEDA_LOADS_DONE_BARRIER();   // also the Q loads: nothing vector-memory is pending below
 
@@ -494,63 +424,11 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
         VEDA_LOADS_DONE_BARRIER();                                                                       \
         step_done();                                                                                     \
     } while (0)
-#define VEDA_SPLIT_STEP(P)                                                                               \
-    do {                                                                                                 \
-        int todo = 1;                                                                                    \
-        const int fl = group ? e1.fl : e0.fl;                                                            \
-        const uint64_t vm = group ? e1.vm : e0.vm;                                                       \
-        MergedStep g0, g1;                                                                               \
-        if (__builtin_expect((fl & (my_bit | kStepHalf)) == my_bit, 1)) {                                \
-            PairStep<D, kExact> w;                                                                       \
-            w.begin(fa, (uint32_t)(2 * (P) * kSlot));                                                    \
-            w.template block0<0>(st);                                                                    \
-            load_tile(f0, 2 * ((P) ^ 1), 0);                                                             \
-            load_tile(f1, 2 * ((P) ^ 1) + 1, 0);                                                         \
-            w.template block0<1>(st);                                                                    \
-            load_tile(f0, 2 * ((P) ^ 1), 1);                                                             \
-            load_tile(f1, 2 * ((P) ^ 1) + 1, 1);                                                         \
-            w.template block0<2>(st);                                                                    \
-            next_head(g0);                                                                               \
-            next_advance();                                                                              \
-            w.template block0<3>(st);                                                                    \
-            next_second(g1);                                                                             \
-            w.finish(st, fa, vm);                                                                        \
-            todo = 0;                                                                                    \
-        }                                                                                                \
-        asm volatile("" : "+s"(todo));                                                                   \
-        if (todo) {                                                                                      \
-            load_tile(f0, 2 * ((P) ^ 1), 0);                                                             \
-            load_tile(f1, 2 * ((P) ^ 1) + 1, 0);                                                         \
-            load_tile(f0, 2 * ((P) ^ 1), 1);                                                             \
-            load_tile(f1, 2 * ((P) ^ 1) + 1, 1);                                                         \
-            next_head(g0);                                                                               \
-            next_advance();                                                                              \
-            next_second(g1);                                                                             \
-            if (fl & my_bit) pair_half_step<D, kExact>(st, fa, (uint32_t)(2 * (P) * kSlot), (uint32_t)vm); \
-        }                                                                                                \
-        e0 = f0; e1 = f1; f0 = g0; f1 = g1;                                                              \
-        VEDA_LOADS_DONE_BARRIER();                                                                       \
-        step_done();                                                                                     \
-        step_done();                                                                                     \
-    } while (0)
-    if constexpr (kSplit) {
-        while (e0.fl) {
-            VEDA_SPLIT_STEP(0);
-            if (!e0.fl) break;
-            VEDA_SPLIT_STEP(1);
-        }
-        if (!solo) {
-            __syncthreads();   // a refilled table is left alone from here on
-            merge_split<D, kExact>(st, smem, group, wave & 1, lane);
-        }
-    } else {
-        while (e0.fl) {
-            VEDA_STEP(0);
-            if (!e0.fl) break;
-            VEDA_STEP(1);
-        }
+    while (e0.fl) {
+        VEDA_STEP(0);
+        if (!e0.fl) break;
+        VEDA_STEP(1);
     }
-#undef VEDA_SPLIT_STEP
 #undef VEDA_STEP
 #undef VEDA_LOADS_DONE_BARRIER
 
@@ -563,29 +441,23 @@ veda_status launch_sparse_attn_bf16_pair(const veda_plan* pl, const AttnArgs& a,
     // the step table needs a bitmap over the tiles the lists may name
     bool table = !walk;
     for (const HeadGeom& g : pl->heads) table = table && (grouped ? g.n_tiles / 2 : g.n_tiles) <= kUnionMaxTiles;
-    const bool split = pl->attn_split;
-    dim3 grid((unsigned)(table || split ? pl->attn_blocks : kXcd * pl->xcd_max_pairs), (unsigned)pl->prob.batch), block(256);
-    // two slots of (K tile + V^T tile), or four, then the step table and the rows' tokens
-    const size_t tables = grouped || split ? sizeof(UnionLds<1, kPairChunk>) : sizeof(UnionLds<4, kPairChunk>);
-    const size_t smem = (size_t)(split ? 4 : 2) * 2 * kTile * d * 2 + (table ? tables : 0) + 4 * 32 * sizeof(int);
-#define VEDA_LAUNCH_PAIR_T(DD, GG, KK, EE, TT, SS)                                                       \
+    dim3 grid((unsigned)(table ? pl->attn_blocks : kXcd * pl->xcd_max_pairs), (unsigned)pl->prob.batch), block(256);
+    // two slots of (K tile + V^T tile), then the step table and the rows' tokens
+    const size_t tables = grouped ? sizeof(UnionLds<1, kPairChunk>) : sizeof(UnionLds<4, kPairChunk>);
+    const size_t smem = (size_t)2 * 2 * kTile * d * 2 + (table ? tables : 0) + 4 * 32 * sizeof(int);
+#define VEDA_LAUNCH_PAIR_T(DD, GG, KK, EE, TT)                                                           \
     do {                                                                                                 \
-        auto kern = sparse_attn_bf16_pair_kernel<DD, GG, KK, EE, TT, SS>;                                \
+        auto kern = sparse_attn_bf16_pair_kernel<DD, GG, KK, EE, TT>;                                    \
         if (smem > 64 * 1024)                                                                            \
             VEDA_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem)); \
         hipLaunchKernelGGL(kern, grid, block, smem, s, a);                                               \
     } while (0)
-#define VEDA_LAUNCH_PAIR_S(DD, GG, KK, SS)                                                               \
-    do {                                                                                                 \
-        if (exact && table) VEDA_LAUNCH_PAIR_T(DD, GG, KK, true, true, SS);                              \
-        else if (exact) VEDA_LAUNCH_PAIR_T(DD, GG, KK, true, false, SS);                                 \
-        else if (table) VEDA_LAUNCH_PAIR_T(DD, GG, KK, false, true, SS);                                 \
-        else VEDA_LAUNCH_PAIR_T(DD, GG, KK, false, false, SS);                                           \
-    } while (0)
 #define VEDA_LAUNCH_PAIR(DD, GG, KK)                                                                     \
     do {                                                                                                 \
-        if (!GG && split) VEDA_LAUNCH_PAIR_S(DD, false, KK, true);                                       \
-        else VEDA_LAUNCH_PAIR_S(DD, GG, KK, false);                                                      \
+        if (exact && table) VEDA_LAUNCH_PAIR_T(DD, GG, KK, true, true);                                  \
+        else if (exact) VEDA_LAUNCH_PAIR_T(DD, GG, KK, true, false);                                     \
+        else if (table) VEDA_LAUNCH_PAIR_T(DD, GG, KK, false, true);                                     \
+        else VEDA_LAUNCH_PAIR_T(DD, GG, KK, false, false);                                               \
     } while (0)
     const int variant = (d == 128 ? 4 : 0) | (grouped ? 2 : 0) | (a.k_tok ? 1 : 0);
     switch (variant) {
@@ -599,7 +471,6 @@ veda_status launch_sparse_attn_bf16_pair(const veda_plan* pl, const AttnArgs& a,
         default: VEDA_LAUNCH_PAIR(128, true, true); break;
     }
 #undef VEDA_LAUNCH_PAIR
-#undef VEDA_LAUNCH_PAIR_S
 #undef VEDA_LAUNCH_PAIR_T
     return launch_status("sparse_attn_bf16_pair_kernel");
 }

@@ -128,12 +128,6 @@ static veda_status build_plan(const veda_problem* p, const int32_t* shapes, int 
     // fp32 tiles that share a workgroup share the form of their products, which lists longer than kF32SplitTiles decide: where
     // such lists can be, tiles stay with their partners.
     const bool alone = toff * p->batch <= kAlone && (p->dtype == VEDA_BF16 || most_tiles <= veda::kF32SplitTiles);
-    // A workgroup of one tile leaves two of its wavefronts without rows; where one workgroup to a compute unit (d = 128: 142 KB of LDS) or
-    // two (d = 64: 74 KB) hold all tiles, those take half of the steps (attn_pair.hip).  Whole calls, whole and shared
-    // lists, us: d = 64, 75 tiles at 19 kept 52.6 45.7, 384 at 13 kept 45.3 42.9; d = 128, 120 tiles at 24 kept 90.5 78.4,
-    // 256 at 32 kept 70.3 63.3.  With more tiles, shared and as they are: d = 128, 384 at 32 kept 91.6 85.1, 512 at 7 kept 66.3 60.0;
-    // d = 64, 640 at 32 kept 69.8 66.6, 1024 at 16 kept 61.0 55.8.
-    pl->attn_split = alone && grp == 1 && p->dtype == VEDA_BF16 && toff * p->batch <= (p->head_dim == 128 ? kAlone / 2 : kAlone);
     std::vector<veda::AttnItem> items;
     for (const veda::AttnShare share : {veda::AttnShare{1, 1}, veda::AttnShare{2, 2}, veda::AttnShare{2, 4}}) {
         if (share.full == 1 && !alone) continue;

@@ -91,7 +91,6 @@ struct veda_plan {
     uint64_t* d_tile_real = nullptr;    // device [total_tiles]: tile_real_slots of each tile
     veda::AttnItem* d_attn_items = nullptr;   // device [attn_blocks]: work of the attention kernels, by workgroup
     int32_t attn_blocks = 0;
-    bool attn_split = false;            // bf16: few items, of one tile each, whose wavefronts share a tile's list
     veda::HeatItem* d_heat_items = nullptr;   // device [heat_blocks]: work of the target scores, by workgroup
     int32_t heat_blocks = 0;
     // Blocks of 64 consecutive tiles that never straddle two heads (the projection kernel's work

@@ -343,10 +343,9 @@ def test_attention_on_hand_made_lists(dtype, d, walk):
 @pytest.mark.parametrize("exact_scale", [False, True])
 @pytest.mark.parametrize("d,rows,cols", [(128, 16, 16), (128, 1, 257), (64, 16, 32), (64, 27, 19), (64, 1, 3)])
 def test_lists_shared_by_the_wavefronts_of_a_tile(d, rows, cols, exact_scale):
-    """256 tiles of a call at d = 128 and 512 at d = 64, up to which two halves of a workgroup share a tile's list, and one more;
-    lists of one tile, around the eight that stay whole, odd ones, and all tiles (more steps than the table holds), one
-    of them with an infinite key: against float64 softmax (bars of the bf16 path, logits of deviation 1), and the bits of the
-    lists merged inside the loop."""
+    """Calls of few tiles, alone in their workgroups (up to 512) and in pairs; lists of one tile, of a few, odd ones, and all
+    tiles (more steps than the table holds), one of them with an infinite key: against float64 softmax (bars of the bf16 path,
+    logits of deviation 1), and the bits of the lists merged inside the loop."""
     dev, rng = torch.device("cuda:0"), np.random.default_rng(43)
     n, grid = rows * cols, (1, 8 * rows, 8 * cols - 3)   # the last column of tiles is ragged
     tokens = int(np.prod(grid))
@@ -377,6 +376,33 @@ def test_lists_shared_by_the_wavefronts_of_a_tile(d, rows, cols, exact_scale):
         assert bool((torch.isfinite(out[0, 0, rows_i].float()).all(dim=1) == fine).all()), i
         assert float(err[fine].max()) <= hz.BF16_MAX_ABS and float(err[fine].mean()) <= hz.BF16_MEAN_ABS, i
         assert float((lse[0, 0, rows_i].double() - want_lse)[fine].abs().max()) <= 2e-2, i
+
+
+@pytest.mark.parametrize("dtype,d,exact_scale", [("bf16", 64, False), ("bf16", 128, False), ("bf16", 128, True), ("f32", 64, False), ("f32", 128, False)])
+def test_a_sample_alone_and_in_a_batch(dtype, d, exact_scale):
+    """176 tiles, thin ones among them, in calls of 1, 2, 3, 5, 6 and 40 samples (one tile to a workgroup, pairs, and thin tiles in
+    fours): a sample's bits do not depend on how many others the call holds."""
+    dev, heads, grid = torch.device("cuda:0"), 2, (5, 9, 61)
+    wl = wlm.custom_workload("batch", heads, d, dtype, grid, False, (30, 100), seed=47)
+    q, k, v = wlm.make_qkv(wl, dev)
+    rng, shapes = np.random.default_rng(6), np.asarray([(4, 4, 4), (1, 8, 8)], np.int32)
+    counts = veda.Plan(1, heads, d, grid, shapes, wl.torch_dtype).tiles
+    lists = [np.sort(rng.choice(n, 20, replace=False)) for n in counts for _ in range(n)]
+    first = None
+    for batch in (1, 2, 3, 5, 6, 40):
+        plan = veda.Plan(batch, heads, d, grid, shapes, wl.torch_dtype)
+        if exact_scale:
+            plan.set_option(veda.VEDA_OPT_EXACT_LOGIT_SCALE, 1)
+        qb, kb, vb = (x.expand(batch, -1, -1, -1).contiguous() for x in (q, k, v))
+        qt, vm, _ = veda.veda_tile_layout(plan, qb)
+        kt, _, _ = veda.veda_tile_layout(plan, kb, want_mask=False)
+        vt, _, _ = veda.veda_tile_layout(plan, vb, veda.VEDA_CHANNEL_MAJOR, want_mask=False)
+        rp = torch.arange(batch * len(lists) + 1, dtype=torch.int32, device=dev) * 20
+        ci = torch.as_tensor(np.concatenate(lists).astype(np.int32)).to(dev).repeat(batch)
+        out, lse = veda.veda_sparse_attn_fwd(plan, qt, kt, vt, vm, rp, ci, 1.0 / math.sqrt(d), want_lse=True)
+        torch.cuda.synchronize()
+        first = first or (out[0].clone(), lse[0].clone())
+        assert bool((out == first[0]).all()) and bool((lse == first[1]).all()), batch
 
 
 @pytest.mark.parametrize("tile_tokens,rows,cols", [(64, 32, 64), (64, 3, 683), (128, 32, 64), (128, 3, 683)])
