@@ -126,9 +126,10 @@ void veda_plan_destroy(veda_plan* plan); /* NULL is allowed */
  * of the two forms over the outputs' root mean square, as measured with 400 tiles a head: 1.3e-5 ... 1.7e-5 after 16
  * kept tiles, 2.2e-5 ... 3.1e-5 after 63, 4.1e-5 ... 5.8e-5 after 192, most of it the fp32 products' rounding, which grows with
  * the root of the list.)  Whatever the option, results that are not finite or too small for their parts (|q * scale| or
- * |logit| of 2^48, sums of p * v outside 2^-48 .. 2^32) are formed again on the fp32 matrix cores.  A workgroup holds
- * two adjacent query tiles and takes one form for both: the longer list decides, and a result of either that has to be
- * formed again, so that the last bits of a row can depend on its neighbour tile. */
+ * |logit| of 2^48, sums of p * v outside 2^-48 .. 2^32) are formed again on the fp32 matrix cores.  In heads of
+ * more than 192 tiles two adjacent query tiles (partners) take one form: the longer list decides, and a result of either
+ * that has to be formed again, so that the last bits of a row can depend on its neighbour tile; in smaller heads a tile
+ * decides for itself.  Nothing else about a call does: not its other samples and heads, nor which tiles share a workgroup. */
 typedef enum { VEDA_OPT_EXACT_LOGIT_SCALE = 0, VEDA_OPT_ATTN_LIST_WALK = 1, VEDA_OPT_FP32_CHAIN_UNIT = 2,
                VEDA_OPT_FP32_PRODUCTS = 3 } veda_option;
 enum { VEDA_PRODUCTS_FP32 = 1, VEDA_PRODUCTS_SPLIT = 2 };

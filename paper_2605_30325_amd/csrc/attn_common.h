@@ -97,6 +97,7 @@ template <bool kTable> __device__ __forceinline__ bool attn_work(const AttnArgs&
 #pragma unroll
         for (int t = 0; t < 4; ++t) it.tile[t] = src[2 + t];
         it.waves = (uint32_t)src[6];
+        it.partners = src[7];
         return it.head >= 0;
     } else {
         int pair;
@@ -105,6 +106,7 @@ template <bool kTable> __device__ __forceinline__ bool attn_work(const AttnArgs&
         pair_tiles(a.heads[it.head], pair, it.tile[0], it.tile[1], hasB);
         it.n_tiles = hasB ? 2 : 1;
         it.tile[2] = it.tile[3] = it.tile[0];
+        it.partners = hasB && a.heads[it.head].n_tiles > kF32SplitTiles ? 1 : 0;
         const uint32_t b = hasB ? 1u : kItemIdle;
         it.waves = kItemSecond << 8 | b << 16 | (b | kItemSecond) << 24;
         return true;

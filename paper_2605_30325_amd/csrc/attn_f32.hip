@@ -1,9 +1,10 @@
 // Stage 4, fp32 (Eq. 2; Sec. 3.1 masked form; Sec. 4.3 tile skipping; Alg. 1 "UnTile"): the
 // accuracy path (1e-4 against the double-precision definition), fp32 products on the bf16 matrix cores.
 //
-// Same work split as the bf16 kernel: a workgroup of four wavefronts of 32 rows owns a pair of partner query
-// tiles, or four thin ones, and walks the union of their kept lists (8 heads of 21x30x52, 10 % kept, thin tiles in fours
-// instead of twos: whole call 3.07 -> 2.93 ms; 2 x 4 heads of 9x24x32, all kept, 5 %).  Padding is handled as in the bf16 kernel (real query rows first; half steps, attn_union.h).
+// Same work split as the bf16 kernel: a workgroup of four wavefronts of 32 rows owns one query tile, a pair of them
+// or four thin ones, and walks the union of their kept lists (8 heads of 21x30x52, 10 % kept, thin tiles in fours instead of
+// twos: whole call 3.44 -> 3.19 ms).  Partners in heads of more than kF32SplitTiles tiles share the form of their products and
+// stay together (plan.hip); otherwise a tile's form is its own.  Padding is handled as in the bf16 kernel (real query rows first; half steps, attn_union.h).
 // Every operand is split into three bf16 parts and a product is six bf16 ones (split_f32.h: why that is no less exact),
 // 32 keys at a time:
 //   S^T = K Q^T from the K planes, in the shadow of its last products V^T converted (landing area -> registers -> planes)
@@ -20,8 +21,9 @@
 // loads one phase earlier, priorities: 1-2 %.
 //
 // Long lists (AttnArgs::split_tiles) take v_mfma_f32_32x32x2_f32 instead, and numbers that are not finite come out of the
-// split products as NaN: a workgroup that finds any in its results, or one too small for its parts (kF32Small), walks again
-// that way.  There a lane owns one query (lane % 32) and one of the two terms of every instruction (h = lane / 32).  The pairing of the reduction index with h is free as long as both operands agree, and it is
+// split products as NaN: a tile that finds any in its results, or one too small for its parts (kF32Small), walks again
+// that way, in heads of more than kF32SplitTiles tiles with its partner.  Which tiles share a workgroup otherwise leaves no trace in the
+// results, nor do the other samples of the call or the way its steps are found.  There a lane owns one query (lane % 32) and one of the two terms of every instruction (h = lane / 32).  The pairing of the reduction index with h is free as long as both operands agree, and it is
 // chosen so that one 16-byte LDS read feeds four instructions:
 //   S^T, step (m, t):  h supplies channel 8m + 4h + t   (K row: float4 at channel 8m + 4h),
 //   O^T, step (c, j, t): h supplies key 32c + 8j + 4h + t, which is exactly register 4j + t of the
@@ -191,7 +193,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
 
     const int my_bit = 32 * r < q_rows ? 1 << which : 128;   // 128: a bit no step has
     // The walk on bf16 matrix cores: every operand as the sum of three bf16 numbers, six products (see the head of the file).
-    auto split_walk = [&]() __attribute__((always_inline)) {
+    auto split_walk = [&](int walk_bit) __attribute__((always_inline)) {
         typedef SplitK<D> K;
         constexpr int G = D / 16, kI = K::kI;
         constexpr uint32_t kV = K::kPlanes, kRaw = 2 * K::kPlanes;   // V^T planes, landing area: 64 KB (d = 128) in all
@@ -234,7 +236,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
         }
         K::meet();
         while (cur.fl) {
-            const bool mine = (cur.fl & my_bit) != 0;
+            const bool mine = (cur.fl & walk_bit) != 0;
             if (cur.c == 0 && (cur.fl & (kStepWhole | kStepPart))) {
                 nx = cur;
                 nx.c = 1;
@@ -362,8 +364,9 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
         __syncthreads();
     };
 
-    // The walk on fp32 matrix cores.
-    auto exact_walk = [&]() __attribute__((always_inline)) {
+    // The walk on fp32 matrix cores, by the wavefronts that take part.
+    auto exact_walk = [&](bool part) __attribute__((always_inline)) {
+        const int walk_bit = part ? my_bit : 128;
         // Q operand: lane (query 32r + idx, half h) holds channels 8m + 4h + t, scaled by softmax_scale*log2(e).
         float qreg[D / 2];
 #pragma unroll
@@ -460,7 +463,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
                 }
             }
         };
-        begin_rows();
+        if (part) begin_rows();
         begin_walk();
         Step e0, e1;
         next_step(e0);
@@ -472,7 +475,7 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
         while (e0.fl) {
             next_step(e1);
             asm volatile("" : "+v"(k0), "+v"(v0));   // the addresses of the reads are formed as they are needed: kept, they would spill
-            const bool mine = (e0.fl & my_bit) != 0, full = !(e0.fl & kStepHalf);
+            const bool mine = (e0.fl & walk_bit) != 0, full = !(e0.fl & kStepHalf);
             f32x16 s0, s1;
             if (mine) {
                 logits(s0, 0);
@@ -531,13 +534,19 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
 
     };
 
-    int longest = 0;
+    // Bit t of `again`: the tile in place t takes the chains, because its list or its partner's is too long or a result of either has to be
+    // formed again.  (A flag beside the mask, and the splits for whatever is left: otherwise 26-35 spilled registers, not 8.)
+    auto and_partner = [&](int t) __attribute__((always_inline)) { return (it.partners >> (t >> 1)) & 1 ? 3 << (t & 2) : 1 << t; };
+    int again = 0, kept = 0;
 #pragma unroll
-    for (int t = 0; t < kLists; ++t) longest = cnt[t] > longest ? cnt[t] : longest;
-    bool chains = longest > a.split_tiles;
+    for (int t = 0; t < kLists; ++t) {
+        if (cnt[t] > 0) kept |= 1 << t;
+        if (cnt[t] > a.split_tiles) again |= and_partner(t);
+    }
+    bool chains = again != 0 && (kept & ~again) == 0;
     float unscale = 1.0f;
     if (!chains) {
-        split_walk();
+        split_walk((again >> which) & 1 ? 128 : my_bit);
         float bad = l_run * 0.0f;   // NaN if anything is not finite
         uint32_t least = ~0u;       // 2 |o| - 1 in bits: zeros are the largest
 #pragma unroll
@@ -547,17 +556,19 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(A
                 bad = fmaf(o[nb][i], 0.0f, bad);
                 least = min(least, (__float_as_uint(o[nb][i]) << 1) - 1u);
             }
-        uint32_t* flag = reinterpret_cast<uint32_t*>(smem);   // the planes are done with
+        int* flag = reinterpret_cast<int*>(smem);   // the planes are done with
         const bool any_bad = __any(bad != 0.0f || least < (__float_as_uint(kF32Small) << 1) - 1u);
-        if (lane == 0) flag[wave] = any_bad ? 1u : 0u;
+        if (lane == 0) flag[wave] = any_bad ? and_partner(which) : 0;
         __syncthreads();
-        chains = __builtin_amdgcn_readfirstlane((int)(flag[0] | flag[1] | flag[2] | flag[3])) != 0;
+        again |= __builtin_amdgcn_readfirstlane(flag[0] | flag[1] | flag[2] | flag[3]);
+        chains = again != 0;
         unscale = 1.0f / kF32VScale;
         __syncthreads();
     }
     if (chains) {
-        exact_walk();
-        unscale = 1.0f;
+        const bool part = ((again >> which) & 1) != 0;
+        exact_walk(part);
+        if (part) unscale = 1.0f;
     }
 
     // Normalise, transpose through LDS ([4 wavefronts][32 rows][D] fp32) and scatter the real rows.

@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <array>
 #include <vector>
 
 namespace veda {
@@ -95,14 +96,17 @@ struct AttnItem {
     int32_t n_tiles;   // 1..4
     int32_t tile[4];   // head-local query tiles; places beyond n_tiles repeat the first
     uint32_t waves;    // byte w: wavefront w's place in tile[] | kItemSecond | kItemIdle
-    int32_t unused;
+    int32_t partners;  // bit 0: the tiles in places 0 and 1 are partners that take one form of products (fp32), bit 1: those in 2 and 3
 };
 constexpr uint32_t kItemSecond = 4u;   // rows 32-63 of its tile, not 0-31
 constexpr uint32_t kItemIdle = 8u;     // no rows
 
 // How many full tiles, or thin ones, share a workgroup.  The more do, the fewer key tiles are loaded and the more steps a
 // workgroup's walk has (1.1-1.3 times a list's length for two full tiles, 1.3-2.0 for four thin ones).
-struct AttnShare { int full, thin; };
+struct AttnShare {
+    int full, thin;
+    bool partners = false;   // tiles stay with their partners along pair_ax (pair_tiles), whatever else shares their workgroup
+};
 
 // Whether two heads' tiles are the same ones.
 inline bool same_tiles(const HeadGeom& a, const HeadGeom& b) {
@@ -112,11 +116,12 @@ inline bool same_tiles(const HeadGeom& a, const HeadGeom& b) {
 // Appends head h's items: those of more than two tiles, which have the most steps, before the others, each kind ordered by
 // its first tile.  Returns the number of the former.  Full tiles are paired along pair_ax (line by line; the odd ones out
 // with those of the next lines), thin ones taken four at a time by 2x2x2 blocks of the tile grid, so that tiles that share a
-// workgroup are neighbours, whose kept lists agree most.  At most two items of a head have wavefronts to spare.
+// workgroup are neighbours, whose kept lists agree most.  At most two items of a head have wavefronts to spare (more where partners
+// stay together: a thin tile with a full one, or a pair of thin ones left over).
 inline size_t attn_items_of_head(const HeadGeom& g, int32_t h, int T, int H, int W, AttnShare share, std::vector<AttnItem>& items) {
     const size_t first = items.size();
-    auto add = [&](const int32_t* tiles, int n, int full) {   // the first `full` of them take two wavefronts
-        AttnItem it = {h, n, {0, 0, 0, 0}, 0u, 0};
+    auto add = [&](const int32_t* tiles, int n, int full, int partners = 0) {   // the first `full` of them take two wavefronts
+        AttnItem it = {h, n, {0, 0, 0, 0}, 0u, partners};
         for (int t = 0; t < 4; ++t) it.tile[t] = tiles[t < n ? t : 0];
         // which of a tile's wavefronts comes first alternates: the second one of an edge tile has less to do, and is then
         // not on the same SIMD in every workgroup
@@ -143,12 +148,23 @@ inline size_t attn_items_of_head(const HeadGeom& g, int32_t h, int T, int H, int
     }
     const int cnt[3] = {g.nt, g.nh, g.nw}, stride[3] = {g.nh * g.nw, g.nw, 1}, ax = g.pair_ax;
     std::vector<int32_t> odd, thin;
+    std::vector<std::array<int32_t, 2>> thin_pairs;   // partners, both thin
+    auto is_thin = [&](int32_t t) { return __builtin_popcountll(tile_real_slots(g, t, T, H, W)) <= 32; };
     for (int32_t i = 0; i < g.n_tiles; ++i) {
         if (i / stride[ax] % cnt[ax] != 0) continue;
+        if (share.partners) {
+            for (int c = 0; c < cnt[ax]; c += 2) {
+                const int32_t pair[2] = {i + c * stride[ax], i + (c + 1) * stride[ax]};
+                if (c + 1 == cnt[ax]) (is_thin(pair[0]) ? thin : odd).push_back(pair[0]);
+                else if (is_thin(pair[0]) && is_thin(pair[1])) thin_pairs.push_back({pair[0], pair[1]});
+                else add(pair, 2, 2, 1);
+            }
+            continue;
+        }
         int32_t held = -1;
         for (int c = 0; c < cnt[ax]; ++c) {
             const int32_t t = i + c * stride[ax];
-            if (__builtin_popcountll(tile_real_slots(g, t, T, H, W)) <= 32) {
+            if (is_thin(t)) {
                 thin.push_back(t);
             } else if (share.full == 1) {
                 add(&t, 1, 1);
@@ -168,6 +184,11 @@ inline size_t attn_items_of_head(const HeadGeom& g, int32_t h, int T, int H, int
         return ((((t / 2) * g.nh + hh / 2) * g.nw + w / 2) * 2 + t % 2) * 4 + hh % 2 * 2 + w % 2;
     };
     std::sort(thin.begin(), thin.end(), [&](int32_t a, int32_t b) { return block(a) < block(b); });
+    std::sort(thin_pairs.begin(), thin_pairs.end(), [&](const auto& a, const auto& b) { return block(a[0]) < block(b[0]); });
+    for (size_t i = 0, n; i < thin_pairs.size(); i += n) {
+        n = share.thin == 4 && i + 1 < thin_pairs.size() ? 2 : 1;
+        add(thin_pairs[i].data(), (int)(2 * n), 0, n == 2 ? 3 : 1);   // pairs lie one behind the other
+    }
     if (odd.size() % 2) {   // a last full tile takes along what would not fill a workgroup
         int32_t tiles[3] = {odd.back(), 0, 0};
         int n = 1;

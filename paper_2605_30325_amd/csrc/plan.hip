@@ -125,13 +125,14 @@ static veda_status build_plan(const veda_problem* p, const int32_t* shapes, int 
     constexpr int64_t kAlone = 512, kPairs = 512;   // workgroups, all samples
     int32_t most_tiles = 0;
     for (const HeadGeom& g : pl->heads) most_tiles = std::max(most_tiles, g.n_tiles);
-    // fp32 tiles that share a workgroup share the form of their products, which lists longer than kF32SplitTiles decide: where
-    // such lists can be, tiles stay with their partners.
-    const bool alone = toff * p->batch <= kAlone && (p->dtype == VEDA_BF16 || most_tiles <= veda::kF32SplitTiles);
+    // fp32 partners share the form of their products where lists can be longer than kF32SplitTiles, and find out in their workgroup: they
+    // stay together, as in the work items of the merged lists.
+    const bool partners = p->dtype == VEDA_F32 && most_tiles > veda::kF32SplitTiles;
     std::vector<veda::AttnItem> items;
-    for (const veda::AttnShare share : {veda::AttnShare{1, 1}, veda::AttnShare{2, 2}, veda::AttnShare{2, 4}}) {
-        if (share.full == 1 && !alone) continue;
+    for (veda::AttnShare share : {veda::AttnShare{1, 1}, veda::AttnShare{2, 2}, veda::AttnShare{2, 4}}) {
+        if (share.full == 1 && (partners || toff * p->batch > kAlone)) continue;
         if (share.full == 2 && share.thin == 2 && toff * p->batch > 4 * kPairs) continue;   // more pairs than kPairs in any case
+        share.partners = partners;
         items = veda::attn_items(pl->heads, p->T, p->H, p->W, veda::kXcd, share);
         int64_t busy = 0;
         for (const veda::AttnItem& it : items) busy += it.head >= 0;

@@ -198,3 +198,55 @@ def test_every_wavefront_of_rows_is_in_one_work_item(tmp_path, grid, grp, full, 
         assert sorted(seen) == want, (h, len(seen), len(want))
         assert thin < 4 or spare <= (0 if grp == 2 else 1 if sum(m > 32 for m in rows) % 2 == 0 else 2), (h, spare)
         assert (dies.max(1) - dies.min(1)).max() <= 1
+
+
+PARTNERS_PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "geometry.h"
+int main(int argc, char** argv) {
+    const int T = atoi(argv[1]), H = atoi(argv[2]), W = atoi(argv[3]);
+    std::vector<veda::HeadGeom> heads;
+    for (int i = 5; i + 3 < argc; i += 4) {
+        const int32_t shape[3] = {atoi(argv[i]), atoi(argv[i + 1]), atoi(argv[i + 2])};
+        veda::HeadGeom g;
+        veda::head_extents(g, shape, 1, T, H, W);
+        g.pair_ax = atoi(argv[i + 3]);
+        heads.push_back(g);
+    }
+    for (const veda::HeadGeom& g : heads) printf("%d %d %d\n", g.nt, g.nh, g.nw);
+    for (const veda::AttnItem& it : veda::attn_items(heads, T, H, W, 8, {2, atoi(argv[4]), true}))
+        printf("%d %d %d %d %d %d %u %d\n", it.head, it.n_tiles, it.tile[0], it.tile[1], it.tile[2], it.tile[3], it.waves, it.partners);
+    return 0;
+}
+"""
+
+
+@pytest.mark.parametrize("thin", [2, 4])
+@pytest.mark.parametrize("grid", [(1, 1, 1), (5, 9, 13), (17, 6, 7), (21, 30, 52), (9, 33, 33)])
+def test_partners_share_a_workgroup(tmp_path, grid, thin):
+    """Where tiles stay with their partners (neighbours along the head's axis): both are in one work item, marked as such, and nothing else
+    is; every tile is in one item, with wavefronts for its real rows."""
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no C++ compiler")
+    (tmp_path / "partners.cc").write_text(PARTNERS_PROGRAM)
+    subprocess.check_call([gxx, "-std=c++17", "-O1", "-Wall", "-Werror", f"-I{CSRC}", str(tmp_path / "partners.cc"), "-o", str(tmp_path / "partners")])
+    heads = [(s, ax) for s in ((4, 4, 4), (1, 8, 8), (16, 2, 2)) for ax in (0, 1, 2)]
+    args = [str(x) for s, ax in heads for x in (*s, ax)]
+    lines = subprocess.run([str(tmp_path / "partners"), *map(str, grid), str(thin), *args], capture_output=True, text=True, check=True).stdout.splitlines()
+    rows = [[int(x) for x in l.split()] for l in lines]
+    items = rows[len(heads):]
+    for h, (s, ax) in enumerate(heads):
+        ids = np.moveaxis(np.arange(int(np.prod(rows[h]))).reshape(rows[h]), ax, 2)
+        want = sorted(tuple(l[i:i + 2]) for l in ids.reshape(-1, ids.shape[2]).tolist() for i in range(0, len(l) - 1, 2))
+        real = np.bincount(vo.token_tile_map(grid, s).reshape(-1), minlength=ids.size)
+        mine = [it for it in items if it[0] == h]
+        assert sorted(t for it in mine for t in it[2:2 + it[1]]) == list(range(ids.size))
+        assert sorted(tuple(it[2 + 2 * p:4 + 2 * p]) for it in mine for p in (0, 1) if it[7] >> p & 1) == want
+        for _, n, *tiles, waves, marks in mine:
+            assert 1 <= n <= thin and marks < 1 << n // 2
+            places = [(waves >> (8 * w)) & 255 for w in range(4)]
+            live = [(p & 3, p >> 2 & 1) for p in places if not p & 8]
+            assert len(set(live)) == len(live) and all(p < n for p, _ in live)
+            assert all((p, r) in live for p in range(n) for r in (0, 1) if r == 0 or real[tiles[p]] > 32)

@@ -1852,6 +1852,50 @@ def test_fp32_products_by_list_length(d, walk):
             assert (outs[option][slots[i]].double() - ref).abs().max() <= 1e-4
 
 
+def _fp32_forms(d, heads, batch, grid, shape, lengths, odd, walk):
+    """Outputs of one call in both orders of the steps, or of its first sample in calls of several sizes."""
+    dev, n = torch.device("cuda:0"), int(np.prod([-(-g // s) for g, s in zip(grid, shape)]))
+    wl = wlm.custom_workload("forms", heads, d, "f32", grid, False, (50, 100), seed=83)
+    q, k, v = wlm.make_qkv(wl, dev)
+    if odd:   # in the first head, some of whose tiles keep them
+        v[0, 0, -1, 3], q[0, 0, 5, 0] = math.inf, math.nan
+        v[0, 0, 7] *= 1e-30
+    plan = veda.Plan(batch, heads, d, grid, np.asarray([shape] * heads, np.int32), torch.float32)
+    plan.set_option(veda.VEDA_OPT_ATTN_LIST_WALK, walk)
+    qt, vm, _ = veda.veda_tile_layout(plan, q.expand(batch, -1, -1, -1).contiguous())
+    kt, _, _ = veda.veda_tile_layout(plan, k.expand(batch, -1, -1, -1).contiguous(), want_mask=False)
+    vt, _, _ = veda.veda_tile_layout(plan, v.expand(batch, -1, -1, -1).contiguous(), veda.VEDA_CHANNEL_MAJOR, want_mask=False)
+    rng = np.random.default_rng(9)
+    lists = [np.sort(rng.choice(n, lengths[rng.integers(len(lengths))], replace=False)) for _ in range(heads * n)] * batch
+    rp = torch.as_tensor(np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.int32)).to(dev)
+    ci = torch.as_tensor(np.concatenate(lists).astype(np.int32)).to(dev)
+    out, lse = veda.veda_sparse_attn_fwd(plan, qt, kt, vt, vm, rp, ci, 1.0 / math.sqrt(d), want_lse=True)
+    torch.cuda.synchronize()
+    assert (not odd) or bool(out[0, 0].isnan().any()) and not bool(out[0, 0].isnan().all())
+    return out[0].nan_to_num(7.0, 8.0, 9.0).cpu(), lse[0].nan_to_num(7.0, 8.0, 9.0).cpu()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads", [1, 6])
+@pytest.mark.parametrize("odd", [False, True])
+def test_fp32_forms_are_the_same_in_both_orders(d, heads, odd):
+    """Ragged grids with lists on both sides of the length at which the split products end, and numbers that are formed again (an
+    infinity, a NaN, values too small for their parts): the rows' bits do not depend on how the steps are found."""
+    table, walked = (_fp32_forms(d, heads, 1, (9, 33, 33), (4, 4, 4), (1, 20, 191, 192, 193, 240), odd, walk) for walk in (0, 1))
+    assert torch.equal(table[0], walked[0]) and torch.equal(table[1], walked[1])
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_forms_of_a_sample_alone_and_in_a_batch(d):
+    """Heads whose lists are all short, with numbers that are formed again: a tile's form is its own, in calls of one
+    tile to a workgroup, of pairs and of thin tiles in fours, and in either order of the steps."""
+    first = _fp32_forms(d, 2, 1, (5, 9, 45), (4, 4, 4), (1, 3, 20), True, 0)
+    for batch in (1, 4, 5, 20):
+        for walk in (0, 1):
+            got = _fp32_forms(d, 2, batch, (5, 9, 45), (4, 4, 4), (1, 3, 20), True, walk)
+            assert torch.equal(got[0], first[0]) and torch.equal(got[1], first[1]), (batch, walk)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_row_sums_have_no_place_for_padded_slots(dtype):
     """A mask that calls padded slots real: their rows have no token, so no sums are kept for them (what lies around
