@@ -73,6 +73,9 @@ inline int32_t tile_anchor_token(const HeadGeom& g, int32_t i, int T, int H, int
     return (int32_t)((t * H + h) * W + w);
 }
 
+// The tables below are those of 64-slot tiles: a plan of whole 128-token tiles has none, its halves' plan has them.
+inline bool slots_64(const HeadGeom& g) { return (int64_t)g.pt * g.ph * g.pw == 64; }
+
 // Real slots of 64-slot tile i: bit l is set if slot l lies inside the grid.
 inline uint64_t tile_real_slots(const HeadGeom& g, int32_t i, int T, int H, int W) {
     const int o = g.grp == 2 ? i >> 1 : i, half = g.grp == 2 ? (i & 1) : 0;
@@ -85,6 +88,25 @@ inline uint64_t tile_real_slots(const HeadGeom& g, int32_t i, int T, int H, int 
     for (int t = 0; rw > 0 && t < rt; ++t)
         for (int h = 0; h < rh; ++h) mask |= (rw == 64 ? ~0ull : (1ull << rw) - 1ull) << ((t * g.ph + h) * g.pw);
     return mask;
+}
+
+// Whether two heads' tiles are the same ones.
+inline bool same_tiles(const HeadGeom& a, const HeadGeom& b) {
+    return a.ot == b.ot && a.oh == b.oh && a.ow == b.ow && a.grp == b.grp && a.pair_ax == b.pair_ax;
+}
+
+// That of every tile, heads in order.
+inline std::vector<uint64_t> tile_real_table(const std::vector<HeadGeom>& heads, int T, int H, int W) {
+    std::vector<uint64_t> real;
+    if (!slots_64(heads[0])) return real;
+    for (size_t h = 0; h < heads.size(); ++h) {
+        const HeadGeom& g = heads[h];
+        const size_t at = real.size();
+        real.resize(at + g.n_tiles);
+        if (h > 0 && same_tiles(g, heads[h - 1])) std::copy(real.begin() + (at - g.n_tiles), real.begin() + at, real.begin() + at);
+        else for (int32_t i = 0; i < g.n_tiles; ++i) real[at + i] = tile_real_slots(g, i, T, H, W);
+    }
+    return real;
 }
 
 // What a workgroup of the attention kernels (four wavefronts of 32 query rows) computes: up to four query tiles of one
@@ -107,11 +129,6 @@ struct AttnShare {
     int full, thin;
     bool partners = false;   // tiles stay with their partners along pair_ax (pair_tiles), whatever else shares their workgroup
 };
-
-// Whether two heads' tiles are the same ones.
-inline bool same_tiles(const HeadGeom& a, const HeadGeom& b) {
-    return a.ot == b.ot && a.oh == b.oh && a.ow == b.ow && a.grp == b.grp && a.pair_ax == b.pair_ax;
-}
 
 // Appends head h's items: those of more than two tiles, which have the most steps, before the others, each kind ordered by
 // its first tile.  Returns the number of the former.  Full tiles are paired along pair_ax (line by line; the odd ones out
@@ -224,6 +241,7 @@ inline std::vector<AttnItem> attn_items(const std::vector<HeadGeom>& heads, int 
     std::vector<std::vector<AttnItem>> per(dies);
     std::vector<AttnItem> items;
     size_t most = 0, many = 0;
+    if (!slots_64(heads[0])) return items;
     for (size_t h = 0; h < heads.size(); ++h) {
         if (h > 0 && same_tiles(heads[h], heads[h - 1])) {
             for (AttnItem& it : items) it.head = (int32_t)h;
@@ -269,6 +287,7 @@ inline std::vector<HeatItem> heat_items(const std::vector<HeadGeom>& heads, int 
     std::vector<std::vector<HeatItem>> per(dies);
     std::vector<HeatItem> items;
     size_t most = 0;
+    if (!slots_64(heads[0])) return items;
     for (size_t h = 0; h < heads.size(); ++h) {
         const HeadGeom& g = heads[h];
         const bool same = h > 0 && same_tiles(g, heads[h - 1]);

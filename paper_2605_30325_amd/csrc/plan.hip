@@ -109,13 +109,7 @@ static veda_status build_plan(const veda_problem* p, const int32_t* shapes, int 
         }
     }
 
-    std::vector<uint64_t> tile_real((size_t)toff);
-    for (int h = 0; h < p->heads; ++h) {
-        const HeadGeom& g = pl->heads[h];
-        uint64_t* const real = tile_real.data() + g.tile_off;
-        if (h > 0 && veda::same_tiles(g, pl->heads[h - 1])) std::copy(real - g.n_tiles, real, real);
-        else for (int32_t i = 0; i < g.n_tiles; ++i) real[i] = veda::tile_real_slots(g, i, p->T, p->H, p->W);
-    }
+    const std::vector<uint64_t> tile_real = veda::tile_real_table(pl->heads, p->T, p->H, p->W);
     // With few tiles, workgroups of one tile each: no key tile is walked that the tile does not keep, and a second workgroup on a
     // compute unit still finds room.  With more, pairs of either kind, then thin tiles in fours.  The attention alone, us, by
     // tiles of the call, alone / pairs / fours: bf16 d = 64, 9x18x18, 25 % kept 75: 20 24 29, 474: 36 41 40, 636: 53 45 42, 954: 68 56 47;
@@ -178,7 +172,7 @@ static veda_status build_plan(const veda_problem* p, const int32_t* shapes, int 
     auto put = [&tables](const auto& v) {   // offset of a table
         const size_t at = (tables.size() + 255) / 256 * 256;
         tables.resize(at + v.size() * sizeof(v[0]));
-        std::memcpy(tables.data() + at, v.data(), v.size() * sizeof(v[0]));
+        if (!v.empty()) std::memcpy(tables.data() + at, v.data(), v.size() * sizeof(v[0]));
         return at;
     };
     const size_t at_heads = put(pl->heads), at_head = put(tile_head), at_n0 = put(tile_n0), at_real = put(tile_real),

@@ -250,3 +250,43 @@ def test_partners_share_a_workgroup(tmp_path, grid, thin):
             live = [(p & 3, p >> 2 & 1) for p in places if not p & 8]
             assert len(set(live)) == len(live) and all(p < n for p, _ in live)
             assert all((p, r) in live for p in range(n) for r in (0, 1) if r == 0 or real[tiles[p]] > 32)
+
+
+TABLES_PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "geometry.h"
+int main(int argc, char** argv) {
+    const int T = atoi(argv[1]), H = atoi(argv[2]), W = atoi(argv[3]), grp = atoi(argv[7]);
+    const int32_t shape[3] = {atoi(argv[4]), atoi(argv[5]), atoi(argv[6])};
+    std::vector<veda::HeadGeom> heads(2);
+    for (veda::HeadGeom& g : heads) {
+        veda::head_extents(g, shape, grp, T, H, W);
+        g.pair_ax = grp == 2 ? 3 : 2;
+    }
+    size_t items = 0;
+    for (const veda::AttnShare s : {veda::AttnShare{1, 1}, veda::AttnShare{2, 2}, veda::AttnShare{2, 4}, veda::AttnShare{2, 4, true}})
+        items += veda::attn_items(heads, T, H, W, 8, s).size();
+    printf("%zu %zu %zu", items, veda::heat_items(heads, T, H, W, 8, 8).size(), veda::tile_real_table(heads, T, H, W).size());
+    return 0;
+}
+"""
+
+
+@pytest.mark.parametrize("grid,shape", [((3, 9, 10), (2, 8, 8)), ((3, 9, 100), (1, 1, 128)), ((21, 45, 80), (8, 4, 4)), ((5, 9, 10), (32, 2, 2))])
+def test_tables_of_ragged_128_token_tiles(tmp_path, grid, shape):
+    """Built with the undefined-behaviour sanitizer: the tables are made for the 64-slot halves, and none for the whole tiles, which
+    have more slots than a mask has bits."""
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("no C++ compiler")
+    flags = [gxx, "-std=c++17", "-O1", "-Wall", "-Werror", "-fsanitize=undefined", "-fno-sanitize-recover=all", f"-I{CSRC}", "-o", str(tmp_path / "tables"), "-x", "c++", "-"]
+    if subprocess.run(flags, input="int main() {}", capture_output=True, text=True).returncode:
+        pytest.skip("no sanitizer library")
+    subprocess.run(flags, input=TABLES_PROGRAM, text=True, check=True)
+    tiles = vo.num_tiles(grid, shape)
+    for grp in (1, 2):
+        r = subprocess.run([str(tmp_path / "tables"), *map(str, grid), *map(str, shape), str(grp)], capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+        items, heat, real = (int(x) for x in r.stdout.split())
+        assert (items, heat, real) == (0, 0, 0) if grp == 1 else items >= 4 * 2 * tiles and heat >= 2 * tiles and real == 4 * tiles
