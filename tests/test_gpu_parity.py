@@ -340,6 +340,65 @@ def test_attention_on_hand_made_lists(dtype, d, walk):
     _hand_made_lists(dtype, d, 1.0, 1.0, walk=walk)
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("grid,batch", [((9, 18, 18), 3), ((9, 18, 18), 6), ((9, 33, 33), 1), ((9, 33, 33), 2)])
+def test_hand_made_lists_that_share_a_workgroup(dtype, d, grid, batch):
+    """Calls whose tiles share workgroups: pairs, full and thin (711 and 757 tiles), and thin tiles in fours (1422 and 1514).  Unsorted lists of
+    1 to 12 tiles, and all of them now and then, that are those of a neighbour along some axis in another order, share none
+    of its tiles or a part: every tile against float64 softmax, from the step table and from lists merged in the loop."""
+    dev, rng = torch.device("cuda:0"), np.random.default_rng(57)
+    shapes = np.asarray([(4, 4, 4), (1, 8, 8), (16, 2, 2)], np.int32)
+    wl = wlm.custom_workload("shared_lists", 3, d, dtype, grid, False, (25, 100), seed=59, batch=batch)
+    q, k, v = wlm.make_qkv(wl, dev)
+    plan = veda.Plan(batch, 3, d, grid, shapes, wl.torch_dtype)
+    lists = []
+    for h in range(3):
+        nt, nh, nw = (-(-g // int(s)) for g, s in zip(grid, shapes[h]))
+        n, of_head = nt * nh * nw, []
+        for i in range(n):
+            near = [i - step for step, at in ((nh * nw, i >= nh * nw), (nw, i // nw % nh), (1, i % nw)) if at]
+            m, kind = int(rng.integers(1, 13)), int(rng.integers(0, 5))
+            other = of_head[near[int(rng.integers(len(near)))]] if near else np.arange(0)
+            if kind == 0 and len(other):
+                own = rng.permutation(other)
+            elif kind == 1 and len(other) < n:
+                own = rng.choice(np.setdiff1d(np.arange(n), other), min(m, n - len(other)), replace=False)
+            elif kind == 2 and len(other):
+                own = rng.permutation(np.union1d(other[: (len(other) + 1) // 2], rng.choice(n, m, replace=False)))
+            elif kind == 3 and i % 7 == 0:
+                own = rng.permutation(n)
+            else:
+                own = rng.choice(n, m, replace=False)
+            of_head.append(own)
+        lists.append(of_head)
+    flat = [x for of_head in lists for x in of_head]
+    rp = torch.as_tensor(np.concatenate([[0], np.cumsum([len(x) for x in flat] * batch)]).astype(np.int32)).to(dev)
+    ci = torch.as_tensor(np.concatenate(flat).astype(np.int32)).to(dev).repeat(batch)
+    qt, vm, _ = veda.veda_tile_layout(plan, q)
+    kt, _, _ = veda.veda_tile_layout(plan, k, want_mask=False)
+    vt, _, _ = veda.veda_tile_layout(plan, v, veda.VEDA_CHANNEL_MAJOR, want_mask=False)
+    scale, outs = 1.0 / math.sqrt(d), []
+    for walk in (0, 1):
+        plan.set_option(veda.VEDA_OPT_ATTN_LIST_WALK, walk)
+        outs.append(veda.veda_sparse_attn_fwd(plan, qt, kt, vt, vm, rp, ci, scale, want_lse=True))
+        torch.cuda.synchronize()
+    peak, total, bar = 0.0, 0.0, (hz.BF16_MAX_ABS, 2e-2) if dtype == "bf16" else (hz.F32_MAX_ABS, 1e-4)
+    for h in range(3):
+        slots = _tile_tokens(tuple(int(x) for x in shapes[h]), grid)
+        for i, kept in enumerate(lists[h]):
+            rows, cols = slots[i][slots[i] >= 0].to(dev), slots[kept].reshape(-1)
+            cols = cols[cols >= 0].to(dev)
+            s = torch.matmul(q[:, h, rows].double(), k[:, h, cols].double().transpose(1, 2).contiguous()) * scale
+            want, want_lse = torch.matmul(torch.softmax(s, dim=2), v[:, h, cols].double()), torch.logsumexp(s, dim=2)
+            for out, lse in outs:
+                err = (out[:, h, rows].double() - want).abs()
+                worst = torch.stack([err.max() / bar[0], (lse[:, h, rows].double() - want_lse).abs().max() / bar[1], err.mean()]).tolist()
+                assert max(worst[:2]) <= 1.0, (h, i, worst)
+                peak, total = max(peak, worst[0]), total + worst[2]
+    _say(f"[parity] shared lists {dtype} d {d} {grid} x {batch}: {peak:.2f} of the bar, mean {total / 2 / len(flat):.2e}")
+    assert dtype == "f32" or total / 2 / len(flat) <= hz.BF16_MEAN_ABS
+
+
 @pytest.mark.parametrize("exact_scale", [False, True])
 @pytest.mark.parametrize("d,rows,cols", [(128, 16, 16), (128, 1, 257), (64, 16, 32), (64, 27, 19), (64, 1, 3)])
 def test_lists_shared_by_the_wavefronts_of_a_tile(d, rows, cols, exact_scale):
@@ -1214,6 +1273,24 @@ def test_edge_tiles_of_every_fill(dtype, d, tile_tokens, grid):
                                              b["rp"], b["ci"], run.softmax_scale, want_lse=True, q_tokens=q, k_tokens=k)
         torch.cuda.synchronize()
         assert np.array_equal(hz.raw_numpy(out), hz.raw_numpy(run.out)) and torch.equal(lse, run.lse)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128)])
+@pytest.mark.parametrize("grid,batch", [((5, 9, 26), 1), ((5, 9, 13), 2)])
+def test_thin_tiles_in_pairs(dtype, d, grid, batch):
+    """Calls of 514 and 570 tiles in 260 and 290 workgroups, most of them pairs of thin tiles: two wavefronts, of a die's workgroups past the
+    32nd (first grid) the other two.  Outputs against the oracle, and the bits of the walk inside the loop."""
+    shapes = [(4, 4, 4), (1, 8, 8), (16, 2, 2), (2, 4, 8), (64, 1, 1), (1, 1, 64), (8, 8, 1)]
+    heads = len(shapes)
+    wl = wlm.custom_workload(f"thin_pairs_{d}", heads, d, dtype, grid, False, (60, 100), seed=29, batch=batch, latent_dim=64 if d == 128 else 32)
+    run = hz.run_gpu_path(wl, k_per_head=wlm.keep_budget(wl, None, np.asarray(shapes)), shapes=shapes)
+    for h in range(heads):
+        hz.check_head(run, h, check_layout=False)
+    b = run.bufs
+    run.plan.set_option(veda.VEDA_OPT_ATTN_LIST_WALK, 1)
+    out, lse = veda.veda_sparse_attn_fwd(run.plan, b["qt"], b["kt"], b["vt"], b["vm"], b["rp"], b["ci"], run.softmax_scale, want_lse=True)
+    torch.cuda.synchronize()
+    assert np.array_equal(hz.raw_numpy(out), hz.raw_numpy(run.out)) and torch.equal(lse, run.lse)
 
 
 def test_rows_three_times_longer_than_any_named_workload():
