@@ -112,11 +112,11 @@ void veda_plan_destroy(veda_plan* plan); /* NULL is allowed */
  * bits when the rows are ascending.
  * VEDA_OPT_FP32_CHAIN_UNIT (0 = as probed, the default; VEDA_CHAINS_MATRIX; VEDA_CHAINS_VECTOR),
  * stage 2 (Eq. 5): where the fixed-order fp32 chains of the projections and of the score matrix
- * run.  They are defined as scalar fmaf chains; on gfx950 chains of v_mfma_f32_32x32x2_f32 give
- * the same bits at twice the rate, which is a measured property of that instruction.
- * veda_plan_create measures it on the plan's device (both forms on chains with rounding,
- * signed zeros and denormal sums and products, once per device) and uses the matrix cores only
- * if every bit agrees; this option overrides the choice either way.
+ * run.  They are defined as scalar fmaf chains; on gfx950 chains of v_mfma_f32_32x32x2_f32, and of
+ * v_mfma_f32_16x16x4_f32 (projections of small calls), give the same bits at twice the rate, which is a
+ * measured property of those instructions.  veda_plan_create measures it on the plan's device (all three
+ * forms on chains with rounding, signed zeros and denormal sums and products, once per device) and uses
+ * the matrix cores only if every bit of both agrees; this option overrides the choice either way.
  * veda_plan_chain_unit tells which unit the plan's next call will use.
  * VEDA_OPT_FP32_PRODUCTS (0 = by the length of the lists, the default; VEDA_PRODUCTS_FP32; VEDA_PRODUCTS_SPLIT), fp32
  * stage 4: products on the fp32 matrix cores, or as six products of exact three-part bf16 splits, which is about
@@ -173,8 +173,9 @@ veda_status veda_tile_layout(const veda_plan*, const void* x, veda_strides sx, v
  * ascending latent index, then one multiply by `scale`, for the score), so any conforming fp32
  * implementation of that order gives the same bits.  On gfx950 the projection chains and the
  * chains of veda_tile_score's score matrix are issued as v_mfma_f32_32x32x2_f32 over ascending
- * index pairs: that this instruction applies its two terms one after the other, each rounded as
- * an fma, denormals kept, is a property measured on gfx950, not one its ISA manual states: the
+ * index pairs (projections of small calls as v_mfma_f32_16x16x4_f32 over ascending fours): that these
+ * instructions apply their terms one after the other, each rounded as an fma, denormals kept, is a
+ * property measured on gfx950, not one its ISA manual states: the
  * library measures it again on every device it meets (veda_plan_create) and runs these chains as
  * scalar fmaf on the vector units wherever a bit differs (VEDA_OPT_FP32_CHAIN_UNIT forces either
  * form).  The fused route (veda_tile_score_select*) forms its scores with plain fmaf chains on
@@ -292,7 +293,8 @@ veda_status veda_tile_score_select_stats_noalloc(const veda_plan*, const float* 
  * of two nearest below that factor (exact in bf16) and the logits by the remaining factor in fp32
  * on their way into the exponential: the error no longer depends on the logits' size (max-abs
  * <= 1.7e-2, mean-abs <= 1e-3, lse 1e-5 up to a standard deviation of 16) at about 4 % more time.
- * f32: fp32 arithmetic (VEDA_OPT_FP32_PRODUCTS). */
+ * f32: fp32 arithmetic (VEDA_OPT_FP32_PRODUCTS).
+ * A sample's bits do not depend on what other samples the call holds. */
 veda_status veda_sparse_attn_fwd(const veda_plan*, const void* q_tiled, const void* k_tiled,
                                  const void* v_tiled, const uint64_t* valid_mask,
                                  const int32_t* row_ptr, const int32_t* col_idx, float softmax_scale,
@@ -325,7 +327,8 @@ veda_status veda_sparse_attn_fwd_qk_tokens(const veda_plan*, const void* q, veda
  *          each in [0, total_tiles), no index twice): only those rows of heat are written, for
  *          every batch entry; NULL with n_query_tiles == 0 means all query tiles.
  *          Small scores: fp32 plans keep them, and their order, down to fp32's smallest subnormal; bf16 plans
- *          return 0 once exp(logit - row maximum) is below about 2^-126.
+ *          return 0 once exp(logit - row maximum) is below about 2^-126.  Rows whose scores are NaN (an operand that is
+ *          not finite) do not count; where a tile has no other, its score is NaN.
  * q_tiled,k_tiled VEDA_TOKEN_MAJOR.  bf16: Q K^T on bf16 MFMA, fp32 accumulation and softmax. */
 veda_status veda_tile_heatmap(const veda_plan*, const void* q_tiled, const void* k_tiled,
                               const uint64_t* valid_mask, float softmax_scale, const int32_t* query_tiles,

@@ -1,7 +1,8 @@
 // Stage 4 -- block-sparse flash attention forward + un-tiling (Eq. 2: softmax over the
 // concatenation of the kept key tiles; Sec. 3.1 masked form; Sec. 4.3 tile-skipping kernel;
 // Alg. 1 "UnTile"): the C entry points.  bf16 plans go to the kernel in attn_pair.hip, fp32
-// plans to the one in attn_f32.hip; both run a workgroup per pair of partner query tiles.
+// plans to the one in attn_f32.hip; both run a workgroup per work item of the plan's table, one to four query
+// tiles of a head (geometry.h, attn_items), or per pair of partners where lists are merged inside the loop.
 #include "attn_common.h"
 
 namespace veda {

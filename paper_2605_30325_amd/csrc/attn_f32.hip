@@ -10,7 +10,7 @@
 //   S^T = K Q^T from the K planes, in the shadow of its last products V^T converted (landing area -> registers -> planes)
 //   O^T += V^T P^T, in the shadow of its last products the next 32 keys' K converted
 // with a barrier after each, so that one set of K planes and one of V^T planes serve (24 KB each at d = 128, 16 KB of
-// landing area; 74 KB with the step table: two workgroups on a compute unit).  The query rows stay split in registers (96
+// landing area; 79 KB with the step table: two workgroups on a compute unit).  The query rows stay split in registers (96
 // at d = 128, with 64 of O^T: this is why 32 keys, not 64).  K rows are read in the order rho, which leaves each lane eight
 // consecutive keys of S^T as in the bf16 kernel.
 // Measured, whole calls: 8 heads of 624 tiles, 10 % kept, 5.9 -> 3.3 ms (the products on fp32 matrix cores at 93 % of their
@@ -51,10 +51,12 @@ constexpr float kF32QScale = 0x1p80f, kF32VScale = 0x1p96f, kF32Small = 0x1p48f;
 typedef UnionLds<4, kF32Chunk> F32Table;
 template <int D, bool kTable>
 constexpr size_t kF32Tokens = (size_t)2 * kTile * D * 4 + (kTable ? sizeof(F32Table) : 4 * 32 * sizeof(float));
+template <int D, bool kTable> constexpr size_t kF32Lds = kF32Tokens<D, kTable> + 4 * 32 * sizeof(int);
+static_assert(2 * kF32Lds<128, true> <= 160 * 1024 && 3 * kF32Lds<64, true> <= 160 * 1024, "workgroups on a compute unit (launch bounds)");
 
 // kTable: the steps come from the table in LDS (attn_union.h), as in the bf16 kernel; otherwise the two
 // lists are merged inside the loop (heads above 16384 tiles, VEDA_OPT_ATTN_LIST_WALK).
-// d = 64: three workgroups on a compute unit (42 KB each); with two, 2 heads of 624 tiles, all kept, 7.34 instead of 7.14 ms.
+// d = 64: three workgroups on a compute unit (47 KB each); with two, 2 heads of 624 tiles, all kept, 7.34 instead of 7.14 ms.
 template <int D, bool kTable>
 __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void sparse_attn_f32_kernel(AttnArgs a) {
     constexpr int kKPitch = D * 4;               // bytes of one K row
@@ -613,7 +615,7 @@ veda_status launch_sparse_attn_f32(const veda_plan* pl, const AttnArgs& a, bool 
 #define VEDA_LAUNCH_F32(DD, TT)                                                                          \
     do {                                                                                                 \
         auto kern = sparse_attn_f32_kernel<DD, TT>;                                                      \
-        constexpr size_t smem = kF32Tokens<DD, TT> + 4 * 32 * sizeof(int);                               \
+        constexpr size_t smem = kF32Lds<DD, TT>;                                                         \
         if (smem > 64 * 1024)                                                                            \
             VEDA_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem)); \
         hipLaunchKernelGGL(kern, grid, block, smem, s, a);                                               \

@@ -5,7 +5,8 @@
 // workgroup the loads, not the matrix cores, set the pace.  Neighbouring query tiles keep
 // largely the same key tiles, so here one workgroup owns TWO neighbouring query tiles (partners
 // along the axis in which the head's tile shape is thinnest: pair_tiles()) and walks the union
-// of their two kept lists: a key tile kept by both is loaded once and used twice.
+// of their two kept lists: a key tile kept by both is loaded once and used twice.  (Calls of few
+// tiles, which leave room for a workgroup each, walk one list: plan.hip.)
 //
 // Four wavefronts of 32 query rows: two for each of the two tiles, or one for each of FOUR neighbouring thin tiles (32
 // real rows or fewer, at the ragged edges of a grid: geometry.h, attn_items).  Every wave attends to all 64 slots of a
@@ -435,6 +436,13 @@ __global__ __launch_bounds__(256, 2) void sparse_attn_bf16_pair_kernel(AttnArgs 
     finish_pair<D>(st, a, tok_s, smem, head, b, tid, wave, lq, hh);
 }
 
+// Two slots of (K tile + V^T tile), then the step table and the rows' tokens.
+constexpr size_t pair_lds(int d, bool grouped, bool table) {
+    const size_t tables = grouped ? sizeof(UnionLds<1, kPairChunk>) : sizeof(UnionLds<4, kPairChunk>);
+    return (size_t)2 * 2 * kTile * d * 2 + (table ? tables : 0) + 4 * 32 * sizeof(int);
+}
+static_assert(2 * pair_lds(128, false, true) <= 160 * 1024, "two workgroups on a compute unit (launch bounds)");
+
 veda_status launch_sparse_attn_bf16_pair(const veda_plan* pl, const AttnArgs& a, bool grouped, bool exact, bool walk,
                                          hipStream_t s) {
     const int d = pl->prob.head_dim;
@@ -442,9 +450,7 @@ veda_status launch_sparse_attn_bf16_pair(const veda_plan* pl, const AttnArgs& a,
     bool table = !walk;
     for (const HeadGeom& g : pl->heads) table = table && (grouped ? g.n_tiles / 2 : g.n_tiles) <= kUnionMaxTiles;
     dim3 grid((unsigned)(table ? pl->attn_blocks : kXcd * pl->xcd_max_pairs), (unsigned)pl->prob.batch), block(256);
-    // two slots of (K tile + V^T tile), then the step table and the rows' tokens
-    const size_t tables = grouped ? sizeof(UnionLds<1, kPairChunk>) : sizeof(UnionLds<4, kPairChunk>);
-    const size_t smem = (size_t)2 * 2 * kTile * d * 2 + (table ? tables : 0) + 4 * 32 * sizeof(int);
+    const size_t smem = pair_lds(d, grouped, table);
 #define VEDA_LAUNCH_PAIR_T(DD, GG, KK, EE, TT)                                                           \
     do {                                                                                                 \
         auto kern = sparse_attn_bf16_pair_kernel<DD, GG, KK, EE, TT>;                                    \

@@ -30,12 +30,12 @@ struct HeadGeom {
     int32_t ot, oh, ow;      // extents of a whole tile
     int32_t ht, hh, hw;      // token offset of the second half inside a whole tile
     int32_t grp;             // 64-slot tiles per whole tile: 1 or 2
-    // Full query tiles are processed two at a time by the attention and heat-map kernels.  Partners
-    // are neighbours along pair_ax (0 = t, 1 = h, 2 = w: the axis along which a tile is thinnest, so
-    // its neighbour is the closest one and keeps the most similar key tiles); a last layer without a
-    // partner is processed alone (heat map, merged lists) or with the next lines' (attn_items).  pair_ax = 3: the two halves of a 128-token tile.
+    // Partners are neighbours along pair_ax (0 = t, 1 = h, 2 = w: the axis along which a tile is thinnest, so
+    // its neighbour is the closest one and keeps the most similar key tiles): the attention kernels take full query tiles two at a
+    // time along it (attn_items; a last layer without a partner goes with the next lines'), and merged lists' work items
+    // are partners or one without (pair_tiles).  pair_ax = 3: the two halves of a 128-token tile.
     int32_t pair_ax;
-    int32_t n_pairs;         // work items (pairs and partnerless tiles) of this head
+    int32_t n_pairs;         // merged lists' work items (pairs and partnerless tiles) of this head
     int32_t log_pw, log_phw; // log2 of pw and of ph*pw (extents multiply to 64, so each is a power of two)
 };
 

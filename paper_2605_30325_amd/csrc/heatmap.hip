@@ -28,12 +28,13 @@
 // per wave, four tiles per workgroup (half the operand reads and loads: 8.3 and 11.7 ms, fp32 3.9), a ring of
 // three or four K tiles (0.5 ms slower: it costs a resident workgroup and the loads are not what is waited for).
 // With scratch, whole calls of the supervision side (gathers, heat map, both top-k, recall), two walks and one: 12 heads
-// of 624 tiles 8.0 -> 5.0 ms, one in 16 tiles of 40 heads of 21x45x80 13.4 -> 8.8 ms.  While a compute unit is busy pass 1 then stands at 79 % vector
-// issue (85 instructions per 8 products; 48 of them are the exponentials' three, 8 the maximum) and 45 % matrix pipe; of the gain, masks
+// of 624 tiles 8.0 -> 5.0 ms, one in 16 tiles of 40 heads of 21x45x80 13.4 -> 8.8 ms; of the gain, masks
 // on the scalar unit and no register copies at the ends of branches gave a fifth,
 // handing work items out as asked for 12 % of the second case.  Operand addresses that never change (two steps to a turn of the
-// loop, the slot a constant) and maxima that quiet no NaN first (61 vector instructions per 8 products): 4.49 -> 4.15 ms and
-// 8.14 -> 7.72.  Tried: the additions on the matrix pipe (v_mfma_f32_4x4x1, one a lane), 5.25 ms: they queue behind the products.
+// loop, the slot a constant) and maxima that quiet no NaN first (61 vector instructions per 8 products, 48 of them the exponentials'
+// three): 4.49 -> 4.15 ms and 8.14 -> 7.72.  While a compute unit is busy its vector units then issue 80 % of the cycles and its matrix
+// pipes 50 %.  The bf16 forms spill 6 to 19 registers (d = 64 with a list none): what a work item keeps from its start for its end,
+// stored and read once per item, not in the walk.  Tried: the additions on the matrix pipe (v_mfma_f32_4x4x1, one a lane), 5.25 ms: they queue behind the products.
 // Padding: a wave runs only the blocks that hold real rows, and key tiles with few real keys are half steps (attn_union.h).
 #include <type_traits>
 

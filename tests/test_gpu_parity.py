@@ -1541,6 +1541,39 @@ def test_target_scores_of_tiles_that_share_wavefronts(dtype, d, grid, shape):
             assert ((full - ref).abs() <= (2e-4 if dtype == "bf16" else 2e-5) * ref).all()
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128)])
+@pytest.mark.parametrize("grid,shape", [((5, 9, 13), (4, 4, 4)), ((9, 6, 10), (16, 2, 2)), ((4, 8, 8), (4, 4, 4))])
+def test_target_scores_where_query_rows_are_nan(dtype, d, grid, shape):
+    """A row of NaN does not count for its tile, a tile of nothing else is NaN, full or not, and the others' scores are those of a call
+    without, with scratch and without."""
+    heads, scale = 2, 1.0 / math.sqrt(d)
+    wl = wlm.custom_workload("nan_rows", heads, d, dtype, grid, False, (50, 100), seed=43)
+    q, k, _ = wlm.make_qkv(wl, torch.device("cuda:0"))
+    plan = veda.Plan(1, heads, d, grid, np.asarray([shape] * heads, np.int32), wl.torch_dtype)
+    n, slots = plan.tiles[0], _tile_tokens(shape, grid)
+    lib, stream, maps = veda.load(), torch.cuda.current_stream().cuda_stream, []
+    kt, vm, _ = veda.veda_tile_layout(plan, k)
+    for odd in (False, True):
+        if odd:
+            q[0, 0, slots[0, 0]] = math.nan
+            for i in (1, n - 1):
+                q[0, 0, slots[i][slots[i] >= 0]] = math.nan
+        qt, _, _ = veda.veda_tile_layout(plan, q, want_mask=False)
+        heat = veda.veda_tile_heatmap(plan, qt, kt, vm, scale).view(heads, n, n)
+        again = torch.empty_like(heat)
+        assert lib.veda_tile_heatmap(plan.handle, qt.data_ptr(), kt.data_ptr(), vm.data_ptr(), scale, None, 0, again.data_ptr(), stream) == veda.VEDA_OK
+        torch.cuda.synchronize()
+        assert torch.equal(heat.isnan(), again.isnan()) and torch.equal(heat.nan_to_num(7.0), again.nan_to_num(7.0))
+        maps.append(heat)
+    clean, odd = maps
+    rest = torch.ones(heads, n, dtype=torch.bool, device="cuda:0")
+    rest[0, [0, 1, n - 1]] = False
+    assert torch.equal(odd[rest], clean[rest]) and bool(odd[0, [1, n - 1]].isnan().all()) and not bool(odd[0, 0].isnan().any())
+    s = torch.softmax((q[0, 0, slots[0, 1:][slots[0, 1:] >= 0]].double() @ k[0, 0].double().T) * scale, dim=1).amax(dim=0)
+    ref = torch.stack([s[t[t >= 0].cuda()].max() for t in slots])
+    assert ((odd[0, 0] - ref).abs() <= (2e-4 if dtype == "bf16" else 2e-5) * ref).all()
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_fp32_target_scores_below_the_smallest_normal_number(d):
     """Key tiles up to 102 below the row's maximum (natural units): their scores are subnormal, keep their order,
